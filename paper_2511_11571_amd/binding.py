@@ -55,6 +55,14 @@ class Shape:
         return _CShape(self.batch, self.heads, self.seqlen, self.head_dim, self.block, self.topk,
                        self.conv_width, self.dtype, self.softmax_scale, self.flags, self.kv_heads)
 
+    def _ref(self):
+        """Address of this shape as the C structure, built once per object (the object is immutable)."""
+        try:
+            return ctypes.addressof(self._cstruct)
+        except AttributeError:
+            object.__setattr__(self, "_cstruct", self.c())
+            return ctypes.addressof(self._cstruct)
+
     @property
     def hkv(self):
         return self.kv_heads if self.kv_heads > 0 else self.heads
@@ -93,12 +101,27 @@ def lib():
     return _lib
 
 
+# Host time of a call counts where the kernels take ten microseconds (a decode step): the entry points
+# of the path are called through prototypes of their own, with plain Python integers for pointers, and
+# the stream comes as a raw handle instead of a torch.cuda.Stream object.
+_fns = {}
+
+
+def _fn(name, sig):
+    """Entry point `name` with argument types `sig`: p = pointer, i = int32, z = size_t, u = uint32."""
+    f = _fns.get(name)
+    if f is None:
+        kinds = {"p": ctypes.c_void_p, "i": ctypes.c_int32, "z": ctypes.c_size_t, "u": ctypes.c_uint32}
+        f = _fns[name] = ctypes.CFUNCTYPE(ctypes.c_int, *(kinds[c] for c in sig))((name, lib()))
+    return f
+
+
 def _p(t):
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+    return 0 if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(st, where):
@@ -107,9 +130,13 @@ def _check(st, where):
 
 
 def routes_per_slice(shape: Shape) -> int:
-    R = ctypes.c_int64(0)
-    _check(lib().moba_routes_per_slice(ctypes.byref(shape.c()), ctypes.byref(R)), "moba_routes_per_slice")
-    return R.value
+    R = shape.__dict__.get("_routes")        # a function of the (immutable) shape
+    if R is None:
+        r = ctypes.c_int64(0)
+        _check(lib().moba_routes_per_slice(ctypes.byref(shape.c()), ctypes.byref(r)), "moba_routes_per_slice")
+        R = r.value
+        object.__setattr__(shape, "_routes", R)
+    return R
 
 
 def workspace_bytes(shape: Shape):
@@ -131,7 +158,7 @@ def centroids(shape: Shape, K, conv_w=None, K_eff=None, out=None):
     if out is None:
         out = torch.empty((shape.batch, shape.hkv, shape.n, shape.head_dim), dtype=torch.float32,
                           device=K.device)
-    _check(lib().moba_centroids(ctypes.byref(shape.c()), _p(K), _p(conv_w), _p(K_eff), _p(out),
+    _check(_fn("moba_centroids", "pppppp")(shape._ref(), _p(K), _p(conv_w), _p(K_eff), _p(out),
                                 _stream()), "moba_centroids")
     return (K_eff if K_eff is not None else K), out
 
@@ -149,8 +176,8 @@ def key_conv_backward(shape: Shape, K, conv_w, dK_eff, ws=None):
         ws = _ws(n.value, K)
     dK = torch.empty_like(K)
     dw = torch.empty_like(conv_w)
-    _check(lib().moba_key_conv_backward(ctypes.byref(shape.c()), _p(K), _p(conv_w), _p(dK_eff), _p(dK),
-                                        _p(dw), _p(ws), ctypes.c_size_t(ws.numel()), _stream()),
+    _check(_fn("moba_key_conv_backward", "pppppppzp")(shape._ref(), _p(K), _p(conv_w), _p(dK_eff), _p(dK),
+                                        _p(dw), _p(ws), ws.numel(), _stream()),
            "moba_key_conv_backward")
     return dK, dw
 
@@ -159,7 +186,7 @@ def _list_buffers(shape, like):
     R = routes_per_slice(shape)
     off = torch.empty((shape.batch, shape.heads, shape.n + 1), dtype=torch.int32, device=like.device)
     ql = torch.empty((shape.batch, shape.heads, max(R, 1)), dtype=torch.int32, device=like.device)
-    return off, (ql[..., :R] if R > 0 else ql[..., :0])
+    return off, (ql if R > 0 else ql[..., :0])
 
 
 def topk(shape: Shape, Q, cent, ws=None):
@@ -171,8 +198,8 @@ def topk(shape: Shape, Q, cent, ws=None):
     off, ql = _list_buffers(shape, Q)
     if ws is None:
         ws = _ws(workspace_bytes(shape)[0], Q)
-    _check(lib().moba_topk(ctypes.byref(shape.c()), _p(Q), _p(cent), _p(idx), _p(off), _p(ql),
-                           _p(ws), ctypes.c_size_t(ws.numel()), _stream()), "moba_topk")
+    _check(_fn("moba_topk", "pppppppzp")(shape._ref(), _p(Q), _p(cent), _p(idx), _p(off), _p(ql),
+                           _p(ws), ws.numel(), _stream()), "moba_topk")
     return idx, (off, ql)
 
 
@@ -187,7 +214,7 @@ def topk_static(shape: Shape, Q, cent, out=None):
         off, ql = _list_buffers(shape, Q)
     else:
         idx, (off, ql) = out
-    _check(lib().moba_topk_static(ctypes.byref(shape.c()), _p(Q), _p(cent), _p(idx), _p(off), _p(ql),
+    _check(_fn("moba_topk_static", "ppppppp")(shape._ref(), _p(Q), _p(cent), _p(idx), _p(off), _p(ql),
                                   _stream()), "moba_topk_static")
     return idx, (off, ql)
 
@@ -211,29 +238,29 @@ class VarlenLayout:
         self.seq_offsets = torch.tensor(self.seq_offsets_host, dtype=torch.int32, device=device)
         self.pad_offsets = torch.tensor(self.pad_offsets_host, dtype=torch.int32, device=device)
         self.block_first = torch.empty(max(self.padded_tokens // block, 1), dtype=torch.int32, device=device)
-        _check(lib().moba_varlen_block_first(ctypes.c_int32(self.num_seqs), _p(self.pad_offsets),
-                                             ctypes.c_int32(block), ctypes.c_int32(self.padded_tokens),
-                                             _p(self.block_first), _stream()), "moba_varlen_block_first")
+        _check(_fn("moba_varlen_block_first", "ipiipp")(self.num_seqs, _p(self.pad_offsets), block,
+                                                        self.padded_tokens, _p(self.block_first), _stream()),
+               "moba_varlen_block_first")
 
-    def _copy(self, fn, name, X, out_rows):
+    def _copy(self, name, X, out_rows):
         assert X.is_contiguous() and X.dim() >= 3
         lead, rows = X.shape[:2], X.shape[2]
         row_bytes = X[0, 0, 0].numel() * X.element_size() if X.dim() > 3 else X.element_size()
         out = torch.empty(lead + (out_rows,) + X.shape[3:], dtype=X.dtype, device=X.device)
-        _check(fn(ctypes.c_int32(self.num_seqs), _p(self.seq_offsets), _p(self.pad_offsets),
-                  ctypes.c_int32(lead[0] * lead[1]), ctypes.c_int32(self.tokens),
-                  ctypes.c_int32(self.padded_tokens), ctypes.c_int32(row_bytes), _p(X), _p(out), _stream()), name)
+        _check(_fn(name, "ippiiiippp")(self.num_seqs, _p(self.seq_offsets), _p(self.pad_offsets),
+                                       lead[0] * lead[1], self.tokens, self.padded_tokens, row_bytes, _p(X), _p(out),
+                                       _stream()), name)
         return out
 
     def pad(self, X):
         """[1, heads, T, ...] -> [1, heads, T', ...], zero rows after every sequence."""
         assert X.shape[2] == self.tokens
-        return self._copy(lib().moba_varlen_pad, "moba_varlen_pad", X, self.padded_tokens)
+        return self._copy("moba_varlen_pad", X, self.padded_tokens)
 
     def unpad(self, Xp):
         """[1, heads, T', ...] -> [1, heads, T, ...]."""
         assert Xp.shape[2] == self.padded_tokens
-        return self._copy(lib().moba_varlen_unpad, "moba_varlen_unpad", Xp, self.tokens)
+        return self._copy("moba_varlen_unpad", Xp, self.tokens)
 
 
 def topk_varlen(shape: Shape, layout: VarlenLayout, Q, cent, ws=None):
@@ -244,8 +271,8 @@ def topk_varlen(shape: Shape, layout: VarlenLayout, Q, cent, ws=None):
     off, ql = _list_buffers(shape, Q)
     if ws is None:
         ws = _ws(workspace_bytes(shape)[0], Q)
-    _check(lib().moba_topk_varlen(ctypes.byref(shape.c()), _p(Q), _p(cent), _p(layout.block_first), _p(idx),
-                                  _p(off), _p(ql), _p(ws), ctypes.c_size_t(ws.numel()), _stream()),
+    _check(_fn("moba_topk_varlen", "ppppppppzp")(shape._ref(), _p(Q), _p(cent), _p(layout.block_first), _p(idx),
+                                  _p(off), _p(ql), _p(ws), ws.numel(), _stream()),
            "moba_topk_varlen")
     return idx, (off, ql)
 
@@ -256,8 +283,8 @@ def build_lists(shape: Shape, idx, ws=None):
     off, ql = _list_buffers(shape, idx)
     if ws is None:
         ws = _ws(workspace_bytes(shape)[0], idx)
-    _check(lib().moba_build_lists(ctypes.byref(shape.c()), _p(idx), _p(off), _p(ql),
-                                  _p(ws), ctypes.c_size_t(ws.numel()), _stream()), "moba_build_lists")
+    _check(_fn("moba_build_lists", "pppppzp")(shape._ref(), _p(idx), _p(off), _p(ql),
+                                  _p(ws), ws.numel(), _stream()), "moba_build_lists")
     return off, ql
 
 
@@ -272,8 +299,8 @@ def forward(shape: Shape, Q, K_eff, V, idx, lists, ws=None, O=None, lse=None):
         lse = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
     if ws is None:
         ws = _ws(workspace_bytes(shape)[1], Q)
-    _check(lib().moba_forward(ctypes.byref(shape.c()), _p(Q), _p(K_eff), _p(V), _p(idx), _p(off),
-                              _p(ql), _p(O), _p(lse), _p(ws), ctypes.c_size_t(ws.numel()),
+    _check(_fn("moba_forward", "ppppppppppzp")(shape._ref(), _p(Q), _p(K_eff), _p(V), _p(idx), _p(off),
+                              _p(ql), _p(O), _p(lse), _p(ws), ws.numel(),
                               _stream()),
            "moba_forward")
     return O, lse
@@ -293,14 +320,14 @@ def backward(shape: Shape, Q, K_eff, V, O, lse, dO, idx, lists, ws=None, out=Non
     if ws is None:
         ws = _ws(workspace_bytes(shape)[2], Q)
     if parts is None:
-        _check(lib().moba_backward(ctypes.byref(shape.c()), _p(Q), _p(K_eff), _p(V), _p(O), _p(lse),
+        _check(_fn("moba_backward", "ppppppppppppppzp")(shape._ref(), _p(Q), _p(K_eff), _p(V), _p(O), _p(lse),
                                    _p(dO), _p(idx), _p(off), _p(ql), _p(dQ), _p(dK), _p(dV),
-                                   _p(ws), ctypes.c_size_t(ws.numel()), _stream()), "moba_backward")
+                                   _p(ws), ws.numel(), _stream()), "moba_backward")
     else:
-        _check(lib().moba_backward_parts(ctypes.byref(shape.c()), _p(Q), _p(K_eff), _p(V), _p(O),
+        _check(_fn("moba_backward_parts", "ppppppppppppppzpu")(shape._ref(), _p(Q), _p(K_eff), _p(V), _p(O),
                                          _p(lse), _p(dO), _p(idx), _p(off), _p(ql), _p(dQ),
-                                         _p(dK), _p(dV), _p(ws), ctypes.c_size_t(ws.numel()), _stream(),
-                                         ctypes.c_uint32(parts)), "moba_backward_parts")
+                                         _p(dK), _p(dV), _p(ws), ws.numel(), _stream(),
+                                         parts), "moba_backward_parts")
     return dQ, dK, dV
 
 
@@ -318,8 +345,8 @@ def decode_forward(shape: Shape, q_len, Q, K_eff, V, cent, want_idx=True):
     lse = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
     idx = (torch.empty((shape.batch, shape.heads, q_len, shape.topk), dtype=torch.int32, device=Q.device)
            if want_idx else None)
-    _check(lib().moba_decode_forward(ctypes.byref(shape.c()), ctypes.c_int32(q_len), _p(Q), _p(K_eff),
-                                     _p(V), _p(cent), ctypes.c_int32(blocks), _p(O), _p(lse), _p(idx),
+    _check(_fn("moba_decode_forward", "pippppipppp")(shape._ref(), q_len, _p(Q), _p(K_eff),
+                                     _p(V), _p(cent), blocks, _p(O), _p(lse), _p(idx),
                                      _stream()), "moba_decode_forward")
     return O, lse, idx
 
@@ -345,13 +372,13 @@ def microbench(copy_bytes=1 << 30, mfma_iters=20000):
     src = torch.ones(copy_bytes // 4, dtype=torch.float32, device="cuda")
     dst = torch.empty_like(src)
     ms = ctypes.c_float(0)
-    _check(lib().moba_microbench_copy(_p(dst), _p(src), ctypes.c_size_t(copy_bytes), ctypes.c_int(5),
-                                      ctypes.byref(ms), _stream()), "moba_microbench_copy")
+    _check(lib().moba_microbench_copy(ctypes.c_void_p(_p(dst)), ctypes.c_void_p(_p(src)), ctypes.c_size_t(copy_bytes), ctypes.c_int(5),
+                                      ctypes.byref(ms), ctypes.c_void_p(_stream())), "moba_microbench_copy")
     out = {"copy_bytes": copy_bytes, "copy_ms": ms.value, "copy_GBs": 2.0 * copy_bytes / (ms.value * 1e-3) / 1e9,
            "mfma_tflops": {}}
     flop = ctypes.c_double(0)
     for wps in (1, 2, 4, 8):
-        _check(lib().moba_microbench_mfma(ctypes.c_int(wps), ctypes.c_int(mfma_iters), _p(dst), ctypes.byref(ms),
-                                          ctypes.byref(flop), _stream()), "moba_microbench_mfma")
+        _check(lib().moba_microbench_mfma(ctypes.c_int(wps), ctypes.c_int(mfma_iters), ctypes.c_void_p(_p(dst)), ctypes.byref(ms),
+                                          ctypes.byref(flop), ctypes.c_void_p(_stream())), "moba_microbench_mfma")
         out["mfma_tflops"][wps] = flop.value / (ms.value * 1e-3) / 1e12
     return out
