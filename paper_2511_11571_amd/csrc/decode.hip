@@ -5,13 +5,30 @@
 // algorithm of Appendix C.1 treats the tail block the same way; here its centroid is never
 // needed, because the own block is not a routing candidate).
 //
-// One workgroup of 16 waves per (query, batch*head): gate scores against the centroids of the
-// complete past blocks (fp32, a thread per centroid), exact top-k by a four-pass radix select on
-// order-preserving keys with ties to the lower block index, then attention over the kept blocks
-// and the own block -- the waves take blocks in turn, each with its own running softmax, merged
-// through LDS.  All arithmetic in
-// fp32; nothing is written to global memory but O, lse and (optionally) the kept blocks.  The
-// work per query is a few hundred KB of reads: the kernel is bound by latency, not by a pipe.
+// One workgroup of 16 waves per (query, batch*head), no workspace: gate scores against the centroids
+// of the complete past blocks, exact top-k, attention over the kept blocks and the own block, all in
+// fp32 arithmetic; nothing is written to global memory but O, lse and (optionally) the kept blocks.
+//
+// The work per query is a few hundred KB of reads from a chip that is mostly idle, so the kernel is
+// bound by how fast ONE compute unit takes them in and by the chain of dependent steps:
+//  - every read of centroids, K and V covers whole rows with neighbouring lanes (16 bytes each): a
+//    lane per row moves a quarter of the bytes per clock on this chip.  The lanes of a row add their
+//    parts of the dot product up by DPP;
+//  - the keys of all kept blocks and the own block count as ONE sequence that the waves walk together:
+//    with a block per wave, 9 kept blocks left 7 of 16 waves idle;
+//  - loads go out in batches of 16 per lane (a batch is one memory latency);
+//  - every group of lanes that holds a key keeps a softmax of its own (m, l, O), merged once at the
+//    end: no cross-lane maximum or sum inside the walk;
+//  - the selection bins the scores linearly between the smallest and the largest (1024 bins, one LDS
+//    atomic per score, well spread), and ranks only the scores of the bin that holds the k-th largest;
+//    the radix select over the bits of the scores remains for ties wider than a workgroup can rank
+//    and for non-finite scores;
+//  - queries that share a key/value head run on the same XCD at the same time (schedule()).
+// 1 query of 131109 keys x 32 slices (d = 64, B = 128, k = 8): 24.8 -> 12.8 us; 16 queries of 32805
+// keys x 16 heads on 4 key/value heads (d = 128, B = 64, k = 32): 59 -> 29 us (there
+// 340 MB go from the L2s to the compute units and 126 MB from behind them: 4.5 TB/s of the latter).
+#include <type_traits>
+
 #include "common.h"
 
 namespace moba {
@@ -23,235 +40,433 @@ __device__ __forceinline__ uint32_t decode_key(float x)
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-template <typename T, int D>
-__device__ __forceinline__ float decode_dot(const T* __restrict__ row, const float* __restrict__ v)
+template <int CTRL, int ROWS = 0xf, typename X>
+__device__ __forceinline__ X dpp(X v)                        // lanes without a source (or outside ROWS) read 0
 {
-    float acc = 0.f;
-#pragma unroll
-    for (int c0 = 0; c0 < D; c0 += 32) {                    // four independent loads at a time
-        float x[4][8];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) Vec8<T>::load(row + c0 + 8 * i, x[i]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc = fmaf(x[i][e], v[c0 + 8 * i + e], acc);
+    static_assert(sizeof(X) == 4, "32-bit values");
+    const int r = __builtin_amdgcn_update_dpp(0, *reinterpret_cast<const int*>(&v), CTRL, ROWS, 0xf, true);
+    return *reinterpret_cast<const X*>(&r);
+}
+
+// sum over the L (8, 16 or 32) neighbouring lanes of a row, in all of them
+template <int L>
+__device__ __forceinline__ float row_sum(float x)
+{
+    x += dpp<0xb1>(x);                                       // quad_perm 1,0,3,2
+    x += dpp<0x4e>(x);                                       // quad_perm 2,3,0,1
+    x += dpp<0x141>(x);                                      // row_half_mirror: the other quad of 8
+    if constexpr (L >= 16) x += dpp<0x140>(x);               // row_mirror: the other half of 16
+    if constexpr (L >= 32) {
+        const uint32_t b = __float_as_uint(x);
+        const auto q = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+        x = __uint_as_float(q[0]) + __uint_as_float(q[1]);
     }
-    return acc;
+    return x;
+}
+
+// f over the lanes that are a multiple of L apart, in all of them (all lanes of a row of L agree or
+// hold different channels): the other half of a 16-lane row by DPP, the rest by lane swaps
+template <int L, typename F>
+__device__ __forceinline__ float across_rows(float x, F f)
+{
+    if constexpr (L <= 8) x = f(x, dpp<0x128>(x));           // row_ror 8
+    if constexpr (L <= 16) {
+        const uint32_t b = __float_as_uint(x);
+        const auto q = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+        x = f(__uint_as_float(q[0]), __uint_as_float(q[1]));
+    }
+    const uint32_t b = __float_as_uint(x);
+    const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return f(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
+
+// a + the two products of bf16 pairs
+__device__ __forceinline__ float dot2(uint32_t x, uint32_t y, float a)
+{
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    return __builtin_amdgcn_fdot2_f32_bf16(*reinterpret_cast<bf16x2_t*>(&x), *reinterpret_cast<bf16x2_t*>(&y), a, false);
+}
+
+// inclusive prefix sum over the 64 lanes of a wave
+__device__ __forceinline__ int wave_prefix(int x)
+{
+    x += dpp<0x111>(x);                                      // row_shr 1, 2, 4, 8: inside rows of 16
+    x += dpp<0x112>(x);
+    x += dpp<0x114>(x);
+    x += dpp<0x118>(x);
+    x += dpp<0x142, 0xa>(x);                                 // row_bcast 15: rows 1 and 3 take the row before
+    x += dpp<0x143, 0xc>(x);                                 // row_bcast 31: rows 2 and 3 take the lower half
+    return x;
 }
 
 constexpr int kDecodeWaves = 16;
 constexpr int kDecodeThreads = kDecodeWaves * kWave;
+constexpr int kDecodeBins = kDecodeThreads;    // bins of the selection: one per thread
+constexpr int kDecodeRank = kDecodeThreads;    // most scores of one bin that are ranked directly: one per thread
+// words that hold the ranked scores, then the waves' (m, l, O)
+template <int D>
+constexpr int kDecodeScratch = 2 * kDecodeRank > kDecodeWaves * (D + 2) ? 2 * kDecodeRank : kDecodeWaves * (D + 2);
 
 template <typename T, int D>
 __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const float* __restrict__ cent, T* __restrict__ O, float* __restrict__ lse,
     int32_t* __restrict__ idx_out, int N, int B, int k, int q_len, int cblocks, float scale, int G,
-    int npast_max)
+    int bhk, int npast_max)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int NT = kDecodeThreads, NW = kDecodeWaves;
-    float* qs = reinterpret_cast<float*>(smem_raw);         // [D] the query
-    float* sc = qs + D;                                     // [npast_max] gate scores
-    uint32_t* hist = reinterpret_cast<uint32_t*>(sc + npast_max);   // [256]
-    int* ctl = reinterpret_cast<int*>(hist + 256);          // prefix, need, number of kept blocks
-    int* sel = ctl + 4;                                     // [k] kept blocks, ascending
-    float* ps = reinterpret_cast<float*>(sel + k + 1);      // [NW][64] probabilities of a step
-    float* mrg = ps + NW * kWave;                           // [NW][D + 2] the waves' (m, l, O)
+    constexpr int LPR = D * (int)sizeof(T) / 16;            // lanes of a K / V row, 16 bytes each
+    constexpr int EPL = 16 / (int)sizeof(T);                // elements of a lane
+    constexpr int RPI = kWave / LPR;                        // rows per load instruction of a wave
+    constexpr int NB = 8;                                   // load instructions of K (and of V) in flight
+    float* sc = reinterpret_cast<float*>(smem_raw);         // [npast_max rounded up to 4] gate scores
+    uint32_t* hist = reinterpret_cast<uint32_t*>(sc + (npast_max + 3) / 4 * 4);   // [kDecodeBins]
+    uint2* cand = reinterpret_cast<uint2*>(hist + kDecodeBins);                   // [kDecodeRank] (key, block) of the k-th's bin
+    float* mrg = reinterpret_cast<float*>(cand);            // [NW][D + 2] the waves' (m, l, O), after the selection
+    uint32_t* keep = reinterpret_cast<uint32_t*>(mrg + kDecodeScratch<D>);        // kept-block bits of the ranked bin
+    float* wmx = reinterpret_cast<float*>(keep + (npast_max + 31) / 32);          // [NW] and
+    float* wmn = wmx + NW;                                  // [NW]: the waves' largest and smallest score
+    int* wcnt = reinterpret_cast<int*>(wmn + NW);           // [NW]
+    int* ctl = wcnt + NW;                                   // [4]
+    int* sel = ctl + 4;                                     // [k + 1] kept blocks, ascending, then the own block
 
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const int r = blockIdx.x, s = blockIdx.y, skv = s / G;  // G query heads share a key/value head
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    int skv, pos;
+    if (!schedule(blockIdx.x, bhk, G * q_len, skv, pos)) return;
+    const int s = skv * G + pos / q_len, r = pos % q_len;   // G query heads share a key/value head
     const int t = N - q_len + r;                            // position of the query
     const int past = t / B;                                 // complete blocks before its own block
     const int64_t qrow = (int64_t)s * q_len + r;
 
-    for (int c = tid; c < D; c += NT) qs[c] = to_f32<T>(Q[qrow * D + c]);
-    __syncthreads();
-
-    // ---- gate scores q . centroid_j for the past blocks, a thread per centroid (all the loads of
-    // a row are independent: one memory latency per row, not one per piece)
-    if (k > 0) {
-        for (int j = tid; j < past; j += NT) {
-            const float4* c = reinterpret_cast<const float4*>(cent + ((int64_t)skv * cblocks + j) * D);
-            float a = 0.f;
-#pragma unroll
-            for (int h = 0; h < D / 4; h += 8) {            // eight independent 16-byte loads at a time
-                float4 x[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = c[h + e];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float4 y = *reinterpret_cast<const float4*>(qs + 4 * (h + e));
-                    a = fmaf(x[e].x, y.x, a); a = fmaf(x[e].y, y.y, a);
-                    a = fmaf(x[e].z, y.z, a); a = fmaf(x[e].w, y.w, a);
-                }
-            }
-            sc[j] = a;
-        }
+    // the lane's pieces of the query, for the gate (channels 64 c + 4 (lane mod 16) ..) and for q . k
+    const int piece = lane % LPR, kslot = lane / LPR;
+    const float c2 = scale * 1.4426950408889634f;           // logits in log2 units
+    uint32_t qb[4];
+    {
+        const uint4 x = *reinterpret_cast<const uint4*>(Q + qrow * D + piece * EPL);
+        qb[0] = x.x; qb[1] = x.y; qb[2] = x.z; qb[3] = x.w;
     }
-    __syncthreads();
+    hist[tid] = 0u;
+    for (int i = tid; i < (past + 31) / 32; i += NT) keep[i] = 0u;
+    if (tid < 4) ctl[tid] = 0;
 
-    // ---- the k largest scores, ties to the lower block (Section 2): radix select, 8 bits a pass
     const int want = min(k, past);
     if (past > k && k > 0) {
-        if (tid == 0) { ctl[0] = 0; ctl[1] = k; }
-        for (int shift = 24; shift >= 0; shift -= 8) {
-            if (tid < 256) hist[tid] = 0u;
-            __syncthreads();
-            const uint32_t prefix = (uint32_t)ctl[0];
-            for (int j = tid; j < past; j += NT) {
-                const uint32_t key = decode_key(sc[j]);
-                if (shift == 24 || (key >> (shift + 8)) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+        // ---- gate scores q . centroid_j: 16 lanes per centroid, D / 16 channels each
+        {
+            constexpr int CL = D / 64;                      // 16-byte loads per lane and row
+            const int cl = lane & 15, cr = lane >> 4;
+            float4 q4[CL];
+#pragma unroll
+            for (int c = 0; c < CL; ++c) {
+                const T* qc = Q + qrow * D + 64 * c + 4 * cl;
+                q4[c] = make_float4(to_f32<T>(qc[0]), to_f32<T>(qc[1]), to_f32<T>(qc[2]), to_f32<T>(qc[3]));
             }
-            __syncthreads();
-            if (wave == 0) {
-                // the bin that holds the need-th largest key: lane l owns bins 4l .. 4l+3; above[l]
-                // = keys in the bins of the lanes above it (suffix sum over the lanes)
-                const int need = ctl[1];
-                int c4[4], mine = 0;
+            const char* cs = reinterpret_cast<const char*>(cent + (int64_t)skv * cblocks * D);
+            float mx = -INFINITY, mn = INFINITY;
+            constexpr int U = 16 / CL;                      // rows in flight per lane group
+            constexpr uint32_t ROW = D * sizeof(float);
+            for (int j0 = 4 * wave; j0 < past; j0 += 4 * NW * U) {
+                float4 x[U][CL];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { c4[i] = (int)hist[4 * lane + i]; mine += c4[i]; }
-                int incl = mine;
+                for (int u = 0; u < U; ++u) {               // (past the end: the last row again, dropped)
+                    const int first = min(j0 + 4 * NW * u, past - 1);               // the same in all lanes
+                    const char* row = cs + (int64_t)first * ROW;
+                    const uint32_t o = (uint32_t)min(cr, past - 1 - first) * ROW + 16u * cl;
 #pragma unroll
-                for (int o = 1; o < kWave; o <<= 1) {
-                    const int v = __shfl_down(incl, o, kWave);
-                    if (lane + o < kWave) incl += v;
+                    for (int c = 0; c < CL; ++c) x[u][c] = *reinterpret_cast<const float4*>(row + o + 256 * c);
                 }
-                const int above = incl - mine;
-                // exactly one lane has above < need <= above + mine (the total is at least need);
-                // should the counts ever fall short, lane 0 takes it with its lowest bin
-                const bool here = (above < need && need <= incl) || (lane == 0 && incl < need);
-                if (here) {
-                    int left = need - above, b = 3;
-                    for (; b > 0; --b) {
-                        if (c4[b] >= left) break;
-                        left -= c4[b];
+                float mine = 0.f;                           // lane cl of a group keeps the score of row u = cl
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float a = 0.f;
+#pragma unroll
+                    for (int c = 0; c < CL; ++c) {
+                        a = fmaf(x[u][c].x, q4[c].x, a); a = fmaf(x[u][c].y, q4[c].y, a);
+                        a = fmaf(x[u][c].z, q4[c].z, a); a = fmaf(x[u][c].w, q4[c].w, a);
                     }
-                    ctl[0] = (int)((prefix << 8) | (uint32_t)(4 * lane + b));
-                    ctl[1] = left;
+                    a = row_sum<16>(a);
+                    mine = cl == u ? a : mine;
                 }
+                const int j = j0 + 4 * NW * cl + cr;
+                if (cl < U && j < past) {
+                    sc[j] = mine;
+                    mx = __builtin_elementwise_maximum(mx, mine);        // (hand a NaN on)
+                    mn = __builtin_elementwise_minimum(mn, mine);
+                }
+            }
+            auto fmx = [](float a, float b) { return __builtin_elementwise_maximum(a, b); };
+            auto fmn = [](float a, float b) { return __builtin_elementwise_minimum(a, b); };
+            mx = fmx(mx, dpp<0xb1>(mx)); mx = fmx(mx, dpp<0x4e>(mx)); mx = fmx(mx, dpp<0x141>(mx));
+            mn = fmn(mn, dpp<0xb1>(mn)); mn = fmn(mn, dpp<0x4e>(mn)); mn = fmn(mn, dpp<0x141>(mn));
+            mx = across_rows<8>(mx, fmx);
+            mn = across_rows<8>(mn, fmn);
+            if (lane == 0) { wmx[wave] = mx; wmn[wave] = mn; }
+        }
+        __syncthreads();
+        // ---- the k largest scores, ties to the lower block (Section 2).  A thread owns up to four
+        // consecutive blocks.
+        // sum of the counts that the waves before this one left in wcnt
+        auto waves_before = [&]() {
+            return __builtin_amdgcn_readlane(wave_prefix(lane < wave ? wcnt[lane] : 0), kWave - 1);
+        };
+        float M = wmx[0], m = wmn[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
+            M = __builtin_elementwise_maximum(M, wmx[w]);
+            m = __builtin_elementwise_minimum(m, wmn[w]);
+        }
+        // bin of a score: a non-decreasing function of it, so that every score of a higher bin is
+        // larger than every score of a lower one
+        const float inv = (float)(kDecodeBins - 1) / (M - m);
+        bool direct = M - m < INFINITY && inv < INFINITY;
+        const int j0 = 4 * tid;
+        float v[4];
+        int bin[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i] = j0 + i < past ? sc[j0 + i] : 0.f;
+            bin[i] = j0 + i < past && direct ? min((int)((v[i] - m) * inv), kDecodeBins - 1) : -1;
+        }
+        int need = k, cut = 0;
+        if (direct) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (bin[i] >= 0) atomicAdd(&hist[bin[i]], 1u);
+            __syncthreads();
+            // a thread per bin, the highest bin first: scores in the bins above it by prefix sums
+            const int bin_here = kDecodeBins - 1 - tid;
+            const int mine = (int)hist[bin_here];
+            const int incl = wave_prefix(mine);
+            if (lane == kWave - 1) wcnt[wave] = incl;
+            __syncthreads();
+            const int above = incl - mine + waves_before();
+            if (above < k && k <= above + mine) { ctl[0] = bin_here; ctl[1] = k - above; ctl[2] = mine; }
+            __syncthreads();
+            cut = ctl[0];
+            need = ctl[1];
+            direct = ctl[2] <= kDecodeRank;                 // else: many equal scores
+        }
+        bool take[4];
+        if (direct) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (bin[i] == cut) cand[atomicAdd(&ctl[3], 1)] = make_uint2(decode_key(v[i]), (uint32_t)(j0 + i));
+            __syncthreads();
+            const int c = ctl[3];
+            if (tid < c) {
+                const uint2 me = cand[tid];
+                int rank = 0;
+                for (int o = 0; o < c; ++o) {
+                    const uint2 x = cand[o];
+                    rank += (int)(x.x > me.x) | ((int)(x.x == me.x) & (int)(x.y < me.y));
+                }
+                if (rank < need) atomicOr(&keep[me.y >> 5], 1u << (me.y & 31));
+            }
+            __syncthreads();
+            const uint32_t bits = j0 < past ? keep[j0 >> 5] >> (j0 & 31) : 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) take[i] = bin[i] > cut || (j0 + i < past && ((bits >> i) & 1u));
+        } else {
+            // radix select over the bits of the order-preserving keys, 8 bits a pass
+            __syncthreads();
+            if (tid == 0) { ctl[0] = 0; ctl[1] = k; }
+            for (int shift = 24; shift >= 0; shift -= 8) {
+                if (tid < 256) hist[tid] = 0u;
+                __syncthreads();
+                const uint32_t prefix = (uint32_t)ctl[0];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t key = decode_key(v[i]);
+                    if (j0 + i < past && (shift == 24 || (key >> (shift + 8)) == prefix))
+                        atomicAdd(&hist[(key >> shift) & 255u], 1u);
+                }
+                __syncthreads();
+                if (wave == 0) {
+                    // the bin that holds the need-th largest key
+                    const int left_all = ctl[1];
+                    // (descending: lane l owns bins 255 - 4l .. 252 - 4l)
+                    int c4[4], mine = 0;
+                    const int b0 = 4 * (kWave - 1 - lane);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { c4[i] = (int)hist[b0 + i]; mine += c4[i]; }
+                    const int incl = wave_prefix(mine), above = incl - mine;
+                    if (above < left_all && left_all <= incl) {      // (exactly one lane)
+                        int left = left_all - above, b = 3;
+                        for (; b > 0; --b) {
+                            if (c4[b] >= left) break;
+                            left -= c4[b];
+                        }
+                        ctl[0] = (int)((prefix << 8) | (uint32_t)(b0 + b));
+                        ctl[1] = left;
+                    }
+                }
+                __syncthreads();
+            }
+            // kept: keys above the k-th largest, and the first `need` blocks whose key equals it
+            const uint32_t T0 = (uint32_t)ctl[0];
+            need = ctl[1];
+            int eq = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) eq += (int)(j0 + i < past && decode_key(v[i]) == T0);
+            const int incl = wave_prefix(eq);
+            if (lane == kWave - 1) wcnt[wave] = incl;
+            __syncthreads();
+            int before = incl - eq + waves_before();
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t key = decode_key(v[i]);
+                const bool tie = j0 + i < past && key == T0;
+                take[i] = (j0 + i < past && key > T0) || (tie && before < need);
+                before += (int)tie;
             }
             __syncthreads();
         }
-        // kept: key above the k-th largest key T, and the first `need` blocks whose key equals T.
-        // Wave 0, a contiguous chunk of blocks per lane, two passes around two prefix sums.
-        if (wave == 0) {
-            const uint32_t T0 = (uint32_t)ctl[0];
-            const int need = ctl[1];
-            const int chunk = (past + kWave - 1) / kWave;
-            const int lo = min(lane * chunk, past), hi = min(lo + chunk, past);
-            int gt = 0, eq = 0;
-            for (int j = lo; j < hi; ++j) {
-                const uint32_t key = decode_key(sc[j]);
-                gt += key > T0;
-                eq += key == T0;
-            }
-            int eq_before = eq, kept;
+        // kept blocks in ascending order: places by prefix sums over the threads
+        int cnt = 0;
 #pragma unroll
-            for (int o = 1; o < kWave; o <<= 1) {
-                const int v = __shfl_up(eq_before, o, kWave);
-                if (lane >= o) eq_before += v;
-            }
-            eq_before -= eq;
-            int quota = min(max(need - eq_before, 0), eq);
-            kept = gt + quota;
-            int pos = kept;
+        for (int i = 0; i < 4; ++i) cnt += (int)take[i];
+        const int incl = wave_prefix(cnt);
+        if (lane == kWave - 1) wcnt[wave] = incl;
+        __syncthreads();
+        int place = incl - cnt + waves_before();
 #pragma unroll
-            for (int o = 1; o < kWave; o <<= 1) {
-                const int v = __shfl_up(pos, o, kWave);
-                if (lane >= o) pos += v;
-            }
-            pos -= kept;
-            for (int j = lo; j < hi; ++j) {
-                const uint32_t key = decode_key(sc[j]);
-                bool take = key > T0;
-                if (key == T0 && quota > 0) { take = true; --quota; }
-                if (take && pos < k) sel[pos++] = j;
-            }
-        }
+        for (int i = 0; i < 4; ++i)
+            if (take[i] && place < k) sel[place++] = j0 + i;
     } else {
-        for (int j = tid; j < want; j += NT) sel[j] = j;    // fewer past blocks than k: keep them all
+        for (int j = tid; j < want; j += NT) sel[j] = j;    // no more past blocks than k: keep them all
     }
+    if (tid == 0) sel[want] = past;
     __syncthreads();
     if (idx_out)
         for (int c = tid; c < k; c += NT) idx_out[qrow * k + c] = c < want ? sel[c] : -1;
 
-    // ---- attention over the kept blocks and the own block (keys own*B .. t), one block per wave
-    // at a time, 64 keys a step.  Scores: a lane per key (the pieces of its K row are independent
-    // loads).  P V: a lane per (key, 16-byte piece of its V row), KPI keys per load instruction,
-    // all instructions of a step independent; the lanes that hold the same piece are summed at
-    // the end.
-    constexpr int PPR = D * (int)sizeof(T) / 16;            // 16-byte pieces per row
-    constexpr int EPP = 16 / (int)sizeof(T);                // elements per piece
-    constexpr int KPI = kWave / PPR;                        // keys per load instruction
-    const int piece = lane % PPR, kslot = lane / PPR;
-    const int nb = want + 1;
-    float m = -INFINITY, l = 0.f, acc[EPP];
+    // ---- attention over want * B + (t mod B) + 1 keys: position p is key p mod B of kept block p / B,
+    // the own block last.  The waves walk the positions together, RPI positions per wave and load
+    // instruction: the queries of a key/value head that run side by side on one XCD then pass the
+    // same stretch of keys at about the same time and find each other's blocks in its L2.
+    const int total = want * B + (t - past * B) + 1;
+    float m = -INFINITY, l = 0.f, acc[EPL];                 // log2 units
 #pragma unroll
-    for (int e = 0; e < EPP; ++e) acc[e] = 0.f;
-    float* pw = ps + wave * kWave;
-    for (int i = wave; i < nb; i += NW) {
-        const int j = i < want ? sel[i] : past;
-        const int nk = i < want ? B : t - past * B + 1;
-        const int64_t base = (int64_t)skv * N + (int64_t)j * B;
-        for (int u0 = 0; u0 < nk; u0 += kWave) {
-            const int u = u0 + lane;
-            // (a lane past the end reads the block's last key again and drops the result: the
-            // loads stay unconditional)
-            const float zz = scale * decode_dot<T, D>(K + (base + min(u, nk - 1)) * D, qs);
-            const float z = u < nk ? zz : -INFINITY;
-            const float m_new = fmaxf(m, wave_max(z));
-            const float p = __expf(z - m_new);              // exp(-inf) = 0 for idle lanes
-            const float alpha = __expf(m - m_new);          // first step: exp(-inf) = 0
-            l = l * alpha + wave_sum(p);
-            m = m_new;
-            pw[lane] = p;
-            __builtin_amdgcn_wave_barrier();
+    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+    constexpr uint32_t ROWB = D * sizeof(T);
+    const char* Ks = reinterpret_cast<const char*>(K) + (int64_t)skv * N * ROWB;
+    const char* Vs = reinterpret_cast<const char*>(V) + (int64_t)skv * N * ROWB;
+    auto widen = [](const uint4& x, float (&f)[EPL]) {
+        const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-            for (int e = 0; e < EPP; ++e) acc[e] *= alpha;
-            const int cnt = min(kWave, nk - u0);
-#pragma unroll 8
-            for (int a0 = 0; a0 < kWave; a0 += KPI) {
-                const int a = a0 + kslot;
-                const float pa = a < cnt ? pw[a] : 0.f;
-                const T* vr = V + (base + u0 + min(a, cnt - 1)) * D + piece * EPP;
-                float v[EPP];
-                if constexpr (sizeof(T) == 2) {
-                    Vec8<T>::load(vr, v);
-                } else {
-                    const float4 x = *reinterpret_cast<const float4*>(vr);
-                    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-                }
-#pragma unroll
-                for (int e = 0; e < EPP; ++e) acc[e] = fmaf(pa, v[e], acc[e]);
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (sizeof(T) == 2) {
+                f[2 * i] = __uint_as_float(w[i] << 16);
+                f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+            } else {
+                f[i] = __uint_as_float(w[i]);
             }
-            __builtin_amdgcn_wave_barrier();
         }
+    };
+    // Blocks of whole load instructions (any B that is a multiple of RPI) and rows within 32 bits: the
+    // RPI positions of an instruction lie in one block, so the block and the row inside it are scalars
+    // that advance by additions.  Otherwise every lane divides.
+    const bool whole = B % RPI == 0 && (int64_t)N * ROWB < ((int64_t)1 << 32);
+    const int step_blk = NW * RPI / B, step_row = NW * RPI % B;
+    int blk = wave * RPI / B, in_blk = wave * RPI % B;      // whole: the next instruction's block and row
+    auto batch = [&](int p0, auto all_live) {
+        constexpr bool ALL = decltype(all_live)::value;     // every position of the batch exists
+        uint4 kr[NB], vr[NB];
+        // (past the end: some row that is attended anyway, weight 0)
+        if (whole) {
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                int row = sel[min(blk, want)] * B + in_blk + kslot;      // sel[want]: the own block
+                if (!ALL) row = min(row, t);
+                const uint32_t o = (uint32_t)row * ROWB + 16u * piece;
+                kr[u] = *reinterpret_cast<const uint4*>(Ks + o);
+                vr[u] = *reinterpret_cast<const uint4*>(Vs + o);
+                blk += step_blk;
+                in_blk += step_row;
+                if (in_blk >= B) { in_blk -= B; ++blk; }
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int pc = min(p0 + u * (NW * RPI) + kslot, total - 1), e = pc / B;
+                const int64_t key = (int64_t)sel[e] * B + (pc - e * B);
+                kr[u] = *reinterpret_cast<const uint4*>(Ks + key * ROWB + 16u * piece);
+                vr[u] = *reinterpret_cast<const uint4*>(Vs + key * ROWB + 16u * piece);
+            }
+        }
+        float z[NB], top = m;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            float a = 0.f;
+            if constexpr (sizeof(T) == 2) {                 // (products exact, fp32 sums)
+                const uint32_t w[4] = {kr[u].x, kr[u].y, kr[u].z, kr[u].w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a = dot2(w[i], qb[i], a);
+            } else {
+                float f[EPL];
+                widen(kr[u], f);
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) a = fmaf(f[e], __uint_as_float(qb[e]), a);
+            }
+            z[u] = row_sum<LPR>(a) * c2;
+            if (!ALL && p0 + u * (NW * RPI) + kslot >= total) z[u] = -INFINITY;
+            top = fmaxf(top, z[u]);
+        }
+        // (a lane group without a live key so far keeps m = -inf, l = 0: exponents are taken against 0)
+        const float ref = ALL ? top : top == -INFINITY ? 0.f : top;
+        const float alpha = __builtin_amdgcn_exp2f(m - ref);
+        m = top;
+        l *= alpha;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[e] *= alpha;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const float p = __builtin_amdgcn_exp2f(z[u] - ref);
+            float f[EPL];
+            widen(vr[u], f);
+            l += p;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, f[e], acc[e]);
+        }
+    };
+    for (int p0 = wave * RPI; p0 < total; p0 += NB * NW * RPI) {
+        if (p0 + (NB - 1) * NW * RPI + RPI <= total) batch(p0, std::true_type());
+        else batch(p0, std::false_type());
     }
-    // the lanes of a wave that hold the same piece (every kslot)
+    // ---- merge: the lane groups of a wave, then the waves through LDS
+    auto weight = [](float a, float b) { return a == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(a - b); };
+    auto add = [](float a, float b) { return a + b; };
+    {
+        const float top = across_rows<LPR>(m, [](float a, float b) { return fmaxf(a, b); });
+        const float wt = weight(m, top);
+        m = top;
+        l = across_rows<LPR>(l * wt, add);
 #pragma unroll
-    for (int o = PPR; o < kWave; o <<= 1)
-#pragma unroll
-        for (int e = 0; e < EPP; ++e) acc[e] += __shfl_xor(acc[e], o, kWave);
-    // ---- merge the waves (a wave without a block has m = -inf, l = 0: weight 0)
+        for (int e = 0; e < EPL; ++e) acc[e] = across_rows<LPR>(acc[e] * wt, add);
+    }
     float* mw = mrg + wave * (D + 2);
     if (lane == 0) { mw[0] = m; mw[1] = l; }
     if (kslot == 0) {
 #pragma unroll
-        for (int e = 0; e < EPP; ++e) mw[2 + piece * EPP + e] = acc[e];
+        for (int e = 0; e < EPL; ++e) mw[2 + piece * EPL + e] = acc[e];
     }
     __syncthreads();
-    float M = -INFINITY;
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, mrg[w * (D + 2)]);
-    float L = 0.f;
-    for (int w = 0; w < NW; ++w) L += mrg[w * (D + 2) + 1] * __expf(mrg[w * (D + 2)] - M);
-    for (int c = tid; c < D; c += NT) {
-        float o = 0.f;
-        for (int w = 0; w < NW; ++w) o = fmaf(mrg[w * (D + 2) + 2 + c], __expf(mrg[w * (D + 2)] - M), o);
-        O[qrow * D + c] = from_f32<T>(o / L);
+    if (tid < D) {
+        float top = -INFINITY, L = 0.f, o = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) top = fmaxf(top, mrg[w * (D + 2)]);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float wt = weight(mrg[w * (D + 2)], top);
+            L = fmaf(wt, mrg[w * (D + 2) + 1], L);
+            o = fmaf(wt, mrg[w * (D + 2) + 2 + tid], o);
+        }
+        O[qrow * D + tid] = from_f32<T>(o / L);
+        if (tid == 0) lse[qrow] = (top + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
     }
-    if (tid == 0) lse[qrow] = M + __logf(L);
 }
 
 template <typename T, int D>
@@ -260,15 +475,15 @@ static hipError_t decode_t(const Dims& s, int q_len, const void* Q, const void* 
                            hipStream_t st)
 {
     const int npast_max = (s.N - 1) / s.B;
-    const size_t lds = sizeof(float) * (size_t)(D + npast_max + 256 + 4 + (s.k + 1) + kDecodeWaves * kWave +
-                                                kDecodeWaves * (D + 2));
+    const size_t lds = sizeof(float) * (size_t)((npast_max + 3) / 4 * 4 + kDecodeBins + kDecodeScratch<D> +
+                                                (npast_max + 31) / 32 + 3 * kDecodeWaves + 4 + s.k + 1);
     if (lds > 64 * 1024) {
         hipError_t e = ensure_dynamic_lds((const void*)decode_kernel<T, D>, (size_t)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((decode_kernel<T, D>), dim3((unsigned)q_len, (unsigned)s.bh), dim3(kDecodeThreads), lds, st,
+    hipLaunchKernelGGL((decode_kernel<T, D>), dim3((unsigned)schedule_grid(s.bhk, s.G * q_len)), dim3(kDecodeThreads), lds, st,
                        (const T*)Q, (const T*)K, (const T*)V, cent, (T*)O, lse, idx, s.N, s.B, s.k, q_len,
-                       cblocks, s.scale, s.G, npast_max);
+                       cblocks, s.scale, s.G, s.bhk, npast_max);
     return hipGetLastError();
 }
 

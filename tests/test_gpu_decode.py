@@ -119,6 +119,20 @@ def test_decode_forward(oracle, case):
         assert np.abs(a - gO)[same].max() < 2 * parity.O_TOL[dtype]
 
 
+# the selection's ends: as many past blocks as the call takes (four scores per thread), one more than
+# the kept ones, block sizes that do not fill a load instruction, top-k far above one bin's scores
+SELECTION = [("n4096_B2",       1, 1, 0, 8193,  64,   2, 40, 3, "bf16"),
+             ("n4095_B2_d128",  1, 1, 0, 8192, 128,   2, 64, 2, "f32"),
+             ("n1667_B3",       1, 2, 1, 5003,  64,   3, 64, 3, "bf16"),
+             ("one_dropped",    1, 1, 0,  330,  64,  32,  9, 2, "bf16"),
+             ("k1000_of_1200",  1, 1, 0, 4803,  64,   4, 1000, 2, "bf16")]
+
+
+@pytest.mark.parametrize("case", SELECTION, ids=[c[0] for c in SELECTION])
+def test_decode_selection_ends(oracle, case):
+    test_decode_forward(oracle, case)
+
+
 def test_decode_ties_go_to_the_lower_block():
     """All keys zero: every gate score is 0, so the kept blocks are 0 .. k-1, and the output is the
     mean of the attended values."""
