@@ -1,0 +1,730 @@
+// MoBA attention on fp32 matrix cores, key-block major, forward and backward: for fp32 tensors, and
+// for bf16 tensors whose key blocks are not whole 32-key groups (the bf16 MFMA kernels' unit).  The
+// cut is that of attn_fwd_km.hip: a workgroup owns up to 64 keys of one key block (paper Section 4.2:
+// key blocks outermost, their routed queries gathered into dense tiles) and walks the block's query
+// list, then the block's own queries under the causal mask, 16 queries per step and wave; a query's
+// contributions from different key blocks are written once, as fp32 rows [query][kept block][part],
+// and a merge kernel adds them up in a fixed order.  v_mfma_f32_16x16x4_f32 everywhere: fp32 operands,
+// products and sums.
+//
+// The plain kernels of attn_reference.hip, which served these shapes, read every key row again for
+// every query (64 FMAs per 256 bytes) and ran at 5 TFLOP/s; here a key row meets 16 queries per read.
+// What bounds these kernels now is the fp32 matrix rate (157 TFLOP/s; 32 clocks per instruction).
+// fp32, 2 x 4 heads, N = 4096, d = 64, B = 64, k = 7: forward 580 -> 80 us, dQ + dK + dV 1960 -> 199 us.
+//
+// Operand layouts (lane = 16 g + m): a contraction over channels takes channels 16 t + 4 g + i in the
+// i-th of four instructions, so that one 16-byte read per lane feeds four; a contraction over keys (or
+// queries) takes rows 4 g + i, which is where the result layout of the product before has them, and
+// its other operand comes from a row-major tile with output channel 4 m + mt, one 16-byte read for the
+// four instructions mt = 0 .. 3.  Tiles in LDS have rows of D + 4 words: both reads are conflict-free.
+#include "mfma.h"
+
+namespace moba {
+
+namespace {
+
+__device__ __forceinline__ f32x4_t mfma4(float a, float b, f32x4_t c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+template <int D>
+struct F32Cfg {
+    static constexpr int LD = D + 4;                   // words per row of a tile in LDS
+    static constexpr int MT = D / 16;                  // 16-channel tiles of a row
+    static constexpr int H = D / 64;                   // 16-byte reads per lane and transposed row
+    static constexpr int NWF = 4;                      // waves per workgroup, forward
+    static constexpr int NWB = D == 64 ? 8 : 4;        // backward
+    static constexpr size_t fwd_lds(int nt) { return sizeof(float) * LD * (size_t)(2 * 16 * nt + NWF * 16); }
+    static constexpr int bwd_wave_words(int nt) { return 2 * 16 * LD + 16 * (16 * nt + 4) + 32; }
+    static constexpr size_t bwd_lds(int nt)
+    {
+        return sizeof(float) * ((size_t)2 * 16 * nt * LD + (size_t)NWB * bwd_wave_words(nt));
+    }
+};
+
+// how a row of T comes in: CPR lanes of 16 bytes, RPI rows per load instruction, NI instructions for 16 rows
+template <typename T, int D>
+struct Gather {
+    static constexpr int CPR = D * (int)sizeof(T) / 16, RPI = kWave / CPR, NI = 16 / RPI, EPL = 16 / (int)sizeof(T);
+};
+
+// the 16 bytes of a lane as fp32 to LDS
+template <typename T>
+__device__ __forceinline__ void put(float* dst, const u32x4_t& x)
+{
+    if constexpr (sizeof(T) == 4) {
+        *reinterpret_cast<u32x4_t*>(dst) = x;
+    } else {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            u32x4_t y;
+            y[0] = x[2 * h] << 16; y[1] = x[2 * h] & 0xffff0000u;
+            y[2] = x[2 * h + 1] << 16; y[3] = x[2 * h + 1] & 0xffff0000u;
+            *reinterpret_cast<u32x4_t*>(dst + 4 * h) = y;
+        }
+    }
+}
+
+// rows first .. first + rows of X -> tile[row][D + 4]; rows nk and beyond read as zero
+template <typename T, int D, int NTHREADS>
+__device__ __forceinline__ void stage_rows(const T* __restrict__ X, float* tile, int rows, int nk, int tid)
+{
+    constexpr int CPR = Gather<T, D>::CPR, EPL = Gather<T, D>::EPL;
+    for (int i = tid; i < rows * CPR; i += NTHREADS) {
+        const int r = i / CPR, c = i % CPR;
+        u32x4_t x = {0u, 0u, 0u, 0u};
+        if (r < nk) x = *reinterpret_cast<const u32x4_t*>(X + (size_t)r * D + c * EPL);
+        put<T>(tile + r * (D + 4) + c * EPL, x);
+    }
+}
+
+// the walk of a workgroup: positions 0 .. nlist - 1 are the block's list, then its own queries from the
+// part's first key on; positions past the end read as the first own query
+struct Walk {
+    const int32_t* src;
+    int nlist, llast, own0, own_e, total;
+    __device__ __forceinline__ int at(int a) const
+    {
+        const int listed = src[min(a, llast)];
+        const int t = a < nlist ? listed : (own0 + (a - nlist)) | own_e;
+        return a >= total ? own0 | own_e : t;
+    }
+};
+
+}  // namespace
+
+// NT: 16-key tiles of a part
+template <typename T, int D, int NT>
+__global__ __launch_bounds__(F32Cfg<D>::NWF * kWave) void fwd_f32_km_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ off,
+    const int32_t* __restrict__ ql, float* __restrict__ PO, float2* __restrict__ Pml, int N, int B, int n, int k,
+    int nsub, int pk, int nsplit, float scale, int64_t R, int bh, int G)
+{
+    using C = F32Cfg<D>;
+    using Ga = Gather<T, D>;
+    constexpr int NW = C::NWF, LD = C::LD;
+    extern __shared__ __align__(16) float sm[];
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, m16 = lane & 15, g = lane >> 4;
+    float* sK = sm;
+    float* sV = sK + 16 * NT * LD;
+    float* stQ = sV + 16 * NT * LD + wave * 16 * LD;
+    int s, u;                                               // slice, (key block, part, share of the walk)
+    if (!schedule(blockIdx.x, bh, n * nsub * nsplit, s, u)) return;
+    const int split = u % nsplit, jc = u / nsplit, j = jc / nsub, c = jc - j * nsub;
+    const int own_first = c * pk, nk = min(pk, B - own_first);
+    const int64_t sbase = (int64_t)s * N, kvbase = (int64_t)(s / G) * N;
+    const int32_t* os = off + (int64_t)s * (n + 1);
+    const int lo = os[j];
+    Walk w;
+    w.nlist = os[j + 1] - lo;
+    w.src = w.nlist > 0 ? ql + (int64_t)s * R + lo : os;
+    w.llast = max(w.nlist - 1, 0);
+    w.own0 = j * B + own_first;
+    w.own_e = k << 24;
+    w.total = w.nlist + (B - own_first);
+    stage_rows<T, D, NW * kWave>(K + (kvbase + w.own0) * D, sK, 16 * NT, nk, tid);
+    stage_rows<T, D, NW * kWave>(V + (kvbase + w.own0) * D, sV, 16 * NT, nk, tid);
+    __syncthreads();
+
+    const float c2 = scale * kLog2e;
+    const int64_t slots = (int64_t)(k + 1) * nsub;
+    const int grow = lane / Ga::CPR, gcol = (lane % Ga::CPR) * Ga::EPL;
+    const T* Qs = Q + sbase * D + gcol;
+    auto ids = [&](int a0, int (&t)[Ga::NI]) {
+#pragma unroll
+        for (int i = 0; i < Ga::NI; ++i) t[i] = w.at(a0 + Ga::RPI * i + grow);
+    };
+    auto fetch = [&](const int (&t)[Ga::NI], u32x4_t (&q)[Ga::NI]) {
+#pragma unroll
+        for (int i = 0; i < Ga::NI; ++i) q[i] = *reinterpret_cast<const u32x4_t*>(Qs + (int64_t)list_query(t[i]) * D);
+    };
+    const int stride = 16 * NW * nsplit;
+    int a0 = 16 * (split * NW + wave);
+    int tA[Ga::NI], tN[Ga::NI];
+    u32x4_t qr[Ga::NI];
+    ids(a0, tA);
+    ids(a0 + stride, tN);
+    fetch(tA, qr);
+    for (; a0 < w.total; a0 += stride) {
+        // park the 16 rows, the list entry behind each; the next step's loads go out
+#pragma unroll
+        for (int i = 0; i < Ga::NI; ++i) {
+            float* row = stQ + (grow + Ga::RPI * i) * LD;
+            put<T>(row + gcol, qr[i]);
+            if (gcol == 0) reinterpret_cast<int*>(row)[D] = tA[i];
+        }
+#pragma unroll
+        for (int i = 0; i < Ga::NI; ++i) tA[i] = tN[i];
+        ids(a0 + 2 * stride, tN);
+        fetch(tA, qr);
+        __builtin_amdgcn_wave_barrier();
+        // S^T: keys x queries
+        f32x4_t x[NT];
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt) x[kt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < C::MT; ++t) {
+            const f32x4_t q = *reinterpret_cast<const f32x4_t*>(stQ + m16 * LD + 16 * t + 4 * g);
+#pragma unroll
+            for (int kt = 0; kt < NT; ++kt) {
+                const f32x4_t a = *reinterpret_cast<const f32x4_t*>(sK + (16 * kt + m16) * LD + 16 * t + 4 * g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[kt] = mfma4(a[i], q[i], x[kt]);
+            }
+        }
+        // own row r sees keys 0 .. r of the part; keys beyond the part's do not exist
+        const int av = a0 + m16, r = av < w.nlist ? nk - 1 : min(av - w.nlist, nk - 1);
+        float mref = -INFINITY;
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                x[kt][i] = 16 * kt + 4 * g + i <= r ? x[kt][i] * c2 : -INFINITY;
+                mref = max_nan(mref, x[kt][i]);
+            }
+        mref = max_nan(mref, __shfl_xor(mref, 16, kWave));
+        mref = max_nan(mref, __shfl_xor(mref, 32, kWave));
+        float l = 0.f;
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                x[kt][i] = fast_exp2(x[kt][i] - mref);
+                l += x[kt][i];
+            }
+        l += __shfl_xor(l, 16, kWave);
+        l += __shfl_xor(l, 32, kWave);
+        // O^T = V^T P^T
+        f32x4_t o[C::MT];
+#pragma unroll
+        for (int mt = 0; mt < C::MT; ++mt) o[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int h = 0; h < C::H; ++h) {
+                    const f32x4_t a = *reinterpret_cast<const f32x4_t*>(sV + (16 * kt + 4 * g + i) * LD + 64 * h + 4 * m16);
+#pragma unroll
+                    for (int mt = 0; mt < 4; ++mt) o[4 * h + mt] = mfma4(a[mt], x[kt][i], o[4 * h + mt]);
+                }
+        // the partial: this lane holds channels 64 h + 16 g .. + 15 of its row
+        if (av < w.total) {
+            // clamped: lists that do not match the rows of kept blocks give a wrong result, never an
+            // address outside the partials
+            const int note = reinterpret_cast<const int*>(stQ + m16 * LD)[D];
+            const int64_t prow = (sbase + min(list_query(note), N - 1)) * slots + (int64_t)min(list_slot(note), k) * nsub + c;
+            float* dst = PO + prow * D + 16 * g;
+#pragma unroll
+            for (int h = 0; h < C::H; ++h)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    *reinterpret_cast<f32x4_t*>(dst + 64 * h + 4 * i) =
+                        f32x4_t{o[4 * h][i], o[4 * h + 1][i], o[4 * h + 2][i], o[4 * h + 3][i]};
+            if (g == 0) Pml[prow] = make_float2(mref, l);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// A query's partials, [kept block or own block][part]: which exist
+struct Slots {
+    int k, nsub, own_parts;
+    __device__ __forceinline__ bool counts(const int32_t* irow, int e, int c) const
+    {
+        return e == k ? c < own_parts : irow[e] >= 0;
+    }
+};
+
+// O_t = sum_p 2^(m_p - M) o_p / sum_p 2^(m_p - M) l_p, lse_t = (M + log2 L) ln 2; D / 4 lanes per query,
+// partials in order, eight loads in flight
+template <typename T, int D>
+__global__ __launch_bounds__(256) void fwd_f32_merge_kernel(
+    const int32_t* __restrict__ idx, const float* __restrict__ PO, const float2* __restrict__ Pml, T* __restrict__ O,
+    float* __restrict__ lse, int N, int B, int k, int nsub, int pk, int64_t rows_total)
+{
+    constexpr int L = D / 4, CH = 8;
+    const int64_t row = (int64_t)blockIdx.x * (256 / L) + threadIdx.x / L;
+    const int part = threadIdx.x % L;
+    if (row >= rows_total) return;
+    const Slots sl = {k, nsub, (int)(row % N) % B / pk + 1};
+    const int slots = (k + 1) * nsub;
+    const int32_t* irow = idx + row * k;
+    const float2* ml = Pml + row * slots;
+    const float* po = PO + row * slots * D + 4 * part;
+    float M = -INFINITY;
+    for (int p = part; p < slots; p += L)                   // the lanes of a query share its partials out
+        if (sl.counts(irow, p / nsub, p % nsub)) M = max_nan(M, ml[p].x);
+    for (int o = 1; o < L; o <<= 1) M = max_nan(M, __shfl_xor(M, o, kWave));
+    float Ls = 0.f;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < slots; p0 += CH) {
+        float2 x[CH];
+        f32x4_t v[CH];
+        bool ok[CH];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int p = min(p0 + i, slots - 1);
+            ok[i] = p0 + i < slots && sl.counts(irow, p / nsub, p % nsub);
+            x[i] = ml[p];
+            v[i] = *reinterpret_cast<const f32x4_t*>(po + (int64_t)p * D);
+        }
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            if (!ok[i]) continue;                           // (holds whatever the workspace held)
+            const float wt = fast_exp2(x[i].x - M);
+            Ls = fmaf(wt, x[i].y, Ls);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[c] = fmaf(wt, v[i][c], acc[c]);
+        }
+    }
+    const float inv = 1.f / Ls;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) O[row * D + 4 * part + c] = from_f32<T>(acc[c] * inv);
+    if (part == 0) lse[row] = (M + fast_log2(Ls)) * kLn2;
+}
+
+// Backward: per step of 16 queries
+//   S = Q K^T, dP = dO V^T - D        queries x keys, so that P and dS are operands over the queries
+//   dV^T += dO^T P, dK^T += Q^T dS    channels x keys, kept in registers for the whole walk
+//   dQ^T  = K^T dS^T                  dS turned over through LDS; written as a partial
+// want_dq / want_dkv: which results the caller asked for.  The dK and dV of a workgroup's waves are
+// added up through LDS; with several shares of a walk or several query heads per key/value head they go
+// to sums[dK | dV][query slice][share][N][D] and kv_sum_f32_kernel adds those up in order.
+template <typename T, int D, int NT>
+__global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
+    const float2* __restrict__ ld, const int32_t* __restrict__ off, const int32_t* __restrict__ ql,
+    float* __restrict__ PdQ, T* __restrict__ dK, T* __restrict__ dV, float* __restrict__ sums, int N, int B, int n,
+    int k, int nsub, int pk, int nsplit, float scale, int64_t R, int bh, int G, int want_dq, int want_dkv)
+{
+    using C = F32Cfg<D>;
+    using Ga = Gather<T, D>;
+    constexpr int NW = C::NWB, LD = C::LD, TL = 16 * NT + 4;
+    extern __shared__ __align__(16) float sm[];
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, m16 = lane & 15, g = lane >> 4;
+    float* sK = sm;
+    float* sV = sK + 16 * NT * LD;
+    float* stQ = sV + 16 * NT * LD + wave * C::bwd_wave_words(NT);
+    float* stG = stQ + 16 * LD;
+    float* sT = stG + 16 * LD;                              // dS of the step, [query][key]
+    float* sl = sT + 16 * TL;                               // [16] lse log2 e, [16] -D
+    int s, u;
+    if (!schedule(blockIdx.x, bh, n * nsub * nsplit, s, u)) return;
+    const int split = u % nsplit, jc = u / nsplit, j = jc / nsub, c = jc - j * nsub;
+    const int own_first = c * pk, nk = min(pk, B - own_first);
+    const int64_t sbase = (int64_t)s * N, kvbase = (int64_t)(s / G) * N;
+    const int32_t* os = off + (int64_t)s * (n + 1);
+    const int lo = os[j];
+    Walk w;
+    w.nlist = os[j + 1] - lo;
+    w.src = w.nlist > 0 ? ql + (int64_t)s * R + lo : os;
+    w.llast = max(w.nlist - 1, 0);
+    w.own0 = j * B + own_first;
+    w.own_e = k << 24;
+    w.total = w.nlist + (B - own_first);
+    stage_rows<T, D, NW * kWave>(K + (kvbase + w.own0) * D, sK, 16 * NT, nk, tid);
+    stage_rows<T, D, NW * kWave>(V + (kvbase + w.own0) * D, sV, 16 * NT, nk, tid);
+    __syncthreads();
+
+    const float c2 = scale * kLog2e;
+    const int64_t slots = (int64_t)(k + 1) * nsub;
+    const int grow = lane / Ga::CPR, gcol = (lane % Ga::CPR) * Ga::EPL;
+    const T* Qs = Q + sbase * D + gcol;
+    const T* Gs = dO + sbase * D + gcol;
+    auto ids = [&](int a0, int (&t)[Ga::NI], int& tl) {
+#pragma unroll
+        for (int i = 0; i < Ga::NI; ++i) t[i] = w.at(a0 + Ga::RPI * i + grow);
+        tl = list_query(w.at(a0 + m16));
+    };
+    auto fetch = [&](int a0, const int (&t)[Ga::NI], int tl, u32x4_t (&q)[Ga::NI], u32x4_t (&gr)[Ga::NI], float2& x) {
+#pragma unroll
+        for (int i = 0; i < Ga::NI; ++i) {
+            q[i] = *reinterpret_cast<const u32x4_t*>(Qs + (int64_t)list_query(t[i]) * D);
+            gr[i] = *reinterpret_cast<const u32x4_t*>(Gs + (int64_t)list_query(t[i]) * D);
+        }
+        x = ld[sbase + tl];
+        if (a0 + m16 >= w.total) x = make_float2(INFINITY, 0.f);           // no such row: P = 0
+    };
+    f32x4_t dKT[C::MT][NT], dVT[C::MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt) {
+            dKT[mt][kt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            dVT[mt][kt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    const int stride = 16 * NW * nsplit;
+    int a0 = 16 * (split * NW + wave);
+    int tA[Ga::NI], tN[Ga::NI], tlA, tlN;
+    u32x4_t qr[Ga::NI], gr[Ga::NI];
+    float2 xl;
+    ids(a0, tA, tlA);
+    ids(a0 + stride, tN, tlN);
+    fetch(a0, tA, tlA, qr, gr, xl);
+    for (; a0 < w.total; a0 += stride) {
+#pragma unroll
+        for (int i = 0; i < Ga::NI; ++i) {
+            float* row = stQ + (grow + Ga::RPI * i) * LD;
+            put<T>(row + gcol, qr[i]);
+            put<T>(row + 16 * LD + gcol, gr[i]);
+            if (gcol == 0) reinterpret_cast<int*>(row)[D] = tA[i];
+        }
+        if (lane < 16) { sl[lane] = xl.x; sl[16 + lane] = xl.y; }
+#pragma unroll
+        for (int i = 0; i < Ga::NI; ++i) tA[i] = tN[i];
+        tlA = tlN;
+        ids(a0 + 2 * stride, tN, tlN);
+        fetch(a0 + stride, tA, tlA, qr, gr, xl);
+        __builtin_amdgcn_wave_barrier();
+        const f32x4_t l4 = *reinterpret_cast<const f32x4_t*>(sl + 4 * g);
+        const f32x4_t nd = *reinterpret_cast<const f32x4_t*>(sl + 16 + 4 * g);
+        f32x4_t x[NT], dp[NT];
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt) { x[kt] = f32x4_t{0.f, 0.f, 0.f, 0.f}; dp[kt] = nd; }
+#pragma unroll
+        for (int t = 0; t < C::MT; ++t) {
+            const f32x4_t q = *reinterpret_cast<const f32x4_t*>(stQ + m16 * LD + 16 * t + 4 * g);
+            const f32x4_t gq = *reinterpret_cast<const f32x4_t*>(stG + m16 * LD + 16 * t + 4 * g);
+#pragma unroll
+            for (int kt = 0; kt < NT; ++kt) {
+                const f32x4_t a = *reinterpret_cast<const f32x4_t*>(sK + (16 * kt + m16) * LD + 16 * t + 4 * g);
+                const f32x4_t b = *reinterpret_cast<const f32x4_t*>(sV + (16 * kt + m16) * LD + 16 * t + 4 * g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    x[kt] = mfma4(q[i], a[i], x[kt]);
+                    dp[kt] = mfma4(gq[i], b[i], dp[kt]);
+                }
+            }
+        }
+        // this lane: key 16 kt + m16 of the part, queries a0 + 4 g + i
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int own = a0 + 4 * g + i - w.nlist, key = 16 * kt + m16;
+                const bool seen = key < nk && (own < 0 || key <= own);
+                const float p = seen ? fast_exp2(fmaf(x[kt][i], c2, -l4[i])) : 0.f;
+                x[kt][i] = p;
+                dp[kt][i] *= p;
+            }
+        if (want_dq) {
+#pragma unroll
+            for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sT[(4 * g + i) * TL + 16 * kt + m16] = dp[kt][i];
+        }
+        if (want_dkv) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int h = 0; h < C::H; ++h) {
+                    const f32x4_t q = *reinterpret_cast<const f32x4_t*>(stQ + (4 * g + i) * LD + 64 * h + 4 * m16);
+                    const f32x4_t gq = *reinterpret_cast<const f32x4_t*>(stG + (4 * g + i) * LD + 64 * h + 4 * m16);
+#pragma unroll
+                    for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+                        for (int mt = 0; mt < 4; ++mt) {
+                            dVT[4 * h + mt][kt] = mfma4(gq[mt], x[kt][i], dVT[4 * h + mt][kt]);
+                            dKT[4 * h + mt][kt] = mfma4(q[mt], dp[kt][i], dKT[4 * h + mt][kt]);
+                        }
+                }
+        }
+        if (want_dq) {
+            __builtin_amdgcn_wave_barrier();
+            f32x4_t o[C::MT];
+#pragma unroll
+            for (int mt = 0; mt < C::MT; ++mt) o[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kt = 0; kt < NT; ++kt) {
+                const f32x4_t b = *reinterpret_cast<const f32x4_t*>(sT + m16 * TL + 16 * kt + 4 * g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int h = 0; h < C::H; ++h) {
+                        const f32x4_t a = *reinterpret_cast<const f32x4_t*>(sK + (16 * kt + 4 * g + i) * LD + 64 * h + 4 * m16);
+#pragma unroll
+                        for (int mt = 0; mt < 4; ++mt) o[4 * h + mt] = mfma4(a[mt], b[i], o[4 * h + mt]);
+                    }
+            }
+            if (a0 + m16 < w.total) {
+                const int note = reinterpret_cast<const int*>(stQ + m16 * LD)[D];
+                const int64_t prow = (sbase + min(list_query(note), N - 1)) * slots + (int64_t)min(list_slot(note), k) * nsub + c;
+                float* dst = PdQ + prow * D + 16 * g;
+#pragma unroll
+                for (int h = 0; h < C::H; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        *reinterpret_cast<f32x4_t*>(dst + 64 * h + 4 * i) =
+                            f32x4_t{o[4 * h][i], o[4 * h + 1][i], o[4 * h + 2][i], o[4 * h + 3][i]};
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (!want_dkv) return;
+    // sum over the waves, in order, through LDS: over the K and V tiles (row-major, keys x channels)
+    __syncthreads();
+    for (int wv = 0; wv < NW; ++wv) {
+        if (wave == wv) {
+#pragma unroll
+            for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+                for (int h = 0; h < C::H; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        // result rows 4 g + i of tile 4 h + mt: channel 64 h + 16 g + 4 i + mt of key 16 kt + m16
+                        float* pk_ = sK + (16 * kt + m16) * LD + 64 * h + 16 * g + 4 * i;
+                        float* pv_ = sV + (16 * kt + m16) * LD + 64 * h + 16 * g + 4 * i;
+                        f32x4_t a = {dKT[4 * h][kt][i], dKT[4 * h + 1][kt][i], dKT[4 * h + 2][kt][i], dKT[4 * h + 3][kt][i]};
+                        f32x4_t b = {dVT[4 * h][kt][i], dVT[4 * h + 1][kt][i], dVT[4 * h + 2][kt][i], dVT[4 * h + 3][kt][i]};
+                        if (wv > 0) {
+                            a += *reinterpret_cast<const f32x4_t*>(pk_);
+                            b += *reinterpret_cast<const f32x4_t*>(pv_);
+                        }
+                        *reinterpret_cast<f32x4_t*>(pk_) = a;
+                        *reinterpret_cast<f32x4_t*>(pv_) = b;
+                    }
+        }
+        __syncthreads();
+    }
+    for (int i = tid; i < 2 * nk * (D / 4); i += NW * kWave) {
+        const int which = i / (nk * (D / 4)), rem = i % (nk * (D / 4)), key = rem / (D / 4), ch = 4 * (rem % (D / 4));
+        f32x4_t v = *reinterpret_cast<const f32x4_t*>((which == 0 ? sK : sV) + key * LD + ch);
+        if (which == 0) v *= scale;
+        const int64_t at = w.own0 + key;
+        if (sums) {
+            *reinterpret_cast<f32x4_t*>(sums + ((((int64_t)which * bh + s) * nsplit + split) * N + at) * D + ch) = v;
+        } else {
+            T* dst = (which == 0 ? dK : dV) + (kvbase + at) * D + ch;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dst[e] = from_f32<T>(v[e]);
+        }
+    }
+}
+
+// dK, dV of a key/value slice = its sums over shares of the walk and query heads, in order
+template <typename T>
+__global__ __launch_bounds__(256) void kv_sum_f32_kernel(const float* __restrict__ sums, T* __restrict__ dK,
+                                                         T* __restrict__ dV, int64_t quads_per_slice, int bhk, int terms)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, per = quads_per_slice * bhk;
+    if (i >= 2 * per) return;
+    const int which = (int)(i / per);
+    const int64_t r = i % per, skv = r / quads_per_slice, q = r % quads_per_slice;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < terms; ++t)
+        acc += *reinterpret_cast<const f32x4_t*>(sums + ((((int64_t)which * bhk + skv) * terms + t) * quads_per_slice + q) * 4);
+    T* dst = (which == 0 ? dK : dV) + r * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dst[e] = from_f32<T>(acc[e]);
+}
+
+// dQ_t = scale * sum of its partials, in order
+template <typename T, int D>
+__global__ __launch_bounds__(256) void dq_f32_merge_kernel(const int32_t* __restrict__ idx, const float* __restrict__ PdQ,
+                                                           T* __restrict__ dQ, int N, int B, int k, int nsub, int pk,
+                                                           float scale, int64_t rows_total)
+{
+    constexpr int L = D / 4, CH = 8;
+    const int64_t row = (int64_t)blockIdx.x * (256 / L) + threadIdx.x / L;
+    const int part = threadIdx.x % L;
+    if (row >= rows_total) return;
+    const Slots sl = {k, nsub, (int)(row % N) % B / pk + 1};
+    const int slots = (k + 1) * nsub;
+    const int32_t* irow = idx + row * k;
+    const float* po = PdQ + row * slots * D + 4 * part;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < slots; p0 += CH) {
+        f32x4_t v[CH];
+        bool ok[CH];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int p = min(p0 + i, slots - 1);
+            ok[i] = p0 + i < slots && sl.counts(irow, p / nsub, p % nsub);
+            v[i] = *reinterpret_cast<const f32x4_t*>(po + (int64_t)p * D);
+        }
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+            if (ok[i]) acc += v[i];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) dQ[row * D + 4 * part + c] = from_f32<T>(acc[c] * scale);
+}
+
+// ---- shapes, workspaces, launches --------------------------------------------------------------
+
+namespace {
+
+struct Cut {
+    int nsub, pk, nt;            // parts per block, keys per part, 16-key tiles per part
+};
+
+// parts of equal size, at most `cap` keys
+Cut cut_of(const Dims& s, int cap)
+{
+    Cut c;
+    c.nsub = (s.B + cap - 1) / cap;
+    c.pk = ((s.B + c.nsub - 1) / c.nsub + 15) / 16 * 16;
+    c.nsub = (s.B + c.pk - 1) / c.pk;
+    c.nt = c.pk / 16;
+    return c;
+}
+Cut fwd_cut(const Dims& s) { return cut_of(s, 64); }
+Cut bwd_cut(const Dims& s) { return cut_of(s, s.D == 64 ? 64 : 32); }    // (d = 128: registers for the dK and dV of 32 keys)
+
+size_t partials(const Dims& s, const Cut& c) { return (size_t)s.bh * s.N * (size_t)(s.k + 1) * c.nsub; }
+
+// Shares a walk is cut into: about four workgroups per compute unit, at least one step of all waves each
+// (on average: the lists of a slice's first blocks are several times longer)
+int shares(const Dims& s, const Cut& c, int waves)
+{
+    const int64_t wgs = (int64_t)s.bh * s.n * c.nsub, steps = ((int64_t)(s.k + 1) * s.B + 16 * waves - 1) / (16 * waves);
+    const int64_t want = (1024 + wgs - 1) / wgs;
+    return (int)(want < steps ? want : steps);
+}
+
+bool sums_needed(const Dims& s, int nsplit) { return s.G * nsplit > 1; }
+
+}  // namespace
+
+// Everything the bf16 MFMA kernels do not cover, except: blocks too short for a 16-key tile to pay
+// (fewer than 8 keys), rows of more than 64 kept blocks (a list entry holds the place in 8 bits), and
+// shapes whose partial rows would take more than 16 GiB.  Those stay on the plain kernels.
+bool f32_km_path(const Dims& s)
+{
+    return !mfma_path(s) && !(s.flags & MOBA_FLAG_REFERENCE_KERNELS) && s.B >= 8 && s.k <= kKeyMajorMaxTopk &&
+           partials(s, bwd_cut(s)) * s.D * sizeof(float) <= ((size_t)16 << 30);
+}
+
+size_t forward_f32_km_ws_bytes(const Dims& s)
+{
+    const size_t p = partials(s, fwd_cut(s));
+    return a256(p * s.D * sizeof(float)) + a256(p * sizeof(float2));
+}
+
+// [D: bh*N][(lse log2 e, -D): bh*N][partial dQ][sums of dK and dV]
+size_t backward_f32_km_ld_offset(const Dims& s) { return a256(sizeof(float) * (size_t)s.bh * s.N); }
+static size_t bwd_partials_offset(const Dims& s)
+{
+    return backward_f32_km_ld_offset(s) + a256(sizeof(float2) * (size_t)s.bh * s.N);
+}
+static size_t bwd_sums_offset(const Dims& s)
+{
+    return bwd_partials_offset(s) + a256(partials(s, bwd_cut(s)) * s.D * sizeof(float));
+}
+static int bwd_shares(const Dims& s) { return s.D == 64 ? shares(s, bwd_cut(s), F32Cfg<64>::NWB) : shares(s, bwd_cut(s), F32Cfg<128>::NWB); }
+size_t backward_f32_km_ws_bytes(const Dims& s)
+{
+    const int ns = bwd_shares(s);
+    return bwd_sums_offset(s) + (sums_needed(s, ns) ? a256(2 * sizeof(float) * (size_t)s.bh * ns * s.N * s.D) : 0);
+}
+
+template <typename T, int D, int NT>
+static hipError_t fwd_launch_nt(const Dims& s, const Cut& c, const void* Q, const void* K, const void* V,
+                                const int32_t* idx, const int32_t* off, const int32_t* ql, float* PO, float2* Pml,
+                                void* O, float* lse, hipStream_t st)
+{
+    using C = F32Cfg<D>;
+    const int ns = shares(s, c, C::NWF);
+    hipError_t e = ensure_dynamic_lds((const void*)fwd_f32_km_kernel<T, D, NT>, C::fwd_lds(NT));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((fwd_f32_km_kernel<T, D, NT>), dim3((unsigned)schedule_grid(s.bh, s.n * c.nsub * ns)),
+                       dim3(C::NWF * kWave), C::fwd_lds(NT), st, (const T*)Q, (const T*)K, (const T*)V, off, ql, PO, Pml,
+                       s.N, s.B, s.n, s.k, c.nsub, c.pk, ns, s.scale, s.R, s.bh, s.G);
+    const int64_t rows = (int64_t)s.bh * s.N;
+    const int rpw = 256 / (D / 4);
+    hipLaunchKernelGGL((fwd_f32_merge_kernel<T, D>), dim3((unsigned)((rows + rpw - 1) / rpw)), dim3(256), 0, st, idx, PO,
+                       Pml, (T*)O, lse, s.N, s.B, s.k, c.nsub, c.pk, rows);
+    return hipGetLastError();
+}
+
+template <typename T, int D, int NT>
+static hipError_t bwd_launch_nt(const Dims& s, const Cut& c, const void* Q, const void* K, const void* V, const void* dO,
+                                const float2* ld, const int32_t* idx, const int32_t* off, const int32_t* ql, float* PdQ,
+                                float* sums, void* dQ, void* dK, void* dV, uint32_t parts, hipStream_t st)
+{
+    using C = F32Cfg<D>;
+    const int ns = bwd_shares(s);
+    const int want_dq = (parts & MOBA_BWD_DQ) != 0, want_dkv = (parts & MOBA_BWD_DKDV) != 0;
+    hipError_t e = ensure_dynamic_lds((const void*)bwd_f32_km_kernel<T, D, NT>, C::bwd_lds(NT));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((bwd_f32_km_kernel<T, D, NT>), dim3((unsigned)schedule_grid(s.bh, s.n * c.nsub * ns)),
+                       dim3(C::NWB * kWave), C::bwd_lds(NT), st, (const T*)Q, (const T*)K, (const T*)V, (const T*)dO, ld,
+                       off, ql, PdQ, (T*)dK, (T*)dV, sums, s.N, s.B, s.n, s.k, c.nsub, c.pk, ns, s.scale, s.R, s.bh, s.G,
+                       want_dq, want_dkv);
+    if (want_dkv && sums) {
+        const int64_t quads = (int64_t)s.N * D / 4, total = 2 * quads * s.bhk;
+        hipLaunchKernelGGL(kv_sum_f32_kernel<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, sums, (T*)dK,
+                           (T*)dV, quads, s.bhk, s.G * ns);
+    }
+    if (want_dq) {
+        const int64_t rows = (int64_t)s.bh * s.N;
+        const int rpw = 256 / (D / 4);
+        hipLaunchKernelGGL((dq_f32_merge_kernel<T, D>), dim3((unsigned)((rows + rpw - 1) / rpw)), dim3(256), 0, st, idx,
+                           PdQ, (T*)dQ, s.N, s.B, s.k, c.nsub, c.pk, s.scale, rows);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_forward_f32_km(const Dims& s, const void* Q, const void* K, const void* V, void* ws,
+                                 const int32_t* idx, const int32_t* off, const int32_t* ql, void* O, float* lse,
+                                 hipStream_t st)
+{
+    const Cut c = fwd_cut(s);
+    float* PO = static_cast<float*>(ws);
+    float2* Pml = reinterpret_cast<float2*>(static_cast<char*>(ws) + a256(partials(s, c) * s.D * sizeof(float)));
+#define MOBA_F32(T, D, NT) return fwd_launch_nt<T, D, NT>(s, c, Q, K, V, idx, off, ql, PO, Pml, O, lse, st)
+#define MOBA_F32_D(T, D)                        \
+    switch (c.nt) {                             \
+        case 1: MOBA_F32(T, D, 1);              \
+        case 2: MOBA_F32(T, D, 2);              \
+        case 3: MOBA_F32(T, D, 3);              \
+        case 4: MOBA_F32(T, D, 4);              \
+    }                                           \
+    return hipErrorInvalidValue
+    if (s.dtype == MOBA_F32) {
+        if (s.D == 64) { MOBA_F32_D(float, 64); } else { MOBA_F32_D(float, 128); }
+    } else {
+        if (s.D == 64) { MOBA_F32_D(bf16_t, 64); } else { MOBA_F32_D(bf16_t, 128); }
+    }
+#undef MOBA_F32_D
+#undef MOBA_F32
+}
+
+// ws as laid out above; the pairs (lse log2 e, -D) must be there (MOBA_BWD_PREPROCESS)
+hipError_t launch_backward_f32_km(const Dims& s, const void* Q, const void* K, const void* V, const void* dO,
+                                  const int32_t* idx, const int32_t* off, const int32_t* ql, void* dQ, void* dK,
+                                  void* dV, void* ws, uint32_t parts, hipStream_t st)
+{
+    const Cut c = bwd_cut(s);
+    char* p = static_cast<char*>(ws);
+    const float2* ld = reinterpret_cast<const float2*>(p + backward_f32_km_ld_offset(s));
+    float* PdQ = reinterpret_cast<float*>(p + bwd_partials_offset(s));
+    float* sums = sums_needed(s, bwd_shares(s)) ? reinterpret_cast<float*>(p + bwd_sums_offset(s)) : nullptr;
+#define MOBA_F32(T, D, NT) return bwd_launch_nt<T, D, NT>(s, c, Q, K, V, dO, ld, idx, off, ql, PdQ, sums, dQ, dK, dV, parts, st)
+#define MOBA_F32_64(T)                          \
+    switch (c.nt) {                             \
+        case 1: MOBA_F32(T, 64, 1);             \
+        case 2: MOBA_F32(T, 64, 2);             \
+        case 3: MOBA_F32(T, 64, 3);             \
+        case 4: MOBA_F32(T, 64, 4);             \
+    }                                           \
+    return hipErrorInvalidValue
+#define MOBA_F32_128(T)                         \
+    switch (c.nt) {                             \
+        case 1: MOBA_F32(T, 128, 1);            \
+        case 2: MOBA_F32(T, 128, 2);            \
+    }                                           \
+    return hipErrorInvalidValue
+    if (s.dtype == MOBA_F32) {
+        if (s.D == 64) { MOBA_F32_64(float); } else { MOBA_F32_128(float); }
+    } else {
+        if (s.D == 64) { MOBA_F32_64(bf16_t); } else { MOBA_F32_128(bf16_t); }
+    }
+#undef MOBA_F32_128
+#undef MOBA_F32_64
+#undef MOBA_F32
+}
+
+}  // namespace moba

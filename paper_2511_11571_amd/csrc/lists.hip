@@ -12,7 +12,7 @@
 // The bit matrix lives in LDS only and covers 1024 key blocks at a time (512 where a slice has more).
 //
 // A list entry holds the query in its low 24 bits (sequences are at most 2^24 long).  Where the
-// key-block-major attention kernels will run (key_major_path() of the shape and its flags) the
+// key-block-major attention kernels will run (lists_with_places() of the shape and its flags) the
 // high byte holds the position e of the block in the query's row of kept blocks: those kernels
 // file the partial result of (query, block) under (query, e) and would otherwise have to search
 // the row for the block (10-15 % of their time); elsewhere it is zero.  The fill pass gets e by walking the
@@ -271,7 +271,7 @@ static hipError_t build_lists_launch(const Dims& s, const int32_t* idx, int32_t*
     hipLaunchKernelGGL(lists_offsets_kernel, dim3(s.bh), block, 0, st, off, s.n);
     if (s.R > 0) {
         static_assert(kKeyMajorMaxTopk <= 255 && kListQ * kKeyMajorMaxTopk <= 65535, "slot byte, 16-bit run starts");
-        if (key_major_path(s))
+        if (lists_with_places(s))
             hipLaunchKernelGGL((lists_chunk_kernel<true, true, RANGE>), grid, block, (size_t)kListQ * s.k, st, idx,
                                cnt2, (const int32_t*)off, ql, s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);
         else

@@ -333,6 +333,21 @@ inline bool shared_workspace(const Dims& s)
     return (s.flags & MOBA_FLAG_SHARED_WORKSPACE) && mfma_path(s) && tile_forward_ok(s) && !key_major_path(s);
 }
 
+// Key-block-major attention on fp32 matrix cores (attn_f32_km.hip): fp32 tensors, and bf16 ones outside
+// mfma_path()
+bool f32_km_path(const Dims& s);
+size_t forward_f32_km_ws_bytes(const Dims& s);
+size_t backward_f32_km_ws_bytes(const Dims& s);
+size_t backward_f32_km_ld_offset(const Dims& s);
+hipError_t launch_forward_f32_km(const Dims& s, const void* Q, const void* K, const void* V, void* ws,
+                                 const int32_t* idx, const int32_t* off, const int32_t* ql, void* O, float* lse,
+                                 hipStream_t st);
+hipError_t launch_backward_f32_km(const Dims& s, const void* Q, const void* K, const void* V, const void* dO,
+                                  const int32_t* idx, const int32_t* off, const int32_t* ql, void* dQ, void* dK,
+                                  void* dV, void* ws, uint32_t parts, hipStream_t st);
+// shapes whose kernels file results by (query, place of the block in its row): the lists carry the place
+inline bool lists_with_places(const Dims& s) { return key_major_path(s) || f32_km_path(s); }
+
 size_t forward_km_ws_bytes(const Dims& s);
 size_t backward_km_ws_bytes(const Dims& s);
 hipError_t launch_dq_km(const Dims& s, const void* Q, const void* K, const void* V, const void* dO,

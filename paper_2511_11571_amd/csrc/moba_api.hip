@@ -86,6 +86,7 @@ size_t bwd_ws_bytes(const Dims& d);
 // forward: operand copies of K and V (+ the per-pair partials of the key-major kernel)
 size_t fwd_ws_bytes(const Dims& d)
 {
+    if (f32_km_path(d)) return align256(forward_f32_km_ws_bytes(d));
     if (!mfma_path(d)) return 256;
     if (key_major_path(d)) return align256(forward_km_ws_bytes(d));
     if (!tile_forward_ok(d)) return 256;                                     // the plain kernel
@@ -101,6 +102,7 @@ size_t bwd_packed_offset(const Dims& d)
 }
 size_t bwd_ws_bytes(const Dims& d)
 {
+    if (f32_km_path(d)) return align256(backward_f32_km_ws_bytes(d));
     if (!mfma_path(d)) return align256(sizeof(float) * (size_t)d.bh * d.N);
     return bwd_packed_offset(d) + align256(sizeof(float2) * (size_t)d.bh * d.N) + dkdv_heads_ws_bytes(d);
 }
@@ -433,6 +435,9 @@ int moba_forward(const moba_shape* shape, const void* Q, const void* K_eff, cons
     if (mfma_path(d) && tile_forward_ok(d))
         return hip_status(launch_forward_mfma(d, Q, K_eff, V, ws, topk_idx, blk_off, blk_q, O, lse,
                                               (hipStream_t)stream));
+    if (f32_km_path(d))
+        return hip_status(launch_forward_f32_km(d, Q, K_eff, V, ws, topk_idx, blk_off, blk_q, O, lse,
+                                                (hipStream_t)stream));
     return hip_status(
         launch_forward_reference(d, Q, K_eff, V, topk_idx, O, lse, (hipStream_t)stream));
 }
@@ -471,7 +476,16 @@ int moba_backward_parts(const moba_shape* shape, const void* Q, const void* K_ef
     if (d.R > 0 && !blk_q) return MOBA_EINVAL;
     if (!ws || ws_bytes < bwd_ws_bytes(d)) return MOBA_EWORKSPACE;
     hipStream_t hs = (hipStream_t)stream;
-    uint32_t plain = parts;
+    if (f32_km_path(d)) {
+        if (parts & MOBA_BWD_PREPROCESS) {
+            float2* ld = reinterpret_cast<float2*>(static_cast<char*>(ws) + backward_f32_km_ld_offset(d));
+            hipError_t e = launch_backward_reference(d, Q, K_eff, V, O, lse, dO, topk_idx, blk_off, blk_q, dQ, dK, dV,
+                                                     (float*)ws, MOBA_BWD_PREPROCESS, ld, hs);
+            if (e != hipSuccess) return hip_status(e);
+        }
+        if ((parts & ~(uint32_t)MOBA_BWD_PREPROCESS) == 0) return MOBA_OK;
+        return hip_status(launch_backward_f32_km(d, Q, K_eff, V, dO, topk_idx, blk_off, blk_q, dQ, dK, dV, ws, parts, hs));
+    }
     if (mfma_path(d)) {
         // D first (plain row-dot kernel), then the MFMA kernels that exist; the rest stays plain
         float2* ld = reinterpret_cast<float2*>(static_cast<char*>(ws) + bwd_packed_offset(d));
@@ -496,7 +510,7 @@ int moba_backward_parts(const moba_shape* shape, const void* Q, const void* K_ef
         return MOBA_OK;
     }
     return hip_status(launch_backward_reference(d, Q, K_eff, V, O, lse, dO, topk_idx, blk_off, blk_q,
-                                                dQ, dK, dV, (float*)ws, plain, nullptr, hs));
+                                                dQ, dK, dV, (float*)ws, parts, nullptr, hs));
 }
 
 int moba_backward(const moba_shape* shape, const void* Q, const void* K_eff, const void* V,
