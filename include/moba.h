@@ -168,7 +168,7 @@ int moba_topk(const moba_shape* shape, const void* Q, const float* centroids,
  * GPU's array: calls that may overlap in time on one GPU (different streams, different threads)
  * race and must be ordered by the caller.  Nothing in the array has to survive between calls.
  */
-#define MOBA_TOPK_STATIC_MAX_BYTES (32u << 20)
+#define MOBA_TOPK_STATIC_MAX_BYTES (36u << 20)
 int moba_topk_static(const moba_shape* shape, const void* Q, const float* centroids,
                      int32_t* topk_idx, int32_t* blk_off, int32_t* blk_q, void* stream);
 

@@ -251,6 +251,14 @@ bool topk_mfma_supported(const Dims& s);
 hipError_t launch_topk_mfma(const Dims& s, const void* Q, const float* cent, int32_t* idx, void* ws,
                             hipStream_t st);
 
+// gate for rows of at most 64 kept blocks (gate_mfma.hip); the terms it shares with topk_mfma.hip
+bool gate_supported(const Dims& s);
+size_t gate_ws_bytes(const Dims& s);
+hipError_t launch_gate(const Dims& s, const void* Q, const float* cent, int32_t* idx, void* ws, hipStream_t st);
+hipError_t launch_split3(const Dims& s, const float* cent, bf16_t* c3, float4* norms, int32_t* redo, hipStream_t st);
+hipError_t launch_topk_redo(const Dims& s, const void* Q, const bf16_t* c3, const int32_t* redo, int32_t* idx,
+                            hipStream_t st);
+
 constexpr int kKeyMajorMaxTopk = 64;      // longest row of kept blocks the key-major kernels take
 
 // keys a key-major workgroup holds in registers as MFMA operands: the whole block up to 128

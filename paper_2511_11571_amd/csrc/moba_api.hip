@@ -70,15 +70,16 @@ int make_dims(const moba_shape* sh, Dims& d, bool ragged_ok = false)
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// top-k: the list builder's per-(256-query chunk, key block) counts, then the three bf16 terms
-// of the centroids (MFMA scoring)
+// top-k: the list builder's per-(256-query chunk, key block) counts, then what the gate needs (the three
+// bf16 terms of the centroids first)
 size_t chunk_counts_bytes(const Dims& d)
 {
     return align256(sizeof(int32_t) * (size_t)d.bh * (d.nchunk + 1) * d.n);
 }
 size_t topk_ws_bytes(const Dims& d)
 {
-    return chunk_counts_bytes(d) + align256(topk_mfma_ws_bytes(d)) + 256;
+    const size_t gate = gate_ws_bytes(d), search = topk_mfma_ws_bytes(d);
+    return chunk_counts_bytes(d) + align256(gate > search ? gate : search) + 256;
 }
 int32_t* chunk_counts(const Dims&, void* ws) { return static_cast<int32_t*>(ws); }
 void* topk_terms(const Dims& d, void* ws) { return static_cast<char*>(ws) + chunk_counts_bytes(d); }
@@ -319,7 +320,8 @@ int topk_call(const moba_shape* shape, const void* Q, const float* centroids, co
     if (d.R > 0 && !blk_q) return MOBA_EINVAL;
     if (d.n > kMaxBlocks && !topk_mfma_supported(d)) return MOBA_EUNSUPPORTED;   // (the MFMA gate takes four times as many)
     if (!ws || ws_bytes < topk_ws_bytes(d)) return MOBA_EWORKSPACE;
-    hipError_t e = topk_mfma_supported(d)
+    hipError_t e = gate_supported(d) ? launch_gate(d, Q, centroids, topk_idx, topk_terms(d, ws), (hipStream_t)stream)
+                   : topk_mfma_supported(d)
                        ? launch_topk_mfma(d, Q, centroids, topk_idx, topk_terms(d, ws), (hipStream_t)stream)
                        : launch_topk_reference(d, Q, centroids, topk_idx, (hipStream_t)stream);
     if (e != hipSuccess) return hip_status(e);

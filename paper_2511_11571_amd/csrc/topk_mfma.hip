@@ -1,5 +1,7 @@
 // Gate scoring and causal top-k on bf16 MFMA (paper Section 2; Appendix C.1, fused
-// top-k selection: scores are produced tile by tile and never written to memory).
+// top-k selection: scores are produced tile by tile and never written to memory) for the long rows that
+// the kernels of gate_mfma.hip leave to it, and the exact search that those hand single strips to and that
+// MOBA_FLAG_GATE_EXACT_SEARCH asks for.
 //
 // Scores must be fp32-accurate (the routing is compared with a 1e-4 score gap), so the
 // fp32 centroids are split into three bf16 terms hi + mid + lo (24 mantissa bits); the
@@ -42,35 +44,6 @@ constexpr int kCandExact = kRecWave / 64; // exact search: a final bin this smal
 constexpr int kBandBins = 24;             // first look: a bin with more approximate scores than this is cut again
 constexpr int kLookSweeps = 3;            // histogram sweeps of the first look at most
 constexpr int kTopkMfmaMaxBlocks = 16384; // the bit rows of a strip (8 bytes per block) still fit the LDS; 16-bit bins and block ids hold it
-
-// c3 <- the three bf16 terms of the fp32 centroids, in MFMA operand order: the 16 bytes lane
-// (m, g) feeds to the MFMA for blocks 16 jt + m, channels 32 ks + 8 g .. + 8, term t, sit at
-// (((slice * ntile + jt) * 3 + t) * (D / 32) + ks) * 1024 + 16 * lane, so that one load
-// instruction of a wave covers 1 KB of consecutive bytes.  Blocks beyond n read as zero.
-template <int D>
-__global__ void split3_kernel(const float* __restrict__ c, bf16_t* __restrict__ out, int n, int ntile,
-                              int64_t chunks)
-{
-    constexpr int KS = D / 32;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= chunks) return;
-    const int lane = (int)(i % 64), ks = (int)((i / 64) % KS), term = (int)((i / (64 * KS)) % 3);
-    const int64_t tile = i / (64 * KS * 3);
-    const int jt = (int)(tile % ntile);
-    const int64_t s = tile / ntile;
-    const int row = 16 * jt + (lane & 15), g = lane >> 4;
-    bf16_t o[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float x = row < n ? c[(s * n + row) * D + 32 * ks + 8 * g + e] : 0.f;
-        const bf16_t hi = f32_to_bf16(x);
-        const float r1 = x - bf16_to_f32(hi);
-        const bf16_t mid = f32_to_bf16(r1);
-        const float r2 = r1 - bf16_to_f32(mid);
-        o[e] = term == 0 ? hi : term == 1 ? mid : f32_to_bf16(r2);
-    }
-    *reinterpret_cast<uint4*>(out + i * 8) = *reinterpret_cast<const uint4*>(o);
-}
 
 // the score whose order_key is `key`; `none` when the key does not belong to a number
 __device__ __forceinline__ float key_score(uint32_t key, float none)
@@ -169,20 +142,22 @@ enum : uint32_t {
     kDone = 4
 };
 
-template <int D, int KL>
+template <int D, int KL, bool REDO>
 __global__ __launch_bounds__(kTopkWaves * kWave) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
 void topk_mfma_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ c3, int ntile_all,
     int32_t* __restrict__ idx, int N, int B, int n, int k, int strips_per_slice, int Wn, int G,
-    int exact_only, const int32_t* __restrict__ blk_first)
+    int exact_only, const int32_t* __restrict__ blk_first, const int32_t* __restrict__ redo)
 {
+    // a workgroup per strip; REDO: the strips redo[1 .. redo[0]] in turn
     extern __shared__ uint32_t smem[];
+    for (int job = blockIdx.x; !REDO || job < redo[0]; job += gridDim.x) {
     constexpr int KS = D / 32;
     constexpr bool LISTS = KL > 0;
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int m16 = lane & 15, g = lane >> 4;
-    const int strip = blockIdx.x;
+    const int strip = REDO ? redo[1 + job] : job;
     uint32_t* hist = smem;
     uint32_t* st_lo = hist + 64 * kHistStride + 64;   // (the first look's rows start one word in, see there)
     uint32_t* st_sh = st_lo + 64;
@@ -826,6 +801,9 @@ void topk_mfma_kernel(
         }
         for (; pos < k; ++pos) row[pos] = -1;
     }
+    if (!REDO) break;
+    __syncthreads();                               // (the next strip clears what this one still reads)
+    }
 }
 
 size_t topk_mfma_ws_bytes(const Dims& s)
@@ -839,8 +817,8 @@ bool topk_mfma_supported(const Dims& s)
            s.n <= kTopkMfmaMaxBlocks && s.k > 0;
 }
 
-template <int D, int KL>
-static hipError_t topk_launch2(const Dims& s, const void* Q, const bf16_t* c3, int32_t* idx,
+template <int D, int KL, bool REDO>
+static hipError_t topk_launch2(const Dims& s, const void* Q, const bf16_t* c3, int32_t* idx, const int32_t* redo,
                                hipStream_t st)
 {
     const int sps = (s.N + 63) / 64;
@@ -848,37 +826,47 @@ static hipError_t topk_launch2(const Dims& s, const void* Q, const bf16_t* c3, i
     const int Wn = ((s.n + 31) / 32) | 1;      // words per bit row, odd for the same reason
     const size_t lds = sizeof(uint32_t) * (size_t)(64 * kHistStride + 64 + 18 * 64 +
                                                    (KL > 0 ? 64 * KL / 2 + 64 : 64 * Wn));
-    hipError_t e = ensure_dynamic_lds((const void*)topk_mfma_kernel<D, KL>, (size_t)lds);
+    hipError_t e = ensure_dynamic_lds((const void*)topk_mfma_kernel<D, KL, REDO>, (size_t)lds);
     if (e != hipSuccess) return e;
-    ProfileScope timing(MOBA_PROFILE_TOPK, st);
-    hipLaunchKernelGGL((topk_mfma_kernel<D, KL>), dim3((unsigned)strips), dim3(kTopkWaves * kWave), lds, st,
-                       (const bf16_t*)Q, c3, (s.n + 15) / 16, idx, s.N, s.B, s.n, s.k, sps, Wn, s.G,
-                       (s.flags & MOBA_FLAG_GATE_EXACT_SEARCH) ? 1 : 0, s.blk_first);
+    const int64_t grid = REDO && strips > 512 ? 512 : strips;       // (usually there is nothing on the list)
+    const int exact = REDO || (s.flags & MOBA_FLAG_GATE_EXACT_SEARCH) ? 1 : 0;
+    auto launch = [&]() {
+        hipLaunchKernelGGL((topk_mfma_kernel<D, KL, REDO>), dim3((unsigned)grid), dim3(kTopkWaves * kWave), lds, st,
+                           (const bf16_t*)Q, c3, (s.n + 15) / 16, idx, s.N, s.B, s.n, s.k, sps, Wn, s.G, exact,
+                           s.blk_first, redo);
+    };
+    if (REDO) launch();
+    else {
+        ProfileScope timing(MOBA_PROFILE_TOPK, st);
+        launch();
+    }
     return hipGetLastError();
 }
 
-template <int D>
-static hipError_t topk_launch(const Dims& s, const void* Q, const bf16_t* c3, int32_t* idx,
+template <int D, bool REDO>
+static hipError_t topk_launch(const Dims& s, const void* Q, const bf16_t* c3, int32_t* idx, const int32_t* redo,
                               hipStream_t st)
 {
-    if (s.k <= kKeptList) return topk_launch2<D, kKeptList>(s, Q, c3, idx, st);
-    if (s.k <= kKeptListLong && s.n > kBitRowBlocks) return topk_launch2<D, kKeptListLong>(s, Q, c3, idx, st);
-    return topk_launch2<D, 0>(s, Q, c3, idx, st);
+    if (s.k <= kKeptList) return topk_launch2<D, kKeptList, REDO>(s, Q, c3, idx, redo, st);
+    if (s.k <= kKeptListLong && s.n > kBitRowBlocks) return topk_launch2<D, kKeptListLong, REDO>(s, Q, c3, idx, redo, st);
+    return topk_launch2<D, 0, REDO>(s, Q, c3, idx, redo, st);
 }
 
 hipError_t launch_topk_mfma(const Dims& s, const void* Q, const float* cent, int32_t* idx, void* ws,
                             hipStream_t st)
 {
-    const int ntile = (s.n + 15) / 16;
-    const int64_t chunks = (int64_t)s.bhk * ntile * 3 * (s.D / 32) * 64;     // centroids: per key/value head
-    if (chunks == 0) return hipSuccess;
+    if (s.bhk == 0 || s.n == 0) return hipSuccess;
     bf16_t* c3 = (bf16_t*)ws;
-    const unsigned grid = (unsigned)((chunks + 255) / 256);
-    if (s.D == 64)
-        hipLaunchKernelGGL(split3_kernel<64>, dim3(grid), dim3(256), 0, st, cent, c3, s.n, ntile, chunks);
-    else
-        hipLaunchKernelGGL(split3_kernel<128>, dim3(grid), dim3(256), 0, st, cent, c3, s.n, ntile, chunks);
-    return s.D == 64 ? topk_launch<64>(s, Q, c3, idx, st) : topk_launch<128>(s, Q, c3, idx, st);
+    hipError_t e = launch_split3(s, cent, c3, nullptr, nullptr, st);
+    if (e != hipSuccess) return e;
+    return s.D == 64 ? topk_launch<64, false>(s, Q, c3, idx, nullptr, st) : topk_launch<128, false>(s, Q, c3, idx, nullptr, st);
+}
+
+// the strips of 64 queries on the list `redo` (gate_mfma.hip), by the exact search
+hipError_t launch_topk_redo(const Dims& s, const void* Q, const bf16_t* c3, const int32_t* redo, int32_t* idx,
+                            hipStream_t st)
+{
+    return s.D == 64 ? topk_launch<64, true>(s, Q, c3, idx, redo, st) : topk_launch<128, true>(s, Q, c3, idx, redo, st);
 }
 
 }  // namespace moba

@@ -1,0 +1,39 @@
+"""fp32 attention on the matrix cores at the block sizes where its tiles of 16 keys and its key splits can go
+wrong: blocks below a tile, one over a tile, beyond what one workgroup holds, no kept blocks, the longest
+rows, shared heads."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2511_11571_amd as moba
+from paper_2511_11571_amd import binding
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+#        d   B    blocks  k  heads kv
+CASES = [(64, 8, 40, 3, 2, 0), (64, 17, 12, 4, 1, 0), (128, 24, 9, 0, 1, 0), (64, 50, 8, 3, 4, 2),
+         (128, 96, 5, 2, 2, 1), (64, 128, 4, 2, 1, 0), (128, 200, 4, 3, 1, 0), (64, 8, 80, 64, 1, 0)]
+
+
+@pytest.mark.parametrize("d,B,n,k,heads,kv", CASES)
+def test_fp32_forward_and_backward(oracle, d, B, n, k, heads, kv):
+    N, hkv = B * n, kv or heads
+    g = torch.Generator().manual_seed(9000 + B)
+    Q, dO = (torch.randn((1, heads, N, d), generator=g) for _ in range(2))
+    K, V = (torch.randn((1, hkv, N, d), generator=g) for _ in range(2))
+    sh = moba.Shape(1, heads, N, d, B, k, 0, binding.F32, 0.0, 0, kv)
+    Q64, K64, V64, dO64 = (x.double().numpy()[0] for x in (Q, K, V, dO))
+    Ke, Ve = (oracle.gqa_expand(x, heads, hkv) for x in (K64, V64))
+    kept, _ = oracle.topk(Q64, oracle.centroids(Ke, B), B, k)
+    idx = torch.from_numpy(kept).reshape(1, heads, N, k).cuda()
+    lists = moba.build_lists(sh, idx)
+    Qd, Kd, Vd, dOd = (x.cuda() for x in (Q, K, V, dO))
+    O, lse = moba.forward(sh, Qd, Kd, Vd, idx, lists)
+    got = (O, *moba.backward(sh, Qd, Kd, Vd, O, lse, dOd, idx, lists))
+    rO, rlse = oracle.attn_fwd(Q64, Ke, Ve, kept, B, 1.0 / np.sqrt(d))
+    rQ, rK, rV = oracle.attn_bwd(Q64, Ke, Ve, kept, dO64, B, 1.0 / np.sqrt(d))
+    want = (rO, rQ, oracle.gqa_reduce(rK, heads, hkv), oracle.gqa_reduce(rV, heads, hkv))
+    assert parity.max_abs(lse.double().cpu().numpy()[0], rlse) < parity.LSE_TOL["f32"]
+    for name, a, b in zip(("O", "dQ", "dK", "dV"), got, want):
+        assert parity.rel_l2(a.double().cpu().numpy()[0], b) < parity.GRAD_TOL["f32"], name

@@ -1,0 +1,60 @@
+"""The gate's kernels at the borders of their dispatch: blocks that fill a tile of 16 or spill one over,
+the last block counts whose scores stay in registers and the first that are swept twice, the lengths of
+row on both sides of each rule, fp32 up to and beyond its limit, and strips that are searched again because too many scores are equal."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2511_11571_amd as moba
+from paper_2511_11571_amd import binding
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+#        dtype   d   blocks  k   B
+CASES = [("bf16", 64, 1, 1, 2), ("bf16", 64, 16, 1, 3), ("bf16", 64, 17, 16, 2), ("bf16", 128, 18, 64, 2),
+         ("bf16", 64, 320, 64, 2), ("bf16", 64, 321, 64, 2), ("bf16", 64, 321, 16, 2), ("bf16", 64, 512, 16, 2),
+         ("bf16", 64, 513, 16, 3), ("bf16", 64, 1000, 1, 2), ("bf16", 64, 2047, 12, 2), ("bf16", 128, 256, 64, 2),
+         ("bf16", 128, 257, 16, 2), ("bf16", 128, 258, 17, 2), ("bf16", 128, 1030, 32, 2), ("bf16", 128, 300, 33, 2),
+         ("f32", 64, 17, 3, 2), ("f32", 128, 255, 64, 2), ("f32", 64, 512, 8, 2), ("f32", 64, 513, 8, 2)]
+
+
+@pytest.mark.parametrize("dtype,d,n,k,B", CASES)
+def test_rows_at_the_borders(oracle, dtype, d, n, k, B):
+    g = torch.Generator().manual_seed(7000 + n + k)
+    N, heads = n * B, 2
+    Q = torch.randn((1, heads, N, d), generator=g).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    cent = torch.randn((1, heads, n, d), generator=g) * 0.2
+    sh = moba.Shape(1, heads, N, d, B, k, 0, binding.BF16 if dtype == "bf16" else binding.F32, 0.0, 0, 0)
+    idx, _ = moba.topk(sh, Q.cuda(), cent.cuda())
+    got = idx.cpu().numpy().reshape(heads * N, k)
+    Q64, C = Q.double().numpy()[0], cent.double().numpy()[0]
+    rows = np.arange(heads * N, dtype=np.int64)[::1 if n < 600 else 7]
+    ref, kth = oracle.topk(Q64, C, B, k, rows=rows)
+    _, exempt = parity.routing_check(oracle, got[rows], ref, kth, Q64, C, B, rows=rows)
+    assert exempt < 0.02
+    assert (np.diff(np.where(got < 0, np.iinfo(np.int32).max, got), axis=-1) >= 0).all()
+
+
+@pytest.mark.parametrize("d,n,k", [(64, 600, 8), (128, 300, 20), (64, 40, 20)])
+def test_equal_scores_keep_the_lowest_blocks(d, n, k):
+    B, N = 2, 2 * n
+    g = torch.Generator().manual_seed(7)
+    Q = torch.randn((1, 1, N, d), generator=g).to(torch.bfloat16).cuda()
+    cent = torch.zeros((1, 1, n, d)).cuda()
+    sh = moba.Shape(1, 1, N, d, B, k, 0, binding.BF16, 0.0, 0, 0)
+    got = moba.topk(sh, Q, cent)[0].cpu().numpy()[0, 0]
+    for t in range(0, N, 5):
+        c = min(k, t // B)
+        assert got[t].tolist() == list(range(c)) + [-1] * (k - c)
+    # packed: a short sequence in front of one with many blocks, neither sees the other
+    lens = [37, N - 37]
+    lay = moba.VarlenLayout(np.array([0, 37, N]), B)
+    Tp = lay.padded_tokens
+    sh = moba.Shape(1, 1, Tp, d, B, k, 0, binding.BF16, 0.0, 0, 0)
+    got = lay.unpad(moba.topk_varlen(sh, lay, lay.pad(Q), torch.zeros((1, 1, Tp // B, d)).cuda())[0])
+    got = got.cpu().numpy()[0, 0]
+    for t in range(0, N, 5):
+        at, first = (t, 0) if t < lens[0] else (t - lens[0], 19)
+        c = min(k, at // B)
+        assert got[t].tolist() == list(range(first, first + c)) + [-1] * (k - c)
