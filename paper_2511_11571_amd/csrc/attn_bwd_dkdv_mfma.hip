@@ -27,8 +27,6 @@
 
 namespace moba {
 
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
 template <int D>
 struct DkvCfg {
     static constexpr int NW = 4;
@@ -48,16 +46,6 @@ struct DkvCfg {
     static constexpr size_t WIDE_OUT = (size_t)NW * 2 * 32 * RSTRIDE * 4;
     static constexpr size_t LDS_WIDE = WIDE_PARK > WIDE_OUT ? WIDE_PARK : WIDE_OUT;
 };
-
-// LDS transpose read: within each group of 16 lanes, lane i receives as element e the 16-bit
-// element (i & 3) of the 8 bytes that lane 4 e + (i >> 2) of the group points at.
-__device__ __forceinline__ uint2 lds_read_tr16(const unsigned char* p)
-{
-    typedef short v4s __attribute__((ext_vector_type(4)));
-    const v4s r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) v4s*)(const_cast<unsigned char*>(p)));
-    return *reinterpret_cast<const uint2*>(&r);
-}
 
 // GPW > 1 (key blocks of whole 64- or 128-key parts): a workgroup owns GPW = 2 or 4 consecutive
 // 32-key groups of one block, wave w the group w mod GPW; a step covers 128 positions of the walk
@@ -423,6 +411,14 @@ __global__ __launch_bounds__(256) void dkdv_heads_kernel(const float* __restrict
     Vec8<bf16_t>::store((which == 0 ? dK : dV) + (skv * chunks_per_slice + ch) * 8, acc);
 }
 
+hipError_t launch_dkdv_heads(const Dims& s, const float* part, void* dK, void* dV, hipStream_t st)
+{
+    const int64_t cps = (int64_t)s.N * s.D / 8, total = 2 * cps * s.bhk;
+    hipLaunchKernelGGL(dkdv_heads_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, part, (bf16_t*)dK,
+                       (bf16_t*)dV, cps, s.bhk, s.G);
+    return hipGetLastError();
+}
+
 template <int D>
 static hipError_t dkdv_launch(const Dims& s, const void* Q, const void* K, const void* V,
                               const void* dO, const float2* ld, const int32_t* off,
@@ -451,11 +447,7 @@ static hipError_t dkdv_launch(const Dims& s, const void* Q, const void* K, const
     else if (gpw == 2) MOBA_DKDV_LAUNCH(2);
     else MOBA_DKDV_LAUNCH(1);
 #undef MOBA_DKDV_LAUNCH
-    if (part) {
-        const int64_t cps = (int64_t)s.N * D / 8, total = 2 * cps * s.bhk;
-        hipLaunchKernelGGL(dkdv_heads_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, part,
-                           (bf16_t*)dK, (bf16_t*)dV, cps, s.bhk, s.G);
-    }
+    if (part) return launch_dkdv_heads(s, part, dK, dV, st);
     return hipGetLastError();
 }
 

@@ -1,0 +1,488 @@
+// The MoBA backward, key-block major, for sparse routing (paper Section 4.2 backward and Appendix C.3:
+// key blocks outermost, the queries routed to a block gathered into dense tiles, S recomputed,
+// dV += P^T dO, dS = P o (dP - D), dK += dS^T Q, dQ += scale dS K).  A workgroup owns up to 128 keys of one
+// key block, 32 per wave, and walks the block's query list, then the block's own queries (causally masked).
+//
+// The paper's kernel adds each block's contribution to dQ with atomic additions into a high-precision
+// buffer.  Here the contribution of (query t, kept block e, part c) is written once, as bf16, to [t][e][c],
+// and a second kernel adds a query's contributions up in fp32 in a fixed order: no atomics,
+// bit-reproducible, and the partial sums stream.
+//
+// Per step of P positions of the walk (NSLOT slots of 32):
+//   gather     every wave brings its share of the rows of Q and dO, whole rows per load instruction, ids two
+//              steps and rows one step ahead, and parks them in LDS;
+//   S, dP      queries x the wave's 32 keys; a lane holds one key and four queries of every 16-query tile,
+//              which packed to bf16 is the B operand of
+//   dV^T, dK^T += dO^T P, Q^T dS    (the parked rows through the LDS transpose read), in registers for the
+//              whole walk, and goes to LDS as dS[key][query];
+//   dQ^T = K^T dS^T    over all keys of the workgroup, the step's queries and channels dealt to the waves;
+//              both operands through the transpose read.
+//
+// One walk for all three gradients: dQ on its own repeats the gather of Q and dO and the products S and dP
+// (5 products instead of 7).  LDS bounds it (per step and wave about as many clocks of LDS reads as of matrix
+// instructions, shared by the waves of the compute unit), at d = 128 the latencies of one wave per SIMD.
+// @MEASURED@
+#include <type_traits>
+
+#include "mfma.h"
+
+namespace moba {
+
+// keys per workgroup: blocks up to 128 whole, larger ones in parts
+__host__ __device__ inline int bwd_part_keys(int B, int D)
+{
+    return B <= km_part_keys(B, D) ? B : B % 128 == 0 ? 128 : 64;
+}
+
+// rows in LDS, by 16-byte pieces: row-major operand reads (16 rows at one piece) and transpose reads (8 rows
+// at two neighbouring pieces) both meet every bank once.  d = 64: padded rows; d = 128: the piece XORed
+// with the row's low four bits rotated by one.
+template <int D>
+__device__ __forceinline__ uint32_t parked(uint32_t row, uint32_t piece)
+{
+    if constexpr (D == 64) return row * 144u + piece * 16u;
+    const uint32_t r = row & 15u;
+    return row * 256u + ((piece ^ ((r << 1 | r >> 3) & 15u)) * 16u);
+}
+
+template <int D, int NG>                               // NG: 32-key groups of a workgroup
+struct BwdKmCfg {
+    static constexpr int NW = NG, NT = NW * kWave;
+    static constexpr int NSLOT = NG == 4 ? 2 : NG;      // (four waves park 16 rows each: registers)
+    static constexpr int HV = NW / NSLOT;               // waves that share the dQ of a slot, by channels
+    static constexpr int P = 32 * NSLOT;                // positions of the walk per step
+    static constexpr int MT = D / 16, KS = D / 32;
+    static constexpr int CPR = D / 8;                   // 16-byte pieces per row = lanes per gathered row
+    static constexpr int RPI = kWave / CPR;             // rows per gather instruction
+    static constexpr int RW = P / NW, NI = RW / RPI;    // rows a wave gathers, instructions per tensor
+    static constexpr int CH = D / HV, MQ = CH / 16;     // channels and tiles of a wave's share of dQ
+    static constexpr int SB = D == 64 ? 144 : 256;      // bytes per parked row
+    static constexpr int SLOT = 64 * SB + 3 * 32 * 4;   // Q rows, dO rows, lse, -D, list entry
+    static constexpr int XS = 2 * P + 32;               // bytes per key of dS (8 rows of 32 bytes: every bank once)
+    static constexpr int EX = 32 * NG * XS, KR = 32 * NG * SB;
+    static constexpr int RST = D + 4;                   // floats per key row when dK and dV are turned over
+    static constexpr size_t WALK = (size_t)NSLOT * SLOT + EX + KR, TURN = (size_t)NW * 32 * RST * 4;
+    static constexpr size_t LDS = WALK > TURN ? WALK : TURN;
+};
+
+template <int D, int NG>
+__global__ __launch_bounds__((BwdKmCfg<D, NG>::NT)) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1)))
+void bwd_km_kernel(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+    const bf16_t* __restrict__ dO, const float2* __restrict__ ld, const int32_t* __restrict__ off,
+    const int32_t* __restrict__ ql, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, bf16_t* __restrict__ PdQ,
+    float* __restrict__ part, int N, int B, int n, int k, int nsub, float scale, int64_t R, int order, int bh, int G)
+{
+    using C = BwdKmCfg<D, NG>;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+    const int m16 = lane & 15, g = lane >> 4;
+    unsigned char* ex = smem + C::NSLOT * C::SLOT;          // dS[key][query of the step]
+    unsigned char* sK = ex + C::EX;                         // the part's K rows, for dQ
+
+    int s, u;                                               // query slice, (key block, part)
+    if (!schedule(blockIdx.x, order * bh, n * nsub, s, u)) return;
+    const int j = u / nsub, c = u - j * nsub;
+    const int own_first = c * (32 * NG);                    // first key of the part inside the block
+    const int own0 = j * B + own_first;                     // ... of the slice; own queries that see keys of this part
+    const int kfirst = 32 * wave;                           // this wave's first key inside the part
+    const int64_t sbase = (int64_t)s * N;
+    const int64_t kvbase = (int64_t)(s / G) * N;            // G query heads share a key/value head
+    const float c2 = scale * kLog2e;
+    const int32_t* os = off + (int64_t)s * (n + 1);
+    const int32_t* qs = ql + (int64_t)s * R;
+    const int lo = os[j], nlist = os[j + 1] - lo;
+    const int total = nlist + (B - own_first);
+    const char* Qg = reinterpret_cast<const char*>(Q + sbase * D);
+    const char* Gg = reinterpret_cast<const char*>(dO + sbase * D);
+
+    // The K rows of the part, their 8-byte pieces (four channels) in the order in which dQ's transpose reads
+    // want them: a lane of the result then holds CH / 4 consecutive channels
+    {
+        const char* Kg = reinterpret_cast<const char*>(K + (kvbase + own0) * D);
+        for (int i = tid; i < 32 * NG * C::CPR; i += C::NT) {
+            const int row = i / C::CPR, piece = i % C::CPR;
+            const uint4 v = *reinterpret_cast<const uint4*>(Kg + (size_t)i * 16);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int ch = 2 * piece + e, half = ch / (C::CH / 4), in = ch % (C::CH / 4);
+                const int pos = half * (C::CH / 4) + 4 * (in % C::MQ) + in / C::MQ;
+                *reinterpret_cast<uint2*>(sK + parked<D>(row, pos >> 1) + 8 * (pos & 1)) =
+                    e ? make_uint2(v.z, v.w) : make_uint2(v.x, v.y);
+            }
+        }
+    }
+    // B operands: the wave's keys and values (lane = key m16 of tile nt)
+    Frag kb[2][C::KS], vb[2][C::KS];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int ks = 0; ks < C::KS; ++ks) {
+            const int64_t o = (kvbase + own0 + kfirst + 16 * nt + m16) * D + 8 * g + 32 * ks;
+            kb[nt][ks].q = *reinterpret_cast<const uint4*>(K + o);
+            vb[nt][ks].q = *reinterpret_cast<const uint4*>(V + o);
+        }
+    f32x4_t dKT[C::MT][2], dVT[C::MT][2];
+#pragma unroll
+    for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            dKT[mt][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            dVT[mt][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+
+    // position a of the walk -> list entry (query, e: the place of this block in the query's row of kept
+    // blocks, filed in the entry's high byte by the list builder); own rows and rows past the end: e = k.
+    // Every load of the walk is unconditional and from an address that is always valid (a load inside a
+    // branch would be waited for at the end of the branch).
+    const int32_t* lsrc = nlist > 0 ? qs + lo : os;
+    const int llast = max(nlist - 1, 0);
+    const int own_e = k << 24;
+    auto query_at = [&](int a) {
+        const int listed = lsrc[min(a, llast)];
+        const int t = a < nlist ? listed : (own0 + (a - nlist)) | own_e;
+        return a >= total ? own0 | own_e : t;
+    };
+    const int grow = lane / C::CPR;                          // row of this lane inside a gather instruction
+    const uint32_t gcol = (uint32_t)(lane % C::CPR);         // its 16-byte piece of the row
+    const int first = C::RW * wave;                          // this wave's rows inside a step
+    // `inside` (a compile-time flag): all positions lie in the block's list -- the bulk of the walk, which
+    // then needs no selects.  t: rows this lane gathers a piece of; tl: the row whose lse, D and entry it brings
+    auto ids = [&](int a0, int (&t)[C::NI], int& tl, auto inside) {
+        const int a = a0 + first;
+        if constexpr (decltype(inside)::value) {
+#pragma unroll
+            for (int i = 0; i < C::NI; ++i) t[i] = lsrc[a + C::RPI * i + grow];
+            tl = lsrc[a + (lane & (C::RW - 1))];
+        } else {
+#pragma unroll
+            for (int i = 0; i < C::NI; ++i) t[i] = query_at(a + C::RPI * i + grow);
+            tl = query_at(a + (lane & (C::RW - 1)));
+        }
+    };
+    // lv: lse in log2 units (+inf past the end: P = 0); dv: -D, the start value of the dP product
+    auto fetch = [&](int a0, const int (&t)[C::NI], int tl, u32x4_t (&qr)[C::NI], u32x4_t (&gr)[C::NI],
+                     float& lv, float& dv, auto inside) {
+#pragma unroll
+        for (int i = 0; i < C::NI; ++i) {
+            const uint32_t o = (uint32_t)list_query(t[i]) * (uint32_t)(2 * D) + gcol * 16u;
+            qr[i] = *reinterpret_cast<const u32x4_t*>(Qg + o);
+            gr[i] = *reinterpret_cast<const u32x4_t*>(Gg + o);
+        }
+        const bool live = decltype(inside)::value || a0 + first + (lane & (C::RW - 1)) < total;
+        const float2 x = ld[sbase + list_query(tl)];          // (lse log2 e, -D) of the row
+        lv = live ? x.x : INFINITY;
+        dv = live ? x.y : 0.f;
+    };
+    int tN[C::NI], tlN, tl;
+    u32x4_t qr[C::NI], gr[C::NI];    // plain vectors: a struct type would be copied through scratch
+    float lv, dv;
+    {
+        int t0[C::NI];
+        ids(0, t0, tl, std::false_type());
+        fetch(0, t0, tl, qr, gr, lv, dv, std::false_type());
+        ids(C::P, tN, tlN, std::false_type());
+    }
+    // the wave's parked rows; row-major operand of this lane; its pointers of the transpose reads (lanes
+    // 4 e + a of a 16-lane group point at contraction row e (+4: 16 rows on), 8-byte piece a)
+    unsigned char* mine = smem + (first / 32) * C::SLOT;
+    const int row0 = first % 32;
+    const int te = (lane >> 2) & 3, ta = lane & 3;
+    const uint32_t trow = (uint32_t)slot_key(g, te);
+    static_assert(slot_key(0, 4) == slot_key(0, 0) + 16, "the second half of a transpose read: 16 rows on");
+    auto tr = [&](const unsigned char* rows, int piece8) {   // A operand: 32 rows as contraction, pieces piece8 + (0 .. 3)
+        const uint32_t p = (uint32_t)piece8 + ta, o = parked<D>(trow, p >> 1) + 8u * (p & 1u);
+        const uint2 a = lds_read_tr16(rows + o), b = lds_read_tr16(rows + o + 16 * C::SB);
+        Frag f;
+        f.u[0] = a.x; f.u[1] = a.y; f.u[2] = b.x; f.u[3] = b.y;
+        return f;
+    };
+    const uint32_t exw = (uint32_t)(kfirst + m16) * C::XS + 8u * g;
+    const uint32_t exr = trow * C::XS + 8u * ta;
+    const int dslot = wave / C::HV, dhalf = wave % C::HV;     // this wave's share of dQ
+    const int64_t slots = (int64_t)(k + 1) * nsub;           // partials per query
+
+    // 32 parked positions (walk positions p0 .. p0 + 31) against this wave's keys
+    auto work = [&](const unsigned char* stQ, int sl, int p0, auto inside) {
+        const unsigned char* stG = stQ + 32 * C::SB;
+        const float* ls = reinterpret_cast<const float*>(stQ + 64 * C::SB);
+        const float* Ds = ls + 32;
+        f32x4_t sc[2][2], dp[2][2];
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+            Frag qa[C::KS], ga[C::KS];
+#pragma unroll
+            for (int ks = 0; ks < C::KS; ++ks) {
+                const uint32_t o = parked<D>(m16, 4 * ks + g) + qt * 16 * C::SB;
+                qa[ks].q = *reinterpret_cast<const uint4*>(stQ + o);
+                ga[ks].q = *reinterpret_cast<const uint4*>(stG + o);
+            }
+            const f32x4_t nd = *reinterpret_cast<const f32x4_t*>(Ds + 16 * qt + 4 * g);   // -D of the rows
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                sc[qt][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                dp[qt][nt] = nd;                              // dP - D comes out of the MFMA
+#pragma unroll
+                for (int ks = 0; ks < C::KS; ++ks) {
+                    sc[qt][nt] = mfma16(qa[ks], kb[nt][ks], sc[qt][nt]);
+                    dp[qt][nt] = mfma16(ga[ks], vb[nt][ks], dp[qt][nt]);
+                }
+            }
+        }
+        // own queries are causal: the wave's key kfirst + 16 nt + m16 must not exceed the query
+        const bool causal = !decltype(inside)::value && p0 + 32 > nlist && p0 < nlist + kfirst + 32;
+        Frag pb[2], sb[2];
+        f32x4_t l4[2];
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) l4[qt] = *reinterpret_cast<const f32x4_t*>(ls + 16 * qt + 4 * g);
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            float p[8], d[8];
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float pv = fast_exp2(fmaf(sc[qt][nt][i], c2, -l4[qt][i]));
+                    if (causal) {
+                        const int a = p0 + 16 * qt + 4 * g + i - nlist;     // own row index, if >= 0
+                        if (a >= 0 && kfirst + 16 * nt + m16 > a) pv = 0.f;
+                    }
+                    p[4 * qt + i] = pv;
+                    d[4 * qt + i] = pv * dp[qt][nt][i];
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                pb[nt].u[e] = pack2(p[2 * e], p[2 * e + 1]);
+                sb[nt].u[e] = pack2(d[2 * e], d[2 * e + 1]);
+            }
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt)
+                *reinterpret_cast<uint2*>(ex + exw + 16 * nt * C::XS + 64 * sl + 32 * qt) =
+                    make_uint2(sb[nt].u[2 * qt], sb[nt].u[2 * qt + 1]);
+        }
+#pragma unroll
+        for (int mt = 0; mt < C::MT; ++mt) {
+            const Frag qT = tr(stQ, 4 * mt), gT = tr(stG, 4 * mt);
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                dVT[mt][nt] = mfma16(gT, pb[nt], dVT[mt][nt]);
+                dKT[mt][nt] = mfma16(qT, sb[nt], dKT[mt][nt]);
+            }
+        }
+    };
+    auto meet = [&]() {
+        if constexpr (C::NW > 1) __syncthreads();
+        else __builtin_amdgcn_wave_barrier();
+    };
+    auto step = [&](int a0, auto inside) {
+#pragma unroll
+        for (int i = 0; i < C::NI; ++i) {
+            const uint32_t o = parked<D>(row0 + C::RPI * i + grow, gcol);
+            *reinterpret_cast<u32x4_t*>(mine + o) = qr[i];
+            *reinterpret_cast<u32x4_t*>(mine + 32 * C::SB + o) = gr[i];
+        }
+        if (lane < C::RW) {
+            float* ls = reinterpret_cast<float*>(mine + 64 * C::SB) + row0 + lane;
+            ls[0] = lv;
+            ls[32] = dv;
+            ls[64] = __int_as_float(tl);
+        }
+        tl = tlN;
+        fetch(a0 + C::P, tN, tl, qr, gr, lv, dv, inside);
+        ids(a0 + 2 * C::P, tN, tlN, inside);
+        meet();                                              // the step's rows are parked; dS of the last one is read
+#pragma unroll
+        for (int sl = 0; sl < C::NSLOT; ++sl) work(smem + sl * C::SLOT, sl, a0 + 32 * sl, inside);
+        int note[2];
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt)
+            note[qt] = *reinterpret_cast<const int*>(smem + dslot * C::SLOT + 64 * C::SB + 256 + 4 * (16 * qt + m16));
+        meet();                                              // dS is whole; the parked rows are read
+        f32x4_t o[2][C::MQ];
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+            for (int mt = 0; mt < C::MQ; ++mt) o[qt][mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kg = 0; kg < NG; ++kg) {
+            Frag xb[2];
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt) {
+                const unsigned char* x = ex + exr + 32 * kg * C::XS + 64 * dslot + 32 * qt;
+                const uint2 a = lds_read_tr16(x), b = lds_read_tr16(x + 16 * C::XS);
+                xb[qt].u[0] = a.x; xb[qt].u[1] = a.y; xb[qt].u[2] = b.x; xb[qt].u[3] = b.y;
+            }
+#pragma unroll
+            for (int mt = 0; mt < C::MQ; ++mt) {
+                const Frag ka = tr(sK + 32 * kg * C::SB, dhalf * (C::CH / 4) + 4 * mt);
+#pragma unroll
+                for (int qt = 0; qt < 2; ++qt) o[qt][mt] = mfma16(ka, xb[qt], o[qt][mt]);
+            }
+        }
+        // the partials: this lane holds CH / 4 consecutive channels of two rows
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+            if (!decltype(inside)::value && a0 + 32 * dslot + 16 * qt + m16 >= total) continue;
+            // clamped: lists that do not match the rows of kept blocks give a wrong result, never an
+            // address outside the partials
+            const int e = min(list_slot(note[qt]), k);
+            const int64_t prow = (sbase + min(list_query(note[qt]), N - 1)) * slots + (int64_t)e * nsub + c;
+            uint4* dst = reinterpret_cast<uint4*>(PdQ + prow * D + dhalf * C::CH + g * (C::CH / 4));
+#pragma unroll
+            for (int h = 0; h < C::MQ / 2; ++h)
+                dst[h] = make_uint4(pack_bf16x2(o[qt][2 * h][0] * scale, o[qt][2 * h][1] * scale),
+                                    pack_bf16x2(o[qt][2 * h][2] * scale, o[qt][2 * h][3] * scale),
+                                    pack_bf16x2(o[qt][2 * h + 1][0] * scale, o[qt][2 * h + 1][1] * scale),
+                                    pack_bf16x2(o[qt][2 * h + 1][2] * scale, o[qt][2 * h + 1][3] * scale));
+        }
+    };
+    __syncthreads();                                          // K is in LDS
+    // the bulk of the walk: this step, the rows fetched in it and the ids looked up in it all lie inside the
+    // block's list; then the general steps (own rows, causal mask, end of the walk)
+    int a0 = 0;
+    for (; a0 + 3 * C::P <= nlist; a0 += C::P) step(a0, std::true_type());
+    for (; a0 < total; a0 += C::P) step(a0, std::false_type());
+
+    // every wave has the whole sums of its own 32 keys: turned over in LDS (channels of a key side by side),
+    // one tensor after the other, and written out.  part != nullptr (key/value heads shared by G query
+    // heads): as fp32 to part[dK | dV][query slice][N][D], for dkdv_heads_kernel to add up
+    if (!dK) return;
+    __syncthreads();                                          // the walk's LDS is no longer read
+    float* red = reinterpret_cast<float*>(smem) + (size_t)wave * 32 * C::RST;
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+#pragma unroll
+        for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+                *reinterpret_cast<f32x4_t*>(red + (16 * nt + m16) * C::RST + 16 * mt + 4 * g) =
+                    which == 0 ? dKT[mt][nt] : dVT[mt][nt];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 2
+        for (int i = lane; i < 32 * C::CPR; i += kWave) {
+            const int key = i / C::CPR, piece = i % C::CPR;
+            const float* src = red + key * C::RST + 8 * piece;
+            const float mul = which == 0 ? scale : 1.f;
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = src[e] * mul;
+            const int64_t row = own0 + kfirst + key;
+            if (part) Vec8<float>::store(part + (((int64_t)which * bh + s) * N + row) * D + 8 * piece, v);
+            else Vec8<bf16_t>::store((which == 0 ? dK : dV) + (kvbase + row) * D + 8 * piece, v);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// dQ_t = sum of the query's partials, in the order [kept block][part], then the parts of its
+// own block up to its own key.  D / 8 lanes per query; the partials of a query are consecutive
+// and are loaded nine at a time, unconditionally (past the end: the last one again, ignored).
+constexpr int kDqMergeChunk = 9;
+
+template <int D>
+__global__ __launch_bounds__(256) void dq_km_merge_kernel(
+    const int32_t* __restrict__ idx, const bf16_t* __restrict__ PdQ, bf16_t* __restrict__ dQ, int N,
+    int B, int k, int nsub, int64_t rows_total)
+{
+    constexpr int G = D / 8, CH = kDqMergeChunk;
+    const int64_t row = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;      // s * N + t
+    const int part = threadIdx.x % G;
+    if (row >= rows_total) return;
+    const int t = (int)(row % N);
+    const int own_parts = (t % B) / bwd_part_keys(B, D) + 1;
+    const int slots = (k + 1) * nsub, klast = max(k - 1, 0);
+    const int64_t p0 = row * slots;
+    const char* orow = reinterpret_cast<const char*>(PdQ + p0 * D + part * 8);
+    // (with k = 0 there is no row of kept blocks: any readable address serves the unused loads)
+    const int32_t* irow = k > 0 ? idx + row * k : reinterpret_cast<const int32_t*>(orow);
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int i0 = 0, e0 = 0, c0 = 0; i0 < slots; i0 += CH) {
+        int jj[CH];
+        u32x4_t raw[CH];
+#pragma unroll
+        for (int i = 0, e = e0, c = c0; i < CH; ++i) {
+            jj[i] = irow[min(e, klast)];
+            raw[i] = *reinterpret_cast<const u32x4_t*>(orow + (int64_t)min(i0 + i, slots - 1) * (2 * D));
+            if (++c == nsub) { c = 0; ++e; }
+        }
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            // the partial counts if it exists and its block was kept (own block: the parts up to
+            // the query's own key); an unused slot holds whatever the workspace held
+            const bool ok = i0 + i < slots && (e0 == k ? c0 < own_parts : jj[i] >= 0);
+            if (++c0 == nsub) { c0 = 0; ++e0; }
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const float lo = __uint_as_float(raw[i][h] << 16), hi = __uint_as_float(raw[i][h] & 0xffff0000u);
+                acc[2 * h] += ok ? lo : 0.f;
+                acc[2 * h + 1] += ok ? hi : 0.f;
+            }
+        }
+    }
+    Vec8<bf16_t>::store(dQ + row * D + part * 8, acc);
+}
+
+// ---- workspace: [D: bh*N fp32][partial dQ: bh*N*(k+1)*parts*D bf16], each 256-byte aligned
+
+size_t backward_km_ws_bytes(const Dims& s)
+{
+    const size_t partials = (size_t)s.bh * s.N * (size_t)(s.k + 1) * (size_t)(s.B / bwd_part_keys(s.B, s.D));
+    return a256(sizeof(float) * (size_t)s.bh * s.N) + a256(sizeof(bf16_t) * partials * s.D);
+}
+
+template <int D, int NG>
+static hipError_t bwd_launch2(const Dims& s, const void* Q, const void* K, const void* V, const void* dO,
+                              const float2* ld, const int32_t* idx, const int32_t* off, const int32_t* ql, void* dQ,
+                              void* dK, void* dV, bf16_t* PdQ, float* part, hipStream_t st)
+{
+    using C = BwdKmCfg<D, NG>;
+    const int nsub = s.B / (32 * NG);
+    hipError_t e = ensure_dynamic_lds((const void*)bwd_km_kernel<D, NG>, C::LDS);
+    if (e != hipSuccess) return e;
+    {
+        ProfileScope timing(MOBA_PROFILE_DKDV, st);
+        const int order = slice_major(s, 2);                // (gathers Q and dO rows)
+        hipLaunchKernelGGL((bwd_km_kernel<D, NG>), dim3((unsigned)schedule_grid(order * s.bh, s.n * nsub)), dim3(C::NT),
+                           C::LDS, st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, ld, off,
+                           ql, (bf16_t*)dK, (bf16_t*)dV, PdQ, part, s.N, s.B, s.n, s.k, nsub, s.scale, s.R, order, s.bh,
+                           s.G);
+    }
+    if (part && dK) {
+        e = launch_dkdv_heads(s, part, dK, dV, st);
+        if (e != hipSuccess) return e;
+    }
+    if (dQ) {
+        ProfileScope timing(MOBA_PROFILE_DQ, st);
+        const int64_t rows = (int64_t)s.bh * s.N;
+        const int rpw = 256 / (D / 8);
+        hipLaunchKernelGGL((dq_km_merge_kernel<D>), dim3((unsigned)((rows + rpw - 1) / rpw)), dim3(256), 0, st,
+                           idx, PdQ, (bf16_t*)dQ, s.N, s.B, s.k, nsub, rows);
+    }
+    return hipGetLastError();
+}
+
+// dQ, dK and dV; a null dQ, or null dK and dV, are not wanted
+hipError_t launch_backward_km(const Dims& s, const void* Q, const void* K, const void* V, const void* dO,
+                              const float2* ld, const int32_t* idx, const int32_t* off, const int32_t* ql, void* dQ,
+                              void* dK, void* dV, float* part, void* ws, hipStream_t st)
+{
+    if (s.bh == 0 || s.N == 0) return hipSuccess;
+    if (!key_major_shape(s)) return hipErrorInvalidValue;
+    if (s.G == 1) part = nullptr;
+    bf16_t* PdQ = reinterpret_cast<bf16_t*>(static_cast<char*>(ws) + a256(sizeof(float) * (size_t)s.bh * s.N));
+#define MOBA_BWD(D, NG) return bwd_launch2<D, NG>(s, Q, K, V, dO, ld, idx, off, ql, dQ, dK, dV, PdQ, part, st)
+    switch (s.D + bwd_part_keys(s.B, s.D) / 32) {
+        case 64 + 1: MOBA_BWD(64, 1);
+        case 64 + 2: MOBA_BWD(64, 2);
+        case 64 + 3: MOBA_BWD(64, 3);
+        case 64 + 4: MOBA_BWD(64, 4);
+        case 128 + 1: MOBA_BWD(128, 1);
+        case 128 + 2: MOBA_BWD(128, 2);
+        case 128 + 4: MOBA_BWD(128, 4);
+    }
+#undef MOBA_BWD
+    return hipErrorInvalidValue;
+}
+
+}  // namespace moba

@@ -35,6 +35,16 @@ __device__ __forceinline__ f32x4_t mfma16(const Frag& a, const Frag& b, f32x4_t 
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
 }
 
+// LDS transpose read: within each group of 16 lanes, lane i receives as element e the 16-bit
+// element (i & 3) of the 8 bytes that lane 4 e + (i >> 2) of the group points at.
+__device__ __forceinline__ uint2 lds_read_tr16(const unsigned char* p)
+{
+    typedef short v4s __attribute__((ext_vector_type(4)));
+    const v4s r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) v4s*)(const_cast<unsigned char*>(p)));
+    return *reinterpret_cast<const uint2*>(&r);
+}
+
 // key (0..31, inside its 32-key group) that contraction slot s of lane group g stands for
 __host__ __device__ __forceinline__ constexpr int slot_key(int g, int s)
 {
@@ -246,6 +256,8 @@ hipError_t launch_dkdv_mfma(const Dims& s, const void* Q, const void* K, const v
                             const void* dO, const float2* ld, const int32_t* off,
                             const int32_t* ql, void* dK, void* dV, float* part, hipStream_t st);
 
+hipError_t launch_dkdv_heads(const Dims& s, const float* part, void* dK, void* dV, hipStream_t st);
+
 size_t topk_mfma_ws_bytes(const Dims& s);
 bool topk_mfma_supported(const Dims& s);
 hipError_t launch_topk_mfma(const Dims& s, const void* Q, const float* cent, int32_t* idx, void* ws,
@@ -358,9 +370,9 @@ inline bool lists_with_places(const Dims& s) { return key_major_path(s) || f32_k
 
 size_t forward_km_ws_bytes(const Dims& s);
 size_t backward_km_ws_bytes(const Dims& s);
-hipError_t launch_dq_km(const Dims& s, const void* Q, const void* K, const void* V, const void* dO,
-                        const float2* ld, const int32_t* idx, const int32_t* off, const int32_t* ql,
-                        void* dQ, void* ws, hipStream_t st);
+hipError_t launch_backward_km(const Dims& s, const void* Q, const void* K, const void* V, const void* dO,
+                              const float2* ld, const int32_t* idx, const int32_t* off, const int32_t* ql, void* dQ,
+                              void* dK, void* dV, float* part, void* ws, hipStream_t st);
 hipError_t launch_forward_km(const Dims& s, const void* Q, const void* K, const void* V, void* ws,
                              const int32_t* idx, const int32_t* off, const int32_t* ql, void* O,
                              float* lse, hipStream_t st);

@@ -496,17 +496,20 @@ int moba_backward_parts(const moba_shape* shape, const void* Q, const void* K_ef
                                                      dQ, dK, dV, (float*)ws, MOBA_BWD_PREPROCESS, ld, hs);
             if (e != hipSuccess) return hip_status(e);
         }
-        if (parts & MOBA_BWD_DQ) {
-            hipError_t e = key_major_path(d)
-                ? launch_dq_km(d, Q, K_eff, V, dO, ld, topk_idx, blk_off, blk_q, dQ, ws, hs)
-                : launch_dq_mfma(d, Q, K_eff, V, dO, lse, topk_idx, blk_off, blk_q, dQ, ws, hs);
+        float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(ld) +
+                                               align256(sizeof(float2) * (size_t)d.bh * d.N));
+        const bool dq = parts & MOBA_BWD_DQ, dkdv = parts & MOBA_BWD_DKDV;
+        if (key_major_path(d))
+            return dq || dkdv ? hip_status(launch_backward_km(d, Q, K_eff, V, dO, ld, topk_idx, blk_off, blk_q,
+                                                              dq ? dQ : nullptr, dkdv ? dK : nullptr,
+                                                              dkdv ? dV : nullptr, part, ws, hs))
+                              : MOBA_OK;
+        if (dq) {
+            hipError_t e = launch_dq_mfma(d, Q, K_eff, V, dO, lse, topk_idx, blk_off, blk_q, dQ, ws, hs);
             if (e != hipSuccess) return hip_status(e);
         }
-        if (parts & MOBA_BWD_DKDV) {
-            float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(ld) +
-                                                   align256(sizeof(float2) * (size_t)d.bh * d.N));
-            hipError_t e = launch_dkdv_mfma(d, Q, K_eff, V, dO, ld, blk_off, blk_q,
-                                            dK, dV, part, hs);
+        if (dkdv) {
+            hipError_t e = launch_dkdv_mfma(d, Q, K_eff, V, dO, ld, blk_off, blk_q, dK, dV, part, hs);
             if (e != hipSuccess) return hip_status(e);
         }
         return MOBA_OK;
