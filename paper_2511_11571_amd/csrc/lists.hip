@@ -10,6 +10,7 @@
 //   3. fill: the bit matrix is rebuilt and its rows are written out in ascending order at
 //      blk_off[j] + chunk start, eight lanes per row.
 // The bit matrix lives in LDS only and covers 1024 key blocks at a time (512 where a slice has more).
+// Short slices take one launch instead (lists_small_kernel).
 //
 // A list entry holds the query in its low 24 bits (sequences are at most 2^24 long).  Where the
 // key-block-major attention kernels will run (lists_with_places() of the shape and its flags) the
@@ -29,9 +30,9 @@ constexpr int kWords = kListQ / 32;             // 8 words of 32 query bits per 
 constexpr int kQueryBits = 24;                  // low bits of a list entry: the query
 
 // f(r, b, e) for every entry b = row r's e-th of the routing rows r = 0 .. rows-1 of this workgroup
-// (k entries per row, rows contiguous in memory), all 256 threads, 16-byte loads when the row length
+// (k entries per row, rows contiguous in memory), all NT threads, 16-byte loads when the row length
 // allows.  The row and place of a thread's entries advance by additions (one division per thread).
-template <typename F>
+template <int NT = 256, typename F>
 __device__ __forceinline__ void for_each_entry_slot(const int32_t* __restrict__ rows0, int rows, int k,
                                                     int tid, F f)
 {
@@ -39,13 +40,13 @@ __device__ __forceinline__ void for_each_entry_slot(const int32_t* __restrict__ 
     if ((k & 3) == 0) {
         const int4* p4 = reinterpret_cast<const int4*>(rows0);
         const int n4 = total >> 2;
-        const int dr = 1024 / k, de = 1024 % k;             // 256 pieces of four entries further on
+        const int dr = 4 * NT / k, de = 4 * NT % k;         // NT pieces of four entries further on
         int r = 4 * tid / k, e = 4 * tid - r * k;           // a 16-byte piece never straddles rows
-        for (int i0 = tid; i0 < n4; i0 += 4 * 256) {
+        for (int i0 = tid; i0 < n4; i0 += 4 * NT) {
             int4 v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                v[u] = i0 + u * 256 < n4 ? p4[i0 + u * 256] : make_int4(-1, -1, -1, -1);
+                v[u] = i0 + u * NT < n4 ? p4[i0 + u * NT] : make_int4(-1, -1, -1, -1);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 f(r, v[u].x, e); f(r, v[u].y, e + 1); f(r, v[u].z, e + 2); f(r, v[u].w, e + 3);
@@ -55,9 +56,9 @@ __device__ __forceinline__ void for_each_entry_slot(const int32_t* __restrict__ 
             }
         }
     } else {
-        const int dr = 256 / k, de = 256 % k;
+        const int dr = NT / k, de = NT % k;
         int r = tid / k, e = tid - r * k;
-        for (int i = tid; i < total; i += 256) {
+        for (int i = tid; i < total; i += NT) {
             f(r, rows0[i], e);
             r += dr;
             e += de;
@@ -258,6 +259,111 @@ __global__ __launch_bounds__(256) void lists_offsets_kernel(int32_t* __restrict_
     for (int j = a; j < b; ++j) { run += os[j + 1]; os[j + 1] = run; }
 }
 
+// ---- short slices: one launch.  A workgroup holds the bit matrix of the slice's blocks up to the last of
+// its `own` blocks, from all queries, and writes the lists of its blocks: the words of their rows, one row
+// after the other, are in list order, so one scan over the threads gives every word its place; the bits of
+// the rows before them are where the first list starts.  Every workgroup of a slice walks the slice's whole
+// routing (from its L2), which buys the three launches and the counts in memory that lists_chunk_kernel and
+// its scans need.  Bound by that walk: an LDS atomic per entry in every workgroup.
+// us, four launches -> one: 2 slices, N = 2048, k = 3: 19 -> 9; 8 slices, N = 4096, k = 7: 25 -> 17;
+// 16 slices, N = 8192, k = 8: 27 -> 26 (65536 entries per slice, no longer taken).
+constexpr int kSmallThreads = 1024;
+constexpr size_t kSmallLds = 144 << 10;         // bit matrix and places, of the 160 KB of a compute unit
+constexpr int kSmallEntries = 1 << 15;          // routing entries per slice
+
+struct SmallLists {
+    int own, wgs;                               // key blocks per workgroup, workgroups per slice
+    size_t lds;
+    bool ok;
+};
+__host__ __device__ inline int small_row_words(int N) { return (N + 31) / 32 | 1; }   // (odd: rows on different banks)
+
+template <bool SLOTS>
+__global__ __launch_bounds__(kSmallThreads) void lists_small_kernel(
+    const int32_t* __restrict__ idx, int32_t* __restrict__ off, int32_t* __restrict__ ql, int N, int B, int n, int k,
+    int own, int wgs, int64_t R, int bh)
+{
+    extern __shared__ __align__(16) uint32_t mask[];     // [hi][words], then SLOTS: e of (own block, query), bytes
+    __shared__ int sums[2][kSmallThreads / kWave];
+    int s, c;
+    if (!schedule(blockIdx.x, bh, wgs, s, c)) return;
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int words = small_row_words(N);
+    const int lo = c * own, hi = min(n, lo + own);
+    uint8_t* slot = reinterpret_cast<uint8_t*>(mask + (size_t)min(n, wgs * own) * words);
+    for (int i = tid; i < hi * words; i += kSmallThreads) mask[i] = 0u;
+    __syncthreads();
+    // only past blocks count: lists never exceed R
+    for_each_entry_slot<kSmallThreads>(idx + (int64_t)s * N * k, N, k, tid, [&](int r, int b, int e) {
+        if (b < 0 || b >= hi || (b + 1) * B > r) return;
+        atomicOr(&mask[b * words + (r >> 5)], 1u << (r & 31));
+        if (SLOTS && b >= lo) slot[(b - lo) * N + r] = (uint8_t)e;
+    });
+    __syncthreads();
+    int before = 0;                                      // entries of the blocks before lo
+    for (int i = tid; i < lo * words; i += kSmallThreads) before += __popc(mask[i]);
+    const int mywords = (hi - lo) * words, per = (mywords + kSmallThreads - 1) / kSmallThreads;
+    const uint32_t* mine = mask + lo * words;
+    const int a = min(mywords, tid * per), z = min(mywords, a + per);
+    int count = 0;
+    for (int i = a; i < z; ++i) count += __popc(mine[i]);
+    int incl = count;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int up = __shfl_up(incl, o, kWave);
+        before += __shfl_xor(before, o, kWave);
+        if (lane >= o) incl += up;
+    }
+    if (lane == kWave - 1) {
+        sums[0][wave] = incl;
+        sums[1][wave] = before;
+    }
+    __syncthreads();
+    int pos = incl - count;
+    for (int w = 0; w < kSmallThreads / kWave; ++w) pos += sums[1][w] + (w < wave ? sums[0][w] : 0);
+    int32_t* os = off + (int64_t)s * (n + 1);
+    int32_t* qs = ql + (int64_t)s * R;
+    int b = a / words, w = a - b * words;
+    for (int i = a; i < z; ++i) {
+        if (w == 0) os[lo + b] = pos;
+        uint32_t word = mine[i];
+        while (word) {
+            const int r = 32 * w + (__ffs(word) - 1);
+            // a routing that breaks the contract must not write outside the slice's lists
+            if (pos < R) qs[pos] = SLOTS ? r | (int)slot[b * N + r] << kQueryBits : r;
+            ++pos;
+            word &= word - 1u;
+        }
+        if (++w == words) { w = 0; ++b; }
+    }
+    if (hi == n && z == mywords && a < z) os[n] = pos;
+}
+
+// Blocks per workgroup: as few as keep the launch within one workgroup per compute unit.  The line is set by
+// the walk (see above: half the entries of the shape that gains nothing) and by what the LDS holds.
+static SmallLists small_lists(const Dims& s)
+{
+    SmallLists p = {0, 0, 0, false};
+    if (s.k <= 0 || s.R <= 0 || s.k > 255) return p;
+    p.own = (int)(((int64_t)s.n * s.bh + 255) / 256);
+    p.wgs = (s.n + p.own - 1) / p.own;
+    const size_t bits = sizeof(uint32_t) * (size_t)s.n * small_row_words(s.N);
+    p.lds = bits + (lists_with_places(s) ? (size_t)p.own * s.N : 0);
+    p.ok = p.lds <= kSmallLds && (int64_t)s.N * s.k <= kSmallEntries;
+    return p;
+}
+
+template <bool SLOTS>
+static hipError_t small_launch(const Dims& s, const SmallLists& p, const int32_t* idx, int32_t* off, int32_t* ql,
+                               hipStream_t st)
+{
+    hipError_t e = ensure_dynamic_lds((const void*)lists_small_kernel<SLOTS>, p.lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((lists_small_kernel<SLOTS>), dim3((unsigned)schedule_grid(s.bh, p.wgs)), dim3(kSmallThreads), p.lds,
+                       st, idx, off, ql, s.N, s.B, s.n, s.k, p.own, p.wgs, s.R, s.bh);
+    return hipGetLastError();
+}
+
 template <int RANGE>
 static hipError_t build_lists_launch(const Dims& s, const int32_t* idx, int32_t* off, int32_t* ql,
                                      int32_t* cnt2, hipStream_t st)
@@ -288,6 +394,8 @@ static hipError_t build_lists_launch(const Dims& s, const int32_t* idx, int32_t*
 hipError_t launch_build_lists(const Dims& s, const int32_t* idx, int32_t* off, int32_t* ql,
                               int32_t* cnt2, hipStream_t st)
 {
+    const SmallLists p = small_lists(s);
+    if (p.ok) return lists_with_places(s) ? small_launch<true>(s, p, idx, off, ql, st) : small_launch<false>(s, p, idx, off, ql, st);
     return s.n <= kRangeMax ? build_lists_launch<kRangeMax>(s, idx, off, ql, cnt2, st)
                             : build_lists_launch<kRangeLong>(s, idx, off, ql, cnt2, st);
 }
