@@ -30,7 +30,7 @@ PEAK_HBM_GBS = 8000.0
 # counters read for a plain copy of known size): profiles/config<N>_hbm_traffic.txt, one row per
 # kernel, last column = bytes per launch.  Not measured -> None.
 PROFILED_KERNEL = {"topk": "topk_mfma_kernel", "forward": ("forward_mfma_kernel", "fwd_km_kernel"),
-                   "bwd_dq": ("dq_mfma_kernel", "dq_km_kernel"), "bwd_dkdv": "dkdv_mfma_kernel"}
+                   "bwd_dq": ("dq_mfma_kernel", "dq_km_merge_kernel"), "bwd_dkdv": ("dkdv_mfma_kernel", "bwd_km_kernel")}
 
 
 def measured_traffic(config, kernel):
@@ -181,7 +181,7 @@ def measure(w, a, moba, binding, workloads, torch):
     lse = torch.empty((w.batch, w.heads, w.N), dtype=torch.float32, device=dev)
     grads = (torch.empty_like(d["Q"]), torch.empty_like(d["K"]), torch.empty_like(d["V"]))
 
-    stages = ["centroids", "topk_lists", "forward", "bwd_pre", "bwd_dq", "bwd_dkdv"]
+    stages = ["centroids", "topk_lists", "forward", "bwd_pre", "bwd"]
     if not w.backward:
         stages = stages[:3]
 
@@ -197,7 +197,7 @@ def measure(w, a, moba, binding, workloads, torch):
         moba.forward(sh, d["Q"], Ke, d["V"], idx, lists, ws=ws_fwd, O=O, lse=lse)
         mark(3)
         if w.backward:
-            for i, part in enumerate((binding.BWD_PREPROCESS, binding.BWD_DQ, binding.BWD_DKDV)):
+            for i, part in enumerate((binding.BWD_PREPROCESS, binding.BWD_DQ | binding.BWD_DKDV)):
                 moba.backward(sh, d["Q"], Ke, d["V"], O, lse, d["dO"], idx, lists, ws=ws_bwd,
                               out=grads, parts=part)
                 mark(4 + i)

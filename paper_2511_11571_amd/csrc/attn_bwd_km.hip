@@ -67,7 +67,8 @@ struct BwdKmCfg {
     static constexpr size_t LDS = WALK > TURN ? WALK : TURN;
 };
 
-template <int D, int NG>
+// KV = false: dQ only (a caller that takes the gradients one call at a time), without dV += P^T dO, dK += dS^T Q
+template <int D, int NG, bool KV>
 __global__ __launch_bounds__((BwdKmCfg<D, NG>::NT)) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1)))
 void bwd_km_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
@@ -264,7 +265,7 @@ void bwd_km_kernel(
                     make_uint2(sb[nt].u[2 * qt], sb[nt].u[2 * qt + 1]);
         }
 #pragma unroll
-        for (int mt = 0; mt < C::MT; ++mt) {
+        for (int mt = 0; KV && mt < C::MT; ++mt) {
             const Frag qT = tr(stQ, 4 * mt), gT = tr(stG, 4 * mt);
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
@@ -349,7 +350,7 @@ void bwd_km_kernel(
     // every wave has the whole sums of its own 32 keys: turned over in LDS (channels of a key side by side),
     // one tensor after the other, and written out.  part != nullptr (key/value heads shared by G query
     // heads): as fp32 to part[dK | dV][query slice][N][D], for dkdv_heads_kernel to add up
-    if (!dK) return;
+    if (!KV) return;
     __syncthreads();                                          // the walk's LDS is no longer read
     float* red = reinterpret_cast<float*>(smem) + (size_t)wave * 32 * C::RST;
 #pragma unroll
@@ -433,28 +434,28 @@ size_t backward_km_ws_bytes(const Dims& s)
     return a256(sizeof(float) * (size_t)s.bh * s.N) + a256(sizeof(bf16_t) * partials * s.D);
 }
 
-template <int D, int NG>
+template <int D, int NG, bool KV>
 static hipError_t bwd_launch2(const Dims& s, const void* Q, const void* K, const void* V, const void* dO,
                               const float2* ld, const int32_t* idx, const int32_t* off, const int32_t* ql, void* dQ,
                               void* dK, void* dV, bf16_t* PdQ, float* part, hipStream_t st)
 {
     using C = BwdKmCfg<D, NG>;
     const int nsub = s.B / (32 * NG);
-    hipError_t e = ensure_dynamic_lds((const void*)bwd_km_kernel<D, NG>, C::LDS);
+    hipError_t e = ensure_dynamic_lds((const void*)bwd_km_kernel<D, NG, KV>, C::LDS);
     if (e != hipSuccess) return e;
     {
-        ProfileScope timing(MOBA_PROFILE_DKDV, st);
+        ProfileScope timing(KV ? MOBA_PROFILE_DKDV : MOBA_PROFILE_DQ, st);
         const int order = slice_major(s, 2);                // (gathers Q and dO rows)
-        hipLaunchKernelGGL((bwd_km_kernel<D, NG>), dim3((unsigned)schedule_grid(order * s.bh, s.n * nsub)), dim3(C::NT),
+        hipLaunchKernelGGL((bwd_km_kernel<D, NG, KV>), dim3((unsigned)schedule_grid(order * s.bh, s.n * nsub)), dim3(C::NT),
                            C::LDS, st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, ld, off,
                            ql, (bf16_t*)dK, (bf16_t*)dV, PdQ, part, s.N, s.B, s.n, s.k, nsub, s.scale, s.R, order, s.bh,
                            s.G);
     }
-    if (part && dK) {
+    if (KV && part) {
         e = launch_dkdv_heads(s, part, dK, dV, st);
         if (e != hipSuccess) return e;
     }
-    if (dQ) {
+    {
         ProfileScope timing(MOBA_PROFILE_DQ, st);
         const int64_t rows = (int64_t)s.bh * s.N;
         const int rpw = 256 / (D / 8);
@@ -464,7 +465,7 @@ static hipError_t bwd_launch2(const Dims& s, const void* Q, const void* K, const
     return hipGetLastError();
 }
 
-// dQ, dK and dV; a null dQ, or null dK and dV, are not wanted
+// dQ, dK and dV; null dK and dV are not wanted
 hipError_t launch_backward_km(const Dims& s, const void* Q, const void* K, const void* V, const void* dO,
                               const float2* ld, const int32_t* idx, const int32_t* off, const int32_t* ql, void* dQ,
                               void* dK, void* dV, float* part, void* ws, hipStream_t st)
@@ -473,7 +474,9 @@ hipError_t launch_backward_km(const Dims& s, const void* Q, const void* K, const
     if (!key_major_shape(s)) return hipErrorInvalidValue;
     if (s.G == 1) part = nullptr;
     bf16_t* PdQ = reinterpret_cast<bf16_t*>(static_cast<char*>(ws) + a256(sizeof(float) * (size_t)s.bh * s.N));
-#define MOBA_BWD(D, NG) return bwd_launch2<D, NG>(s, Q, K, V, dO, ld, idx, off, ql, dQ, dK, dV, PdQ, part, st)
+#define MOBA_BWD(D, NG)                                                                                            \
+    return dK ? bwd_launch2<D, NG, true>(s, Q, K, V, dO, ld, idx, off, ql, dQ, dK, dV, PdQ, part, st)              \
+              : bwd_launch2<D, NG, false>(s, Q, K, V, dO, ld, idx, off, ql, dQ, dK, dV, PdQ, part, st)
     switch (s.D + bwd_part_keys(s.B, s.D) / 32) {
         case 64 + 1: MOBA_BWD(64, 1);
         case 64 + 2: MOBA_BWD(64, 2);

@@ -499,11 +499,10 @@ int moba_backward_parts(const moba_shape* shape, const void* Q, const void* K_ef
         float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(ld) +
                                                align256(sizeof(float2) * (size_t)d.bh * d.N));
         const bool dq = parts & MOBA_BWD_DQ, dkdv = parts & MOBA_BWD_DKDV;
-        if (key_major_path(d))
-            return dq || dkdv ? hip_status(launch_backward_km(d, Q, K_eff, V, dO, ld, topk_idx, blk_off, blk_q,
-                                                              dq ? dQ : nullptr, dkdv ? dK : nullptr,
-                                                              dkdv ? dV : nullptr, part, ws, hs))
-                              : MOBA_OK;
+        // (dK and dV on their own: the kernel that walks for them alone)
+        if (key_major_path(d) && dq)
+            return hip_status(launch_backward_km(d, Q, K_eff, V, dO, ld, topk_idx, blk_off, blk_q, dQ,
+                                                 dkdv ? dK : nullptr, dkdv ? dV : nullptr, part, ws, hs));
         if (dq) {
             hipError_t e = launch_dq_mfma(d, Q, K_eff, V, dO, lse, topk_idx, blk_off, blk_q, dQ, ws, hs);
             if (e != hipSuccess) return hip_status(e);
