@@ -29,8 +29,9 @@ PEAK_HBM_GBS = 8000.0
 # under profiles/ (FETCH_SIZE and WRITE_SIZE per dispatch, already scaled there by what the same
 # counters read for a plain copy of known size): profiles/config<N>_hbm_traffic.txt, one row per
 # kernel, last column = bytes per launch.  Not measured -> None.
-PROFILED_KERNEL = {"topk": "topk_mfma_kernel", "forward": ("forward_mfma_kernel", "fwd_km_kernel"),
-                   "bwd_dq": ("dq_mfma_kernel", "dq_km_merge_kernel"), "bwd_dkdv": ("dkdv_mfma_kernel", "bwd_km_kernel")}
+PROFILED_KERNEL = {"topk": ("topk_mfma_kernel", "gate_many_kernel", "gate_few_kernel"),
+                   "forward": ("forward_mfma_kernel", "fwd_km_kernel"),
+                   "bwd_dq": "dq_mfma_kernel", "bwd_dkdv": ("dkdv_mfma_kernel", "bwd_km_kernel")}
 
 
 def measured_traffic(config, kernel):
@@ -165,10 +166,17 @@ def measure(w, a, moba, binding, workloads, torch):
     flags |= {"auto": 0, "tiles": binding.FLAG_QUERY_TILES, "keymajor": binding.FLAG_KEY_MAJOR}[a.attention]
     if w.backward and not a.separate_workspaces:
         flags |= binding.FLAG_SHARED_WORKSPACE      # forward and backward share the prepared copies of K and V
-    sh = moba.Shape(w.batch, w.heads, w.N, w.d, w.B, w.k, w.conv_width,
-                    binding.BF16 if w.dtype == "bf16" else binding.F32, 0.0, flags, w.kv_heads)
+
+    def shape(flags):
+        return moba.Shape(w.batch, w.heads, w.N, w.d, w.B, w.k, w.conv_width,
+                          binding.BF16 if w.dtype == "bf16" else binding.F32, 0.0, flags, w.kv_heads)
+    sh = shape(flags)
     R = moba.routes_per_slice(sh)
     sizes = moba.workspace_bytes(sh)
+    # the kernels' choice shows in the workspace: only the key-block-major ones keep partials there
+    cuts = [moba.workspace_bytes(shape(flags & ~(binding.FLAG_KEY_MAJOR | binding.FLAG_QUERY_TILES) | cut))
+            for cut in (binding.FLAG_KEY_MAJOR, binding.FLAG_QUERY_TILES)]
+    key_major = w.dtype == "bf16" and cuts[0] != cuts[1] and sizes == cuts[0]
     ws_topk = torch.empty(max(sizes[0], 256), dtype=torch.uint8, device="cuda")
     if flags & binding.FLAG_SHARED_WORKSPACE:
         ws_fwd = ws_bwd = torch.empty(max(sizes[1], sizes[2], 256), dtype=torch.uint8, device="cuda")
@@ -220,7 +228,7 @@ def measure(w, a, moba, binding, workloads, torch):
                 for i, name in enumerate(stages)}
 
     return {"t": t, "d": d, "sh": sh, "R": R, "dev": dev, "ms_step": ms_step, "stage_ms": stage_ms,
-            "kernel_ms": kernel_ms, "stages": stages}
+            "kernel_ms": kernel_ms, "stages": stages, "key_major": key_major}
 
 
 def decode_bench(w, a, moba, binding, torch):
@@ -395,12 +403,15 @@ def main():
     # kernels, timed by the library with HIP events around each launch (kernel_ms; the stage
     # times above also hold the small preparation kernels of a stage).  The dK/dV kernel
     # executes 4 of the backward's matrix products (S, dP, dV, dK = 8d flop per attended pair),
-    # the dQ kernel 3 (S, dP, dQ = 6d), the forward 2 (4d): bf16 MFMA work.  The gate/top-k
+    # the dQ kernel 3 (S, dP, dQ = 6d), the forward 2 (4d): bf16 MFMA work.  Key-block-major shapes
+    # have one walk for the whole backward (10d, bwd_dkdv) and a merge (bwd_dq, no products).  The gate/top-k
     # kernel is priced against HBM: it has to read Q and the centroids and write the routing.
     es = 2 if w.dtype == "bf16" else 4
     mfma = (w.dtype == "bf16") and not a.reference_kernels
-    work = {"forward": ("flop", fwd_flop), "bwd_dq": ("flop", 6.0 * w.d * pairs),
-            "bwd_dkdv": ("flop", 8.0 * w.d * pairs),
+    one_walk = m["key_major"]
+    work = {"forward": ("flop", fwd_flop),
+            "bwd_dq": ("byte", float(w.bh * w.N * (w.k + 2) * w.d * es)) if one_walk else ("flop", 6.0 * w.d * pairs),
+            "bwd_dkdv": ("flop", (10.0 if one_walk else 8.0) * w.d * pairs),
             "topk": ("byte", float(w.bh * (w.N * w.d * es + w.n * w.d * 4 + w.N * w.k * 4)))}
     timed = {k: v for k, v in kernel_ms.items() if k in work and (w.backward or not k.startswith("bwd"))}
     if timed:
@@ -427,17 +438,18 @@ def main():
             if work[kname][0] == "flop" and kms > 0:
                 tf = work[kname][1] / (kms * 1e-3) / 1e12
                 kernel_frac[kname] = {"tflops": tf, "frac_of_mfma_peak": tf / PEAK_BF16_TFLOPS}
-    # the backward as the metric counts it: 10d flop per attended pair over both of its kernels (the
-    # per-kernel figures above count what each kernel executes: S and dP are computed in both)
-    if mfma and "bwd_dq" in timed and "bwd_dkdv" in timed:
+    # the backward as the metric counts it: 10d flop per attended pair over its kernels (the
+    # per-kernel figures above count what each kernel executes: separate dQ and dK/dV kernels both compute S and dP)
+    if mfma and "bwd_dkdv" in timed:
         for kname in ("bwd_dq", "bwd_dkdv"):
-            kernel_frac[kname]["counts"] = "executed flop of this kernel (%dd per attended pair)" % (
-                6 if kname == "bwd_dq" else 8)
-        bms = timed["bwd_dq"] + timed["bwd_dkdv"]
+            if kname in kernel_frac:
+                kernel_frac[kname]["counts"] = "executed flop of this kernel (%dd per attended pair)" % round(
+                    work[kname][1] / (w.d * pairs))
+        bms = timed.get("bwd_dq", 0.0) + timed["bwd_dkdv"]
         tf = bwd_flop / (bms * 1e-3) / 1e12
         kernel_frac["backward"] = {"tflops": tf, "frac_of_mfma_peak": tf / PEAK_BF16_TFLOPS, "ms": bms,
                                    "counts": "algorithmic flop of the backward (10d per attended pair) over "
-                                             "the dQ and the dK/dV kernel"}
+                                             "its kernels"}
         ams = bms + timed.get("forward", 0.0)
         tf = (fwd_flop + bwd_flop) / (ams * 1e-3) / 1e12
         kernel_frac["attention_stage"] = {"tflops": tf, "frac_of_mfma_peak": tf / PEAK_BF16_TFLOPS, "ms": ams,

@@ -53,7 +53,7 @@ typedef enum moba_dtype { MOBA_F32 = 0, MOBA_BF16 = 1 } moba_dtype;
 
 /* flags */
 #define MOBA_FLAG_REFERENCE_KERNELS 1u /* use the plain (non-MFMA) kernels for every stage */
-#define MOBA_FLAG_KEY_MAJOR 2u         /* attention forward and dQ by key block with one partial per
+#define MOBA_FLAG_KEY_MAJOR 2u         /* attention forward and backward by key block with a partial per
                                         * (query, block) pair and a merge kernel (paper Section 4.2):
                                         * force it where that path exists (bf16; B a multiple of 32
                                         * up to 128 (d = 64) / 64 (d = 128), or a multiple of that;
@@ -313,8 +313,8 @@ int moba_last_hip_error(void);
 enum {
     MOBA_PROFILE_TOPK = 0,    /* gate scores + top-k selection                    */
     MOBA_PROFILE_FORWARD = 1, /* forward attention tile kernel                    */
-    MOBA_PROFILE_DQ = 2,      /* backward dQ tile kernel                          */
-    MOBA_PROFILE_DKDV = 3,    /* backward dK / dV kernel                          */
+    MOBA_PROFILE_DQ = 2,      /* backward dQ tile kernel; key-block major: the merge of the partials */
+    MOBA_PROFILE_DKDV = 3,    /* backward dK / dV kernel; key-block major: the walk for dQ, dK and dV */
     MOBA_PROFILE_KERNELS = 4
 };
 int moba_profile_begin(void);
