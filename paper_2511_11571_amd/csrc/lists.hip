@@ -8,8 +8,8 @@
 //   2. scan: per key block an exclusive scan over chunks (start of each chunk's segment
 //      inside the block's list), then an exclusive scan of the block totals (blk_off).
 //   3. fill: the bit matrix is rebuilt and its rows are written out in ascending order at
-//      blk_off[j] + chunk start, eight lanes per row.
-// The bit matrix lives in LDS only and covers 1024 key blocks at a time (512 where a slice has more).
+//      blk_off[j] + chunk start, eight lanes per row (or entry by entry, see below).
+// The bit matrix lives in LDS only and covers 512 or 1024 key blocks at a time.
 // Short slices take one launch instead (lists_small_kernel).
 //
 // A list entry holds the query in its low 24 bits (sequences are at most 2^24 long).  Where the
@@ -18,13 +18,19 @@
 // file the partial result of (query, block) under (query, e) and would otherwise have to search
 // the row for the block (10-15 % of their time); elsewhere it is zero.  The fill pass gets e by walking the
 // routing rows a second time: entry e of row r names block b, whose place in b's run of this
-// workgroup is the number of set bits below r in b's row of the bit matrix.
+// workgroup is the number of set bits below r in b's row of the bit matrix, and is stored there at once.
+// (Collecting e per run in LDS first and writing row by row took longer at every shape measured; without
+// places the walk over the rows of the matrix is the faster one up to 4096 blocks.)
+// us, both passes and scans, before -> after: 32 slices, N = 524288, 4096 blocks, k = 8: 4180 -> 2890;
+// 16 slices, N = 131072, 1024 blocks, k = 8: 261 -> 151, 2048 blocks, k = 32: 693 -> 637; 8 slices, N = 131072,
+// 4096 blocks, k = 32: 552 -> 356; 16 slices, N = 16384, 256 blocks, k = 16: 55 -> 38.  Bound by the scattered
+// 4-byte stores and, in the count, by the walk over a matrix that is mostly empty.
 #include "mfma.h"
 
 namespace moba {
 
 constexpr int kRangeMax = 1024;                 // key blocks per LDS bit matrix at most (32 KB)
-constexpr int kRangeLong = 512;                 // ... where a slice has more blocks than that
+constexpr int kRangeLong = 512;                 // the shorter one, see launch_build_lists
 constexpr int kListQ = kChunkQ;                  // queries per workgroup: one chunk
 constexpr int kWords = kListQ / 32;             // 8 words of 32 query bits per block
 constexpr int kQueryBits = 24;                  // low bits of a list entry: the query
@@ -82,10 +88,6 @@ __global__ __launch_bounds__(256) void lists_chunk_kernel(
 {
     __shared__ __align__(16) uint32_t mask[kRange * kWords];
     __shared__ int32_t start[FILL ? kRange : 1];         // where this workgroup's queries start in each list
-    __shared__ uint16_t lbase[SLOTS ? kRange : 1];       // where block b's run starts among this workgroup's entries
-    extern __shared__ uint8_t slot[];                    // SLOTS: e of every entry, run by run (kListQ * k bytes)
-    __shared__ int wsum[4];
-    const int slot_last = kListQ * k - 1;
     // consecutive query chunks of a slice go to the same XCD: the 128-byte lines of a block's
     // list are completed by neighbouring chunks and should meet in one L2 before they are written back
     int c, s;
@@ -127,49 +129,26 @@ __global__ __launch_bounds__(256) void lists_chunk_kernel(
             }
             crow[j] = c0;
         }
-    } else {
-        if constexpr (SLOTS) {
-            // runs of the blocks one after the other: exclusive scan of the rows' bit counts
-            // (four consecutive blocks per thread, threads by shuffles, waves through LDS)
-            int c4[4], mine = 0;
+    } else if constexpr (SLOTS) {
+        int32_t* qs = ql + (int64_t)s * R;
+        for_each_entry_slot(rows0, rows, k, tid, [&](int r, int b, int e) {
+            b -= lo;
+            if (b >= 0 && b < nblk && (b + lo + 1) * B <= t0 + r) {
+                const uint32_t* mrow = mask + b * kWords;
+                const int last = r >> 5;
+                int rank = 0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int b = 4 * tid + u;
-                int c = 0;
-                if (b < nblk)
-#pragma unroll
-                    for (int wd = 0; wd < kWords; ++wd) c += __popc(mask[b * kWords + wd]);
-                c4[u] = c;
-                mine += c;
-            }
-            int incl = mine;
-#pragma unroll
-            for (int o = 1; o < kWave; o <<= 1) {
-                const int up = __shfl_up(incl, o, kWave);
-                if ((tid & (kWave - 1)) >= o) incl += up;
-            }
-            if ((tid & (kWave - 1)) == kWave - 1) wsum[tid / kWave] = incl;
-            __syncthreads();
-            int run = incl - mine;
-            for (int wv = 0; wv < tid / kWave; ++wv) run += wsum[wv];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (4 * tid + u < nblk) lbase[4 * tid + u] = (uint16_t)run;
-                run += c4[u];
-            }
-            __syncthreads();
-            // a query keeps at most k blocks, so the runs hold at most kListQ * k entries
-            for_each_entry_slot(rows0, rows, k, tid, [&](int r, int b, int e) {
-                b -= lo;
-                if (b >= 0 && b < nblk && (b + lo + 1) * B <= t0 + r) {
-                    const uint32_t* mrow = mask + b * kWords;
-                    int rank = __popc(mrow[r >> 5] & ((1u << (r & 31)) - 1u));
-                    for (int wd = 0; wd < (r >> 5); ++wd) rank += __popc(mrow[wd]);
-                    slot[min((int)lbase[b] + rank, slot_last)] = (uint8_t)e;
+                for (int wd = 0; wd < kWords; ++wd) {
+                    const uint32_t below = wd < last ? ~0u : wd == last ? (1u << (r & 31)) - 1u : 0u;
+                    rank += __popc(mrow[wd] & below);
                 }
-            });
-            __syncthreads();
-        }
+                const int64_t pos = (int64_t)start[b] + rank;
+                // a routing that breaks the contract (repeats, too many kept blocks) must not
+                // write outside the slice's lists
+                if (pos < R) qs[pos] = (t0 + r) | e << kQueryBits;
+            }
+        });
+    } else {
         // Eight lanes per block, one 32-query word each: a lane writes the queries of its word
         // after those of the lanes before it.  The 256 queries of this workgroup are neighbours
         // in every list, so a store instruction touches one short run of addresses per block.
@@ -185,13 +164,8 @@ __global__ __launch_bounds__(256) void lists_chunk_kernel(
                 if (lane8 >= o) incl += up;
             }
             int64_t pos = (int64_t)start[b] + (incl - cnt);
-            int local = SLOTS ? (int)lbase[b] + (incl - cnt) : 0;
             while (word) {
-                int entry = t0 + 32 * lane8 + (__ffs(word) - 1);
-                if constexpr (SLOTS) entry |= (int)slot[min(local++, slot_last)] << kQueryBits;
-                // a routing that breaks the contract (repeats, too many kept blocks) must not
-                // write outside the slice's lists
-                if (pos < R) qs[pos] = entry;
+                if (pos < R) qs[pos] = t0 + 32 * lane8 + (__ffs(word) - 1);      // (as above)
                 ++pos;
                 word &= word - 1u;
             }
@@ -376,10 +350,9 @@ static hipError_t build_lists_launch(const Dims& s, const int32_t* idx, int32_t*
                        s.nchunk);
     hipLaunchKernelGGL(lists_offsets_kernel, dim3(s.bh), block, 0, st, off, s.n);
     if (s.R > 0) {
-        static_assert(kKeyMajorMaxTopk <= 255 && kListQ * kKeyMajorMaxTopk <= 65535, "slot byte, 16-bit run starts");
+        static_assert(kKeyMajorMaxTopk <= 127, "the place of a block in the high byte of an entry");
         if (lists_with_places(s))
-            hipLaunchKernelGGL((lists_chunk_kernel<true, true, RANGE>), grid, block, (size_t)kListQ * s.k, st, idx,
-                               cnt2, (const int32_t*)off, ql, s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);
+            hipLaunchKernelGGL((lists_chunk_kernel<true, true, RANGE>), grid, block, 0, st, idx, cnt2, (const int32_t*)off, ql, s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);
         else
             hipLaunchKernelGGL((lists_chunk_kernel<true, false, RANGE>), grid, block, 0, st, idx, cnt2,
                                (const int32_t*)off, ql, s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);
@@ -388,16 +361,19 @@ static hipError_t build_lists_launch(const Dims& s, const int32_t* idx, int32_t*
 }
 
 // Up to kRangeMax blocks one range covers a slice and a workgroup reads its routing rows once.
-// Beyond that the rows are read once per range anyway, and a workgroup's cost is that of walking
-// its bit matrix, however few pairs fall into it: smaller ranges, more workgroups (N = 524288,
-// B = 128, top-k 8: fill pass 3.9 ms with ranges of 1024 blocks, 2.6 ms with 512, 3.5 ms with 256).
+// Beyond that the rows are read once per range anyway, and without places a workgroup's cost is that of
+// walking the rows of its bit matrix, however few pairs fall into it: smaller ranges, more workgroups.
+// With places the rows are walked by the count alone: the full range (8 slices, N = 131072, 4096 blocks,
+// k = 60: 830 us against 1080 with 512), but the short one where it covers a slice (16 slices, N = 65536,
+// 512 blocks, k = 8: 68 against 72; half the LDS, more workgroups in flight).
 hipError_t launch_build_lists(const Dims& s, const int32_t* idx, int32_t* off, int32_t* ql,
                               int32_t* cnt2, hipStream_t st)
 {
     const SmallLists p = small_lists(s);
     if (p.ok) return lists_with_places(s) ? small_launch<true>(s, p, idx, off, ql, st) : small_launch<false>(s, p, idx, off, ql, st);
-    return s.n <= kRangeMax ? build_lists_launch<kRangeMax>(s, idx, off, ql, cnt2, st)
-                            : build_lists_launch<kRangeLong>(s, idx, off, ql, cnt2, st);
+    const bool full = lists_with_places(s) ? s.n > kRangeLong : s.n <= kRangeMax;
+    return full ? build_lists_launch<kRangeMax>(s, idx, off, ql, cnt2, st)
+                : build_lists_launch<kRangeLong>(s, idx, off, ql, cnt2, st);
 }
 
 }  // namespace moba

@@ -14,6 +14,8 @@ SHAPES = [
     (2, 4, 4096, 64, 64, 7), (4, 16, 4096, 64, 128, 4), (1, 2, 8192, 64, 128, 4), (1, 2, 8192, 64, 128, 5),
     (1, 1, 8192, 128, 64, 3), (1, 3, 8192, 128, 64, 3), (5, 7, 3 * 1056, 64, 32, 9), (1, 16, 8192, 64, 128, 8),
     (1, 1, 32 * 600, 64, 32, 4), (1, 1, 32 * 1100, 64, 32, 3),
+    # the chunked builder at the edges of its ranges of blocks, the last chunk of 256 queries whole and not
+    (1, 1, 64 * 512, 64, 64, 3), (1, 1, 64 * 513, 64, 64, 2), (1, 1, 32 * 1024, 64, 32, 5), (1, 1, 32 * 1025, 64, 32, 2),
 ]
 
 
