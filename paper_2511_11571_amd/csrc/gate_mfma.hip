@@ -5,7 +5,7 @@
 // bits); the queries are bf16, every product is exact in fp32.  A wave owns 16 QT consecutive queries
 // and works alone -- no workgroup barrier anywhere; the four waves of a workgroup only share the L1.
 //
-// Few candidates (at most 512 blocks, see kGateFew): the exact scores of 16 queries are computed once, into
+// Few candidates (at most 320 blocks, see kGateFew): the exact scores of 16 queries are computed once, into
 // registers, and the threshold with exactly k scores above it is searched there.
 //
 // Many candidates, two sweeps instead of keeping the scores:
@@ -43,9 +43,8 @@ template <> struct GateCfg<32> {
     static constexpr int QT = 2, GR = 32, SEG = 72;
 };
 // tiles of 16 blocks whose scores a wave keeps in registers: as many as three waves per SIMD (d = 128: two,
-// the operands are larger) leave room for; kGateMore: two waves per SIMD
+// the operands are larger) leave room for
 template <int D> constexpr int kGateFew = D == 64 ? 20 : 16;
-constexpr int kGateMore = 32;
 constexpr int kGateWaves = 4;
 constexpr int kGateBand = 64;                     // candidates of a strip that can be scored again
 constexpr int kGateIdBits = 14;
@@ -202,7 +201,7 @@ __device__ __forceinline__ void few_strip(const bf16_t* __restrict__ Q, const bf
 
 // every strip of the call has few candidates
 template <int D, int TA>
-__global__ __launch_bounds__(kGateWaves * kWave) __attribute__((amdgpu_waves_per_eu(D == 64 && TA < kGateMore ? 3 : 2)))
+__global__ __launch_bounds__(kGateWaves * kWave) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
 void gate_few_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ c3, int ntile_all, int32_t* __restrict__ idx, int N, int B,
     int k, int strips, int bh, int G, const int32_t* __restrict__ blk_first)
@@ -625,19 +624,26 @@ __global__ __launch_bounds__(kGateWaves * kWave) void gate_f32_kernel(
 
 // ---- host ------------------------------------------------------------------------------------------
 
-// most blocks of a call without rows of many candidates.  kGateMore tiles at d = 64 only (d = 128 has no
-// registers for them), and for short rows only: above 16 kept blocks the histogram search is as fast
-static int few_blocks(const Dims& s) { return 16 * (s.D == 128 ? kGateFew<128> : s.k <= 16 ? kGateMore : kGateFew<64>); }
+// most blocks of a call without rows of many candidates
+static int few_blocks(const Dims& s) { return 16 * (s.D == 128 ? kGateFew<128> : kGateFew<64>); }
 
+// Where these kernels run and where the histogram search of topk_mfma.hip does, both measured over
+// N <= 131072 with 4 and 16 heads (us, search -> here, 16 heads where not said otherwise):
+//  - scores in registers: every call it takes (d = 64, 300 blocks of 32, k = 16: 84 -> 64); very short rows up to
+//    256 blocks only (300 blocks of 128, k = 3: 179 -> 193; keeping 512 blocks, d = 64, k = 3: 335 -> 576)
+//  - two sweeps, rows of at most 8: enough strips to fill the chip with one wave per 64 queries (700 blocks of 32,
+//    k = 8: 185 -> 167, with 4 heads 73 -> 95) and enough blocks (2048 of 64, k = 8: 1682 -> 1262; d = 128, 300 of
+//    64: 162 -> 162).  Rows of 15 and 16 overflow their candidates too often (2048 of 64: 1867 -> 2390)
+//  - two sweeps, rows of 17 to 32 at d = 128: after a key conv only, which gives the centroids a common part and
+//    the histogram's windows little to cut (2048 of 64, k = 32: 4400 -> 3700; without it 3001 -> 3330)
+// Longer rows stay with the search (N = 32768, B = 32, k = 64, d = 64: 446 against 630).
 bool gate_supported(const Dims& s)
 {
     if (s.k <= 0 || s.k > 64 || (s.flags & (MOBA_FLAG_REFERENCE_KERNELS | MOBA_FLAG_GATE_EXACT_SEARCH))) return false;
     if (s.dtype != MOBA_BF16) return s.n <= 16 * kGateF32Tiles;
-    // Long rows over many blocks stay with the histogram search: selecting is most of the work there, and
-    // more of the strips have to be searched again (N = 32768, B = 32, k = 64, d = 64: 446 us against 630;
-    // N = 33664, B = 32, k = 59, d = 128: 5 % of the strips searched again)
-    if (s.k > (s.D == 64 ? 16 : 32) && s.n > few_blocks(s)) return false;
-    return s.n <= (1 << kGateIdBits);
+    if (s.n <= few_blocks(s)) return s.k >= 8 || s.n <= 256;
+    if (s.n > (1 << kGateIdBits) || s.n < (s.D == 64 ? 513 : 448) || (int64_t)s.bh * s.N < 300000) return false;
+    return s.k <= 8 || (s.D == 128 && s.k > 16 && s.k <= 32 && s.W > 1);
 }
 
 // workspace: [the three terms][norms of every block][list of strips to search exactly: count, strips]
@@ -718,8 +724,7 @@ hipError_t launch_gate(const Dims& s, const void* Q, const float* cent, int32_t*
     if (e != hipSuccess) return e;
     if (!may)
         return s.D == 128 ? few_launch<128, kGateFew<128>>(s, Q, c3, idx, st)
-             : s.n <= 16 * kGateFew<64> ? few_launch<64, kGateFew<64>>(s, Q, c3, idx, st)
-                                        : few_launch<64, kGateMore>(s, Q, c3, idx, st);
+                          : few_launch<64, kGateFew<64>>(s, Q, c3, idx, st);
     e = s.D == 64 ? many_launch<64, 16>(s, Q, c3, norms, redo, idx, st)
         : s.k <= 16 ? many_launch<128, 16>(s, Q, c3, norms, redo, idx, st)
                     : many_launch<128, 32>(s, Q, c3, norms, redo, idx, st);

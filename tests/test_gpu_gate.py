@@ -58,3 +58,21 @@ def test_equal_scores_keep_the_lowest_blocks(d, n, k):
         at, first = (t, 0) if t < lens[0] else (t - lens[0], 19)
         c = min(k, at // B)
         assert got[t].tolist() == list(range(first, first + c)) + [-1] * (k - c)
+
+
+# the two sweeps take calls of many rows only: (d, blocks, k, B, heads, conv width), both sides of each rule
+@pytest.mark.parametrize("d,n,k,B,heads,conv", [(64, 513, 8, 32, 19, 0), (64, 512, 8, 32, 19, 0), (64, 1025, 3, 32, 10, 0),
+                                                (64, 513, 9, 32, 19, 0), (128, 448, 8, 32, 21, 0), (128, 447, 8, 32, 21, 0),
+                                                (128, 500, 32, 32, 19, 4), (128, 500, 17, 32, 19, 3), (128, 500, 32, 32, 19, 0)])
+def test_two_sweeps_keep_what_the_exact_search_keeps(d, n, k, B, heads, conv):
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    N = n * B
+    Q = torch.randn((1, heads, N, d), generator=g, device="cuda").to(torch.bfloat16)
+    cent = torch.randn((1, heads, n, d), generator=g, device="cuda") * 0.2
+    cent[:, -1] = 0.0                                # one head of equal scores: its strips are searched again
+    got, want = (moba.topk(moba.Shape(1, heads, N, d, B, k, conv, binding.BF16, 0.0, flags, 0), Q, cent)[0]
+                 for flags in (0, binding.FLAG_GATE_EXACT_SEARCH))
+    # scores equal up to the rounding of fp32 sums taken in another order: 2^-22 of their scale apart, a
+    # chance of about k n 2^-22 per 1000 rows
+    assert (got != want).any(-1).float().mean() < 1e-4
+    assert torch.equal(got[:, -1], want[:, -1])
