@@ -56,12 +56,13 @@ class Shape:
                        self.conv_width, self.dtype, self.softmax_scale, self.flags, self.kv_heads)
 
     def _ref(self):
-        """Address of this shape as the C structure, built once per object (the object is immutable)."""
-        try:
-            return ctypes.addressof(self._cstruct)
-        except AttributeError:
-            object.__setattr__(self, "_cstruct", self.c())
-            return ctypes.addressof(self._cstruct)
+        """Address of this shape as the C structure, built once per object (the object is immutable).  The
+        first structure stored stays: another thread may be inside a call that reads it, and nothing but
+        this object keeps it alive."""
+        s = self.__dict__.get("_cstruct")
+        if s is None:
+            s = self.__dict__.setdefault("_cstruct", self.c())
+        return ctypes.addressof(s)
 
     @property
     def hkv(self):

@@ -169,3 +169,27 @@ def test_convolution_in_place_is_rejected(lib):
     assert lib.moba_centroids(ctypes.byref(sh), one, one, one, one, None) == -1      # K_eff == K
     sh1 = _shape(conv_width=0).c()
     assert lib.moba_centroids(ctypes.byref(sh1), None, None, None, one, None) == -1   # K missing
+
+
+def test_threads_that_meet_on_a_new_shape_share_one_c_structure(monkeypatch):
+    """Two threads make their first call with one Shape at the same time: the structure whose address either
+    of them hands to C has to stay alive.  The first thread is held between finding no structure and storing
+    its own until the second one has its address."""
+    import threading
+    sh = _shape()
+    build, second_done = binding.Shape.c, threading.Event()
+    first = threading.Thread(target=lambda: got.append(sh._ref()))
+
+    def c(self):
+        if threading.current_thread() is first:
+            other = threading.Thread(target=lambda: (got.append(sh._ref()), second_done.set()))
+            other.start()
+            assert second_done.wait(10)
+            other.join()
+        return build(self)
+
+    got = []
+    monkeypatch.setattr(binding.Shape, "c", c)
+    first.start()
+    first.join()
+    assert got == [ctypes.addressof(sh._cstruct)] * 2
