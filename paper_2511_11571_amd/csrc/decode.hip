@@ -415,8 +415,9 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
             if (!ALL && p0 + u * (NW * RPI) + kslot >= total) z[u] = -INFINITY;
             top = fmaxf(top, z[u]);
         }
-        // (a lane group without a live key so far keeps m = -inf, l = 0: exponents are taken against 0)
-        const float ref = ALL ? top : top == -INFINITY ? 0.f : top;
+        // (a lane group without a key so far that exists and has a finite logit keeps m = -inf, l = 0: exponents
+        // are taken against 0)
+        const float ref = top == -INFINITY ? 0.f : top;
         const float alpha = __builtin_amdgcn_exp2f(m - ref);
         m = top;
         l *= alpha;

@@ -163,3 +163,27 @@ def test_decode_argument_checks():
         moba.decode_forward(sh, 4, Q, K, K, few)
     with pytest.raises(moba.MobaError):
         moba.decode_forward(sh, 4, Q, K, K, None)
+
+
+@pytest.mark.parametrize("dtype,d,period", [("bf16", 64, 128), ("bf16", 128, 64), ("f32", 64, 64), ("f32", 128, 32)])
+def test_decode_keys_without_weight(dtype, d, period):
+    """Keys whose logit is -inf weigh nothing, also where all the keys that one group of lanes reads in its
+    first batch of loads are such keys (every `period`-th key: those groups then see nothing else)."""
+    heads, B, k, q_len, N = 2, 128, 8, 2, 40 * 128
+    Q, K, V = make(1, heads, 0, N, d, dtype, 31, q_len)
+    Q[..., 0] = Q[..., 0].abs() + 0.5
+    npast = (N - 1) // B
+    cent = K[:, :, :npast * B].reshape(1, heads, npast, B, d).mean(3, dtype=torch.float32)
+    K[:, :, ::period, 0] = -float("inf")
+    sh = moba.Shape(1, heads, N, d, B, k, 0, binding.BF16 if dtype == "bf16" else binding.F32)
+    O, lse, idx = moba.decode_forward(sh, q_len, Q.cuda(), K.cuda(), V.cuda(), cent.cuda())
+    for h in range(heads):
+        for r in range(q_len):
+            t = N - q_len + r
+            keys = torch.cat([torch.arange(j * B, (j + 1) * B) for j in idx[0, h, r].tolist()] +
+                             [torch.arange(t // B * B, t + 1)])
+            keys = keys[keys % period != 0]
+            z = K[0, h, keys].double() @ Q[0, h, r].double() / d ** 0.5
+            ref = torch.softmax(z, 0) @ V[0, h, keys].double()
+            assert (O[0, h, r].double().cpu() - ref).abs().max() < parity.O_TOL[dtype]
+            assert abs(float(lse[0, h, r]) - float(torch.logsumexp(z, 0))) < parity.LSE_TOL[dtype]
