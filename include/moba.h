@@ -144,13 +144,16 @@ int moba_key_conv_backward(const moba_shape* shape, const void* K, const float* 
  *                  ascending (deterministic); block j's list is
  *                  blk_q[blk_off[j] .. blk_off[j+1]).  Bits 0..23 of an entry are the
  *                  query's position in the sequence.  Bits 24..31 are for the library's
- *                  own use: where the shape and flags select the key-block-major
- *                  attention kernels they hold the position of block j in that query's
- *                  row of topk_idx, otherwise zero.  Lists MUST therefore be built (here or
- *                  by moba_build_lists) with the shape and flags they are used with: the
- *                  key-block-major kernels file their partial results by that position, and
- *                  lists built without it (e.g. with MOBA_FLAG_QUERY_TILES, then used with
- *                  MOBA_FLAG_KEY_MAJOR) give a wrong result that no status code reports.
+ *                  own use: where the shape and flags select kernels that file partial
+ *                  results per (query, key block) -- the key-block-major ones and those for
+ *                  fp32 tensors and for bf16 with B not a multiple of 32 -- they hold the
+ *                  position of block j in that query's row of topk_idx, otherwise zero.
+ *                  Lists MUST therefore be built (here or by moba_build_lists) with the
+ *                  shape and flags they are used with: for the bf16 key-block-major kernels
+ *                  lists built without the positions (e.g. with MOBA_FLAG_QUERY_TILES, then
+ *                  used with MOBA_FLAG_KEY_MAJOR) give a wrong result that no status code
+ *                  reports.  (The other kernels take lists of the same routing built for any
+ *                  flags or dtype.)
  *   ws             at least topk_ws bytes from moba_workspace_bytes
  */
 int moba_topk(const moba_shape* shape, const void* Q, const float* centroids,

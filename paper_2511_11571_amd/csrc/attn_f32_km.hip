@@ -4,7 +4,8 @@
 // key blocks outermost, their routed queries gathered into dense tiles) and walks the block's query
 // list, then the block's own queries under the causal mask, 16 queries per step and wave; a query's
 // contributions from different key blocks are written once, as fp32 rows [query][kept block][part],
-// and a merge kernel adds them up in a fixed order.  v_mfma_f32_16x16x4_f32 everywhere: fp32 operands,
+// and a merge kernel adds them up in a fixed order.  The place of a kept block comes with the list entry, and
+// is looked up in the query's row where the lists were built for other kernels and do not hold it.  v_mfma_f32_16x16x4_f32 everywhere: fp32 operands,
 // products and sums.
 //
 // The plain kernels of attn_reference.hip, which served these shapes, read every key row again for
@@ -92,13 +93,24 @@ struct Walk {
     }
 };
 
+// Where block j stands in the query's row of kept blocks (own rows: k).  The list entry says it where the
+// lists were built for these kernels; lists built for others say 0.  `there` is what the row holds at the
+// place of the entry; if that is not j, the row is searched.  -1: the row does not hold j.
+__device__ __forceinline__ int place_of(int entry, int there, const int32_t* __restrict__ irow, int j, int k)
+{
+    int e = list_slot(entry);
+    if (e >= k || there == j) return e;
+    for (e = k - 1; e >= 0 && irow[e] != j; --e) {}
+    return e;
+}
+
 }  // namespace
 
 // NT: 16-key tiles of a part
 template <typename T, int D, int NT>
 __global__ __launch_bounds__(F32Cfg<D>::NWF * kWave) void fwd_f32_km_kernel(
-    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ off,
-    const int32_t* __restrict__ ql, float* __restrict__ PO, float2* __restrict__ Pml, int N, int B, int n, int k,
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ idx,
+    const int32_t* __restrict__ off, const int32_t* __restrict__ ql, float* __restrict__ PO, float2* __restrict__ Pml, int N, int B, int n, int k,
     int nsub, int pk, int nsplit, float scale, int64_t R, int bh, int G)
 {
     using C = F32Cfg<D>;
@@ -131,33 +143,36 @@ __global__ __launch_bounds__(F32Cfg<D>::NWF * kWave) void fwd_f32_km_kernel(
     const int64_t slots = (int64_t)(k + 1) * nsub;
     const int grow = lane / Ga::CPR, gcol = (lane % Ga::CPR) * Ga::EPL;
     const T* Qs = Q + sbase * D + gcol;
-    auto ids = [&](int a0, int (&t)[Ga::NI]) {
+    const int32_t* kept = k > 0 ? idx + sbase * k : os;     // (k = 0: no rows; any readable address serves)
+    // t: entries of the rows this lane gathers a piece of; tl: of row m16, there: what its row of kept blocks
+    // holds at the entry's place
+    auto ids = [&](int a0, int (&t)[Ga::NI], int& tl) {
 #pragma unroll
         for (int i = 0; i < Ga::NI; ++i) t[i] = w.at(a0 + Ga::RPI * i + grow);
+        tl = w.at(a0 + m16);
     };
-    auto fetch = [&](const int (&t)[Ga::NI], u32x4_t (&q)[Ga::NI]) {
+    auto fetch = [&](const int (&t)[Ga::NI], int tl, u32x4_t (&q)[Ga::NI], int& there) {
 #pragma unroll
         for (int i = 0; i < Ga::NI; ++i) q[i] = *reinterpret_cast<const u32x4_t*>(Qs + (int64_t)list_query(t[i]) * D);
+        there = kept[(int64_t)list_query(tl) * k + min(list_slot(tl), max(k - 1, 0))];
     };
     const int stride = 16 * NW * nsplit;
     int a0 = 16 * (split * NW + wave);
-    int tA[Ga::NI], tN[Ga::NI];
+    int tA[Ga::NI], tN[Ga::NI], tlA, tlN, thereA;
     u32x4_t qr[Ga::NI];
-    ids(a0, tA);
-    ids(a0 + stride, tN);
-    fetch(tA, qr);
+    ids(a0, tA, tlA);
+    ids(a0 + stride, tN, tlN);
+    fetch(tA, tlA, qr, thereA);
     for (; a0 < w.total; a0 += stride) {
-        // park the 16 rows, the list entry behind each; the next step's loads go out
+        // park the 16 rows; the next step's loads go out
+        const int tl = tlA, there = thereA;
 #pragma unroll
-        for (int i = 0; i < Ga::NI; ++i) {
-            float* row = stQ + (grow + Ga::RPI * i) * LD;
-            put<T>(row + gcol, qr[i]);
-            if (gcol == 0) reinterpret_cast<int*>(row)[D] = tA[i];
-        }
+        for (int i = 0; i < Ga::NI; ++i) put<T>(stQ + (grow + Ga::RPI * i) * LD + gcol, qr[i]);
 #pragma unroll
         for (int i = 0; i < Ga::NI; ++i) tA[i] = tN[i];
-        ids(a0 + 2 * stride, tN);
-        fetch(tA, qr);
+        tlA = tlN;
+        ids(a0 + 2 * stride, tN, tlN);
+        fetch(tA, tlA, qr, thereA);
         __builtin_amdgcn_wave_barrier();
         // S^T: keys x queries
         f32x4_t x[NT];
@@ -210,11 +225,11 @@ __global__ __launch_bounds__(F32Cfg<D>::NWF * kWave) void fwd_f32_km_kernel(
                     for (int mt = 0; mt < 4; ++mt) o[4 * h + mt] = mfma4(a[mt], x[kt][i], o[4 * h + mt]);
                 }
         // the partial: this lane holds channels 64 h + 16 g .. + 15 of its row
-        if (av < w.total) {
-            // clamped: lists that do not match the rows of kept blocks give a wrong result, never an
-            // address outside the partials
-            const int note = reinterpret_cast<const int*>(stQ + m16 * LD)[D];
-            const int64_t prow = (sbase + min(list_query(note), N - 1)) * slots + (int64_t)min(list_slot(note), k) * nsub + c;
+        // (clamped: lists that do not match the rows of kept blocks give a wrong result, never an address
+        // outside the partials)
+        const int e = place_of(tl, there, kept + (int64_t)list_query(tl) * k, j, k);
+        if (av < w.total && e >= 0) {
+            const int64_t prow = (sbase + min(list_query(tl), N - 1)) * slots + (int64_t)min(e, k) * nsub + c;
             float* dst = PO + prow * D + 16 * g;
 #pragma unroll
             for (int h = 0; h < C::H; ++h)
@@ -295,8 +310,8 @@ __global__ __launch_bounds__(256) void fwd_f32_merge_kernel(
 template <typename T, int D, int NT>
 __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
-    const float2* __restrict__ ld, const int32_t* __restrict__ off, const int32_t* __restrict__ ql,
-    float* __restrict__ PdQ, T* __restrict__ dK, T* __restrict__ dV, float* __restrict__ sums, int N, int B, int n,
+    const float2* __restrict__ ld, const int32_t* __restrict__ idx, const int32_t* __restrict__ off,
+    const int32_t* __restrict__ ql, float* __restrict__ PdQ, T* __restrict__ dK, T* __restrict__ dV, float* __restrict__ sums, int N, int B, int n,
     int k, int nsub, int pk, int nsplit, float scale, int64_t R, int bh, int G, int want_dq, int want_dkv)
 {
     using C = F32Cfg<D>;
@@ -333,18 +348,21 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
     const int grow = lane / Ga::CPR, gcol = (lane % Ga::CPR) * Ga::EPL;
     const T* Qs = Q + sbase * D + gcol;
     const T* Gs = dO + sbase * D + gcol;
+    const int32_t* kept = k > 0 ? idx + sbase * k : os;     // (as in the forward, like `there` below)
     auto ids = [&](int a0, int (&t)[Ga::NI], int& tl) {
 #pragma unroll
         for (int i = 0; i < Ga::NI; ++i) t[i] = w.at(a0 + Ga::RPI * i + grow);
-        tl = list_query(w.at(a0 + m16));
+        tl = w.at(a0 + m16);
     };
-    auto fetch = [&](int a0, const int (&t)[Ga::NI], int tl, u32x4_t (&q)[Ga::NI], u32x4_t (&gr)[Ga::NI], float2& x) {
+    auto fetch = [&](int a0, const int (&t)[Ga::NI], int tl, u32x4_t (&q)[Ga::NI], u32x4_t (&gr)[Ga::NI], float2& x,
+                     int& there) {
 #pragma unroll
         for (int i = 0; i < Ga::NI; ++i) {
             q[i] = *reinterpret_cast<const u32x4_t*>(Qs + (int64_t)list_query(t[i]) * D);
             gr[i] = *reinterpret_cast<const u32x4_t*>(Gs + (int64_t)list_query(t[i]) * D);
         }
-        x = ld[sbase + tl];
+        x = ld[sbase + list_query(tl)];
+        there = kept[(int64_t)list_query(tl) * k + min(list_slot(tl), max(k - 1, 0))];
         if (a0 + m16 >= w.total) x = make_float2(INFINITY, 0.f);           // no such row: P = 0
     };
     f32x4_t dKT[C::MT][NT], dVT[C::MT][NT];
@@ -357,26 +375,26 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
         }
     const int stride = 16 * NW * nsplit;
     int a0 = 16 * (split * NW + wave);
-    int tA[Ga::NI], tN[Ga::NI], tlA, tlN;
+    int tA[Ga::NI], tN[Ga::NI], tlA, tlN, thereA;
     u32x4_t qr[Ga::NI], gr[Ga::NI];
     float2 xl;
     ids(a0, tA, tlA);
     ids(a0 + stride, tN, tlN);
-    fetch(a0, tA, tlA, qr, gr, xl);
+    fetch(a0, tA, tlA, qr, gr, xl, thereA);
     for (; a0 < w.total; a0 += stride) {
+        const int tl = tlA, there = thereA;
 #pragma unroll
         for (int i = 0; i < Ga::NI; ++i) {
             float* row = stQ + (grow + Ga::RPI * i) * LD;
             put<T>(row + gcol, qr[i]);
             put<T>(row + 16 * LD + gcol, gr[i]);
-            if (gcol == 0) reinterpret_cast<int*>(row)[D] = tA[i];
         }
         if (lane < 16) { sl[lane] = xl.x; sl[16 + lane] = xl.y; }
 #pragma unroll
         for (int i = 0; i < Ga::NI; ++i) tA[i] = tN[i];
         tlA = tlN;
         ids(a0 + 2 * stride, tN, tlN);
-        fetch(a0 + stride, tA, tlA, qr, gr, xl);
+        fetch(a0 + stride, tA, tlA, qr, gr, xl, thereA);
         __builtin_amdgcn_wave_barrier();
         const f32x4_t l4 = *reinterpret_cast<const f32x4_t*>(sl + 4 * g);
         const f32x4_t nd = *reinterpret_cast<const f32x4_t*>(sl + 16 + 4 * g);
@@ -448,9 +466,9 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
                         for (int mt = 0; mt < 4; ++mt) o[4 * h + mt] = mfma4(a[mt], b[i], o[4 * h + mt]);
                     }
             }
-            if (a0 + m16 < w.total) {
-                const int note = reinterpret_cast<const int*>(stQ + m16 * LD)[D];
-                const int64_t prow = (sbase + min(list_query(note), N - 1)) * slots + (int64_t)min(list_slot(note), k) * nsub + c;
+            const int e = place_of(tl, there, kept + (int64_t)list_query(tl) * k, j, k);
+            if (a0 + m16 < w.total && e >= 0) {
+                const int64_t prow = (sbase + min(list_query(tl), N - 1)) * slots + (int64_t)min(e, k) * nsub + c;
                 float* dst = PdQ + prow * D + 16 * g;
 #pragma unroll
                 for (int h = 0; h < C::H; ++h)
@@ -630,7 +648,7 @@ static hipError_t fwd_launch_nt(const Dims& s, const Cut& c, const void* Q, cons
     hipError_t e = ensure_dynamic_lds((const void*)fwd_f32_km_kernel<T, D, NT>, C::fwd_lds(NT));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((fwd_f32_km_kernel<T, D, NT>), dim3((unsigned)schedule_grid(s.bh, s.n * c.nsub * ns)),
-                       dim3(C::NWF * kWave), C::fwd_lds(NT), st, (const T*)Q, (const T*)K, (const T*)V, off, ql, PO, Pml,
+                       dim3(C::NWF * kWave), C::fwd_lds(NT), st, (const T*)Q, (const T*)K, (const T*)V, idx, off, ql, PO, Pml,
                        s.N, s.B, s.n, s.k, c.nsub, c.pk, ns, s.scale, s.R, s.bh, s.G);
     const int64_t rows = (int64_t)s.bh * s.N;
     const int rpw = 256 / (D / 4);
@@ -651,7 +669,7 @@ static hipError_t bwd_launch_nt(const Dims& s, const Cut& c, const void* Q, cons
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((bwd_f32_km_kernel<T, D, NT>), dim3((unsigned)schedule_grid(s.bh, s.n * c.nsub * ns)),
                        dim3(C::NWB * kWave), C::bwd_lds(NT), st, (const T*)Q, (const T*)K, (const T*)V, (const T*)dO, ld,
-                       off, ql, PdQ, (T*)dK, (T*)dV, sums, s.N, s.B, s.n, s.k, c.nsub, c.pk, ns, s.scale, s.R, s.bh, s.G,
+                       idx, off, ql, PdQ, (T*)dK, (T*)dV, sums, s.N, s.B, s.n, s.k, c.nsub, c.pk, ns, s.scale, s.R, s.bh, s.G,
                        want_dq, want_dkv);
     if (want_dkv && sums) {
         const int64_t quads = (int64_t)s.N * D / 4, total = 2 * quads * s.bhk;

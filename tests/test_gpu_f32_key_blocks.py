@@ -37,3 +37,27 @@ def test_fp32_forward_and_backward(oracle, d, B, n, k, heads, kv):
     assert parity.max_abs(lse.double().cpu().numpy()[0], rlse) < parity.LSE_TOL["f32"]
     for name, a, b in zip(("O", "dQ", "dK", "dV"), got, want):
         assert parity.rel_l2(a.double().cpu().numpy()[0], b) < parity.GRAD_TOL["f32"], name
+
+
+@pytest.mark.parametrize("dtype,d,B,n,k,kv", [("f32", 64, 32, 24, 5, 0), ("f32", 128, 96, 6, 3, 1), ("bf16", 64, 50, 12, 4, 0)])
+def test_lists_without_places(dtype, d, B, n, k, kv):
+    """Lists built for kernels that file nothing by the place of a block (here: the plain ones) hold no places:
+    attention finds them in the rows of kept blocks, and the results are the same bit for bit."""
+    N, heads, code = B * n, 2, binding.F32 if dtype == "f32" else binding.BF16
+    g = torch.Generator(device="cuda").manual_seed(d + B)
+    Q, K, V, dO = (torch.randn((1, h, N, d), generator=g, device="cuda").to(torch.float32 if code == binding.F32 else torch.bfloat16)
+                   for h in (heads, kv or heads, kv or heads, heads))
+    sh = moba.Shape(1, heads, N, d, B, k, 0, code, 0.0, 0, kv)
+    plain = moba.Shape(1, heads, N, d, B, k, 0, code, 0.0, binding.FLAG_REFERENCE_KERNELS, kv)
+    _, cent = moba.centroids(sh, K)
+    idx, lists = moba.topk(sh, Q, cent)
+    bare = moba.build_lists(plain, idx)
+    R = int(lists[0][0, 0, -1])
+    assert bool((lists[1][..., :R] >> 24 > 0).any()) and bool((bare[1][..., :R] >> 24 == 0).all())
+    out = []
+    for some in (lists, bare):
+        ws = [torch.full((size,), 0xff, dtype=torch.uint8, device="cuda") for size in moba.workspace_bytes(sh)]  # (NaN)
+        O, lse = moba.forward(sh, Q, K, V, idx, some, ws=ws[1])
+        out.append((O, lse, *moba.backward(sh, Q, K, V, O, lse, dO, idx, some, ws=ws[2])))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
