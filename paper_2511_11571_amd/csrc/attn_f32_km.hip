@@ -29,6 +29,8 @@ __device__ __forceinline__ f32x4_t mfma4(float a, float b, f32x4_t c)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+constexpr float kFltLargest = 3.402823466e+38f;
+
 template <int D>
 struct F32Cfg {
     static constexpr int LD = D + 4;                   // words per row of a tile in LDS
@@ -67,17 +69,70 @@ __device__ __forceinline__ void put(float* dst, const u32x4_t& x)
     }
 }
 
-// rows first .. first + rows of X -> tile[row][D + 4]; rows nk and beyond read as zero
+// rows first .. first + rows of X -> tile[row][D + 4]; rows nk and beyond read as zero.  True: this thread
+// brought an infinity or a NaN
 template <typename T, int D, int NTHREADS>
-__device__ __forceinline__ void stage_rows(const T* __restrict__ X, float* tile, int rows, int nk, int tid)
+__device__ __forceinline__ bool stage_rows(const T* __restrict__ X, float* tile, int rows, int nk, int tid)
 {
     constexpr int CPR = Gather<T, D>::CPR, EPL = Gather<T, D>::EPL;
+    bool odd = false;
     for (int i = tid; i < rows * CPR; i += NTHREADS) {
         const int r = i / CPR, c = i % CPR;
         u32x4_t x = {0u, 0u, 0u, 0u};
         if (r < nk) x = *reinterpret_cast<const u32x4_t*>(X + (size_t)r * D + c * EPL);
         put<T>(tile + r * (D + 4) + c * EPL, x);
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            odd = odd || (x[h] & 0x7f800000u) == 0x7f800000u;
+            if (sizeof(T) == 2) odd = odd || (x[h] & 0x7f80u) == 0x7f80u;
+        }
     }
+    return odd;
+}
+
+// A key that a query does not see has weight zero, and the matrix instructions add 0 * x for it: no zero where x
+// is an infinity or a NaN.  Only a block's own queries fail to see keys of it.  So where a part holds such a
+// value, every wave does the own rows of its walk once more afterwards, one query at a time over the keys that
+// it sees: f(query, number of keys of the part that it sees).
+template <typename F>
+__device__ __forceinline__ void own_rows_again(int a0, int stride, int nlist, int total, int own0, int nk, F f)
+{
+    __threadfence_block();                                  // (the walk's partials go first)
+#pragma unroll 1
+    for (; a0 < total; a0 += stride)
+#pragma unroll 1
+        for (int a = max(a0, nlist); a < min(a0 + 16, total); ++a) f(own0 + (a - nlist), min(a - nlist + 1, nk));
+}
+
+template <typename T, int D>
+__device__ __forceinline__ float row_dot(const T* __restrict__ a, const T* __restrict__ b)
+{
+    float acc = 0.f;
+#pragma unroll 1
+    for (int c = 0; c < D; c += 8) {
+        float x[8], y[8];
+        Vec8<T>::load(a + c, x);
+        Vec8<T>::load(b + c, y);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc = fmaf(x[e], y[e], acc);
+    }
+    return acc;
+}
+
+// out[0 .. D) <- the weights (a lane each, the first `seen` lanes) times as many rows of X; w: 64 words of LDS
+template <typename T, int D>
+__device__ __forceinline__ void weigh_rows(float weight, int seen, const T* __restrict__ X, float* w, float* out, int lane)
+{
+    w[lane] = weight;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+    for (int ch = lane; ch < D; ch += kWave) {
+        float acc = 0.f;
+#pragma unroll 1
+        for (int u = 0; u < seen; ++u) acc = fmaf(w[u], to_f32<T>(X[(size_t)u * D + ch]), acc);
+        out[ch] = acc;
+    }
+    __builtin_amdgcn_wave_barrier();
 }
 
 // the walk of a workgroup: positions 0 .. nlist - 1 are the block's list, then its own queries from the
@@ -136,7 +191,9 @@ __global__ __launch_bounds__(F32Cfg<D>::NWF * kWave) void fwd_f32_km_kernel(
     w.own_e = k << 24;
     w.total = w.nlist + (B - own_first);
     stage_rows<T, D, NW * kWave>(K + (kvbase + w.own0) * D, sK, 16 * NT, nk, tid);
-    stage_rows<T, D, NW * kWave>(V + (kvbase + w.own0) * D, sV, 16 * NT, nk, tid);
+    __shared__ int odd[NW];                                 // of the V rows that each wave brought
+    const bool mine = stage_rows<T, D, NW * kWave>(V + (kvbase + w.own0) * D, sV, 16 * NT, nk, tid);
+    odd[wave] = __ballot(mine) != 0;
     __syncthreads();
 
     const float c2 = scale * kLog2e;
@@ -201,11 +258,12 @@ __global__ __launch_bounds__(F32Cfg<D>::NWF * kWave) void fwd_f32_km_kernel(
         mref = max_nan(mref, __shfl_xor(mref, 16, kWave));
         mref = max_nan(mref, __shfl_xor(mref, 32, kWave));
         float l = 0.f;
+        const float ref = fmaxf(mref, -kFltLargest);             // (no finite logit in this part: no weight)
 #pragma unroll
         for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                x[kt][i] = fast_exp2(x[kt][i] - mref);
+                x[kt][i] = fast_exp2(x[kt][i] - ref);
                 l += x[kt][i];
             }
         l += __shfl_xor(l, 16, kWave);
@@ -241,6 +299,17 @@ __global__ __launch_bounds__(F32Cfg<D>::NWF * kWave) void fwd_f32_km_kernel(
         }
         __builtin_amdgcn_wave_barrier();
     }
+    int any = 0;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) any |= odd[v];
+    if (!any) return;
+    own_rows_again(16 * (split * NW + wave), stride, w.nlist, w.total, w.own0, nk, [&](int t, int seen) {
+        const float z = lane < seen ? c2 * row_dot<T, D>(Q + (sbase + t) * D, K + (kvbase + w.own0 + lane) * D) : -INFINITY;
+        const float top = wave_max(z), p = fast_exp2(z - fmaxf(top, -kFltLargest)), l = wave_sum(p);
+        const int64_t prow = (sbase + t) * slots + (int64_t)k * nsub + c;
+        weigh_rows<T, D>(p, seen, V + (kvbase + w.own0) * D, stQ, PO + prow * D, lane);
+        if (lane == 0) Pml[prow] = make_float2(top, l);
+    });
 }
 
 // A query's partials, [kept block or own block][part]: which exist
@@ -339,8 +408,10 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
     w.own0 = j * B + own_first;
     w.own_e = k << 24;
     w.total = w.nlist + (B - own_first);
-    stage_rows<T, D, NW * kWave>(K + (kvbase + w.own0) * D, sK, 16 * NT, nk, tid);
-    stage_rows<T, D, NW * kWave>(V + (kvbase + w.own0) * D, sV, 16 * NT, nk, tid);
+    __shared__ int odd[NW];                                 // of the rows that each wave brought
+    bool mine = stage_rows<T, D, NW * kWave>(K + (kvbase + w.own0) * D, sK, 16 * NT, nk, tid);
+    mine = stage_rows<T, D, NW * kWave>(V + (kvbase + w.own0) * D, sV, 16 * NT, nk, tid) || mine;
+    odd[wave] = __ballot(mine) != 0;
     __syncthreads();
 
     const float c2 = scale * kLog2e;
@@ -480,45 +551,60 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
         }
         __builtin_amdgcn_wave_barrier();
     }
-    if (!want_dkv) return;
-    // sum over the waves, in order, through LDS: over the K and V tiles (row-major, keys x channels)
-    __syncthreads();
-    for (int wv = 0; wv < NW; ++wv) {
-        if (wave == wv) {
+    int any = 0;
 #pragma unroll
-            for (int kt = 0; kt < NT; ++kt)
-#pragma unroll
-                for (int h = 0; h < C::H; ++h)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        // result rows 4 g + i of tile 4 h + mt: channel 64 h + 16 g + 4 i + mt of key 16 kt + m16
-                        float* pk_ = sK + (16 * kt + m16) * LD + 64 * h + 16 * g + 4 * i;
-                        float* pv_ = sV + (16 * kt + m16) * LD + 64 * h + 16 * g + 4 * i;
-                        f32x4_t a = {dKT[4 * h][kt][i], dKT[4 * h + 1][kt][i], dKT[4 * h + 2][kt][i], dKT[4 * h + 3][kt][i]};
-                        f32x4_t b = {dVT[4 * h][kt][i], dVT[4 * h + 1][kt][i], dVT[4 * h + 2][kt][i], dVT[4 * h + 3][kt][i]};
-                        if (wv > 0) {
-                            a += *reinterpret_cast<const f32x4_t*>(pk_);
-                            b += *reinterpret_cast<const f32x4_t*>(pv_);
-                        }
-                        *reinterpret_cast<f32x4_t*>(pk_) = a;
-                        *reinterpret_cast<f32x4_t*>(pv_) = b;
-                    }
-        }
+    for (int v = 0; v < NW; ++v) any |= odd[v];
+    if (want_dkv) {
+        // sum over the waves, in order, through LDS: over the K and V tiles (row-major, keys x channels)
         __syncthreads();
-    }
-    for (int i = tid; i < 2 * nk * (D / 4); i += NW * kWave) {
-        const int which = i / (nk * (D / 4)), rem = i % (nk * (D / 4)), key = rem / (D / 4), ch = 4 * (rem % (D / 4));
-        f32x4_t v = *reinterpret_cast<const f32x4_t*>((which == 0 ? sK : sV) + key * LD + ch);
-        if (which == 0) v *= scale;
-        const int64_t at = w.own0 + key;
-        if (sums) {
-            *reinterpret_cast<f32x4_t*>(sums + ((((int64_t)which * bh + s) * nsplit + split) * N + at) * D + ch) = v;
-        } else {
-            T* dst = (which == 0 ? dK : dV) + (kvbase + at) * D + ch;
+        for (int wv = 0; wv < NW; ++wv) {
+            if (wave == wv) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) dst[e] = from_f32<T>(v[e]);
+                for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+                    for (int h = 0; h < C::H; ++h)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            // result rows 4 g + i of tile 4 h + mt: channel 64 h + 16 g + 4 i + mt of key 16 kt + m16
+                            float* pk_ = sK + (16 * kt + m16) * LD + 64 * h + 16 * g + 4 * i;
+                            float* pv_ = sV + (16 * kt + m16) * LD + 64 * h + 16 * g + 4 * i;
+                            f32x4_t a = {dKT[4 * h][kt][i], dKT[4 * h + 1][kt][i], dKT[4 * h + 2][kt][i], dKT[4 * h + 3][kt][i]};
+                            f32x4_t b = {dVT[4 * h][kt][i], dVT[4 * h + 1][kt][i], dVT[4 * h + 2][kt][i], dVT[4 * h + 3][kt][i]};
+                            if (wv > 0) {
+                                a += *reinterpret_cast<const f32x4_t*>(pk_);
+                                b += *reinterpret_cast<const f32x4_t*>(pv_);
+                            }
+                            *reinterpret_cast<f32x4_t*>(pk_) = a;
+                            *reinterpret_cast<f32x4_t*>(pv_) = b;
+                        }
+            }
+            __syncthreads();
+        }
+        for (int i = tid; i < 2 * nk * (D / 4); i += NW * kWave) {
+            const int which = i / (nk * (D / 4)), rem = i % (nk * (D / 4)), key = rem / (D / 4), ch = 4 * (rem % (D / 4));
+            f32x4_t v = *reinterpret_cast<const f32x4_t*>((which == 0 ? sK : sV) + key * LD + ch);
+            if (which == 0) v *= scale;
+            const int64_t at = w.own0 + key;
+            if (sums) {
+                *reinterpret_cast<f32x4_t*>(sums + ((((int64_t)which * bh + s) * nsplit + split) * N + at) * D + ch) = v;
+            } else {
+                T* dst = (which == 0 ? dK : dV) + (kvbase + at) * D + ch;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dst[e] = from_f32<T>(v[e]);
+            }
         }
     }
+    if (!any || !want_dq) return;
+    own_rows_again(16 * (split * NW + wave), stride, w.nlist, w.total, w.own0, nk, [&](int t, int seen) {
+        float ds = 0.f;
+        if (lane < seen) {
+            const int64_t key = (kvbase + w.own0 + lane) * D;
+            const float2 x = ld[sbase + t];
+            const float z = c2 * row_dot<T, D>(Q + (sbase + t) * D, K + key);
+            ds = fast_exp2(z - x.x) * (row_dot<T, D>(dO + (sbase + t) * D, V + key) + x.y);
+        }
+        weigh_rows<T, D>(ds, seen, K + (kvbase + w.own0) * D, stQ, PdQ + ((sbase + t) * slots + (int64_t)k * nsub + c) * D, lane);
+    });
 }
 
 // dK, dV of a key/value slice = its sums over shares of the walk and query heads, in order

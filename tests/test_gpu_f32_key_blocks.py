@@ -61,3 +61,33 @@ def test_lists_without_places(dtype, d, B, n, k, kv):
         out.append((O, lse, *moba.backward(sh, Q, K, V, O, lse, dO, idx, some, ws=ws[2])))
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,d,B,n,k,kv", [("f32", 64, 64, 12, 3, 0), ("f32", 128, 96, 6, 2, 1), ("bf16", 64, 50, 8, 3, 0)])
+def test_keys_that_a_query_does_not_see_cannot_reach_it(dtype, d, B, n, k, kv):
+    """Infinities and NaN in keys and values: a query's output and gradient are finite exactly where the plain
+    kernels, which touch nothing but the keys that a query sees, find them finite, and equal there."""
+    N, heads, code = B * n, 2, binding.F32 if dtype == "f32" else binding.BF16
+    dt, hkv = torch.float32 if code == binding.F32 else torch.bfloat16, kv or heads
+    g = torch.Generator(device="cuda").manual_seed(3 * d + B)
+    Q, K, V, dO = (torch.randn((1, h, N, d), generator=g, device="cuda").to(dt) for h in (heads, hkv, hkv, heads))
+    Q[..., 0] = Q[..., 0].abs() + 0.5
+    shapes = [moba.Shape(1, heads, N, d, B, k, 0, code, 0.0, f, kv) for f in (0, binding.FLAG_REFERENCE_KERNELS)]
+    _, cent = moba.centroids(shapes[0], K)
+    idx, _ = moba.topk(shapes[0], Q, cent)
+    inf, last = float("inf"), (n - 1) * B
+    # in the last block, which no other query keeps; and keys of no weight, among them a block's first
+    V[:, :, last + B // 2, 3], K[:, :, last + B // 2 + 1, 5], V[:, :, last + B - 1, 9] = inf, float("nan"), float("nan")
+    K[:, :, 2 * B:3 * B:7, 0] = -inf
+    out = []
+    for sh in shapes:
+        lists = moba.build_lists(sh, idx)
+        O, lse = moba.forward(sh, Q, K, V, idx, lists)
+        out.append((O, lse, moba.backward(sh, Q, K, V, O, lse, dO, idx, lists)[0]))
+    tol = 1e-5 if dtype == "f32" else 2 ** -7              # fp32 sums in another order; two roundings to bf16
+    for name, a, b in zip(("O", "lse", "dQ"), *out):
+        a, b = a.double(), b.double()
+        seen = torch.isfinite(b)
+        assert torch.equal(torch.isfinite(a), seen), name
+        assert not bool(seen.all()) and float(seen.double().mean()) > 0.4, name
+        assert float((a - b)[seen].norm() / b[seen].norm()) < tol, name
