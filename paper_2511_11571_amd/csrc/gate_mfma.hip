@@ -312,8 +312,9 @@ void gate_many_kernel(
                 }
             const float qn = sqrtf(fsum_g(q2));
             const float acc = 7.62939453e-6f * rc;                      // 2^-17 |c|
-            eps1[qt] = qn * (1.001f * r1 + acc) + 1e-37f;
-            eps2[qt] = qn * (1.001f * r2 + acc) + 1e-37f;
+            // (a floor under both: kGateKeys / eps stays finite for a query of zeros as well)
+            eps1[qt] = qn * (1.001f * r1 + acc) + 1e-30f;
+            eps2[qt] = qn * (1.001f * r2 + acc) + 1e-30f;
             finite = finite && eps1[qt] < 1e37f && qn * rc < 1e37f;
         }
         if (__ballot(!finite)) {
@@ -332,7 +333,7 @@ void gate_many_kernel(
         }
     };
     // sweep 1: group maxima
-    float scale[QT], off[QT], thr[QT];                                  // key of a score: score * scale + off; collected from thr on
+    float scale[QT], base[QT], thr[QT];                                 // key of a score: (score - base) * scale + 1.5; collected from thr on
     {
         f32x4_t gm[QT][C::GR / 4];
 #pragma unroll
@@ -376,7 +377,7 @@ void gate_many_kernel(
             // apart beyond their block: it keeps every candidate or goes to the exact ranking.)
             scale[qt] = all ? 0.f : kGateKeys / (mx - lo + 3.f * e);
             thr[qt] = all ? (16 * qt + m16 < rows_here ? -kFltMax : kFltMax) : lo - e;   // (rows past the last: nothing)
-            off[qt] = all ? 1.f : 1.5f - thr[qt] * scale[qt];
+            base[qt] = all ? 0.f : thr[qt];                              // (the difference first: no key falls below 1)
         }
     }
     // sweep 2: candidates.  The lanes g = 2 p and 2 p + 1 of a query fill the segment p of SEG words from
@@ -409,7 +410,7 @@ void gate_many_kernel(
             for (int i = 0; i < 4; ++i) {
                 if (KC == 16 && hits[qt][i] == 0) continue;             // (few of many: most scores end here)
                 if (__builtin_amdgcn_inverse_ballot_w64(hits[qt][i])) {
-                    const uint32_t key = min((uint32_t)fmaf(sc[qt][i], scale[qt], off[qt]), (uint32_t)kGateTopKey + 1u);
+                    const uint32_t key = min((uint32_t)fmaf(sc[qt][i] - base[qt], scale[qt], 1.5f), (uint32_t)kGateTopKey + 1u);
                     cand[at[qt]] = (key << kGateIdBits) + (id + i);
                     at[qt] += dir;
                 }

@@ -76,3 +76,22 @@ def test_two_sweeps_keep_what_the_exact_search_keeps(d, n, k, B, heads, conv):
     # chance of about k n 2^-22 per 1000 rows
     assert (got != want).any(-1).float().mean() < 1e-4
     assert torch.equal(got[:, -1], want[:, -1])
+
+
+def test_zero_queries_in_strips_of_many_blocks():
+    """A packed batch whose short sequences begin inside a strip that also sees a long one: their queries have
+    one to three candidates, and with a query of zeros these are equal: the lowest blocks are kept."""
+    lens, heads, d, B, k = [69968, 48, 53, 37, 9000], 4, 64, 16, 1
+    offs = np.concatenate([[0], np.cumsum(lens)])
+    lay = moba.VarlenLayout(offs, B)
+    Tp = lay.padded_tokens
+    g = torch.Generator(device="cuda").manual_seed(12)
+    Q = torch.randn((1, heads, Tp, d), generator=g, device="cuda").to(torch.bfloat16)
+    Q[:, :, 69968:lay.pad_offsets_host[4]] = 0.0
+    cent = torch.randn((1, heads, Tp // B, d), generator=g, device="cuda") * 0.2
+    got, want = (moba.topk_varlen(moba.Shape(1, heads, Tp, d, B, k, 0, binding.BF16, 0.0, flags, 0), lay, Q, cent)[0]
+                 for flags in (0, binding.FLAG_GATE_EXACT_SEARCH))
+    own = np.arange(48) // B
+    first = 69968 // B
+    assert got[0, 0, 69968:69968 + 48, 0].tolist() == [first if o > 0 else -1 for o in own]
+    assert torch.equal(got, want)
