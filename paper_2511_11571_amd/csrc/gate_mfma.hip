@@ -12,10 +12,10 @@
 //  1. hi term only: a lane keeps the maxima of GR groups of its blocks.  A query has 4 GR groups; at
 //     least k of its scores reach the k-th largest of their maxima (each group's maximum is a score of
 //     its own), and not many more do while 4 GR is well above k.  So that value, less the error of the
-//     hi term, is a lower bound of the k-th largest score -- proved, not estimated.
+//     hi term, is a lower bound of the k-th largest score (kSumError: what is assumed of the matrix unit's sums).
 //  2. hi + mid: every block above that bound becomes a candidate (18-bit score above the bound, block)
 //     in LDS, about 1.1 to 1.5 k of them.  The k-th largest candidate is searched in registers; where
-//     the next one is closer than the error of hi + mid (2^-17 of the scores' scale), the candidates
+//     the next one is closer than the error of hi + mid (2^-16 of |q| |c| at d = 64, 2^-15 at 128), the candidates
 //     inside that error are scored again from all three terms and ranked exactly, ties to the lower block.
 // Strips that do not fit (more candidates or closer scores than there is room for: many equal scores;
 // non-finite values) are put on a list for the exact radix search of topk_mfma.hip.
@@ -283,8 +283,13 @@ void gate_many_kernel(
         if (lane == 0) redo[1 + atomicAdd(redo, 1)] = s * per_slice + per_slice - 1 - t0 / 64;
     };
 
-    // ---- many candidates.  Errors of the approximate scores: |q . (c - hi)| <= |q| |c - hi|, plus what
-    // fp32 sums of D terms can lose
+    // ---- many candidates.  Errors of the approximate scores against the three-term ones: |q . (c - hi)|
+    // <= |q| |c - hi|, plus what the fp32 sums of both can lose.  Every product is exact, and in whatever order the
+    // matrix unit adds them, an addition is taken to lose at most 2^-23 of the largest number in it (cutting off
+    // what does not fit; rounding to nearest would halve that).  The terms go smallest first, so only the D
+    // additions of the hi term meet numbers of the size of |q| |c|; those of the others lose 2^-8 and 2^-16 as
+    // much: less than 1.02 D 2^-23 |q| |c| per score, twice that for the difference of two.
+    constexpr float kSumError = 2.04f * D / 8388608.f;
     float eps1[QT], eps2[QT];
     {
         float r1 = 0.f, r2 = 0.f, rc = 0.f;
@@ -311,7 +316,7 @@ void gate_many_kernel(
                     q2 = fmaf(a, a, fmaf(b, b, q2));
                 }
             const float qn = sqrtf(fsum_g(q2));
-            const float acc = 7.62939453e-6f * rc;                      // 2^-17 |c|
+            const float acc = kSumError * rc;
             // (a floor under both: kGateKeys / eps stays finite for a query of zeros as well)
             eps1[qt] = qn * (1.001f * r1 + acc) + 1e-30f;
             eps2[qt] = qn * (1.001f * r2 + acc) + 1e-30f;
@@ -439,7 +444,7 @@ void gate_many_kernel(
             y[qt][j] = p < pair ? v : 0u;
         }
         total[qt] = sum_g(cnt[qt]);
-        full = full || total[qt] < need[qt];                            // (cannot be: the bound is proved)
+        full = full || total[qt] < need[qt];                            // (cannot be, see kSumError)
     }
     // the k-th largest candidate; how close the next one is
     uint32_t cut[QT];

@@ -1,6 +1,8 @@
 """The gate's kernels at the borders of their dispatch: blocks that fill a tile of 16 or spill one over,
-the last block counts whose scores stay in registers and the first that are swept twice, the lengths of
-row on both sides of each rule, fp32 up to and beyond its limit, and strips that are searched again because too many scores are equal."""
+the last block counts whose scores stay in registers and the first that do not, the lengths of row on both
+sides of each rule, fp32 up to and beyond its limit, equal scores.  The two sweeps run on calls of 300000 query rows
+and more only: those have tests of their own, against the exact search, with shared key/value heads, packed
+batches, and strips that are searched again because too many scores are equal."""
 import numpy as np
 import pytest
 import torch
@@ -72,10 +74,43 @@ def test_two_sweeps_keep_what_the_exact_search_keeps(d, n, k, B, heads, conv):
     cent[:, -1] = 0.0                                # one head of equal scores: its strips are searched again
     got, want = (moba.topk(moba.Shape(1, heads, N, d, B, k, conv, binding.BF16, 0.0, flags, 0), Q, cent)[0]
                  for flags in (0, binding.FLAG_GATE_EXACT_SEARCH))
-    # scores equal up to the rounding of fp32 sums taken in another order: 2^-22 of their scale apart, a
-    # chance of about k n 2^-22 per 1000 rows
-    assert (got != want).any(-1).float().mean() < 1e-4
-    assert torch.equal(got[:, -1], want[:, -1])
+    # (both decide by the same three-term sums)
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("d,k,heads,kv,lens", [(64, 8, 8, 2, [900, 33, 26000, 500, 12000]), (64, 1, 8, 4, [17000, 20000, 700]),
+                                               (128, 3, 8, 1, [5, 21000, 18000]), (128, 8, 10, 0, [30000, 1200])])
+def test_two_sweeps_on_packed_batches_and_shared_heads(d, k, heads, kv, lens):
+    """Strips that begin in one sequence and end in another, strips of a long one with few candidates of a
+    short one among them, centroids of a key/value head that several query heads share; the last of these has
+    equal scores, so that its strips are searched again."""
+    B = 32
+    lay = moba.VarlenLayout(np.concatenate([[0], np.cumsum(lens)]), B)
+    Tp, hkv = lay.padded_tokens, kv or heads
+    assert heads * Tp >= 300000 and Tp // B > 512
+    g = torch.Generator(device="cuda").manual_seed(d + k)
+    Q = torch.randn((1, heads, Tp, d), generator=g, device="cuda").to(torch.bfloat16)
+    cent = torch.randn((1, hkv, Tp // B, d), generator=g, device="cuda") * 0.2
+    if hkv > 1:
+        cent[:, -1] = 0.0
+    shapes = [moba.Shape(1, heads, Tp, d, B, k, 0, binding.BF16, 0.0, flags, kv) for flags in (0, binding.FLAG_GATE_EXACT_SEARCH)]
+    got, want = (moba.topk_varlen(sh, lay, Q, cent)[0] for sh in shapes)
+    assert torch.equal(got, want)
+    got, want = (moba.topk(sh, Q, cent)[0] for sh in shapes)             # the same as one sequence
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("d,n,k,B,heads", [(64, 600, 8, 32, 16), (128, 450, 5, 32, 22)])
+def test_two_sweeps_of_scores_closer_than_their_sums_can_tell(d, n, k, B, heads):
+    """Queries and centroids of one sign with a common part: the scores are near |q| |c| and differ by about 2^-14 of
+    it, so that every row has candidates inside the error of the two-term scores."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    N = n * B
+    Q = (1.0 + 0.1 * torch.rand((1, heads, N, d), generator=g, device="cuda")).to(torch.bfloat16)
+    cent = 1.0 + 2.0 ** -10 * torch.randn((1, heads, n, d), generator=g, device="cuda")
+    got, want = (moba.topk(moba.Shape(1, heads, N, d, B, k, 0, binding.BF16, 0.0, flags, 0), Q, cent)[0]
+                 for flags in (0, binding.FLAG_GATE_EXACT_SEARCH))
+    assert torch.equal(got, want)
 
 
 def test_zero_queries_in_strips_of_many_blocks():
