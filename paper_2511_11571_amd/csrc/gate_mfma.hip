@@ -32,11 +32,12 @@
 
 namespace moba {
 
-// Classes by the longest row of kept blocks.  A wave takes 16 QT queries: more of them share every operand
-// load, but their candidates (SEG per half query) cap the waves per compute unit, and the kernel lives on
-// waves: at N = 524288, B = 128, k = 8 it takes 23.7 ms with two waves per SIMD and 15.4 with three.
+// Classes by the longest row of kept blocks, 8 and 32 (where each runs: gate_supported()).  A wave takes 16 QT
+// queries: more of them share every operand load, but their candidates (SEG per half query) cap the waves per
+// compute unit, and the kernel lives on waves: at N = 524288, B = 128, k = 8 it takes 23.7 ms with two waves per
+// SIMD and 15.4 with three.
 template <int KC> struct GateCfg;
-template <> struct GateCfg<16> {
+template <> struct GateCfg<8> {
     static constexpr int QT = 4, GR = 8, SEG = 24;
 };
 template <> struct GateCfg<32> {
@@ -214,9 +215,8 @@ void gate_few_kernel(
                      gate_lds + wave * select_words<TA>(k));
 }
 
-// Rows of many candidates and, in the last workgroups of every slice, those of few: a strip of either kind
-// takes 30 to 60 us however few there are, so the two overlap (N = 19904, B = 64, 4 slices: 90 us in two
-// launches).
+// Rows of many candidates and, in the last workgroups of every slice, those of few: in one launch the few ones fill
+// what the last of the many leave idle.
 template <int D, int KC>
 __global__ __launch_bounds__(kGateWaves * kWave) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
 void gate_many_kernel(
@@ -413,7 +413,7 @@ void gate_many_kernel(
             if (any == 0) continue;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if (KC == 16 && hits[qt][i] == 0) continue;             // (few of many: most scores end here)
+                if (KC == 8 && hits[qt][i] == 0) continue;             // (few of many: most scores end here)
                 if (__builtin_amdgcn_inverse_ballot_w64(hits[qt][i])) {
                     const uint32_t key = min((uint32_t)fmaf(sc[qt][i] - base[qt], scale[qt], 1.5f), (uint32_t)kGateTopKey + 1u);
                     cand[at[qt]] = (key << kGateIdBits) + (id + i);
@@ -640,8 +640,11 @@ static int few_blocks(const Dims& s) { return 16 * (s.D == 128 ? kGateFew<128> :
 //  - two sweeps, rows of at most 8: enough strips to fill the chip with one wave per 64 queries (700 blocks of 32,
 //    k = 8: 185 -> 167, with 4 heads 73 -> 95) and enough blocks (2048 of 64, k = 8: 1682 -> 1262; d = 128, 300 of
 //    64: 162 -> 162).  Rows of 15 and 16 overflow their candidates too often (2048 of 64: 1867 -> 2390)
-//  - two sweeps, rows of 17 to 32 at d = 128: after a key conv only, which gives the centroids a common part and
-//    the histogram's windows little to cut (2048 of 64, k = 32: 4400 -> 3700; without it 3001 -> 3330)
+//  - two sweeps, rows of 17 to 32 at d = 128: from 2048 blocks on and behind a key conv of width 3 or 4 only, which
+//    blurs the centroids and leaves the histogram's windows little to cut (calls with lists, k = 17 / 32; 2048 of 64:
+//    width 4 4498 -> 3959 / 4653 -> 4405, width 3 4328 -> 3928 / 4545 -> 4369, width 2 4073 -> 3902 / 4430 -> 4350, none
+//    3307 -> 3831 / 3621 -> 4246; 2048 of 32: width 4 2152 -> 1977 / 2299 -> 2184, width 2 1870 -> 1954 / 2036 -> 2158;
+//    1000 of 64: width 4 1411 -> 1403 / 1469 -> 1543)
 // Longer rows stay with the search (N = 32768, B = 32, k = 64, d = 64: 446 against 630).
 bool gate_supported(const Dims& s)
 {
@@ -649,7 +652,7 @@ bool gate_supported(const Dims& s)
     if (s.dtype != MOBA_BF16) return s.n <= 16 * kGateF32Tiles;
     if (s.n <= few_blocks(s)) return s.k >= 8 || s.n <= 256;
     if (s.n > (1 << kGateIdBits) || s.n < (s.D == 64 ? 513 : 448) || (int64_t)s.bh * s.N < 300000) return false;
-    return s.k <= 8 || (s.D == 128 && s.k > 16 && s.k <= 32 && s.W > 1);
+    return s.k <= 8 || (s.D == 128 && s.k > 16 && s.k <= 32 && s.n >= 2048 && s.W >= 3);
 }
 
 // workspace: [the three terms][norms of every block][list of strips to search exactly: count, strips]
@@ -731,8 +734,8 @@ hipError_t launch_gate(const Dims& s, const void* Q, const float* cent, int32_t*
     if (!may)
         return s.D == 128 ? few_launch<128, kGateFew<128>>(s, Q, c3, idx, st)
                           : few_launch<64, kGateFew<64>>(s, Q, c3, idx, st);
-    e = s.D == 64 ? many_launch<64, 16>(s, Q, c3, norms, redo, idx, st)
-        : s.k <= 16 ? many_launch<128, 16>(s, Q, c3, norms, redo, idx, st)
+    e = s.D == 64 ? many_launch<64, 8>(s, Q, c3, norms, redo, idx, st)
+        : s.k <= 8 ? many_launch<128, 8>(s, Q, c3, norms, redo, idx, st)
                     : many_launch<128, 32>(s, Q, c3, norms, redo, idx, st);
     if (e != hipSuccess) return e;
     return launch_topk_redo(s, Q, c3, redo, idx, st);

@@ -65,7 +65,8 @@ def test_equal_scores_keep_the_lowest_blocks(d, n, k):
 # the two sweeps take calls of many rows only: (d, blocks, k, B, heads, conv width), both sides of each rule
 @pytest.mark.parametrize("d,n,k,B,heads,conv", [(64, 513, 8, 32, 19, 0), (64, 512, 8, 32, 19, 0), (64, 1025, 3, 32, 10, 0),
                                                 (64, 513, 9, 32, 19, 0), (128, 448, 8, 32, 21, 0), (128, 447, 8, 32, 21, 0),
-                                                (128, 500, 32, 32, 19, 4), (128, 500, 17, 32, 19, 3), (128, 500, 32, 32, 19, 0)])
+                                                (128, 500, 32, 32, 19, 4), (128, 500, 17, 32, 19, 3), (128, 500, 32, 32, 19, 0),
+                                                (128, 2048, 32, 32, 5, 4), (128, 2048, 17, 32, 5, 3), (128, 2047, 24, 32, 5, 4)])
 def test_two_sweeps_keep_what_the_exact_search_keeps(d, n, k, B, heads, conv):
     g = torch.Generator(device="cuda").manual_seed(n + k)
     N = n * B
