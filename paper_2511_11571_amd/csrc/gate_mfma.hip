@@ -11,7 +11,11 @@
 // Many candidates, two sweeps instead of keeping the scores:
 //  1. hi term only: a lane keeps the maxima of GR groups of its blocks.  A query has 4 GR groups; at
 //     least k of its scores reach the k-th largest of their maxima (each group's maximum is a score of
-//     its own), and not many more do while 4 GR is well above k.  So that value, less the error of the
+//     its own), and not many more do while 4 GR is well above k and the best blocks lie in different groups.
+//     Neighbouring blocks are often alike, so 32 (rows up to 8) or 128 blocks in a row lie in different groups: one
+//     maximum per score where groups of four neighbours take half of one, 2 % of the kernel, but on centroids
+//     smoothed over 32 blocks those overflow (4096 blocks of 32, d = 64, k = 8, 4 heads: 1697 us, now 894; over
+//     6 blocks 878 -> 785).  So that value, less the error of the
 //     hi term, is a lower bound of the k-th largest score (kSumError: what is assumed of the matrix unit's sums).
 //  2. hi + mid: every block above that bound becomes a candidate (18-bit score above the bound, block)
 //     in LDS, about 1.1 to 1.5 k of them.  The k-th largest candidate is searched in registers; where
@@ -290,7 +294,7 @@ void gate_many_kernel(
     // additions of the hi term meet numbers of the size of |q| |c|; those of the others lose 2^-8 and 2^-16 as
     // much: less than 1.02 D 2^-23 |q| |c| per score, twice that for the difference of two.
     constexpr float kSumError = 2.04f * D / 8388608.f;
-    float eps1[QT], eps2[QT];
+    float qn[QT], e1, e2;                                               // |q|; errors per |q| of one and of two terms
     {
         float r1 = 0.f, r2 = 0.f, rc = 0.f;
         const float4* nr = norms + (int64_t)(s / G) * 16 * ntile_all;
@@ -304,6 +308,10 @@ void gate_many_kernel(
             r2 = max_nan(r2, __shfl_xor(r2, o, kWave));
             rc = max_nan(rc, __shfl_xor(rc, o, kWave));
         }
+        const float acc = kSumError * rc;
+        auto uniform = [](float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); };
+        e1 = uniform(1.001f * r1 + acc);
+        e2 = uniform(1.001f * r2 + acc);
         bool finite = true;
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) {
@@ -315,18 +323,16 @@ void gate_many_kernel(
                     const float a = __uint_as_float(qb[qt][ks].u[e] << 16), b = __uint_as_float(qb[qt][ks].u[e] & 0xffff0000u);
                     q2 = fmaf(a, a, fmaf(b, b, q2));
                 }
-            const float qn = sqrtf(fsum_g(q2));
-            const float acc = kSumError * rc;
-            // (a floor under both: kGateKeys / eps stays finite for a query of zeros as well)
-            eps1[qt] = qn * (1.001f * r1 + acc) + 1e-30f;
-            eps2[qt] = qn * (1.001f * r2 + acc) + 1e-30f;
-            finite = finite && eps1[qt] < 1e37f && qn * rc < 1e37f;
+            qn[qt] = sqrtf(fsum_g(q2));
+            finite = finite && qn[qt] * e1 < 1e37f && qn[qt] * rc < 1e37f;
         }
         if (__ballot(!finite)) {
             search_again();
             return;
         }
     }
+    // (a floor under both: kGateKeys / error stays finite for a query of zeros as well)
+    auto error = [&](float per, int qt) { return fmaf(qn[qt], per, 1e-30f); };
     auto mask_edges = [&](int jt, f32x4_t (&sc)[QT]) {                  // blocks that are no candidates: -inf
         if (jt >= ilo && jt < ihi) return;
 #pragma unroll
@@ -349,7 +355,8 @@ void gate_many_kernel(
             mask_edges(jt, sc);
 #pragma unroll
             for (int qt = 0; qt < QT; ++qt)
-                gm[qt][u / 4][u % 4] = max_nan(max_nan(max_nan(sc[qt][0], sc[qt][1]), sc[qt][2]), max_nan(sc[qt][3], gm[qt][u / 4][u % 4]));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) gm[qt][u % (C::GR / 4)][i] = max_nan(sc[qt][i], gm[qt][u % (C::GR / 4)][i]);
         });
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) {
@@ -377,7 +384,7 @@ void gate_many_kernel(
             const float var = fmaxf(fsum_g(sq) * inv - mean * mean, 0.f);
             search_threshold<C::GR / 4>(gm[qt], C::GR / 4, need[qt], need[qt] >> 4, 0,
                                         mean + sqrtf(var) * normal_quantile(((float)need[qt] + 0.5f) * inv), lo, hi, b);
-            const float e = eps1[qt] + eps2[qt];
+            const float e = error(e1, qt) + error(e2, qt);
             // (Keys of an `all` query tell nothing
             // apart beyond their block: it keeps every candidate or goes to the exact ranking.)
             scale[qt] = all ? 0.f : kGateKeys / (mx - lo + 3.f * e);
@@ -446,13 +453,16 @@ void gate_many_kernel(
         total[qt] = sum_g(cnt[qt]);
         full = full || total[qt] < need[qt];                            // (cannot be, see kSumError)
     }
-    // the k-th largest candidate; how close the next one is
+    // The k-th largest candidate; where the next one is within `width` of it, those within `width` of the k-th go on
+    // the band: scored again from all three terms, in the order of the other kernels, so that all agree on close ones.
+    // Those above stay in, those below out, the band decides the rest.
     uint32_t cut[QT];
-    int nband = 0;                                                      // the same in all lanes
+    int nband = 0, upto[QT];                                            // the same in all lanes
     if (!__ballot(full)) {
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) {
             cut[qt] = search_key<SEG / 2>(y[qt], 1u << kGateIdBits, 0xffffffffu, need[qt], total[qt]);
+            upto[qt] = nband;
             uint32_t kth = 0xffffffffu, next = 0u;
 #pragma unroll
             for (int j = 0; j < SEG / 2; ++j) {
@@ -461,54 +471,57 @@ void gate_many_kernel(
             }
             kth = umin_g(kth) >> kGateIdBits;
             next = umax_g(next) >> kGateIdBits;
-            const uint32_t width = (uint32_t)fminf(2.f * eps2[qt] * scale[qt], kGateKeys) + 2u;
+            const uint32_t width = (uint32_t)fminf(2.f * error(e2, qt) * scale[qt], kGateKeys) + 2u;
             const bool close = need[qt] > 0 && total[qt] > need[qt] && kth - next <= width;
             if (!__ballot(close)) continue;
-            // score the candidates within `width` of the k-th again, from all three terms in the order of the
-            // other kernels (so all agree on close ones); those above stay in, those below out: the band
-            // decides the rest
-            const uint32_t blo = kth > width ? kth - width : 1u, bhi = min(kth + width, (uint32_t)kGateTopKey + 1u);
+            const uint32_t blo = !close ? 1u : kth > width ? kth - width : 1u;      // (not close: no key lies between)
+            const uint32_t bhi = !close ? 0u : min(kth + width, (uint32_t)kGateTopKey + 1u);
             int sure = 0;
 #pragma unroll
-            for (int j = 0; j < SEG / 2; ++j) sure += (int)((y[qt][j] >> kGateIdBits) > bhi);
+            for (int j = 0; j < SEG / 2; ++j) {
+                const uint32_t key = y[qt][j] >> kGateIdBits;
+                sure += (int)(key > bhi);
+                const bool in = key >= blo && key <= bhi;
+                const uint64_t m = __ballot(in);
+                if (m == 0) continue;
+                const int p = nband + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                if (in && p < kGateBand) band[p].y = (uint32_t)(16 * qt + m16) << 16 | (y[qt][j] & ((1u << kGateIdBits) - 1u));
+                nband += __popcll(m);
+            }
+            upto[qt] = nband;
             sure = sum_g(sure);
             if (close) {
                 cut[qt] = (bhi + 1u) << kGateIdBits;
                 if (g == 0) band_want[16 * qt + m16] = need[qt] - sure;
-            }
-#pragma unroll 1
-            for (int j = 0; j < SEG / 2; ++j) {
-                uint32_t v = 0;
-#pragma unroll
-                for (int u = 0; u < SEG / 2; ++u) v = j == u ? y[qt][u] : v;
-                const uint32_t key = v >> kGateIdBits;
-                uint64_t m = __ballot(close && key >= blo && key <= bhi);
-                while (m) {
-                    const int who = __ffsll((unsigned long long)m) - 1;
-                    m &= m - 1;
-                    const int blk = __builtin_amdgcn_readlane((int)(v & ((1u << kGateIdBits) - 1u)), who);
-                    const int q = 16 * qt + (who & 15), in = blk & 15;
-                    const char* tb = c3s + (int64_t)(blk >> 4) * (3 * KS * 1024) + lane * 16;
-                    f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int term = 2; term >= 0; --term)
-#pragma unroll
-                        for (int ks = 0; ks < KS; ++ks) {
-                            Frag a;
-                            a.q = *reinterpret_cast<const uint4*>(tb + (term * KS + ks) * 1024);
-                            sc = mfma16(a, qb[qt][ks], sc);
-                        }
-                    const float mine = in & 2 ? (in & 1 ? sc[3] : sc[2]) : (in & 1 ? sc[1] : sc[0]);
-                    const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), 4 * (in & 12) + (who & 15)));
-                    if (nband < kGateBand && lane == 0) band[nband] = make_uint2(order_key(a), (uint32_t)(q << 16 | blk));
-                    ++nband;
-                }
             }
         }
     }
     if (__ballot(full) || nband > kGateBand) {
         search_again();
         return;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (nband > 0) {
+        int at_band = 0;
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+#pragma unroll 1
+            for (; at_band < upto[qt]; ++at_band) {
+                const uint32_t what = (uint32_t)__builtin_amdgcn_readfirstlane((int)band[at_band].y);
+                const int blk = (int)(what & 0xffffu), in = blk & 15;
+                const char* tb = c3s + (int64_t)(blk >> 4) * (3 * KS * 1024) + lane * 16;
+                f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int term = 2; term >= 0; --term)
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        Frag a;
+                        a.q = *reinterpret_cast<const uint4*>(tb + (term * KS + ks) * 1024);
+                        sc = mfma16(a, qb[qt][ks], sc);
+                    }
+                const float mine = in & 2 ? (in & 1 ? sc[3] : sc[2]) : (in & 1 ? sc[1] : sc[0]);
+                if (lane == 4 * (in & 12) + (int)((what >> 16) & 15u)) band[at_band].x = order_key(mine);
+            }
     }
     __builtin_amdgcn_wave_barrier();
     if (nband > 0) {

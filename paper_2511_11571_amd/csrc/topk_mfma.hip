@@ -1,6 +1,6 @@
 // Gate scoring and causal top-k on bf16 MFMA (paper Section 2; Appendix C.1, fused
 // top-k selection: scores are produced tile by tile and never written to memory) for the long rows that
-// the kernels of gate_mfma.hip leave to it, and the exact search that those hand single strips to and that
+// the kernels of gate_mfma.hip leave to it, for single strips that those hand to it, and the exact search that
 // MOBA_FLAG_GATE_EXACT_SEARCH asks for.
 //
 // Scores must be fp32-accurate (the routing is compared with a 1e-4 score gap), so the
@@ -154,7 +154,11 @@ void topk_mfma_kernel(
     for (int job = blockIdx.x; !REDO || job < redo[0]; job += gridDim.x) {
     constexpr int KS = D / 32;
     constexpr bool LISTS = KL > 0;
-    const int tid = threadIdx.x, lane = tid % kWave;
+    int tid = threadIdx.x;
+    // (what the loop's body computes from these alone would be moved out of the loop and spilled: 81 registers at d = 128)
+    if constexpr (REDO)
+        asm volatile("" : "+v"(tid), "+s"(Q), "+s"(c3), "+s"(idx), "+s"(N), "+s"(B), "+s"(n), "+s"(k), "+s"(Wn), "+s"(ntile_all));
+    const int lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int m16 = lane & 15, g = lane >> 4;
     const int strip = REDO ? redo[1 + job] : job;
@@ -828,8 +832,9 @@ static hipError_t topk_launch2(const Dims& s, const void* Q, const bf16_t* c3, i
                                                    (KL > 0 ? 64 * KL / 2 + 64 : 64 * Wn));
     hipError_t e = ensure_dynamic_lds((const void*)topk_mfma_kernel<D, KL, REDO>, (size_t)lds);
     if (e != hipSuccess) return e;
-    const int64_t grid = REDO && strips > 512 ? 512 : strips;       // (usually there is nothing on the list)
-    const int exact = REDO || (s.flags & MOBA_FLAG_GATE_EXACT_SEARCH) ? 1 : 0;
+    // (the list is mostly empty: as many workgroups as run at once, no more)
+    const int64_t most = D == 64 ? 1536 : 1024, grid = REDO && strips > most ? most : strips;
+    const int exact = s.flags & MOBA_FLAG_GATE_EXACT_SEARCH ? 1 : 0;
     auto launch = [&]() {
         hipLaunchKernelGGL((topk_mfma_kernel<D, KL, REDO>), dim3((unsigned)grid), dim3(kTopkWaves * kWave), lds, st,
                            (const bf16_t*)Q, c3, (s.n + 15) / 16, idx, s.N, s.B, s.n, s.k, sps, Wn, s.G, exact,
@@ -862,7 +867,10 @@ hipError_t launch_topk_mfma(const Dims& s, const void* Q, const float* cent, int
     return s.D == 64 ? topk_launch<64, false>(s, Q, c3, idx, nullptr, st) : topk_launch<128, false>(s, Q, c3, idx, nullptr, st);
 }
 
-// the strips of 64 queries on the list `redo` (gate_mfma.hip), by the exact search
+// the strips of 64 queries on the list `redo` (gate_mfma.hip).  Data with many near-equal blocks puts most strips on
+// it, so these too get the first look, and every place for a workgroup is used (4096 blocks of 32 of 32 near-equal
+// kinds, d = 64, k = 8, 4 heads, gate and lists: 4.75 ms; with the exact search in 512 workgroups 7.0; without the
+// two sweeps before it 3.7).
 hipError_t launch_topk_redo(const Dims& s, const void* Q, const bf16_t* c3, const int32_t* redo, int32_t* idx,
                             hipStream_t st)
 {

@@ -114,6 +114,22 @@ def test_two_sweeps_of_scores_closer_than_their_sums_can_tell(d, n, k, B, heads)
     assert torch.equal(got, want)
 
 
+@pytest.mark.parametrize("d,n,k,heads,over", [(64, 1024, 8, 10, 3), (64, 1024, 8, 10, 16), (64, 1024, 2, 10, 100), (128, 1030, 8, 10, 16),
+                                              (128, 2048, 32, 5, 3)])
+def test_two_sweeps_of_neighbours_alike(d, n, k, heads, over):
+    """Centroids smoothed over neighbouring blocks: a query's best blocks lie side by side, and near-equal ones
+    send strips to the other search."""
+    B = 32
+    g = torch.Generator(device="cuda").manual_seed(n + over)
+    Q = torch.randn((1, heads, n * B, d), generator=g, device="cuda").to(torch.bfloat16)
+    window = torch.hann_window(2 * over + 1, device="cuda").view(1, 1, -1)
+    cent = torch.randn((heads * d, 1, n), generator=g, device="cuda")
+    cent = torch.nn.functional.conv1d(cent, 0.2 * window / window.norm(), padding=over).view(1, heads, d, n).transpose(2, 3).contiguous()
+    got, want = (moba.topk(moba.Shape(1, heads, n * B, d, B, k, 4, binding.BF16, 0.0, flags, 0), Q, cent)[0]
+                 for flags in (0, binding.FLAG_GATE_EXACT_SEARCH))
+    assert torch.equal(got, want)
+
+
 def test_zero_queries_in_strips_of_many_blocks():
     """A packed batch whose short sequences begin inside a strip that also sees a long one: their queries have
     one to three candidates, and with a query of zeros these are equal: the lowest blocks are kept."""
