@@ -95,7 +95,16 @@ typedef struct moba_shape {
 /* In the argument tables below h stands for the query heads (shape.heads) and kv for the key/value
  * heads (shape.kv_heads, or heads when that is 0). */
 
-/* Host-only helpers.  R and the byte counts are written to host memory. */
+/* Host-only helpers.  R and the byte counts are written to host memory.
+ * Forward and backward workspaces hold a partial result per (query, kept or own block) pair and part of
+ * the block where the kernels file such partials: batch * heads * seqlen * (topk + 1) * parts of them.
+ *   bf16, key-block-major kernels: 2 d + 8 bytes each forward, 2 d backward; parts of 128 keys (d = 64) or
+ *       64 (d = 128; backward: 128 where B is a multiple of that, else 64).
+ *   fp32 tensors, and bf16 with B not a multiple of 32 (B >= 8, topk <= 64): 4 d + 8 bytes each forward, 4 d
+ *       backward; parts of at most 64 keys (backward at d = 128: 32).  fp32, 16 heads, N = 32768, d = 64:
+ *       1.2 GB each with B = 64 and topk = 8, 9.0 and 8.7 GB with B = 32 and topk = 64.  Where the backward's
+ *       partials would take more than 16 GiB both directions run on the plain kernels instead, which need
+ *       next to no workspace and are several times slower: cut such calls by heads or batch. */
 int moba_routes_per_slice(const moba_shape* shape, int64_t* R);
 int moba_workspace_bytes(const moba_shape* shape, size_t* topk_ws, size_t* fwd_ws, size_t* bwd_ws);
 

@@ -42,6 +42,10 @@ def test_lists_of_a_routing(shape, dtype):
     batch, heads, N, d, B, k = shape
     bh, n = batch * heads, N // B
     sh = moba.Shape(batch, heads, N, d, B, k, 0, moba.binding.BF16 if dtype == "bf16" else moba.binding.F32)
+    # lists hold places where the attention kernels file partial results by them, which shows in the workspaces:
+    # fp32 (every shape here), and bf16 where the automatic choice is the key-block-major one
+    flagged = lambda flags: moba.workspace_bytes(moba.Shape(batch, heads, N, d, B, k, 0, sh.dtype, 0.0, flags))[1]
+    with_places = dtype == "f32" or flagged(0) == flagged(moba.binding.FLAG_KEY_MAJOR) != flagged(moba.binding.FLAG_QUERY_TILES)
     idx = _routing(np.random.default_rng(N + k), bh, N, B, k)
     off, ql = moba.build_lists(sh, torch.from_numpy(idx).view(batch, heads, N, k).cuda())
     off, ql = off.cpu().numpy().reshape(bh, n + 1), ql.cpu().numpy().reshape(bh, -1)
@@ -53,5 +57,4 @@ def test_lists_of_a_routing(shape, dtype):
         assert (off[s] == want).all()
         got = ql[s, :want[-1]]
         assert ((got & 0xffffff) == t[order]).all()
-        places = got >> 24                  # zero throughout where the attention kernels do not want them
-        assert (places == e[order]).all() or not places.any()
+        assert ((got >> 24) == (e[order] if with_places else 0)).all()
