@@ -29,7 +29,7 @@ PEAK_HBM_GBS = 8000.0
 # under profiles/ (FETCH_SIZE and WRITE_SIZE per dispatch, already scaled there by what the same
 # counters read for a plain copy of known size): profiles/config<N>_hbm_traffic.txt, one row per
 # kernel, last column = bytes per launch.  Not measured -> None.
-PROFILED_KERNEL = {"topk": ("topk_mfma_kernel", "gate_many_kernel", "gate_few_kernel"),
+PROFILED_KERNEL = {"topk": ("gate_many_kernel", "gate_few_kernel", "topk_mfma_kernel"),   # (the first one that ran)
                    "forward": ("forward_mfma_kernel", "fwd_km_kernel"),
                    "bwd_dq": "dq_mfma_kernel", "bwd_dkdv": ("dkdv_mfma_kernel", "bwd_km_kernel")}
 
@@ -40,13 +40,14 @@ def measured_traffic(config, kernel):
     if names is None or not os.path.exists(path):
         return None
     names = (names,) if isinstance(names, str) else names
-    for line in open(path):
-        f = line.split()
-        if len(f) == 4 and f[0] in names:
-            try:
-                return float(f[3])
-            except ValueError:
-                pass
+    rows = [f for f in (line.split() for line in open(path)) if len(f) == 4]
+    for name in names:
+        for f in rows:
+            if f[0] == name:
+                try:
+                    return float(f[3])
+                except ValueError:
+                    pass
     return None
 
 

@@ -416,8 +416,8 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
             top = fmaxf(top, z[u]);
         }
         // (a lane group without a key so far that exists and has a finite logit keeps m = -inf, l = 0: exponents
-        // are taken against 0)
-        const float ref = top == -INFINITY ? 0.f : top;
+        // are taken against the lowest number, which leaves them -inf)
+        const float ref = fmaxf(top, -3.402823466e+38f);
         const float alpha = __builtin_amdgcn_exp2f(m - ref);
         m = top;
         l *= alpha;

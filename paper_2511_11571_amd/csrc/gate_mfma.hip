@@ -22,10 +22,10 @@
 //     the next one is closer than the error of hi + mid (2^-16 of |q| |c| at d = 64, 2^-15 at 128), the candidates
 //     inside that error are scored again from all three terms and ranked exactly, ties to the lower block.
 // Strips that do not fit (more candidates or closer scores than there is room for: many equal scores;
-// non-finite values) are put on a list for the exact radix search of topk_mfma.hip.
+// non-finite values) are put on a list for the search of topk_mfma.hip.
 //
-// What bounds it: VALU issue in the sweeps (2 instructions per score in the first, about 5 in the second
-// against 1 and 2 MFMAs per 64) and the searches.  The kernel before it, a histogram of all scores by LDS
+// What bounds it: VALU issue in the sweeps (per 16 x 16 scores 4 instructions in the first, about 5 in the second,
+// against d / 32 and d / 16 MFMAs) and the searches.  The kernel before it, a histogram of all scores by LDS
 // atomics and an exact three-term sweep, took 46 us at N = 8192, B = 128, k = 8, 16 heads (now 29), 22.3 ms
 // at N = 524288, B = 128, k = 8, 32 slices (now 15.4 + 0.3) and 4.4 ms at N = 131072, d = 128, B = 64,
 // k = 32, 16 heads (now 3.4 + 0.3).
@@ -281,7 +281,7 @@ void gate_many_kernel(
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) load_q(qt, qb[qt]);
 
-    // hands the 64 queries around this strip to the exact search (which numbers them from the last on)
+    // hands the 64 queries around this strip to the search (which numbers them from the last on)
     auto search_again = [&]() {
         const int per_slice = (N + 63) / 64;
         if (lane == 0) redo[1 + atomicAdd(redo, 1)] = s * per_slice + per_slice - 1 - t0 / 64;
@@ -668,7 +668,7 @@ bool gate_supported(const Dims& s)
     return s.k <= 8 || (s.D == 128 && s.k > 16 && s.k <= 32 && s.n >= 2048 && s.W >= 3);
 }
 
-// workspace: [the three terms][norms of every block][list of strips to search exactly: count, strips]
+// workspace: [the three terms][norms of every block][list of strips to search again: count, strips]
 static bool gate_may_redo(const Dims& s) { return s.n > few_blocks(s); }
 static size_t terms_bytes(const Dims& s) { return a256(3 * sizeof(bf16_t) * (size_t)s.bhk * ((s.n + 15) / 16 * 16) * s.D); }
 static size_t norms_bytes(const Dims& s) { return a256(sizeof(float4) * (size_t)s.bhk * ((s.n + 15) / 16 * 16)); }
