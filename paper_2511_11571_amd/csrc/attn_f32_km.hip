@@ -10,7 +10,9 @@
 //
 // The plain kernels of attn_reference.hip, which served these shapes, read every key row again for
 // every query (64 FMAs per 256 bytes) and ran at 5 TFLOP/s; here a key row meets 16 queries per read.
-// What bounds these kernels now is the fp32 matrix rate (157 TFLOP/s; 32 clocks per instruction).
+// What bounds them now is the latency between the dependent steps of few waves: at the shape below the matrix
+// pipe is busy 49 (forward) and 43 % (backward) of the clocks, the LDS pipe 15 and 17 %, VALU issue 21 and 16 %,
+// and waves wait 60 and 42 % of their cycles.
 // fp32, 2 x 4 heads, N = 4096, d = 64, B = 64, k = 7: forward 580 -> 80 us, dQ + dK + dV 1960 -> 199 us.
 //
 // Operand layouts (lane = 16 g + m): a contraction over channels takes channels 16 t + 4 g + i in the
@@ -75,7 +77,7 @@ template <typename T, int D, int NTHREADS>
 __device__ __forceinline__ bool stage_rows(const T* __restrict__ X, float* tile, int rows, int nk, int tid)
 {
     constexpr int CPR = Gather<T, D>::CPR, EPL = Gather<T, D>::EPL;
-    bool odd = false;
+    uint32_t top = 0u;                                      // largest magnitude, as bits: infinities and NaN come last
     for (int i = tid; i < rows * CPR; i += NTHREADS) {
         const int r = i / CPR, c = i % CPR;
         u32x4_t x = {0u, 0u, 0u, 0u};
@@ -83,26 +85,52 @@ __device__ __forceinline__ bool stage_rows(const T* __restrict__ X, float* tile,
         put<T>(tile + r * (D + 4) + c * EPL, x);
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
-            odd = odd || (x[h] & 0x7f800000u) == 0x7f800000u;
-            if (sizeof(T) == 2) odd = odd || (x[h] & 0x7f80u) == 0x7f80u;
+            top = max(top, x[h] & 0x7fffffffu);
+            if constexpr (sizeof(T) == 2) top = max(top, x[h] << 16 & 0x7fffffffu);
         }
     }
-    return odd;
+    return top >= 0x7f800000u;
 }
 
 // A key that a query does not see has weight zero, and the matrix instructions add 0 * x for it: no zero where x
 // is an infinity or a NaN.  Only a block's own queries fail to see keys of it.  So where a part holds such a
 // value, every wave does the own rows of its walk once more afterwards, one query at a time over the keys that
 // it sees: f(query, number of keys of the part that it sees).
-template <typename F>
-__device__ __forceinline__ void own_rows_again(int a0, int stride, int nlist, int total, int own0, int nk, F f)
-{
-    __threadfence_block();                                  // (the walk's partials go first)
+// It works out afresh where it is, from a block and thread number that the compiler cannot know to be the same:
+// what it shares with the walk would be kept in registers all along that, 3 % of the forward at d = 128.
+struct OwnRows {
+    int s, c, lane, wave, a0, stride, nlist, total, own0, nk;
+    int64_t q0, kv0;                                        // rows of the slice's first query, of the part's first key
+    __device__ __forceinline__ OwnRows(const int32_t* __restrict__ off, int N, int B, int n, int nsub, int pk, int nsplit, int bh,
+                                       int G, int waves)
+    {
+        int tid = threadIdx.x, block = blockIdx.x, u;
+        asm volatile("" : "+v"(tid), "+s"(block));
+        lane = tid % kWave;
+        wave = tid / kWave;
+        schedule(block, bh, n * nsub * nsplit, s, u);
+        const int jc = u / nsplit, j = jc / nsub;
+        c = jc - j * nsub;
+        nk = min(pk, B - c * pk);
+        own0 = j * B + c * pk;
+        const int32_t* os = off + (int64_t)s * (n + 1) + j;
+        nlist = os[1] - os[0];
+        total = nlist + (B - c * pk);
+        a0 = 16 * (u % nsplit * waves + wave);
+        stride = 16 * waves * nsplit;
+        q0 = (int64_t)s * N;
+        kv0 = (int64_t)(s / G) * N + own0;
+    }
+    template <typename F>
+    __device__ __forceinline__ void again(F f)
+    {
+        __threadfence_block();                              // (the walk's partials go first)
 #pragma unroll 1
-    for (; a0 < total; a0 += stride)
+        for (; a0 < total; a0 += stride)
 #pragma unroll 1
-        for (int a = max(a0, nlist); a < min(a0 + 16, total); ++a) f(own0 + (a - nlist), min(a - nlist + 1, nk));
-}
+            for (int a = max(a0, nlist); a < min(a0 + 16, total); ++a) f(own0 + (a - nlist), min(a - nlist + 1, nk));
+    }
+};
 
 template <typename T, int D>
 __device__ __forceinline__ float row_dot(const T* __restrict__ a, const T* __restrict__ b)
@@ -303,12 +331,13 @@ __global__ __launch_bounds__(F32Cfg<D>::NWF * kWave) void fwd_f32_km_kernel(
 #pragma unroll
     for (int v = 0; v < NW; ++v) any |= odd[v];
     if (!any) return;
-    own_rows_again(16 * (split * NW + wave), stride, w.nlist, w.total, w.own0, nk, [&](int t, int seen) {
-        const float z = lane < seen ? c2 * row_dot<T, D>(Q + (sbase + t) * D, K + (kvbase + w.own0 + lane) * D) : -INFINITY;
+    OwnRows own(off, N, B, n, nsub, pk, nsplit, bh, G, NW);
+    own.again([&](int t, int seen) {
+        const float z = own.lane < seen ? scale * kLog2e * row_dot<T, D>(Q + (own.q0 + t) * D, K + (own.kv0 + own.lane) * D) : -INFINITY;
         const float top = wave_max(z), p = fast_exp2(z - fmaxf(top, -kFltLargest)), l = wave_sum(p);
-        const int64_t prow = (sbase + t) * slots + (int64_t)k * nsub + c;
-        weigh_rows<T, D>(p, seen, V + (kvbase + w.own0) * D, stQ, PO + prow * D, lane);
-        if (lane == 0) Pml[prow] = make_float2(top, l);
+        const int64_t prow = ((own.q0 + t) * (k + 1) + k) * nsub + own.c;
+        weigh_rows<T, D>(p, seen, V + own.kv0 * D, sm + (2 * 16 * NT + own.wave * 16) * LD, PO + prow * D, own.lane);
+        if (own.lane == 0) Pml[prow] = make_float2(top, l);
     });
 }
 
@@ -487,17 +516,17 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
                 }
             }
         }
-        // this lane: key 16 kt + m16 of the part, queries a0 + 4 g + i
+        // this lane: key 16 kt + m16 of the part, queries a0 + 4 g + i, which see the keys below `seen`
 #pragma unroll
-        for (int kt = 0; kt < NT; ++kt)
+        for (int i = 0; i < 4; ++i) {
+            const int a = a0 + 4 * g + i, seen = a < w.nlist ? nk : min(a - w.nlist + 1, nk);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int own = a0 + 4 * g + i - w.nlist, key = 16 * kt + m16;
-                const bool seen = key < nk && (own < 0 || key <= own);
-                const float p = seen ? fast_exp2(fmaf(x[kt][i], c2, -l4[i])) : 0.f;
+            for (int kt = 0; kt < NT; ++kt) {
+                const float p = 16 * kt + m16 < seen ? fast_exp2(fmaf(x[kt][i], c2, -l4[i])) : 0.f;
                 x[kt][i] = p;
                 dp[kt][i] *= p;
             }
+        }
         if (want_dq) {
 #pragma unroll
             for (int kt = 0; kt < NT; ++kt)
@@ -595,15 +624,17 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
         }
     }
     if (!any || !want_dq) return;
-    own_rows_again(16 * (split * NW + wave), stride, w.nlist, w.total, w.own0, nk, [&](int t, int seen) {
+    OwnRows own(off, N, B, n, nsub, pk, nsplit, bh, G, NW);
+    own.again([&](int t, int seen) {
         float ds = 0.f;
-        if (lane < seen) {
-            const int64_t key = (kvbase + w.own0 + lane) * D;
-            const float2 x = ld[sbase + t];
-            const float z = c2 * row_dot<T, D>(Q + (sbase + t) * D, K + key);
-            ds = fast_exp2(z - x.x) * (row_dot<T, D>(dO + (sbase + t) * D, V + key) + x.y);
+        if (own.lane < seen) {
+            const int64_t key = (own.kv0 + own.lane) * D;
+            const float2 x = ld[own.q0 + t];
+            const float z = scale * kLog2e * row_dot<T, D>(Q + (own.q0 + t) * D, K + key);
+            ds = fast_exp2(z - x.x) * (row_dot<T, D>(dO + (own.q0 + t) * D, V + key) + x.y);
         }
-        weigh_rows<T, D>(ds, seen, K + (kvbase + w.own0) * D, stQ, PdQ + ((sbase + t) * slots + (int64_t)k * nsub + c) * D, lane);
+        weigh_rows<T, D>(ds, seen, K + own.kv0 * D, sm + 2 * 16 * NT * LD + own.wave * C::bwd_wave_words(NT),
+                         PdQ + (((own.q0 + t) * (k + 1) + k) * nsub + own.c) * D, own.lane);
     });
 }
 
