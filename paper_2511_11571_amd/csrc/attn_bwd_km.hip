@@ -19,8 +19,9 @@
 //              both operands through the transpose read.
 //
 // One walk for all three gradients: dQ on its own repeats the gather of Q and dO and the products S and dP
-// (5 products instead of 7).  LDS bounds it (per step and wave about as many clocks of LDS reads as of matrix
-// instructions, shared by the waves of the compute unit), at d = 128 the latencies of one wave per SIMD.
+// (5 products instead of 7).  No pipe is full: at N = 65536, d = 64, B = 128, k = 8, 32 slices the LDS pipe is busy
+// 64 % of the clocks (42 % of that bank conflicts), the matrix pipe 33, VALU issue 36; at N = 16384, d = 128, B = 64,
+// k = 16, 16 slices 37, 22 and 22 %.  What is left are the latencies of two waves per SIMD, one at d = 128.
 // Against separate walks for dQ and for dK and dV: N = 524288, d = 64, B = 128, k = 8, 32 slices: 28.0 -> 18.3 ms
 // (3.2 TB/s of gathered rows and partials); whole steps, N = 10080, B = 96, k = 10, 18 slices: 700 -> 562 us,
 // N = 16384, d = 128, B = 64, k = 16, 16 slices: 2617 -> 2056 us.
