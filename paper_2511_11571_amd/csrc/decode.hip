@@ -21,8 +21,8 @@
 //    end: no cross-lane maximum or sum inside the walk;
 //  - the selection bins the scores linearly between the smallest and the largest (1024 bins, one LDS
 //    atomic per score, well spread), and ranks only the scores of the bin that holds the k-th largest;
-//    the radix select over the bits of the scores remains for ties wider than a workgroup can rank
-//    and for non-finite scores;
+//    the radix select over the bits of the scores remains for bins of more than 128 scores (ties, or one
+//    score far from the rest) and for non-finite scores;
 //  - queries that share a key/value head run on the same XCD at the same time (schedule()).
 // 1 query of 131109 keys x 32 slices (d = 64, B = 128, k = 8): 24.8 -> 12.8 us; 16 queries of 32805
 // keys x 16 heads on 4 key/value heads (d = 128, B = 64, k = 32): 59 -> 29 us (there
@@ -102,7 +102,10 @@ __device__ __forceinline__ int wave_prefix(int x)
 constexpr int kDecodeWaves = 16;
 constexpr int kDecodeThreads = kDecodeWaves * kWave;
 constexpr int kDecodeBins = kDecodeThreads;    // bins of the selection: one per thread
-constexpr int kDecodeRank = kDecodeThreads;    // most scores of one bin that are ranked directly: one per thread
+// Most scores of one bin that are ranked directly.  Each of them meets all the others, the radix select takes the
+// same time for any number: a score 10000 times the rest puts those into one bin (1 query, 1024 blocks, k = 8, whole call:
+// 52.0 us ranked, 17.8 by the radix select).
+constexpr int kDecodeRank = 128;
 // words that hold the ranked scores, then the waves' (m, l, O)
 template <int D>
 constexpr int kDecodeScratch = 2 * kDecodeRank > kDecodeWaves * (D + 2) ? 2 * kDecodeRank : kDecodeWaves * (D + 2);
@@ -247,7 +250,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
             __syncthreads();
             cut = ctl[0];
             need = ctl[1];
-            direct = ctl[2] <= kDecodeRank;                 // else: many equal scores
+            direct = ctl[2] <= kDecodeRank;                 // else: many scores close together
         }
         bool take[4];
         if (direct) {

@@ -187,3 +187,21 @@ def test_decode_keys_without_weight(dtype, d, period):
             ref = torch.softmax(z, 0) @ V[0, h, keys].double()
             assert (O[0, h, r].double().cpu() - ref).abs().max() < parity.O_TOL[dtype]
             assert abs(float(lse[0, h, r]) - float(torch.logsumexp(z, 0))) < parity.LSE_TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,past,k,sink", [("bf16", 1024, 8, 1e6), ("bf16", 160, 12, 1e5), ("f32", 2000, 40, 1e5), ("f32", 200, 3, -1e5)])
+def test_decode_one_score_far_from_the_rest(dtype, past, k, sink):
+    """One block's score is so large (or so small) that the others share one or a few bins of the selection, with more
+    of them there than are ranked directly: the kept blocks are still the best k."""
+    heads, B, d = 3, 4, 64
+    Q, K, V = make(1, heads, 0, past * B + 2, d, dtype, 77, 1)
+    g = torch.Generator().manual_seed(past)
+    cent = torch.randn((1, heads, past, d), generator=g)
+    cent[:, :, 5] = sink * Q[:, :, 0].float() / d
+    sh = moba.Shape(1, heads, past * B + 2, d, B, k, 0, binding.BF16 if dtype == "bf16" else binding.F32)
+    idx = moba.decode_forward(sh, 1, Q.cuda(), K.cuda(), V.cuda(), cent.cuda())[2].cpu()
+    z = torch.einsum("bhqd,bhnd->bhqn", Q.double(), cent.double())
+    for h in range(heads):
+        best = z[0, h, 0].sort(descending=True)
+        assert best.values[k - 1] - best.values[k] > 1e-5 * z[0, h, 0].abs().median()      # (a draw that fp32 sums tell apart)
+        assert idx[0, h, 0].tolist() == sorted(best.indices[:k].tolist())
