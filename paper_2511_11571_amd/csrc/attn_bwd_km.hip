@@ -380,51 +380,41 @@ void bwd_km_kernel(
 }
 
 // dQ_t = sum of the query's partials, in the order [kept block][part], then the parts of its
-// own block up to its own key.  D / 8 lanes per query; the partials of a query are consecutive
-// and are loaded nine at a time, unconditionally (past the end: the last one again, ignored).
-constexpr int kDqMergeChunk = 9;
-
-template <int D>
+// own block up to its own key.
+template <int D, int CH>
 __global__ __launch_bounds__(256) void dq_km_merge_kernel(
     const int32_t* __restrict__ idx, const bf16_t* __restrict__ PdQ, bf16_t* __restrict__ dQ, int N,
-    int B, int k, int nsub, int64_t rows_total)
+    int B, int k, int nsub)
 {
-    constexpr int G = D / 8, CH = kDqMergeChunk;
-    const int64_t row = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;      // s * N + t
-    const int part = threadIdx.x % G;
-    if (row >= rows_total) return;
-    const int t = (int)(row % N);
-    const int own_parts = (t % B) / bwd_part_keys(B, D) + 1;
-    const int slots = (k + 1) * nsub, klast = max(k - 1, 0);
-    const int64_t p0 = row * slots;
-    const char* orow = reinterpret_cast<const char*>(PdQ + p0 * D + part * 8);
-    // (with k = 0 there is no row of kept blocks: any readable address serves the unused loads)
-    const int32_t* irow = k > 0 ? idx + row * k : reinterpret_cast<const int32_t*>(orow);
+    using R = MergeRow<D>;
+    constexpr int PER = (CH + R::LANES - 1) / R::LANES;          // partials of a chunk a lane looks up
+    const R r(idx, N, B, k, nsub, bwd_part_keys(B, D));
+    const char* orow = reinterpret_cast<const char*>(PdQ + r.row * r.slots * D + r.piece * 8);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int i0 = 0, e0 = 0, c0 = 0; i0 < slots; i0 += CH) {
-        int jj[CH];
+    for (int i0 = 0; i0 < r.slots; i0 += CH) {
         u32x4_t raw[CH];
+        uint32_t there[PER];                                     // bit i: the i-th of these partials counts
 #pragma unroll
-        for (int i = 0, e = e0, c = c0; i < CH; ++i) {
-            jj[i] = irow[min(e, klast)];
-            raw[i] = *reinterpret_cast<const u32x4_t*>(orow + (int64_t)min(i0 + i, slots - 1) * (2 * D));
-            if (++c == nsub) { c = 0; ++e; }
+        for (int p = 0; p < PER; ++p) {
+            const uint64_t all = __ballot(r.counts(i0 + p * R::LANES + r.piece));
+            there[p] = (uint32_t)(r.lane & 32 ? all >> 32 : all) >> (r.lane & 31 & ~(R::LANES - 1));
         }
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            // the partial counts if it exists and its block was kept (own block: the parts up to
-            // the query's own key); an unused slot holds whatever the workspace held
-            const bool ok = i0 + i < slots && (e0 == k ? c0 < own_parts : jj[i] >= 0);
-            if (++c0 == nsub) { c0 = 0; ++e0; }
+        for (int i = 0; i < CH; ++i)
+            raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(orow + (int64_t)min(i0 + i, r.slots - 1) * (2 * D)));
 #pragma unroll
-            for (int h = 0; h < 4; ++h) {
-                const float lo = __uint_as_float(raw[i][h] << 16), hi = __uint_as_float(raw[i][h] & 0xffff0000u);
-                acc[2 * h] += ok ? lo : 0.f;
-                acc[2 * h + 1] += ok ? hi : 0.f;
+        for (int i = 0; i < CH; ++i) {
+            // (an unused slot holds whatever the workspace held)
+            const uint32_t mask = (uint32_t)-(int)((there[i / R::LANES] >> (i % R::LANES)) & 1u);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t x = raw[i][q] & mask;
+                acc[2 * q] += __uint_as_float(x << 16);
+                acc[2 * q + 1] += __uint_as_float(x & 0xffff0000u);
             }
         }
     }
-    Vec8<bf16_t>::store(dQ + row * D + part * 8, acc);
+    Vec8<bf16_t>::store(dQ + r.row * D + r.piece * 8, acc);
 }
 
 // ---- workspace: [D: bh*N fp32][partial dQ: bh*N*(k+1)*parts*D bf16], each 256-byte aligned
@@ -458,10 +448,19 @@ static hipError_t bwd_launch2(const Dims& s, const void* Q, const void* K, const
     }
     {
         ProfileScope timing(MOBA_PROFILE_DQ, st);
-        const int64_t rows = (int64_t)s.bh * s.N;
-        const int rpw = 256 / (D / 8);
-        hipLaunchKernelGGL((dq_km_merge_kernel<D>), dim3((unsigned)((rows + rpw - 1) / rpw)), dim3(256), 0, st,
-                           idx, PdQ, (bf16_t*)dQ, s.N, s.B, s.k, nsub, rows);
+        const dim3 grid((unsigned)((int64_t)s.bh * s.N / MergeRow<D>::ROWS));
+#define MOBA_MERGE(CH)                                                                                              \
+    hipLaunchKernelGGL((dq_km_merge_kernel<D, CH>), grid, dim3(256), 0, st, idx, PdQ, (bf16_t*)dQ, s.N, s.B, s.k,   \
+                       nsub);                                                                                       \
+    break
+        switch (merge_chunk((s.k + 1) * nsub)) {
+            case 4: MOBA_MERGE(4);
+            case 6: MOBA_MERGE(6);
+            case 9: MOBA_MERGE(9);
+            case 11: MOBA_MERGE(11);
+            default: MOBA_MERGE(13);
+        }
+#undef MOBA_MERGE
     }
     return hipGetLastError();
 }

@@ -54,61 +54,6 @@ struct FwdCfg {
                                   4 * 2 * (RANGE + 1) + 4 * NW + 8 + LCAP + 64;
 };
 
-// ---- the slot-ordered transposed copy alone (see mfma.h; the key-major kernels use it unscaled;
-// the copies of the query-tile kernels are made in prepare.hip) -----------
-
-template <int D>
-__global__ __launch_bounds__(256) void slot_major_copy_kernel(const bf16_t* __restrict__ X,
-                                                              const uint32_t* __restrict__ vmax,
-                                                              bf16_t* __restrict__ Xt,
-                                                              int64_t groups_per_slice)
-{
-    __shared__ bf16_t tile[32 * (D + 8)];
-    const int64_t kap = blockIdx.x;            // group index over all slices
-    const int s = (int)(kap / groups_per_slice);
-    const bf16_t* src = X + kap * 32 * D;
-    for (int i = threadIdx.x; i < 32 * D / 8; i += 256) {
-        const int r = i / (D / 8), c = i % (D / 8);
-        float v[8];
-        Vec8<bf16_t>::load(src + r * D + c * 8, v);
-        if (vmax) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = ldexpf(v[e], -scale_exponent(vmax[s * D + c * 8 + e]));
-        }
-        Vec8<bf16_t>::store(&tile[r * (D + 8) + c * 8], v);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < (D / 16) * 64; i += 256) {
-        const int mt = i / 64, lane = i % 64, g = lane >> 4, m = lane & 15;
-        const int ch = tile_chan<D>(mt, m);
-        uint32_t w[4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const uint32_t lo = tile[slot_key(g, 2 * p) * (D + 8) + ch];
-            const uint32_t hi = tile[slot_key(g, 2 * p + 1) * (D + 8) + ch];
-            w[p] = lo | (hi << 16);
-        }
-        *reinterpret_cast<uint4*>(Xt + slot_major_offset<D>(kap, mt, lane)) =
-            make_uint4(w[0], w[1], w[2], w[3]);
-    }
-}
-
-// Xt <- slot-ordered transposed copy of X, each channel scaled by 2^-e (e from its largest
-// magnitude vmax[bh][D], fp32 bits); vmax == nullptr: plain copy.
-hipError_t launch_slot_major_copy(const Dims& s, const void* X, void* Xt, const uint32_t* vmax,
-                                  hipStream_t st)
-{
-    const int64_t gps = s.N / 32, groups = (int64_t)s.bh * gps;
-    if (groups == 0) return hipSuccess;
-    if (s.D == 64)
-        hipLaunchKernelGGL(slot_major_copy_kernel<64>, dim3((unsigned)groups), dim3(256), 0, st,
-                           (const bf16_t*)X, vmax, (bf16_t*)Xt, gps);
-    else
-        hipLaunchKernelGGL(slot_major_copy_kernel<128>, dim3((unsigned)groups), dim3(256), 0, st,
-                           (const bf16_t*)X, vmax, (bf16_t*)Xt, gps);
-    return hipGetLastError();
-}
-
 // ---- the tile kernel -------------------------------------------------------------------
 
 // monotone map fp32 -> int32 (and back): larger float <=> larger int

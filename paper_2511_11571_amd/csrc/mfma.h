@@ -14,6 +14,9 @@
 // means key  slot_key(g, s)  -- so the other operand of the next product only has to use
 // the same slot order, and P never moves between lanes.
 #pragma once
+#include <type_traits>
+#include <utility>
+
 #include "common.h"
 
 namespace moba {
@@ -33,6 +36,15 @@ union Frag {               // one A or B operand
 __device__ __forceinline__ f32x4_t mfma16(const Frag& a, const Frag& b, f32x4_t c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
+}
+
+// The 32 x 32 x 16 form.  With lane = 32*h + m:
+//   A operand: lane holds row m, contraction slots 8h .. 8h+7 (B: col m)
+//   C result : lane holds col m, element i is row 8 (i >> 2) + 4 h + (i & 3)
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ f32x16_t mfma32(const Frag& a, const Frag& b, f32x16_t c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b.v, c, 0, 0, 0);
 }
 
 // LDS transpose read: within each group of 16 lanes, lane i receives as element e the 16-bit
@@ -79,6 +91,25 @@ __device__ __forceinline__ int scale_exponent(uint32_t vmax_bits)
 
 // maximum that hands a NaN on (v_maximum3_f32 on gfx950; fmaxf would drop it)
 __device__ __forceinline__ float max_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+// the value of lane FROM of this lane's group of GROUP (a power of two up to 32) neighbouring lanes
+template <int GROUP, int FROM>
+__device__ __forceinline__ float from_lane_of_group(float x)
+{
+    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), FROM << 5 | (31 & ~(GROUP - 1))));
+}
+// sum and maximum (NaN-propagating) of a lane's value and that of the lane 32 away
+__device__ __forceinline__ float sum_halves(float x)
+{
+    const uint32_t b = __float_as_uint(x);
+    const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float max_halves(float x)
+{
+    const uint32_t b = __float_as_uint(x);
+    const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return max_nan(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 // channel maximum (fp32 bits of a magnitude) of a tensor that holds an infinity or a NaN
 __device__ __forceinline__ bool nonfinite_bits(uint32_t magnitude_bits) { return magnitude_bits >= 0x7f800000u; }
 
@@ -214,6 +245,56 @@ __device__ __forceinline__ void build_block_lists(const int32_t* __restrict__ id
     __syncthreads();
 }
 
+// f(integral_constant 0), f(integral_constant 1), ...
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// ---- merging a query's partials (attn_fwd_km.hip, attn_bwd_km.hip) ---------------------------
+// D / 8 neighbouring lanes share a query; its partials [e][c] lie side by side and are taken CH at a time,
+// every load unconditional (past the end: the last one again, ignored), so that a lane has CH
+// 16-byte loads in flight.  What goes with a partial -- is it there, its (m, l) -- is looked up once per
+// query, by the lane that stands at its place in the chunk.  (Every lane looking up every partial for itself
+// kept the address and data units busy all the time: 4.4 of 4.4 ms at 151 M partials of d = 64.)
+template <int D>
+struct MergeRow {
+    static constexpr int LANES = D / 8, ROWS = 256 / LANES;             // a query's lanes; queries of a workgroup
+    int64_t row;                                                        // slice * N + t
+    int lane, piece, own_parts, slots, k, nsub;
+    const int32_t* irow;
+
+    // ROWS divides B and with it N: a workgroup's queries lie in one slice
+    __device__ __forceinline__ MergeRow(const int32_t* idx, int N, int B, int k_, int nsub_, int part_keys)
+        : lane(threadIdx.x % kWave), piece(threadIdx.x % LANES), slots((k_ + 1) * nsub_), k(k_), nsub(nsub_)
+    {
+        row = (int64_t)blockIdx.x * ROWS + threadIdx.x / LANES;
+        own_parts = 1;
+        if (nsub > 1) {
+            const int t = (int)(blockIdx.x % (uint32_t)(N / ROWS)) * ROWS + (int)(threadIdx.x / LANES);
+            own_parts = (t % B) / part_keys + 1;
+        }
+        irow = idx + row * k;                                            // (k = 0: never read)
+    }
+    // is slot si there?  Its block was kept; of the own block: the parts up to the query's own key
+    __device__ __forceinline__ bool counts(int si) const
+    {
+        int e = si, c = 0;
+        if (nsub > 1) { e = si / nsub; c = si - e * nsub; }
+        const int j = k > 0 ? irow[min(e, k - 1)] : 0;
+        return si < slots && (e == k ? c < own_parts : j >= 0);
+    }
+};
+// partials per chunk, one of the instantiated sizes: the one with the fewest loads past a query's end
+inline int merge_chunk(int slots)
+{
+    int best = 13;
+    for (int c : {11, 9, 6, 4})
+        if ((slots + c - 1) / c * c < (slots + best - 1) / best * best) best = c;
+    return best;
+}
+
 // ---- prepared copies of K and V (prepare.hip) ------------------------------------------------
 // "MFMA operand order": the 16 bytes lane (m, g) feeds to the MFMA as rows 16 mt + m, channels
 // 32 ks + 8 g .. + 8 of 32-key group kap sit at ((kap * 2 + mt) * (D / 32) + ks) * 1024 + 16 * lane.
@@ -237,8 +318,6 @@ size_t prepared_layout(const Dims& s, unsigned mask, void* base, Prepared* out);
 hipError_t launch_prepare(const Dims& kv, const void* K, const void* V, const Prepared& p, hipStream_t st);
 bool shared_workspace(const Dims& s);
 
-hipError_t launch_slot_major_copy(const Dims& s, const void* X, void* Xt, const uint32_t* vmax,
-                                  hipStream_t st);
 size_t forward_mfma_ws_bytes(const Dims& s);
 hipError_t launch_forward_mfma(const Dims& s, const void* Q, const void* K, const void* V,
                                void* ws, const int32_t* idx, const int32_t* off, const int32_t* ql,
