@@ -75,7 +75,8 @@ void bwd_km_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const float2* __restrict__ ld, const int32_t* __restrict__ off,
     const int32_t* __restrict__ ql, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, bf16_t* __restrict__ PdQ,
-    float* __restrict__ part, int N, int B, int n, int k, int nsub, float scale, int64_t R, int order, int bh, int G)
+    float* __restrict__ part, int N, int B, int n, int k, int nsub, float scale, int64_t R, int order, int bh, int G,
+    int inter)
 {
     using C = BwdKmCfg<D, NG>;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -85,7 +86,7 @@ void bwd_km_kernel(
     unsigned char* sK = ex + C::EX;                         // the part's K rows, for dQ
 
     int s, u;                                               // query slice, (key block, part)
-    if (!schedule(blockIdx.x, order * bh, n * nsub, s, u)) return;
+    if (!schedule(blockIdx.x, order * bh, n * nsub, s, u, inter)) return;
     const int j = u / nsub, c = u - j * nsub;
     const int own_first = c * (32 * NG);                    // first key of the part inside the block
     const int own0 = j * B + own_first;                     // ... of the slice; own queries that see keys of this part
@@ -440,7 +441,7 @@ static hipError_t bwd_launch2(const Dims& s, const void* Q, const void* K, const
         hipLaunchKernelGGL((bwd_km_kernel<D, NG, KV>), dim3((unsigned)schedule_grid(order * s.bh, s.n * nsub)), dim3(C::NT),
                            C::LDS, st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, ld, off,
                            ql, (bf16_t*)dK, (bf16_t*)dV, PdQ, part, s.N, s.B, s.n, s.k, nsub, s.scale, s.R, order, s.bh,
-                           s.G);
+                           s.G, interleave(s, 2));
     }
     if (KV && part) {
         e = launch_dkdv_heads(s, part, dK, dV, st);

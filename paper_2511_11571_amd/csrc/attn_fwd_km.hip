@@ -55,7 +55,7 @@ void fwd_km_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const int32_t* __restrict__ off, const int32_t* __restrict__ ql,
     bf16_t* __restrict__ PO, float* __restrict__ Pml, int N, int B, int n, int k, int nsub,
-    float scale, int64_t R, int bh, int G)
+    float scale, int64_t R, int bh, int G, int inter)
 {
     using C = KmCfg<D, NG>;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -66,7 +66,7 @@ void fwd_km_kernel(
     unsigned char* sV = sK + C::PART;
 
     int s, u;                                               // slice, (key block, part)
-    if (!schedule(blockIdx.x, bh, n * nsub, s, u)) return;
+    if (!schedule(blockIdx.x, bh, n * nsub, s, u, inter)) return;
     const int j = u / nsub, c = u - j * nsub;
     const int own_first = c * (32 * NG);                    // first key of the part inside the block
     const int64_t sbase = (int64_t)s * N;
@@ -388,7 +388,7 @@ static hipError_t km_launch2(const Dims& s, const void* Q, const void* K, const 
         const int bhs = slice_major(s, 1) * s.bh;           // (gathers Q rows)
         hipLaunchKernelGGL((fwd_km_kernel<D, NG>), dim3((unsigned)schedule_grid(bhs, s.n * nsub)),
                            dim3(C::NT), C::LDS, st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V,
-                           off, ql, PO, Pml, s.N, s.B, s.n, s.k, nsub, s.scale, s.R, bhs, s.G);
+                           off, ql, PO, Pml, s.N, s.B, s.n, s.k, nsub, s.scale, s.R, bhs, s.G, interleave(s, 1));
     }
     const dim3 grid((unsigned)((int64_t)s.bh * s.N / MergeRow<D>::ROWS));
 #define MOBA_MERGE(CH)                                                                                              \
