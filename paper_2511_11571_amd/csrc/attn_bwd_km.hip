@@ -19,12 +19,13 @@
 //              both operands through the transpose read.
 //
 // One walk for all three gradients: dQ on its own repeats the gather of Q and dO and the products S and dP
-// (5 products instead of 7).  No pipe is full: at N = 65536, d = 64, B = 128, k = 8, 32 slices the LDS pipe is busy
-// 64 % of the clocks (42 % of that bank conflicts), the matrix pipe 33, VALU issue 36; at N = 16384, d = 128, B = 64,
-// k = 16, 16 slices 37, 22 and 22 %.  What is left are the latencies of two waves per SIMD, one at d = 128.
-// Against separate walks for dQ and for dK and dV: N = 524288, d = 64, B = 128, k = 8, 32 slices: 28.0 -> 18.3 ms
-// (3.2 TB/s of gathered rows and partials); whole steps, N = 10080, B = 96, k = 10, 18 slices: 700 -> 562 us,
-// N = 16384, d = 128, B = 64, k = 16, 16 slices: 2617 -> 2056 us.
+// (5 products instead of 7).  No pipe is full: at N = 524288, d = 64, B = 128, k = 8, 32 slices VALU issue is
+// busy 34 % of the clocks, the matrix pipe 31 %, the LDS pipe about half; the latencies of two waves per SIMD
+// (d = 64), one (d = 128) are what is left.  Neither whole-line nor streaming stores of the partials nor rows
+// gathered from one place make much of a difference there (17.9 -> 17.6 and 16.4 ms).
+// Against separate walks for dQ and for dK and dV: N = 524288: 28.0 -> 18.6 ms, with the rows laid out as
+// parked() says 17.9; N = 10080, B = 96, k = 10, 18 slices: 210 us; N = 16384, d = 128, B = 64, k = 16, 16 slices: 778 us,
+// with that and operands read ahead 705.
 #include <type_traits>
 
 #include "mfma.h"
@@ -37,15 +38,17 @@ __host__ __device__ inline int bwd_part_keys(int B, int D)
     return B <= km_part_keys(B, D) ? B : B % 128 == 0 ? 128 : 64;
 }
 
-// rows in LDS, by 16-byte pieces: row-major operand reads (16 rows at one piece) and transpose reads (8 rows
-// at two neighbouring pieces) both meet every bank once.  d = 64: padded rows; d = 128: the piece XORed
-// with the row's low four bits rotated by one.
+// rows in LDS, by 16-byte pieces: row-major operand reads (16 rows at one piece; the 16 lanes served together are
+// 0-3, 12-15 and 20-27, i.e. rows 0-3 and 12-15 at one piece and rows 4-11 at the next) and transpose reads (8
+// rows at two neighbouring pieces) both meet every bank once: 4 and 3 clocks per instruction.  (Rows of 144
+// bytes: 8 and 4; a piece XORed with the row rotated by one: 8 and 3.)  d = 64: padded rows; d = 128: the piece XORed
+// with bits of the row.
 template <int D>
 __device__ __forceinline__ uint32_t parked(uint32_t row, uint32_t piece)
 {
-    if constexpr (D == 64) return row * 144u + piece * 16u;
-    const uint32_t r = row & 15u;
-    return row * 256u + ((piece ^ ((r << 1 | r >> 3) & 15u)) * 16u);
+    if constexpr (D == 64) return row * 160u + piece * 16u;
+    const uint32_t r = row, x = (r >> 3 & 1u) | (r & 3u) << 1 | ((r >> 2 ^ r >> 3) & 1u) << 3;
+    return row * 256u + ((piece ^ x) * 16u);
 }
 
 template <int D, int NG>                               // NG: 32-key groups of a workgroup
@@ -59,9 +62,9 @@ struct BwdKmCfg {
     static constexpr int RPI = kWave / CPR;             // rows per gather instruction
     static constexpr int RW = P / NW, NI = RW / RPI;    // rows a wave gathers, instructions per tensor
     static constexpr int CH = D / HV, MQ = CH / 16;     // channels and tiles of a wave's share of dQ
-    static constexpr int SB = D == 64 ? 144 : 256;      // bytes per parked row
+    static constexpr int SB = D == 64 ? 160 : 256;      // bytes per parked row
     static constexpr int SLOT = 64 * SB + 3 * 32 * 4;   // Q rows, dO rows, lse, -D, list entry
-    static constexpr int XS = 2 * P + 32;               // bytes per key of dS (8 rows of 32 bytes: every bank once)
+    static constexpr int XS = 2 * P + 8;                // bytes per key of dS (written by 16 rows at a time: every bank once)
     static constexpr int EX = 32 * NG * XS, KR = 32 * NG * SB;
     static constexpr int RST = D + 4;                   // floats per key row when dK and dV are turned over
     static constexpr size_t WALK = (size_t)NSLOT * SLOT + EX + KR, TURN = (size_t)NW * 32 * RST * 4;
@@ -207,39 +210,58 @@ void bwd_km_kernel(
     const int dslot = wave / C::HV, dhalf = wave % C::HV;     // this wave's share of dQ
     const int64_t slots = (int64_t)(k + 1) * nsub;           // partials per query
 
+    auto ahead = [&]() { if constexpr (D == 128) __builtin_amdgcn_sched_barrier(0); };
     // 32 parked positions (walk positions p0 .. p0 + 31) against this wave's keys
     auto work = [&](const unsigned char* stQ, int sl, int p0, auto inside) {
         const unsigned char* stG = stQ + 32 * C::SB;
         const float* ls = reinterpret_cast<const float*>(stQ + 64 * C::SB);
         const float* Ds = ls + 32;
-        f32x4_t sc[2][2], dp[2][2];
+        // d = 128, one wave per SIMD: every operand is read well ahead of its product, with scheduling barriers
+        // in between -- left alone, the compiler reads an operand right before it is used, and the wave waits for
+        // it (N = 16384, B = 64, k = 16, 16 slices: 751 -> 705 us).  At d = 64 the second wave fills those waits.
+        f32x4_t sc[2][2], dp[2][2], nd[2], l4[2];
+        Frag qa[2][C::KS], ga[2][C::KS];
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt) {
-            Frag qa[C::KS], ga[C::KS];
 #pragma unroll
             for (int ks = 0; ks < C::KS; ++ks) {
                 const uint32_t o = parked<D>(m16, 4 * ks + g) + qt * 16 * C::SB;
-                qa[ks].q = *reinterpret_cast<const uint4*>(stQ + o);
-                ga[ks].q = *reinterpret_cast<const uint4*>(stG + o);
+                qa[qt][ks].q = *reinterpret_cast<const uint4*>(stQ + o);
+                ga[qt][ks].q = *reinterpret_cast<const uint4*>(stG + o);
             }
-            const f32x4_t nd = *reinterpret_cast<const f32x4_t*>(Ds + 16 * qt + 4 * g);   // -D of the rows
+            nd[qt] = *reinterpret_cast<const f32x4_t*>(Ds + 16 * qt + 4 * g);   // -D of the rows
+            l4[qt] = *reinterpret_cast<const f32x4_t*>(ls + 16 * qt + 4 * g);
+        }
+        ahead();
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
                 sc[qt][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                dp[qt][nt] = nd;                              // dP - D comes out of the MFMA
-#pragma unroll
-                for (int ks = 0; ks < C::KS; ++ks) {
-                    sc[qt][nt] = mfma16(qa[ks], kb[nt][ks], sc[qt][nt]);
-                    dp[qt][nt] = mfma16(ga[ks], vb[nt][ks], dp[qt][nt]);
-                }
+                dp[qt][nt] = nd[qt];                          // dP - D comes out of the MFMA
             }
+#pragma unroll
+            for (int ks = 0; ks < C::KS; ++ks)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt) {
+                    sc[qt][nt] = mfma16(qa[qt][ks], kb[nt][ks], sc[qt][nt]);
+                    dp[qt][nt] = mfma16(ga[qt][ks], vb[nt][ks], dp[qt][nt]);
+                }
         }
+        constexpr int AHEAD = D == 64 ? 1 : 3;                // transposed operands read ahead
+        Frag qT[AHEAD + 1], gT[AHEAD + 1];
+        auto transposed = [&](int mt) {
+            qT[mt % (AHEAD + 1)] = tr(stQ, 4 * mt);
+            gT[mt % (AHEAD + 1)] = tr(stG, 4 * mt);
+        };
+        if (KV) {
+#pragma unroll
+            for (int mt = 0; mt < AHEAD; ++mt) transposed(mt);
+        }
+        ahead();
         // own queries are causal: the wave's key kfirst + 16 nt + m16 must not exceed the query
         const bool causal = !decltype(inside)::value && p0 + 32 > nlist && p0 < nlist + kfirst + 32;
         Frag pb[2], sb[2];
-        f32x4_t l4[2];
-#pragma unroll
-        for (int qt = 0; qt < 2; ++qt) l4[qt] = *reinterpret_cast<const f32x4_t*>(ls + 16 * qt + 4 * g);
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
             float p[8], d[8];
@@ -268,12 +290,14 @@ void bwd_km_kernel(
         }
 #pragma unroll
         for (int mt = 0; KV && mt < C::MT; ++mt) {
-            const Frag qT = tr(stQ, 4 * mt), gT = tr(stG, 4 * mt);
+            if (mt + AHEAD < C::MT) transposed(mt + AHEAD);
+            ahead();
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
-                dVT[mt][nt] = mfma16(gT, pb[nt], dVT[mt][nt]);
-                dKT[mt][nt] = mfma16(qT, sb[nt], dKT[mt][nt]);
+                dVT[mt][nt] = mfma16(gT[mt % (AHEAD + 1)], pb[nt], dVT[mt][nt]);
+                dKT[mt][nt] = mfma16(qT[mt % (AHEAD + 1)], sb[nt], dKT[mt][nt]);
             }
+            ahead();
         }
     };
     auto meet = [&]() {
@@ -303,27 +327,37 @@ void bwd_km_kernel(
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt)
             note[qt] = *reinterpret_cast<const int*>(smem + dslot * C::SLOT + 64 * C::SB + 256 + 4 * (16 * qt + m16));
+        // dQ^T = K^T dS^T: key groups outside, channel tiles inside; K's operands KA ahead (they do not
+        // wait for the other waves), dS's all at once
+        constexpr int KA = D == 64 ? 1 : 4;
+        Frag ka[KA + 1], xb[NG][2];
+        auto keys = [&](int it) {
+            ka[it % (KA + 1)] = tr(sK + 32 * (it / C::MQ) * C::SB, dhalf * (C::CH / 4) + 4 * (it % C::MQ));
+        };
+#pragma unroll
+        for (int it = 0; it < KA; ++it) keys(it);
         meet();                                              // dS is whole; the parked rows are read
+#pragma unroll
+        for (int kg = 0; kg < NG; ++kg)
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt) {
+                const unsigned char* x = ex + exr + 32 * kg * C::XS + 64 * dslot + 32 * qt;
+                const uint2 a = lds_read_tr16(x), b = lds_read_tr16(x + 16 * C::XS);
+                xb[kg][qt].u[0] = a.x; xb[kg][qt].u[1] = a.y; xb[kg][qt].u[2] = b.x; xb[kg][qt].u[3] = b.y;
+            }
         f32x4_t o[2][C::MQ];
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
             for (int mt = 0; mt < C::MQ; ++mt) o[qt][mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kg = 0; kg < NG; ++kg) {
-            Frag xb[2];
+        for (int it = 0; it < NG * C::MQ; ++it) {
+            if (it + KA < NG * C::MQ) keys(it + KA);
+            ahead();
 #pragma unroll
-            for (int qt = 0; qt < 2; ++qt) {
-                const unsigned char* x = ex + exr + 32 * kg * C::XS + 64 * dslot + 32 * qt;
-                const uint2 a = lds_read_tr16(x), b = lds_read_tr16(x + 16 * C::XS);
-                xb[qt].u[0] = a.x; xb[qt].u[1] = a.y; xb[qt].u[2] = b.x; xb[qt].u[3] = b.y;
-            }
-#pragma unroll
-            for (int mt = 0; mt < C::MQ; ++mt) {
-                const Frag ka = tr(sK + 32 * kg * C::SB, dhalf * (C::CH / 4) + 4 * mt);
-#pragma unroll
-                for (int qt = 0; qt < 2; ++qt) o[qt][mt] = mfma16(ka, xb[qt], o[qt][mt]);
-            }
+            for (int qt = 0; qt < 2; ++qt)
+                o[qt][it % C::MQ] = mfma16(ka[it % (KA + 1)], xb[it / C::MQ][qt], o[qt][it % C::MQ]);
+            ahead();
         }
         // the partials: this lane holds CH / 4 consecutive channels of two rows
 #pragma unroll
