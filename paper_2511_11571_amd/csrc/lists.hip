@@ -10,7 +10,8 @@
 //   3. fill: the bit matrix is rebuilt and its rows are written out in ascending order at
 //      blk_off[j] + chunk start, eight lanes per row (or entry by entry, see below).
 // The bit matrix lives in LDS only and covers 512 or 1024 key blocks at a time.
-// Short slices take one launch instead (lists_small_kernel).
+// Slices with few counts take no scans: the fill pass adds the counts up itself (starts_from_counts()).  Short slices
+// take one launch instead (lists_small_kernel).
 //
 // A list entry holds the query in its low 24 bits (sequences are at most 2^24 long).  Where the
 // key-block-major attention kernels will run (lists_with_places() of the shape and its flags) the
@@ -80,10 +81,67 @@ __device__ __forceinline__ void for_each_entry(const int32_t* __restrict__ rows0
     for_each_entry_slot(rows0, rows, k, tid, [&](int r, int b, int) { f(r, b); });
 }
 
-// kRange: key blocks per LDS bit matrix (blockIdx.y counts the ranges of a slice's blocks)
-template <bool FILL, bool SLOTS, int kRange>
+// What lists_scan_kernel and lists_offsets_kernel leave, worked out by the fill pass itself from the counts of all
+// chunks: start[j] of chunk c for the n <= kRange blocks; the last chunk's workgroup writes off[0 .. n].
+// scratch: 2 * kRange words
+template <int kRange>
+__device__ __forceinline__ void starts_from_counts(const int32_t* __restrict__ counts, int32_t* __restrict__ off, int n,
+                                                   int nchunk, int c, int32_t* scratch, int32_t* start, int tid)
+{
+    constexpr int EPT = kRange / 256;
+    __shared__ int wsum[4];
+    int32_t* total = scratch;
+    int32_t* before = scratch + kRange;
+    for (int j = tid; j < n; j += 256) total[j] = before[j] = 0;
+    __syncthreads();
+    const int dc = 256 / n, dj = 256 - dc * n;               // 256 counts further on
+    int ch = tid / n, j = tid - ch * n;
+#pragma unroll 4
+    for (int i = tid; i < nchunk * n; i += 256) {
+        const int v = counts[i];
+        if (v) {
+            atomicAdd(&total[j], v);
+            if (ch < c) atomicAdd(&before[j], v);
+        }
+        ch += dc;
+        j += dj;
+        if (j >= n) { j -= n; ++ch; }
+    }
+    __syncthreads();
+    int v[EPT], sum = 0;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        v[e] = tid * EPT + e < n ? total[tid * EPT + e] : 0;
+        sum += v[e];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int up = __shfl_up(incl, o, kWave);
+        if (tid % kWave >= o) incl += up;
+    }
+    if (tid % kWave == kWave - 1) wsum[tid / kWave] = incl;
+    __syncthreads();
+    int run = incl - sum;
+    for (int w = 0; w < tid / kWave; ++w) run += wsum[w];
+    const bool last = c == nchunk - 1;
+    if (last && tid == 0) off[0] = 0;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        const int b = tid * EPT + e;
+        if (b >= n) break;
+        start[b] = run + before[b];
+        run += v[e];
+        if (last) off[b + 1] = run;
+    }
+    __syncthreads();
+}
+
+// kRange: key blocks per LDS bit matrix (blockIdx.y counts the ranges of a slice's blocks).
+// SELF (fill, one range): no scans went before, see above
+template <bool FILL, bool SLOTS, int kRange, bool SELF = false>
 __global__ __launch_bounds__(256) void lists_chunk_kernel(
-    const int32_t* __restrict__ idx, int32_t* __restrict__ cnt2, const int32_t* __restrict__ off,
+    const int32_t* __restrict__ idx, int32_t* __restrict__ cnt2, int32_t* __restrict__ off,
     int32_t* __restrict__ ql, int N, int B, int n, int k, int nchunk, int64_t R, int bh)
 {
     __shared__ __align__(16) uint32_t mask[kRange * kWords];
@@ -99,13 +157,16 @@ __global__ __launch_bounds__(256) void lists_chunk_kernel(
     const int nblk = min(hi, (t0 + rows - 1) / B) - lo;   // kept blocks are < own block of the last query
     const int tid = threadIdx.x;
     int32_t* crow = cnt2 + ((int64_t)s * (nchunk + 1) + c) * n + lo;
+    if constexpr (SELF)
+        starts_from_counts<kRange>(cnt2 + (int64_t)s * (nchunk + 1) * n, off + (int64_t)s * (n + 1), n, nchunk, c,
+                                   reinterpret_cast<int32_t*>(mask), start, tid);
     if (nblk <= 0) {
         if (!FILL)
             for (int j = tid; j < hi - lo; j += 256) crow[j] = 0;
         return;
     }
     for (int i = tid; i < nblk * kWords; i += 256) mask[i] = 0u;
-    if (FILL) {
+    if (FILL && !SELF) {
         const int32_t* orow = off + (int64_t)s * (n + 1) + lo;
         for (int j = tid; j < nblk; j += 256) {
             start[j] = orow[j] + crow[j];
@@ -338,25 +399,40 @@ static hipError_t small_launch(const Dims& s, const SmallLists& p, const int32_t
     return hipGetLastError();
 }
 
+// Most counts of a slice (chunks x blocks) that every workgroup of the fill pass adds up for itself, in place of
+// two launches of 4.5 to 6 us.  us, scans + fill -> fill: 2048 counts (16 slices, N = 8192, 64 blocks) 17.0 -> 11.0;
+// 4200 (18 slices, N = 10080, 105 blocks) 23.4 -> 19.6; 16384 (16 slices, N = 16384, 256 blocks) 34.3 -> 44.1.
+constexpr int kSelfCounts = 6144;
+
 template <int RANGE>
 static hipError_t build_lists_launch(const Dims& s, const int32_t* idx, int32_t* off, int32_t* ql,
                                      int32_t* cnt2, hipStream_t st)
 {
     const int nranges = (s.n + RANGE - 1) / RANGE;
     dim3 grid(schedule_grid(s.bh, s.nchunk), nranges), block(256);
-    hipLaunchKernelGGL((lists_chunk_kernel<false, false, RANGE>), grid, block, 0, st, idx, cnt2,
-                       (const int32_t*)off, ql, s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);
+    hipLaunchKernelGGL((lists_chunk_kernel<false, false, RANGE>), grid, block, 0, st, idx, cnt2, off, ql, s.N, s.B,
+                       s.n, s.k, s.nchunk, s.R, s.bh);
+    static_assert(kKeyMajorMaxTopk <= 127, "the place of a block in the high byte of an entry");
+#define MOBA_FILL(SELF)                                                                                               \
+    do {                                                                                                              \
+        if (lists_with_places(s))                                                                                     \
+            hipLaunchKernelGGL((lists_chunk_kernel<true, true, RANGE, SELF>), grid, block, 0, st, idx, cnt2, off, ql, \
+                               s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);                                              \
+        else                                                                                                          \
+            hipLaunchKernelGGL((lists_chunk_kernel<true, false, RANGE, SELF>), grid, block, 0, st, idx, cnt2, off, ql, \
+                               s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);                                              \
+    } while (0)
+    if constexpr (RANGE == kRangeLong) {
+        if (s.R > 0 && s.n <= RANGE && (int64_t)s.nchunk * s.n <= kSelfCounts) {
+            MOBA_FILL(true);
+            return hipGetLastError();
+        }
+    }
     hipLaunchKernelGGL(lists_scan_kernel, dim3((s.n + 31) / 32, s.bh), block, 0, st, cnt2, off, s.n,
                        s.nchunk);
     hipLaunchKernelGGL(lists_offsets_kernel, dim3(s.bh), block, 0, st, off, s.n);
-    if (s.R > 0) {
-        static_assert(kKeyMajorMaxTopk <= 127, "the place of a block in the high byte of an entry");
-        if (lists_with_places(s))
-            hipLaunchKernelGGL((lists_chunk_kernel<true, true, RANGE>), grid, block, 0, st, idx, cnt2, (const int32_t*)off, ql, s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);
-        else
-            hipLaunchKernelGGL((lists_chunk_kernel<true, false, RANGE>), grid, block, 0, st, idx, cnt2,
-                               (const int32_t*)off, ql, s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);
-    }
+    if (s.R > 0) MOBA_FILL(false);
+#undef MOBA_FILL
     return hipGetLastError();
 }
 
