@@ -132,7 +132,8 @@ int moba_centroids(const moba_shape* shape, const void* K, const float* conv_w,
  *   dK_eff   in   [b,kv,N,d] dtype: gradient with respect to K_eff (dK of moba_backward)
  *   dK       out  [b,kv,N,d] dtype: gradient with respect to K; must not overlap dK_eff
  *   dconv_w  out  [kv,d,W] fp32, summed over the batch in a fixed order
- *   ws            at least moba_key_conv_backward_workspace bytes
+ *   ws            moba_key_conv_backward_workspace bytes; short sequences also run, more slowly, on
+ *                 as little as 4 * W * d bytes per 2048 (d = 128; 64: 4096) rows and slice, rounded up to 256, + 256
  * conv_width must be at least 1.
  */
 int moba_key_conv_backward_workspace(const moba_shape* shape, size_t* ws_bytes);

@@ -244,8 +244,9 @@ hipError_t launch_centroids(const Dims& s, const void* K, const float* w, void* 
 hipError_t launch_decode(const Dims& s, int q_len, const void* Q, const void* K, const void* V,
                          const float* cent, int cblocks, void* O, float* lse, int32_t* idx, hipStream_t st);
 hipError_t launch_conv_backward(const Dims& s, const void* K, const float* w, const void* G, void* dK,
-                                float* dw, void* ws, hipStream_t st);
+                                float* dw, void* ws, size_t ws_bytes, hipStream_t st);
 size_t conv_bwd_ws_bytes(const Dims& s);
+size_t conv_bwd_least_ws_bytes(const Dims& s);
 hipError_t launch_varlen_copy(bool pad, const int32_t* seq_off, const int32_t* pad_off, int num_seqs,
                               int64_t slices, int tokens, int padded_tokens, int row_bytes, const void* src,
                               void* dst, hipStream_t st);

@@ -13,12 +13,23 @@
 
 namespace moba {
 
-constexpr int kConvRows = 128;     // rows per chunk
+constexpr int kConvRows = 128;     // rows per chunk at most
+
+// Rows per chunk: fewer where chunks of 128 rows would leave compute units without a workgroup -- a chunk is a
+// serial walk, and its W - 1 extra rows cost less than idle units.  4 slices of N = 16384, d = 128, W = 4: 131 us with
+// 128 rows (32 workgroups), 24 with 16 (256 workgroups).
+static int conv_rows(const Dims& s)
+{
+    const int cpw = 256 / (s.D / 8);
+    int rows = kConvRows;
+    while (rows > 16 && (int64_t)s.bh * (s.N / rows / cpw) < 512) rows /= 2;
+    return rows;
+}
 
 template <typename T, int D, int W>
 __global__ __launch_bounds__(256) void conv_bwd_kernel(
     const T* __restrict__ K, const float* __restrict__ w, const T* __restrict__ G,
-    T* __restrict__ dK, float* __restrict__ part, int heads, int N, int nck)
+    T* __restrict__ dK, float* __restrict__ part, int heads, int N, int rows)
 {
     constexpr int GL = D / 8;          // lanes per chunk
     constexpr int CPW = 256 / GL;      // chunks per workgroup
@@ -27,7 +38,7 @@ __global__ __launch_bounds__(256) void conv_bwd_kernel(
     const int lane8 = threadIdx.x % GL;
     const int s = blockIdx.y;
     // a chunk past the end of the sequence has no rows: it only takes part in the dw sum
-    const int r0 = min(N, ck * kConvRows), r1 = min(N, r0 + kConvRows);
+    const int r0 = min(N, ck * rows), r1 = min(N, r0 + rows);
     const int64_t base = (int64_t)s * N * D + lane8 * 8;
 
     float wr[W][8], kw[W][8], acc[W][8], dwa[W][8];    // kw[l] = K[u-l]; acc[l] = unfinished dK[u-l]
@@ -102,40 +113,50 @@ __global__ __launch_bounds__(256) void conv_bwd_kernel(
     for (int i = threadIdx.x; i < D * W; i += 256) p[i] = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
 }
 
-// dw[h][c][l] = sum over the slices of head h (batch order) and over their workgroups (ascending)
+// dw[h][c][l] = sum over the slices of head h (batch order) and over their workgroups (ascending): four
+// neighbouring waves take every fourth of these terms, and their sums are added in order
 __global__ __launch_bounds__(256) void conv_bwd_reduce_kernel(const float* __restrict__ part,
                                                               float* __restrict__ dw, int batch,
-                                                              int heads, int nck, int DW)
+                                                              int heads, int wgs, int DW)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;      // (c, l) of head blockIdx.y
-    const int h = blockIdx.y;
-    if (i >= DW) return;
+    __shared__ float red[4][kWave];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int i = min(blockIdx.x * kWave + lane, DW - 1);      // (c, l) of head blockIdx.y
+    const int h = blockIdx.y, terms = batch * wgs;
     float sum = 0.f;
-    for (int b = 0; b < batch; ++b) {
-        const float* p = part + ((int64_t)(b * heads + h) * nck) * DW + i;
-        for (int ck = 0; ck < nck; ++ck) sum += p[(int64_t)ck * DW];
+#pragma unroll 8
+    for (int t = wave; t < terms; t += 4) {
+        const int b = t / wgs, wg = t - b * wgs;
+        sum += part[((int64_t)(b * heads + h) * wgs + wg) * DW + i];
     }
-    dw[(int64_t)h * DW + i] = sum;
+    red[wave][lane] = sum;
+    __syncthreads();
+    if (wave == 0 && blockIdx.x * kWave + lane < DW)
+        dw[(int64_t)h * DW + i] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
 }
 
-size_t conv_bwd_ws_bytes(const Dims& s)
+static size_t conv_wgs(const Dims& s, int rows)
 {
-    const int nck = (s.N + kConvRows - 1) / kConvRows;
-    const int cpw = 256 / (s.D / 8);
-    return sizeof(float) * (size_t)s.bh * ((nck + cpw - 1) / cpw) * s.D * (s.W > 0 ? s.W : 1);
+    const int nck = (s.N + rows - 1) / rows, cpw = 256 / (s.D / 8);
+    return (size_t)((nck + cpw - 1) / cpw);
 }
+static size_t conv_bytes(const Dims& s, int rows)
+{
+    return sizeof(float) * (size_t)s.bh * conv_wgs(s, rows) * s.D * (s.W > 0 ? s.W : 1);
+}
+// what the call wants, and the least that it takes (chunks of kConvRows)
+size_t conv_bwd_ws_bytes(const Dims& s) { return conv_bytes(s, conv_rows(s)); }
+size_t conv_bwd_least_ws_bytes(const Dims& s) { return conv_bytes(s, kConvRows); }
 
 template <typename T, int D>
 static hipError_t launch_w(const Dims& s, const void* K, const float* w, const void* G, void* dK,
-                           float* dw, float* part, hipStream_t st)
+                           float* dw, float* part, int rows, hipStream_t st)
 {
-    const int nck = (s.N + kConvRows - 1) / kConvRows;
-    const int cpw = 256 / (D / 8);
-    dim3 grid((unsigned)((nck + cpw - 1) / cpw), (unsigned)s.bh), block(256);
+    dim3 grid((unsigned)conv_wgs(s, rows), (unsigned)s.bh), block(256);
 #define MOBA_CASE(WV)                                                                       \
     case WV:                                                                                \
         hipLaunchKernelGGL((conv_bwd_kernel<T, D, WV>), grid, block, 0, st, (const T*)K, w, \
-                           (const T*)G, (T*)dK, part, s.heads, s.N, nck);                   \
+                           (const T*)G, (T*)dK, part, s.heads, s.N, rows);                   \
         break;
     switch (s.W) {
         MOBA_CASE(1) MOBA_CASE(2) MOBA_CASE(3) MOBA_CASE(4)
@@ -146,21 +167,23 @@ static hipError_t launch_w(const Dims& s, const void* K, const float* w, const v
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int DW = D * s.W;
-    hipLaunchKernelGGL(conv_bwd_reduce_kernel, dim3((unsigned)((DW + 255) / 256), (unsigned)s.heads),
+    hipLaunchKernelGGL(conv_bwd_reduce_kernel, dim3((unsigned)((DW + kWave - 1) / kWave), (unsigned)s.heads),
                        dim3(256), 0, st, part, dw, s.bh / s.heads, s.heads, (int)grid.x, DW);
     return hipGetLastError();
 }
 
 hipError_t launch_conv_backward(const Dims& s, const void* K, const float* w, const void* G, void* dK,
-                                float* dw, void* ws, hipStream_t st)
+                                float* dw, void* ws, size_t ws_bytes, hipStream_t st)
 {
     if (s.bh == 0 || s.N == 0) return hipSuccess;
     float* part = static_cast<float*>(ws);
+    int rows = conv_rows(s);
+    while (rows < kConvRows && conv_bytes(s, rows) > ws_bytes) rows *= 2;
     if (s.dtype == MOBA_BF16)
-        return s.D == 64 ? launch_w<bf16_t, 64>(s, K, w, G, dK, dw, part, st)
-                         : launch_w<bf16_t, 128>(s, K, w, G, dK, dw, part, st);
-    return s.D == 64 ? launch_w<float, 64>(s, K, w, G, dK, dw, part, st)
-                     : launch_w<float, 128>(s, K, w, G, dK, dw, part, st);
+        return s.D == 64 ? launch_w<bf16_t, 64>(s, K, w, G, dK, dw, part, rows, st)
+                         : launch_w<bf16_t, 128>(s, K, w, G, dK, dw, part, rows, st);
+    return s.D == 64 ? launch_w<float, 64>(s, K, w, G, dK, dw, part, rows, st)
+                     : launch_w<float, 128>(s, K, w, G, dK, dw, part, rows, st);
 }
 
 }  // namespace moba

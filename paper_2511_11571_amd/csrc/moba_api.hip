@@ -290,8 +290,8 @@ int moba_key_conv_backward(const moba_shape* shape, const void* K, const float* 
     const int st = make_dims(shape, d);
     if (st != MOBA_OK) return st;
     if (d.W < 1 || !K || !conv_w || !dK_eff || !dK || !dconv_w || dK == dK_eff) return MOBA_EINVAL;
-    if (!ws || ws_bytes < align256(conv_bwd_ws_bytes(kv_view(d))) + 256) return MOBA_EWORKSPACE;
-    return hip_status(launch_conv_backward(kv_view(d), K, conv_w, dK_eff, dK, dconv_w, ws, (hipStream_t)stream));
+    if (!ws || ws_bytes < align256(conv_bwd_least_ws_bytes(kv_view(d))) + 256) return MOBA_EWORKSPACE;
+    return hip_status(launch_conv_backward(kv_view(d), K, conv_w, dK_eff, dK, dconv_w, ws, ws_bytes, (hipStream_t)stream));
 }
 
 int moba_build_lists(const moba_shape* shape, const int32_t* topk_idx, int32_t* blk_off,
