@@ -402,11 +402,12 @@ __global__ __launch_bounds__(256) void dkdv_heads_kernel(const float* __restrict
     const int which = (int)(i / per_tensor);
     const int64_t r = i % per_tensor, skv = r / chunks_per_slice, ch = r % chunks_per_slice;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
     for (int gq = 0; gq < G; ++gq) {
-        float v[8];
-        Vec8<float>::load(part + ((((int64_t)which * bhk + skv) * G + gq) * chunks_per_slice + ch) * 8, v);
+        const f32x4_t* p = reinterpret_cast<const f32x4_t*>(part + ((((int64_t)which * bhk + skv) * G + gq) * chunks_per_slice + ch) * 8);
+        const f32x4_t a = __builtin_nontemporal_load(p), b = __builtin_nontemporal_load(p + 1);     // (read once)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += v[e];
+        for (int e = 0; e < 4; ++e) { acc[e] += a[e]; acc[4 + e] += b[e]; }
     }
     Vec8<bf16_t>::store((which == 0 ? dK : dV) + (skv * chunks_per_slice + ch) * 8, acc);
 }
