@@ -14,7 +14,9 @@
 // Structure, operand copies and workgroup schedule are the forward kernel's (see there): row
 // lists per key block in LDS, K and V read in MFMA operand order, XCD-aware schedule.  The Q
 // and dO tiles sit in LDS unpadded, with the 16-byte chunks of row r permuted by r & 7 so
-// that a gather of arbitrary rows still spreads over the banks.
+// that a gather of arbitrary rows still spreads over the banks.  As there, the issue of vector
+// instructions bounds it: 957 -> 945 us (16 heads of 32768, B = 32, k = 64) with adds that hit no
+// bank twice.
 #include "mfma.h"
 
 namespace moba {
@@ -29,11 +31,12 @@ struct DqCfg {
     static constexpr int NW = D == 64 ? MOBA_DQ_NW64 : 8;
     static constexpr int NT = NW * kWave;
     static constexpr int ROWB = D * 2;                 // bytes per Q / dO row in LDS
-    static constexpr int OSTRIDE = D + 1;              // words per accumulator row
+    static constexpr int OSTRIDE = D;                  // words per accumulator row
     static constexpr int MT = D / 16;
     static constexpr int KS = D / 32;
     static constexpr int RANGE = 1024;                 // key blocks per set of row lists (at most)
-    static constexpr int LCAP = 16384;                 // (row, block) pairs per set of row lists
+    static constexpr int LPAIRS = 16384;               // (row, block) pairs per set of row lists
+    static constexpr int LCAP = LPAIRS + 3 * RANGE;    // bytes of the lists, each on a word of its own
     static constexpr size_t LDS = (size_t)2 * TILE * ROWB + 4 * TILE * OSTRIDE + 4 * 3 * TILE +
                                   4 * 2 * (RANGE + 1) + 4 * NW + 8 + LCAP + 64;
 };
@@ -161,24 +164,21 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
             gb[ks].q = *reinterpret_cast<const uint4*>(Gs + o);
         }
     };
-    // x: dS^T (scaled) of this lane's row -> dQ accumulators
-    auto accumulate = [&](int row, const float (&x)[8], const Frag (&kt)[C::MT], bool valid) {
+    // x: dS^T (scaled) of this lane's row -> dQ accumulators.  The product leaves row r4[i] (4 g + i of
+    // the sixteen), channel tile_chan(mt, m16), which sits at word 16 mt + m16 of an accumulator row
+    auto accumulate = [&](const int (&r4)[4], const float (&x)[8], const Frag (&kt)[C::MT]) {
         Frag pb;
 #pragma unroll
         for (int e = 0; e < 4; ++e) pb.u[e] = pack2(x[2 * e], x[2 * e + 1]);
-        int oi[C::MT][4];
+        f32x4_t o[C::MT];
 #pragma unroll
-        for (int mt = 0; mt < C::MT; ++mt) {
-            const f32x4_t o = mfma16(kt[mt], pb, f32x4_t{0.f, 0.f, 0.f, 0.f});
+        for (int mt = 0; mt < C::MT; ++mt) o[mt] = mfma16(pb, kt[mt], f32x4_t{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-            for (int i = 0; i < 4; ++i) oi[mt][i] = (int)o[i];   // toward zero; |o| ~ 2^12..2^20
-        }
-        if (valid) {
-            int* arow = acc + (uint32_t)row * C::OSTRIDE + g * (D / 4);
+        for (int i = 0; i < 4; ++i) {
+            int* arow = acc + (uint32_t)r4[i] * C::OSTRIDE + m16;
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) atomicAdd(&arow[4 * mt + i], oi[mt][i]);
+                atomicAdd(&arow[16 * mt], (int)o[mt][i]);         // toward zero; |o| ~ 2^12..2^20
         }
     };
 
@@ -192,6 +192,7 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
         Frag qb[C::KS], gb[C::KS];
         gather(row, qb, gb);
         const float pe = pexp[row], nD = Dr[row];
+        const int own4 = 32 * unit + 16 * st + 4 * g, r4[4] = {own4, own4 + 1, own4 + 2, own4 + 3};
         for (int kap = kfirst; kap <= kown; ++kap) {
             const bool own = kap == kown;
             Frag ka[2][C::KS], va[2][C::KS], kt[C::MT];
@@ -217,13 +218,13 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
                 const bool vis = !own || 16 * (e >> 2) + 4 * g + (e & 3) <= 16 * st + m16;
                 x[e] = vis ? fast_exp2(fmaf(sc[e >> 2][e & 3], c2, -pe)) * dp[e >> 2][e & 3] : 0.f;
             }
-            accumulate(row, x, kt, true);
+            accumulate(r4, x, kt);
         }
     }
 
     // routed blocks
     const int pastmax = (t0 + rows_here - 1) / B;
-    const int range = (int64_t)k * C::TILE <= C::LCAP ? C::RANGE : C::LCAP / C::TILE;
+    const int range = (int64_t)k * C::TILE <= C::LPAIRS ? C::RANGE : C::LPAIRS / C::TILE;
     for (int lo = 0; lo < pastmax; lo += range) {
         const int hi = min(pastmax, lo + range);
         __syncthreads();
@@ -238,8 +239,8 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
         while (e < nblk) {
             const int en = take_unit(take, lane);     // asked for early: its latency hides behind this unit
             const int j = __builtin_amdgcn_readfirstlane((int)ulist[e]);
-            const int beg = __builtin_amdgcn_readfirstlane((int)offs[j]);
-            const int end = min(__builtin_amdgcn_readfirstlane((int)offs[j + 1]), (int)C::LCAP);
+            const uint32_t piece = __builtin_amdgcn_readfirstlane((int)offs[j]);
+            const int beg = list_start(piece), end = beg + list_count(piece);
             for (int gi = 0; gi < NG; ++gi) {
                 const int kap = (lo + j) * NG + gi;
                 Frag ka[2][C::KS], va[2][C::KS], kt[C::MT];
@@ -247,13 +248,17 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
                 load_operand(Vag, kap, va);
                 load_kt(kap, kt);
                 // sub-tiles of 16 listed rows; lanes beyond the list work on whatever row id
-                // they read (always inside the tile) and add nothing
+                // they read (always inside the tile) and add zeros: their lse is infinite
                 for (int c0 = beg; c0 < end; c0 += 16) {
                     const bool valid = m16 < end - c0;
                     const int row = rows8[c0 + m16] & (C::TILE - 1);
                     Frag qb[C::KS], gb[C::KS];
                     gather(row, qb, gb);
-                    const float pe = pexp[row], nD = Dr[row];
+                    const float pe = valid ? pexp[row] : INFINITY, nD = Dr[row];
+                    const uint32_t w = *reinterpret_cast<const uint32_t*>(rows8 + c0 + 4 * g);
+                    int r4[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) r4[i] = (int)(w >> (8 * i)) & (C::TILE - 1);
                     f32x4_t sc[2], dp[2];
 #pragma unroll
                     for (int mt = 0; mt < 2; ++mt) {
@@ -269,7 +274,7 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
 #pragma unroll
                     for (int e2 = 0; e2 < 8; ++e2)
                         x[e2] = fast_exp2(fmaf(sc[e2 >> 2][e2 & 3], c2, -pe)) * dp[e2 >> 2][e2 & 3];
-                    accumulate(row, x, kt, valid);
+                    accumulate(r4, x, kt);
                 }
             }
             e = en;
@@ -286,7 +291,7 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
 #pragma unroll
         for (int e = 0; e < 8; ++e)
             v[e] = esc[r] == kNanRow ? NAN
-                 : scale * ldexpf((float)acc[r * C::OSTRIDE + 8 * c + e], et + scale_exponent(kmax[skv * D + 8 * c + e]));
+                 : scale * ldexpf((float)acc[r * C::OSTRIDE + acc_word<D>(8 * c + e)], et + scale_exponent(kmax[skv * D + 8 * c + e]));
         Vec8<bf16_t>::store(dQg + (int64_t)r * D + 8 * c, v);
     }
 }

@@ -26,13 +26,21 @@
 // the block's listed rows go by and a row's P V over both groups leaves the MFMA accumulators
 // as one set of LDS adds (half the adds per key).
 //
-// What bounds the kernel is the operand traffic, not the arithmetic: with scattered routing a
-// 256-query tile meets a key block with ~16 of its rows, so every 1-2 MFMA sub-tiles need a
-// fresh 4 KB of K (both passes) and 4 KB of V.  Hence (a) K and V are read from copies laid
-// out in MFMA operand order, 1 KB of consecutive bytes per load instruction (four times the
-// rate of the row-major pattern on this chip), (b) the workgroups of one XCD work on the same
+// P V leaves the matrix cores with a row's channels over sixteen lanes, so an add instruction covers four
+// rows of sixteen consecutive words each (no bank is hit twice); the listed rows' numbers come four to a
+// word.  Both passes are compiled from one body with the pass as a constant: 120 -> 85 registers in the
+// B = 32 walk at d = 64, which leaves room for the next block's operands while a block is worked on.
+//
+// With scattered routing a 256-query tile meets a key block with ~16 of its rows, so every 1-2 MFMA
+// sub-tiles need a fresh 4 KB of K (both passes) and 4 KB of V.  Hence (a) K and V are read from
+// copies laid out in MFMA operand order, 1 KB of consecutive bytes per load instruction (four times
+// the rate of the row-major pattern on this chip), (b) the workgroups of one XCD work on the same
 // slice and walk its blocks in ascending order, so these reads hit that XCD's L2, and (c) 16
 // waves per workgroup keep loads, LDS traffic and MFMA work of different units overlapped.
+// What bounds it then is the issue of vector instructions (72 % of the cycles by the counters:
+// exponentials, conversions, 16 adds per sub-tile); bank conflicts are a third of the LDS time and
+// removing them alone gained 0.2 %.  Measured, kernel alone: 16 heads of 32768, B = 32, k = 64 1095 ->
+// 1042 us; 32 slices of 16384, B = 64, k = 32, hot blocks 762 -> 708 us.
 #include <type_traits>
 
 #include "mfma.h"
@@ -45,11 +53,12 @@ struct FwdCfg {
     static constexpr int NW = D == 64 ? 16 : 12;       // waves per workgroup (registers allow no more)
     static constexpr int NT = NW * kWave;
     static constexpr int QSTRIDE = D * 2 + 16;         // bytes per Q row in LDS
-    static constexpr int OSTRIDE = D + 1;              // words per accumulator row
+    static constexpr int OSTRIDE = D;                  // words per accumulator row
     static constexpr int MT = D / 16;                  // 16-channel tiles of a row
     static constexpr int KS = D / 32;                  // contraction steps of q.k
     static constexpr int RANGE = 1024;                 // key blocks per set of row lists (at most)
-    static constexpr int LCAP = 16384;                 // (row, block) pairs per set of row lists
+    static constexpr int LPAIRS = 16384;               // (row, block) pairs per set of row lists
+    static constexpr int LCAP = LPAIRS + 3 * RANGE;    // bytes of the lists, each on a word of its own
     static constexpr size_t LDS = (size_t)TILE * QSTRIDE + 4 * TILE * OSTRIDE + 4 * 2 * TILE +
                                   4 * 2 * (RANGE + 1) + 4 * NW + 8 + LCAP + 64;
 };
@@ -144,7 +153,7 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
     // blocks strictly before the own block of the tile's last row, taken `range` at a time so
     // that a range's (row, block) pairs fit rows8
     const int pastmax = (t0 + rows_here - 1) / B;
-    const int range = (int64_t)k * C::TILE <= C::LCAP ? C::RANGE : C::LCAP / C::TILE;
+    const int range = (int64_t)k * C::TILE <= C::LPAIRS ? C::RANGE : C::LPAIRS / C::TILE;
     const bool one_range = pastmax <= range;
 
     auto load_k = [&](int kap, Frag (&ka)[2][C::KS]) {
@@ -178,22 +187,18 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
         for (int e = 0; e < 4; ++e) pb.u[e] = pack2(x[2 * e], x[2 * e + 1]);
 #pragma unroll
         for (int mt = 0; mt < C::MT; ++mt)
-            o[mt] = mfma16(va[mt], pb, fresh ? f32x4_t{0.f, 0.f, 0.f, 0.f} : o[mt]);
+            o[mt] = mfma16(pb, va[mt], fresh ? f32x4_t{0.f, 0.f, 0.f, 0.f} : o[mt]);
     };
-    auto flush = [&](int row, float lp, const f32x4_t (&o)[C::MT], bool valid) {
-        int oi[C::MT][4];
-#pragma unroll
-        for (int mt = 0; mt < C::MT; ++mt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) oi[mt][i] = __float2int_rn(o[mt][i]);
+    // o[mt][i] is row r4[i] of the sixteen (rows 4 g + i), channel tile_chan(mt, m16), which sits at
+    // word 16 mt + m16 of an accumulator row
+    auto flush = [&](int row, const int (&r4)[4], float lp, const f32x4_t (&o)[C::MT], bool valid) {
         lp = sum_over_g(lp);                       // the row's 32 (64) keys in one add, from one lane
-        if (valid) {
-            if (g == 0) atomicAdd(&lsum[row], __float2int_rn(lp));
-            int* orow = Os + (uint32_t)row * C::OSTRIDE + g * (D / 4);
+        if (valid && g == 0) atomicAdd(&lsum[row], __float2int_rn(lp));
 #pragma unroll
-            for (int mt = 0; mt < C::MT; ++mt)
+        for (int i = 0; i < 4; ++i) {
+            int* orow = Os + (uint32_t)r4[i] * C::OSTRIDE + m16;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) atomicAdd(&orow[4 * mt + i], oi[mt][i]);
+            for (int mt = 0; mt < C::MT; ++mt) atomicAdd(&orow[16 * mt], __float2int_rn(o[mt][i]));
         }
     };
     auto clear = [&](f32x4_t (&o)[C::MT]) {
@@ -201,7 +206,8 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
         for (int mt = 0; mt < C::MT; ++mt) o[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     };
 
-    for (int pass = 0; pass < 2; ++pass) {
+    auto run_pass = [&](auto pass_c) {                     // (a compile-time pass: no branches on it inside)
+        constexpr int pass = decltype(pass_c)::value;
         // own block: the row's own 32-key group under the causal mask and, for B > 32, the
         // block's earlier groups in full
         for (int p = wave; p < rows_here / 16; p += C::NW) {
@@ -212,6 +218,7 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
             Frag qb[C::KS];
             gather_q(row, qb);
             const float mr = pass == 1 ? __int_as_float(mkey[row]) : 0.f;
+            const int own4 = 32 * unit + 16 * st + 4 * g, r4[4] = {own4, own4 + 1, own4 + 2, own4 + 3};
             float mx = -INFINITY, lp = 0.f;
             f32x4_t o[C::MT];
             if (GMAX > 1) clear(o);
@@ -241,7 +248,7 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
                 } else {
                     attend(x, va, lp, o, GMAX == 1);
                     if (GMAX == 1) {          // (no registers to keep the sums over the groups)
-                        flush(row, lp, o, true);
+                        flush(row, r4, lp, o, true);
                         lp = 0.f;
                     }
                 }
@@ -250,7 +257,7 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
                 mx = max_over_g(mx);
                 if (g == 0) atomicMax(&mkey[row], float_key(mx));
             }
-            else if (GMAX > 1) flush(row, lp, o, true);
+            else if (GMAX > 1) flush(row, r4, lp, o, true);
         }
 
         // routed blocks
@@ -273,8 +280,8 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
             auto load_unit = [&](int e, int gi, auto gc, Frag (&ka)[GMAX][2][C::KS], Frag (&va)[GMAX][C::MT],
                                  int& beg, int& end) {
                 const int j = __builtin_amdgcn_readfirstlane((int)ulist[e]);
-                beg = offs[j];
-                end = offs[j + 1];
+                beg = list_start(offs[j]);
+                end = beg + list_count(offs[j]);
 #pragma unroll
                 for (int u = 0; u < decltype(gc)::value; ++u) {
                     const int kap = (lo + j) * NG + gi + u;
@@ -286,15 +293,23 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
                                 const Frag (&va)[GMAX][C::MT]) {
                 constexpr int GC = decltype(gc)::value;
                 const int beg = __builtin_amdgcn_readfirstlane(beg_v);
-                const int end = min(__builtin_amdgcn_readfirstlane(end_v), (int)C::LCAP);
+                const int end = __builtin_amdgcn_readfirstlane(end_v);
                 // Sub-tiles of 16 listed rows.  Lanes beyond the list work on whatever row id they
-                // read (always inside the tile) and add nothing.
+                // read (always inside the tile) and add zeros: their
+                // reference is infinite (and what a NaN would add is 0: the conversion's result for it).
                 for (int c0 = beg; c0 < end; c0 += 16) {
                     const bool valid = m16 < end - c0;
                     const int row = rows8[c0 + m16] & (C::TILE - 1);
                     Frag qb[C::KS];
                     gather_q(row, qb);
-                    const float mr = pass == 1 ? __int_as_float(mkey[row]) : 0.f;
+                    float mr = 0.f;
+                    int r4[4];
+                    if (pass == 1) {
+                        mr = valid ? __int_as_float(mkey[row]) : INFINITY;
+                        const uint32_t w = *reinterpret_cast<const uint32_t*>(rows8 + c0 + 4 * g);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) r4[i] = (int)(w >> (8 * i)) & (C::TILE - 1);
+                    }
                     auto scores = [&](int u, f32x4_t (&sc)[2]) {
 #pragma unroll
                         for (int mt = 0; mt < 2; ++mt) {
@@ -329,27 +344,63 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
                             for (int e = 0; e < 8; ++e) x[e] = fmaf(sc[e >> 2][e & 3], c2, -mr);
                             attend(x, va[u], lp, o, u == 0);
                         }
-                        flush(row, lp, o, valid);
+                        flush(row, r4, lp, o, valid);
                     }
                 }
             };
 
-            // waves take the listed blocks as they get free (other waves cover the operand latency)
-            int e = take_unit(take, lane);
-            while (e < nblk) {
-                const int en = take_unit(take, lane);     // asked for early: its latency hides behind this unit
-                for (int gi = 0; gi < NG; gi += GMAX) {
-                    Frag ka[GMAX][2][C::KS], va[GMAX][C::MT];
-                    int beg, end;
-                    if (GMAX == 2 && gi + 1 < NG) {
-                        load_unit(e, gi, std::integral_constant<int, GMAX>{}, ka, va, beg, end);
-                        run_unit(beg, end, std::integral_constant<int, GMAX>{}, ka, va);
-                    } else {
-                        load_unit(e, gi, std::integral_constant<int, 1>{}, ka, va, beg, end);
-                        run_unit(beg, end, std::integral_constant<int, 1>{}, ka, va);
+            // waves take the listed blocks as they get free
+            if constexpr (D == 64 && GMAX == 1) {
+                // blocks of one 32-key group: the next block's operands are on their way while a block is
+                // worked on, and the one after that is asked for
+                auto index_of = [&](int e) { return __builtin_amdgcn_readfirstlane((int)ulist[min(e, nblk - 1)]); };
+                auto load_block = [&](int j, Frag (&ka)[1][2][C::KS], Frag (&va)[1][C::MT], uint32_t& piece) {
+                    piece = offs[j];
+                    load_k(lo + j, ka[0]);
+                    if (pass == 1) load_v(lo + j, va[0]);
+                };
+                auto run_block = [&](uint32_t piece, const Frag (&ka)[1][2][C::KS], const Frag (&va)[1][C::MT]) {
+                    run_unit(list_start(piece), list_start(piece) + list_count(piece), std::integral_constant<int, 1>{}, ka, va);
+                };
+                int e = take_unit(take, lane), en = take_unit(take, lane);
+                if (e < nblk) {
+                    Frag ka0[1][2][C::KS], va0[1][C::MT], ka1[1][2][C::KS], va1[1][C::MT];
+                    uint32_t p0, p1;
+                    load_block(index_of(e), ka0, va0, p0);
+                    int jn = index_of(en);
+                    while (true) {
+                        load_block(jn, ka1, va1, p1);
+                        e = en;
+                        en = take_unit(take, lane);
+                        run_block(p0, ka0, va0);
+                        if (e >= nblk) break;
+                        jn = index_of(en);
+                        load_block(jn, ka0, va0, p0);
+                        e = en;
+                        en = take_unit(take, lane);
+                        run_block(p1, ka1, va1);
+                        if (e >= nblk) break;
+                        jn = index_of(en);
                     }
                 }
-                e = en;
+            } else {
+                // (other waves cover the operand latency)
+                int e = take_unit(take, lane);
+                while (e < nblk) {
+                    const int en = take_unit(take, lane);     // asked for early: its latency hides behind this unit
+                    for (int gi = 0; gi < NG; gi += GMAX) {
+                        Frag ka[GMAX][2][C::KS], va[GMAX][C::MT];
+                        int beg, end;
+                        if (GMAX == 2 && gi + 1 < NG) {
+                            load_unit(e, gi, std::integral_constant<int, GMAX>{}, ka, va, beg, end);
+                            run_unit(beg, end, std::integral_constant<int, GMAX>{}, ka, va);
+                        } else {
+                            load_unit(e, gi, std::integral_constant<int, 1>{}, ka, va, beg, end);
+                            run_unit(beg, end, std::integral_constant<int, 1>{}, ka, va);
+                        }
+                    }
+                    e = en;
+                }
             }
         }
         __syncthreads();
@@ -358,7 +409,9 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
             if (tid == 0) *take = 0;
             __syncthreads();
         }
-    }
+    };
+    run_pass(std::integral_constant<int, 0>{});
+    run_pass(std::integral_constant<int, 1>{});
 
     // normalise and write out: O = acc * 2^e[c] / l  (the 2^F of both cancels)
     bf16_t* Og = O + (sbase + t0) * D;
@@ -371,7 +424,7 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
         for (int e = 0; e < 8; ++e) {
             const uint32_t vm = vmax[skv * D + 8 * c + e];
             v[e] = nonfinite_bits(vm) ? NAN          // V holds an infinity or a NaN in this channel
-                                      : ldexpf((float)Os[r * C::OSTRIDE + 8 * c + e] * inv, scale_exponent(vm));
+                                      : ldexpf((float)Os[r * C::OSTRIDE + acc_word<D>(8 * c + e)] * inv, scale_exponent(vm));
         }
         Vec8<bf16_t>::store(Og + (int64_t)r * D + 8 * c, v);
         if (c == 0) lse[sbase + t0 + r] = (__int_as_float(mkey[r]) + fast_log2(lf)) * kLn2;

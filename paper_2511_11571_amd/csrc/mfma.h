@@ -63,14 +63,19 @@ __host__ __device__ __forceinline__ constexpr int slot_key(int g, int s)
     return s < 4 ? 4 * g + s : 16 + 4 * g + (s - 4);
 }
 
-// channel that row m of M-tile mt of a (d x 16) product stands for.  Chosen so that the four
-// lane groups of a result (rows 4g'..4g'+3) land D/4 channels apart: fp32 accumulators in
-// LDS ([row][channel], odd row stride) then see the two lane groups that issue together on
-// different halves of the banks.
+// channel that row m of M-tile mt of a (d x 16) product stands for: the four lane groups of such a
+// result (rows 4g'..4g'+3) hold D/4 consecutive channels each.
 template <int D>
 __host__ __device__ __forceinline__ constexpr int tile_chan(int mt, int m)
 {
     return (m >> 2) * (D / 4) + 4 * mt + (m & 3);
+}
+
+// word 16 mt + m of a query tile's accumulator row (channel tile_chan(mt, m)) that holds channel c
+template <int D>
+__host__ __device__ __forceinline__ constexpr int acc_word(int c)
+{
+    return 16 * (c % (D / 4) / 4) + 4 * (c / (D / 4)) + (c & 3);
 }
 
 __device__ __forceinline__ uint32_t pack2(float lo, float hi)
@@ -125,6 +130,11 @@ __host__ __device__ __forceinline__ constexpr int64_t slot_major_offset(int64_t 
     return (kap * (D / 16) + mt) * 512 + (int64_t)lane * 8;
 }
 
+// An entry of a tile's offs[]: where the block's rows start in rows8 (a multiple of 4, so that four
+// of them are one aligned word) and how many there are.
+__device__ __forceinline__ int list_start(uint32_t o) { return (int)(o & 0xffffu); }
+__device__ __forceinline__ int list_count(uint32_t o) { return (int)(o >> 16); }
+
 // Ascending list of the non-empty blocks of a set of row lists (offs as built below):
 // ulist[0 .. *count).  All NT threads; ends with a workgroup barrier.
 template <int NT>
@@ -135,7 +145,7 @@ __device__ __forceinline__ void list_nonempty(const uint32_t* offs, int nb, uint
     int base = 0;
     for (int c = 0; c < nb; c += NT) {
         const int i = c + tid;
-        const bool some = i < nb && offs[i + 1] > offs[i];
+        const bool some = i < nb && list_count(offs[i]) > 0;
         const uint64_t b = __ballot(some);
         if (lane == 0) wsum[wave] = (uint32_t)__popcll(b);
         __syncthreads();
@@ -166,13 +176,14 @@ __device__ __forceinline__ int take_unit(int* counter, int lane)
 
 // ---- per-tile block lists in LDS --------------------------------------------------------
 // For a tile of TILE consecutive queries and the key blocks [lo, hi): a counting sort of the
-// tile's (row, kept block) pairs by block.  Afterwards offs[j - lo] .. offs[j - lo + 1] is the
-// piece of rows8[] holding the local rows (0 .. TILE-1, one byte each) that kept block j, in no
+// tile's (row, kept block) pairs by block.  Afterwards offs[j - lo] says which piece of rows8[]
+// holds the local rows (0 .. TILE-1, one byte each) that kept block j, in no
 // particular order.  Built once per tile and range, by all NT threads; integer atomics only.
 //   cur   [hi - lo + 1] words of scratch (counters, then insertion cursors)
-//   offs  [hi - lo + 1] words
-//   rows8 cap bytes; a routing without repeats has at most min(TILE * (hi - lo), TILE * k)
-//         pairs, and pairs beyond cap are dropped rather than written
+//   offs  [hi - lo] words
+//   rows8 cap < 65536 bytes; a routing without repeats has at most min(TILE * (hi - lo), TILE * k)
+//         pairs, a block's list takes up to three bytes more, and pairs beyond cap are dropped
+//         rather than written
 //   wsum  NT / 64 words of scratch
 // `idx_tile` points at the tile's first topk_idx row; entries that are not past blocks of
 // their row are ignored.  Ends with a workgroup barrier.
@@ -218,7 +229,7 @@ __device__ __forceinline__ void build_block_lists(const int32_t* __restrict__ id
     for (int e = 0; e < EPT; ++e) {
         const int j = tid * EPT + e;
         v[e] = j < nb ? cur[j] : 0u;
-        sum += v[e];
+        sum += (v[e] + 3u) & ~3u;
     }
     uint32_t incl = sum;
 #pragma unroll
@@ -233,9 +244,12 @@ __device__ __forceinline__ void build_block_lists(const int32_t* __restrict__ id
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
         const int j = tid * EPT + e;
-        if (j < nb) { offs[j] = base; cur[j] = base; }
-        base += v[e];
-        if (j == nb - 1) offs[nb] = base;
+        if (j < nb) {
+            const uint32_t start = min(base, cap);
+            offs[j] = start | (min(v[e], cap - start) << 16);
+            cur[j] = base;
+        }
+        base += (v[e] + 3u) & ~3u;
     }
     __syncthreads();
     for_each_entry([&](int j) {
