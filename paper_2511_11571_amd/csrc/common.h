@@ -40,12 +40,19 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 template <typename T> struct Vec8;
 
 template <> struct Vec8<float> {
+    struct Raw { float4 a, b; };
+    static __device__ __forceinline__ Raw raw(const float* p)
+    {
+        return {*reinterpret_cast<const float4*>(p), *reinterpret_cast<const float4*>(p + 4)};
+    }
+    static __device__ __forceinline__ void unpack(const Raw& r, float (&v)[8])
+    {
+        v[0] = r.a.x; v[1] = r.a.y; v[2] = r.a.z; v[3] = r.a.w;
+        v[4] = r.b.x; v[5] = r.b.y; v[6] = r.b.z; v[7] = r.b.w;
+    }
     static __device__ __forceinline__ void load(const float* p, float (&v)[8])
     {
-        float4 a = *reinterpret_cast<const float4*>(p);
-        float4 b = *reinterpret_cast<const float4*>(p + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+        unpack(raw(p), v);
     }
     static __device__ __forceinline__ void store(float* p, const float (&v)[8])
     {
@@ -57,9 +64,11 @@ template <> struct Vec8<float> {
 };
 
 template <> struct Vec8<bf16_t> {
-    static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8])
+    using Raw = uint4;
+    static __device__ __forceinline__ Raw raw(const bf16_t* p) { return *reinterpret_cast<const uint4*>(p); }
+    static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8]) { unpack(raw(p), v); }
+    static __device__ __forceinline__ void unpack(const Raw& a, float (&v)[8])
     {
-        uint4 a = *reinterpret_cast<const uint4*>(p);
         v[0] = __uint_as_float(a.x << 16); v[1] = __uint_as_float(a.x & 0xffff0000u);
         v[2] = __uint_as_float(a.y << 16); v[3] = __uint_as_float(a.y & 0xffff0000u);
         v[4] = __uint_as_float(a.z << 16); v[5] = __uint_as_float(a.z & 0xffff0000u);
