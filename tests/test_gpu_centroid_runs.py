@@ -47,3 +47,26 @@ def test_centroids_of_runs_with_remainders(batch, heads, n, d, B, W, dtype):
     blocks = got.double().view(batch, heads, n, B, d)
     # B - 1 additions of fp32 and a division
     assert ((cent - blocks.mean(3)).abs() <= (B + 1) * 2.0 ** -24 * blocks.abs().mean(3)).all()
+
+
+# (slices, n, d, B, W): calls that take another number of rows together than their slices on their own (2^19 lanes and
+# more; with a filter 2^16), and their neighbours: runs of 16, 32, 8 and 8 rows of d = 64, 14 in one, 16 and 32 of d = 128
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("slices,n,d,B,W", [(8, 1024, 64, 128, 0), (8, 1024, 64, 256, 0), (8, 1024, 64, 64, 0), (8, 2048, 64, 32, 0),
+                                            (8, 8192, 64, 14, 0), (16, 512, 128, 64, 0), (16, 512, 128, 128, 3), (8, 128, 128, 128, 2),
+                                            (8, 128, 128, 124, 4), (8, 1024, 64, 32, 1)])
+def test_centroids_of_a_call_and_of_its_slices(slices, n, d, B, W, dtype):
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    code = binding.BF16 if dtype == "bf16" else binding.F32
+    g = torch.Generator(device="cuda").manual_seed(n + B)
+    K = torch.randn((1, slices, n * B, d), generator=g, device="cuda").to(t)
+    w = torch.randn((slices, d, W), generator=g, device="cuda") if W else None
+    whole = moba.centroids(moba.Shape(1, slices, n * B, d, B, 1, W, code), K, w, torch.full_like(K, 9.0))
+    part = moba.Shape(1, 1, n * B, d, B, 1, W, code)
+    # a run's rows are filtered and added one after the other, however many of them are requested together: the same bits
+    for s in range(slices):
+        ws = w[s:s + 1].contiguous() if W else None
+        Keff, cent = moba.centroids(part, K[:, s:s + 1].contiguous(), ws, torch.full_like(K[:, :1], 9.0))
+        assert torch.equal(whole[0][:, s:s + 1], Keff) and torch.equal(whole[1][:, s:s + 1], cent)
+    if W == 0:
+        assert torch.equal(whole[0], K)
