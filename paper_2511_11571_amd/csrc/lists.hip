@@ -415,9 +415,22 @@ static hipError_t small_launch(const Dims& s, const SmallLists& p, const int32_t
 }
 
 // Most counts of a slice (chunks x blocks) that every workgroup of the fill pass adds up for itself, in place of
-// two launches of 4.5 to 6 us.  us, scans + fill -> fill: 2048 counts (16 slices, N = 8192, 64 blocks) 17.0 -> 11.0;
-// 4200 (18 slices, N = 10080, 105 blocks) 23.4 -> 19.6; 16384 (16 slices, N = 16384, 256 blocks) 34.3 -> 44.1.
+// two launches, and most such additions of all workgroups together: a workgroup's own are a few rounds of loads and LDS
+// adds before its work, all workgroups' are time of the chip that two scans do not take.
+// us of the whole builder, scans -> itself, by counts / workgroups:
+//   2048 / 512 (16 slices, N = 8192, 64 blocks) 17.1 -> 13.6;  4096 / 64 16.6 -> 13.9;  4096 / 512 17.2 -> 14.5;
+//   6144 / 768 18.7 -> 17.4;  6084 / 156 16.7 -> 16.1;  8192 / 64 17.1 -> 18.3;  9216 / 96 17.5 -> 19.6
+//   (the first line: between 6144 and 8192);
+//   4608 / 768 (3.5 M additions) 18.6 -> 16.6;  2048 / 3072 (6.3 M) 38.7 -> 38.8;  4608 / 1536 (7.1 M) 50.7 -> 51.5;
+//   4096 / 2048 (8.4 M) 33.7 -> 33.0;  4096 / 3072 (12.6 M) 67.8 -> 68.1;  6084 / 3744 (22.8 M) 47.5 -> 54.5;
+//   4096 / 6144 (25 M) 43.7 -> 52.6  (the second: at 8 M)
 constexpr int kSelfCounts = 6144;
+constexpr int64_t kSelfAdditions = (int64_t)8 << 20;
+static bool fill_adds_up(const Dims& s)
+{
+    const int64_t counts = (int64_t)s.nchunk * s.n;
+    return s.R > 0 && counts <= kSelfCounts && counts * s.nchunk * s.bh <= kSelfAdditions;
+}
 
 template <int RANGE>
 static hipError_t build_lists_launch(const Dims& s, const int32_t* idx, int32_t* off, int32_t* ql,
@@ -438,7 +451,7 @@ static hipError_t build_lists_launch(const Dims& s, const int32_t* idx, int32_t*
                                s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);                                              \
     } while (0)
     if constexpr (RANGE == kRangeLong) {
-        if (s.R > 0 && s.n <= RANGE && (int64_t)s.nchunk * s.n <= kSelfCounts) {
+        if (s.n <= RANGE && fill_adds_up(s)) {
             MOBA_FILL(true);
             return hipGetLastError();
         }

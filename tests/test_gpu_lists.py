@@ -17,6 +17,8 @@ SHAPES = [
     # the chunked builder at the edges of its ranges of blocks, the last chunk of 256 queries whole and not
     # (and of the counts its fill pass adds up itself: 6084 and 6280, blocks that straddle threads' turns)
     (1, 2, 64 * 156, 64, 64, 5), (1, 2, 64 * 157, 64, 64, 5), (2, 3, 224 * 37, 64, 224, 6),
+    # the most additions of all its workgroups together, 192 chunks x 32 blocks from 1344 and 1536 of them
+    (1, 7, 1536 * 32, 64, 1536, 2), (1, 8, 1536 * 32, 64, 1536, 2),
     (1, 1, 64 * 512, 64, 64, 3), (1, 1, 64 * 513, 64, 64, 2), (1, 1, 32 * 1024, 64, 32, 5), (1, 1, 32 * 1025, 64, 32, 2),
 ]
 
