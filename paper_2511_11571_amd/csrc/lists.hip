@@ -10,8 +10,8 @@
 //   3. fill: the bit matrix is rebuilt and its rows are written out in ascending order at
 //      blk_off[j] + chunk start, eight lanes per row (or entry by entry, see below).
 // The bit matrix lives in LDS only and covers 512 or 1024 key blocks at a time.
-// Slices with few counts take no scans: the fill pass adds the counts up itself (starts_from_counts()).  Short slices
-// take one launch instead (lists_small_kernel).
+// Lists with places (see below) of slices with few counts take no scans: the fill pass adds the counts up itself
+// (starts_from_counts(), fill_adds_up()).  Short slices take one launch instead (lists_small_kernel).
 //
 // A list entry holds the query in its low 24 bits (sequences are at most 2^24 long).  Where the
 // key-block-major attention kernels will run (lists_with_places() of the shape and its flags) the
@@ -441,25 +441,24 @@ static hipError_t build_lists_launch(const Dims& s, const int32_t* idx, int32_t*
     hipLaunchKernelGGL((lists_chunk_kernel<false, false, RANGE>), grid, block, 0, st, idx, cnt2, off, ql, s.N, s.B,
                        s.n, s.k, s.nchunk, s.R, s.bh);
     static_assert(kKeyMajorMaxTopk <= 127, "the place of a block in the high byte of an entry");
-#define MOBA_FILL(SELF)                                                                                               \
-    do {                                                                                                              \
-        if (lists_with_places(s))                                                                                     \
-            hipLaunchKernelGGL((lists_chunk_kernel<true, true, RANGE, SELF>), grid, block, 0, st, idx, cnt2, off, ql, \
-                               s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);                                              \
-        else                                                                                                          \
-            hipLaunchKernelGGL((lists_chunk_kernel<true, false, RANGE, SELF>), grid, block, 0, st, idx, cnt2, off, ql, \
-                               s.N, s.B, s.n, s.k, s.nchunk, s.R, s.bh);                                              \
-    } while (0)
+    const bool places = lists_with_places(s);
+#define MOBA_FILL(PLACES, SELF)                                                                                          \
+    hipLaunchKernelGGL((lists_chunk_kernel<true, PLACES, RANGE, SELF>), grid, block, 0, st, idx, cnt2, off, ql, s.N, s.B, \
+                       s.n, s.k, s.nchunk, s.R, s.bh)
+    // (without places this range serves slices of more than kRangeMax blocks, which have too many counts)
     if constexpr (RANGE == kRangeLong) {
-        if (s.n <= RANGE && fill_adds_up(s)) {
-            MOBA_FILL(true);
+        if (places && s.n <= RANGE && fill_adds_up(s)) {
+            MOBA_FILL(true, true);
             return hipGetLastError();
         }
     }
     hipLaunchKernelGGL(lists_scan_kernel, dim3((s.n + 31) / 32, s.bh), block, 0, st, cnt2, off, s.n,
                        s.nchunk);
     hipLaunchKernelGGL(lists_offsets_kernel, dim3(s.bh), block, 0, st, off, s.n);
-    if (s.R > 0) MOBA_FILL(false);
+    if (s.R > 0) {
+        if (places) MOBA_FILL(true, false);
+        else MOBA_FILL(false, false);
+    }
 #undef MOBA_FILL
     return hipGetLastError();
 }
