@@ -39,3 +39,24 @@ def test_key_major_against_the_plain_kernels(batch, heads, kv, N, d, B, k):
         x, y = x.float(), y.float()
         assert bool(torch.isfinite(x).all())
         assert float((x - y).norm() / y.norm()) < 2 ** -7
+
+
+def test_forward_partials_are_divided_with_one_rounding():
+    """Scores of zero: the probabilities are 1 and a query's only partial is sum / count, with whole numbers above and
+    below.  The reciprocal of the count is a correctly rounded one, which shows where the quotient lies half-way
+    between two bf16 values or next to it."""
+    import numpy as np
+    import paper_2511_11571_amd as moba
+    b = moba.binding
+    for d, B in ((64, 128), (64, 96), (128, 64)):
+        heads = 2048
+        sh = moba.Shape(1, heads, B, d, B, 0, 0, b.BF16, 0.0, b.FLAG_KEY_MAJOR, 0)
+        g = torch.Generator(device="cuda").manual_seed(B)
+        Q = torch.zeros((1, heads, B, d), dtype=torch.bfloat16, device="cuda")
+        V = torch.randint(0, 256, Q.shape, generator=g, device="cuda").to(torch.bfloat16)
+        idx = torch.empty((1, heads, B, 0), dtype=torch.int32, device="cuda")
+        O, _ = moba.forward(sh, Q, Q, V, idx, moba.build_lists(sh, idx))
+        inv = np.float32(1) / np.arange(1, B + 1, dtype=np.float32)
+        total = V.cpu().double().cumsum(2).numpy().astype(np.float32)             # exact
+        want = torch.from_numpy(total * inv[:, None]).to(torch.bfloat16)
+        assert torch.equal(O.cpu(), want)
