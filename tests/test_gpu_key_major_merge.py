@@ -60,3 +60,72 @@ def test_forward_partials_are_divided_with_one_rounding():
         total = V.cpu().double().cumsum(2).numpy().astype(np.float32)             # exact
         want = torch.from_numpy(total * inv[:, None]).to(torch.bfloat16)
         assert torch.equal(O.cpu(), want)
+
+
+# Limits of the relative errors (2-norms) against 64 bits.  Roundings to bf16 of P, of a partial and of the result (O); of dS, of
+# a partial and of the result (dQ); of dS (dK) or P (dV) and the result; D from rounded O.  With normally distributed inputs they
+# come to 2.6e-3, 2.9e-3, 2.5e-3 and 2.4e-3; with one bit less in any single one of them, at least one of the four
+# comes to 3.6e-3, 3.9e-3, 3.7e-3 and 3.5e-3 or more (the same roundings carried out in 64 bits on the CPU).
+LIMITS = {"O": 3.0e-3, "dQ": 3.3e-3, "dK": 2.9e-3, "dV": 2.8e-3}
+
+
+@pytest.mark.parametrize("heads,kv,N,d,B,k", [
+    (2, 0, 2048, 64, 128, 8), (1, 0, 2016, 64, 96, 10), (2, 1, 2048, 128, 64, 16), (1, 0, 2048, 64, 256, 4),
+    (1, 0, 2048, 128, 256, 3), (1, 0, 2048, 64, 32, 12)])
+def test_key_major_errors_against_64_bits(heads, kv, N, d, B, k):
+    import paper_2511_11571_amd as moba
+    b = moba.binding
+    g = torch.Generator(device="cuda").manual_seed(N + d + k)
+    hkv = kv or heads
+    Q, K, V, dO = (torch.randn((1, h, N, d), generator=g, device="cuda").to(torch.bfloat16) for h in (heads, hkv, hkv, heads))
+    sh = moba.Shape(1, heads, N, d, B, k, 0, b.BF16, 0.0, b.FLAG_KEY_MAJOR, kv)
+    _, cent = moba.centroids(sh, K)
+    idx, lists = moba.topk(sh, Q, cent)
+    O, lse = moba.forward(sh, Q, K, V, idx, lists)
+    dQ, dK, dV = moba.backward(sh, Q, K, V, O, lse, dO, idx, lists)
+    t = torch.arange(N, device="cuda") // B
+    causal = torch.ones((N, N), dtype=torch.bool, device="cuda").tril()
+    want = {"O": [], "lse": [], "dQ": [], "dK": [], "dV": []}
+    for h in range(heads):
+        q, kk, v, do = Q[0, h].double(), K[0, h * hkv // heads].double(), V[0, h * hkv // heads].double(), dO[0, h].double()
+        kept = (idx[0, h, :, :, None] == torch.arange(N // B, device="cuda")).any(1)
+        seen = kept.repeat_interleave(B, 1) | (causal & (t[:, None] == t[None]))
+        s = (q @ kk.T / d ** 0.5).masked_fill(~seen, -float("inf"))
+        L = torch.logsumexp(s, 1)
+        p = (s - L[:, None]).exp()
+        o = p @ v
+        ds = p * (do @ v.T - (do * o).sum(1)[:, None]) / d ** 0.5
+        for name, x in (("O", o), ("lse", L), ("dQ", ds @ kk), ("dK", ds.T @ q), ("dV", p.T @ do)):
+            want[name].append(x)
+    want = {name: torch.stack(x) for name, x in want.items()}
+    if kv:
+        want["dK"], want["dV"] = (want[x].view(hkv, heads // hkv, N, d).sum(1) for x in ("dK", "dV"))
+    for name, x in (("O", O), ("dQ", dQ), ("dK", dK), ("dV", dV)):
+        assert float((x[0].double() - want[name]).norm() / want[name].norm()) < LIMITS[name], name
+    # scores of about 4 units of log2 or less in fp32, sums of at most 2^11 terms in a few stages, one logarithm
+    assert float((lse[0].double() - want["lse"]).pow(2).mean().sqrt()) < 2.0 ** -20
+
+
+# (heads, N, d, B, k): slices that an XCD takes together, forward / backward, of those it has: 4 / 2 of 4, 3 / 3 of 3, 2 / 1 of
+# 4, 3 / 1 of 3
+@pytest.mark.parametrize("heads,N,d,B,k", [(32, 4096, 128, 128, 2), (24, 4096, 64, 128, 3), (32, 8192, 128, 128, 2), (24, 5376, 128, 64, 2)])
+def test_slices_worked_through_together_give_what_each_gives_alone(heads, N, d, B, k):
+    import paper_2511_11571_amd as moba
+    b = moba.binding
+    g = torch.Generator(device="cuda").manual_seed(heads + N)
+    Q, K, V, dO = (torch.randn((1, heads, N, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))
+
+    def step(Q, K, V, dO):
+        sh = moba.Shape(1, Q.shape[1], N, d, B, k, 0, b.BF16, 0.0, b.FLAG_KEY_MAJOR, 0)
+        _, cent = moba.centroids(sh, K)
+        idx, lists = moba.topk(sh, Q, cent)
+        # (partials that nothing fills are NaN)
+        ws = [torch.full((x,), 0xff, dtype=torch.uint8, device="cuda") for x in moba.workspace_bytes(sh)[1:]]
+        O, lse = moba.forward(sh, Q, K, V, idx, lists, ws=ws[0])
+        return (O, lse) + tuple(moba.backward(sh, Q, K, V, O, lse, dO, idx, lists, ws=ws[1]))
+
+    whole = step(Q, K, V, dO)
+    for h in range(0, heads, 8):                           # one slice per XCD
+        part = step(*(x[:, h:h + 8].contiguous() for x in (Q, K, V, dO)))
+        for x, y in zip(whole, part):
+            assert bool(torch.isfinite(y.float()).all()) and torch.equal(x[:, h:h + 8], y)
