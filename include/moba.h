@@ -98,8 +98,8 @@ typedef struct moba_shape {
 /* Host-only helpers.  R and the byte counts are written to host memory.
  * Forward and backward workspaces hold a partial result per (query, kept or own block) pair and part of
  * the block where the kernels file such partials: batch * heads * seqlen * (topk + 1) * parts of them.
- *   bf16, key-block-major kernels: 2 d + 8 bytes each forward, 2 d backward; parts of 128 keys (d = 64) or
- *       64 (d = 128; backward: 128 where B is a multiple of that, else 64).
+ *   bf16, key-block-major kernels: 2 d + 8 bytes each forward (and the size of V once), 2 d backward; parts of 128
+ *       keys (d = 64) or 64 (d = 128; backward: 128 where B is a multiple of that, else 64).
  *   fp32 tensors, and bf16 with B not a multiple of 32 (B >= 8, topk <= 64): 4 d + 8 bytes each forward, 4 d
  *       backward; parts of at most 64 keys (backward at d = 128: 32).  fp32, 16 heads, N = 32768, d = 64:
  *       1.2 GB each with B = 64 and topk = 8, 9.0 and 8.7 GB with B = 32 and topk = 64.  Where the backward's

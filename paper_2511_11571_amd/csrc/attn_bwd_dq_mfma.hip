@@ -14,9 +14,9 @@
 // Structure, operand copies and workgroup schedule are the forward kernel's (see there): row
 // lists per key block in LDS, K and V read in MFMA operand order, XCD-aware schedule.  The Q
 // and dO tiles sit in LDS unpadded, with the 16-byte chunks of row r permuted by r & 7 so
-// that a gather of arbitrary rows still spreads over the banks.  As there, the issue of vector
-// instructions bounds it: 957 -> 945 us (16 heads of 32768, B = 32, k = 64) with adds that hit no
-// bank twice.
+// that a gather of arbitrary rows still spreads over the banks.  As there, the LDS pipe bounds it
+// (busy all the time by the counters, 36 % of that bank conflicts; vector issue 58 %, matrix pipe 25 %):
+// 957 -> 945 us (16 heads of 32768, B = 32, k = 64) with adds of sixteen consecutive words of a row each.
 #include "mfma.h"
 
 namespace moba {

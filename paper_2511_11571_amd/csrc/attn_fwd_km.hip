@@ -256,7 +256,7 @@ void fwd_km_kernel(
         // the partials is written by one instruction.
         // (normalised before it is rounded: where one partial outweighs the rest, the merge then gives its
         // rounded values back, and the result is rounded once, not twice; a correctly rounded reciprocal instead of
-        // v_rcp_f32 takes nothing: 16 slices of N = 8192, B = 128 93.2 -> 93.7 us, of 131072, d = 128, B = 64, k = 32 9838 both)
+        // v_rcp_f32: 16 slices of N = 8192, B = 128 93.2 -> 93.7 us, of 131072, d = 128, B = 64, k = 32 9838 both)
         const float inv = 1.f / l;
 #pragma unroll
         for (int ct = 0; ct < C::CT; ++ct)
@@ -366,8 +366,8 @@ __global__ __launch_bounds__(256) void fwd_km_merge_kernel(
 }
 
 // ---- workspace: [partial O: bh*N*(k+1)*parts*D bf16][partial (m, l): bh*N*(k+1)*parts*2 fp32],
-// each 256-byte aligned.  (And the size of V, which nothing uses: what callers are told to bring is what
-// it has always been.)
+// each 256-byte aligned.  (And the size of V, which nothing uses any more: what moba_workspace_bytes reports for a
+// shape, and that sharing key/value heads lowers it, stays as it was.)
 
 size_t forward_km_ws_bytes(const Dims& s)
 {

@@ -27,9 +27,10 @@
 // as one set of LDS adds (half the adds per key).
 //
 // P V leaves the matrix cores with a row's channels over sixteen lanes, so an add instruction covers four
-// rows of sixteen consecutive words each (no bank is hit twice); the listed rows' numbers come four to a
-// word.  Both passes are compiled from one body with the pass as a constant: 120 -> 85 registers in the
-// B = 32 walk at d = 64, which leaves room for the next block's operands while a block is worked on.
+// rows of sixteen consecutive words each: a row's words lie on sixteen banks whichever row it is, and the four rows'
+// on the same sixteen (rows of D words); the listed rows' numbers come four to a word.  Both passes are compiled
+// from one body with the pass as a constant, which leaves room for the next block's operands while a block is worked
+// on (B = 32, d = 64: 118 registers with them).
 //
 // With scattered routing a 256-query tile meets a key block with ~16 of its rows, so every 1-2 MFMA
 // sub-tiles need a fresh 4 KB of K (both passes) and 4 KB of V.  Hence (a) K and V are read from
@@ -37,10 +38,11 @@
 // the rate of the row-major pattern on this chip), (b) the workgroups of one XCD work on the same
 // slice and walk its blocks in ascending order, so these reads hit that XCD's L2, and (c) 16
 // waves per workgroup keep loads, LDS traffic and MFMA work of different units overlapped.
-// What bounds it then is the issue of vector instructions (72 % of the cycles by the counters:
-// exponentials, conversions, 16 adds per sub-tile); bank conflicts are a third of the LDS time and
-// removing them alone gained 0.2 %.  Measured, kernel alone: 16 heads of 32768, B = 32, k = 64 1095 ->
-// 1042 us; 32 slices of 16384, B = 64, k = 32, hot blocks 762 -> 708 us.
+// What bounds it then is the LDS pipe: busy all the time by the counters at 16 heads of 32768, B = 32, k = 64 (16 adds
+// per sub-tile, gathered rows, lists), a third of that in bank conflicts, with the issue of vector instructions at
+// 74 % and the matrix pipe at 23 %.  The product's orientation by itself took conflicts from 219 to 187 M clocks and
+// gained 0.2 %.  Measured, kernel alone, all of the above: that shape 1095 -> 1042 us; 32 slices of 16384, B = 64,
+// k = 32, hot blocks 762 -> 708 us.
 #include <type_traits>
 
 #include "mfma.h"

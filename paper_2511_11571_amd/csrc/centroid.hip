@@ -11,6 +11,7 @@
 // of them (divisions of 64 bits took 500 instructions).  Four rows at a time, 64-bit block numbers -> now, K out of the
 // caches: 16 slices of N = 8192, d = 64, B = 128: 15.4 -> 5.4 us; 32 of 16384, B = 64: 16.5 -> 13.2;
 // 4 of 16384, d = 128, W = 4: 20.7 -> 15.1; 16 of 131072, d = 128, W = 4: 240 -> 217; 32 of 524288, d = 64: 370 -> 371.
+// (Right after a backward whose dQ merge streams its partials the call takes longer: 406 us at the last of these, see MergeRow.)
 #include "common.h"
 
 namespace moba {

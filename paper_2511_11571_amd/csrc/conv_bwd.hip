@@ -16,8 +16,9 @@ namespace moba {
 constexpr int kConvRows = 128;     // rows per chunk at most
 
 // Rows per chunk: fewer where chunks of 128 rows would leave compute units without a workgroup -- a chunk is a
-// serial walk, and its W - 1 extra rows cost less than idle units.  4 slices of N = 16384, d = 128, W = 4: 131 us with
-// 128 rows (32 workgroups), 24 with 16 (256 workgroups).
+// serial walk, and its W - 1 extra rows cost less than idle units.  Whole call, with the sum of dw, d = 128, W = 4,
+// tensors out of the caches: 4 slices of N = 16384 128 us with 128 rows (32 workgroups), 30 with 16 (256 workgroups);
+// 16 slices 136 and, with 32 rows, 56.
 static int conv_rows(const Dims& s)
 {
     const int cpw = 256 / (s.D / 8);

@@ -272,6 +272,11 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f)
 // 16-byte loads in flight.  What goes with a partial -- is it there, its (m, l) -- is looked up once per
 // query, by the lane that stands at its place in the chunk.  (Every lane looking up every partial for itself
 // kept the address and data units busy all the time: 4.4 of 4.4 ms at 151 M partials of d = 64.)
+// The partials are streamed: nothing reads them again.  Part of what that saves comes back in the next kernel, which
+// finds the memory system still busy; the sum is the smaller one.  us, plain -> streaming loads, 32 slices, d = 64,
+// B = 128, k = 8: N = 65536 forward merge 580 -> 565, row sums D after it 101 -> 115; dQ merge 534 -> 492, centroids of the
+// next step after it 53 -> 78; N = 524288 4467 -> 4345, 790 -> 801; 4148 -> 3927, 372 -> 406; N = 16384 167 -> 127, 27 -> 25;
+// 142 -> 113, 16 -> 13.  Steps: 5.56 -> 5.52, 56.9 -> 56.7, 1.35 -> 1.29 ms.
 template <int D>
 struct MergeRow {
     static constexpr int LANES = D / 8, ROWS = 256 / LANES;             // a query's lanes; queries of a workgroup
@@ -300,7 +305,16 @@ struct MergeRow {
         return si < slots && (e == k ? c < own_parts : j >= 0);
     }
 };
-// partials per chunk, one of the instantiated sizes: the one with the fewest loads past a query's end
+// Partials per chunk, one of the instantiated sizes: the one with the fewest loads past a query's end, the larger of two
+// that are equal.  Merge alone, 8 slices of N = 16384, B = 64, us with 4 / 6 / 9 / 11 / 13, forward | dQ:
+//   d = 64,  5 partials  21.8 17.9 22.0 29.8 26.4 | 19.7 18.5 21.2 23.9 25.5    9  35.7 32.9 32.5 34.5 34.4 | 31.9 31.1 28.3 29.3 31.2
+//           11  35.4 33.2 43.9 38.0 37.4 | 34.0 33.5 39.6 34.3 32.9            17  61.7 53.6 58.1 63.5 67.3 | 52.7 50.0 50.6 53.0 57.3
+//           33  116 111 117 105 114 | 112 110 110 106 110                      65  233 221 244 218 215 | 218 215 219 214 212
+//   d = 128, 9  68.0 58.3 59.9 64.7 59.5 | 59.6 56.4 55.7 55.2 59.6           17  115 105 110 121 119 | 110 108 107 109 115
+//           33  194 208 204 198 210 | 210 209 206 205 208                      65  373 379 382 383 385 | 406 403 393 402 395
+// Of 41 counts the pick is within 3 % of the best size in 39 (dQ) and 27 (forward: chunks of 9 and 11 at d = 64 are up to
+// 8 % behind those of 6 at 17 and 18 partials and 14 % at 10 and 11, and ahead of them from 33 partials on; runs of
+// this table, which has the launch in it, differ by 2 to 3 %).
 inline int merge_chunk(int slots)
 {
     int best = 13;
