@@ -16,7 +16,8 @@
 // and dO tiles sit in LDS unpadded, with the 16-byte chunks of row r permuted by r & 7 so
 // that a gather of arbitrary rows still spreads over the banks.  As there, the LDS pipe bounds it
 // (busy all the time by the counters, 36 % of that bank conflicts; vector issue 58 %, matrix pipe 25 %):
-// 957 -> 945 us (16 heads of 32768, B = 32, k = 64) with adds of sixteen consecutive words of a row each.
+// 957 -> 945 us (16 heads of 32768, B = 32, k = 64) with adds of sixteen consecutive words of a row each, 945 -> 920 without
+// those of a list's last sixteen places that no row has.
 #include "mfma.h"
 
 namespace moba {
@@ -70,7 +71,8 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
 
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int m16 = lane & 15, g = lane >> 4;
+    constexpr bool QUADS = D == 64;                        // skip the adds of four places that no row has (listed_at())
+    const int m16 = lane & 15, g = lane >> 4, at16 = QUADS ? listed_at(m16) : m16;
     int s, pos;
     if (!schedule(blockIdx.x, bh, ntiles, s, pos)) return;
     const int tile = ntiles - 1 - pos;                 // late, long tiles first
@@ -166,7 +168,8 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
     };
     // x: dS^T (scaled) of this lane's row -> dQ accumulators.  The product leaves row r4[i] (4 g + i of
     // the sixteen), channel tile_chan(mt, m16), which sits at word 16 mt + m16 of an accumulator row
-    auto accumulate = [&](const int (&r4)[4], const float (&x)[8], const Frag (&kt)[C::MT]) {
+    // (of every g the first `quads` rows count)
+    auto accumulate = [&](const int (&r4)[4], const float (&x)[8], const Frag (&kt)[C::MT], int quads) {
         Frag pb;
 #pragma unroll
         for (int e = 0; e < 4; ++e) pb.u[e] = pack2(x[2 * e], x[2 * e + 1]);
@@ -175,6 +178,7 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
         for (int mt = 0; mt < C::MT; ++mt) o[mt] = mfma16(pb, kt[mt], f32x4_t{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
+            if (QUADS && i >= quads) break;
             int* arow = acc + (uint32_t)r4[i] * C::OSTRIDE + m16;
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt)
@@ -218,7 +222,7 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
                 const bool vis = !own || 16 * (e >> 2) + 4 * g + (e & 3) <= 16 * st + m16;
                 x[e] = vis ? fast_exp2(fmaf(sc[e >> 2][e & 3], c2, -pe)) * dp[e >> 2][e & 3] : 0.f;
             }
-            accumulate(r4, x, kt);
+            accumulate(r4, x, kt, 4);
         }
     }
 
@@ -250,15 +254,19 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
                 // sub-tiles of 16 listed rows; lanes beyond the list work on whatever row id
                 // they read (always inside the tile) and add zeros: their lse is infinite
                 for (int c0 = beg; c0 < end; c0 += 16) {
-                    const bool valid = m16 < end - c0;
-                    const int row = rows8[c0 + m16] & (C::TILE - 1);
+                    const bool valid = at16 < end - c0;
+                    const int row = rows8[c0 + at16] & (C::TILE - 1);
                     Frag qb[C::KS], gb[C::KS];
                     gather(row, qb, gb);
                     const float pe = valid ? pexp[row] : INFINITY, nD = Dr[row];
-                    const uint32_t w = *reinterpret_cast<const uint32_t*>(rows8 + c0 + 4 * g);
                     int r4[4];
+                    if constexpr (QUADS) {
+                        listed_rows(rows8[c0 + 4 * (m16 & 3) + g] & (C::TILE - 1), r4);
+                    } else {
+                        const uint32_t w = *reinterpret_cast<const uint32_t*>(rows8 + c0 + 4 * g);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) r4[i] = (int)(w >> (8 * i)) & (C::TILE - 1);
+                        for (int i = 0; i < 4; ++i) r4[i] = (int)(w >> (8 * i)) & (C::TILE - 1);
+                    }
                     f32x4_t sc[2], dp[2];
 #pragma unroll
                     for (int mt = 0; mt < 2; ++mt) {
@@ -274,7 +282,7 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
 #pragma unroll
                     for (int e2 = 0; e2 < 8; ++e2)
                         x[e2] = fast_exp2(fmaf(sc[e2 >> 2][e2 & 3], c2, -pe)) * dp[e2 >> 2][e2 & 3];
-                    accumulate(r4, x, kt);
+                    accumulate(r4, x, kt, (end - c0 + 3) >> 2);
                 }
             }
             e = en;

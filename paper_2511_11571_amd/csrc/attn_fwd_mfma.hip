@@ -41,7 +41,8 @@
 // What bounds it then is the LDS pipe: busy all the time by the counters at 16 heads of 32768, B = 32, k = 64 (16 adds
 // per sub-tile, gathered rows, lists), a third of that in bank conflicts, with the issue of vector instructions at
 // 74 % and the matrix pipe at 23 %.  The product's orientation by itself took conflicts from 219 to 187 M clocks and
-// gained 0.2 %.  Measured, kernel alone, all of the above: that shape 1095 -> 1042 us; 32 slices of 16384, B = 64,
+// gained 0.2 %; a list's last adds left out where no row has them (d = 64, B = 32) gain 1 to 2 % (8 heads of 32768, k = 30, copies
+// included: 378 -> 370 us).  Measured, kernel alone, all of the above but that: that shape 1095 -> 1042 us; 32 slices of 16384, B = 64,
 // k = 32, hot blocks 762 -> 708 us.
 #include <type_traits>
 
@@ -120,7 +121,8 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
 
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int m16 = lane & 15, g = lane >> 4;
+    constexpr bool QUADS = D == 64 && GMAX == 1;           // skip the adds of four places that no row has (listed_at())
+    const int m16 = lane & 15, g = lane >> 4, at16 = QUADS ? listed_at(m16) : m16;
     int s, pos;
     if (!schedule(blockIdx.x, bh, ntiles, s, pos)) return;
     const int tile = ntiles - 1 - pos;                 // late, long tiles first
@@ -192,12 +194,13 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
             o[mt] = mfma16(pb, va[mt], fresh ? f32x4_t{0.f, 0.f, 0.f, 0.f} : o[mt]);
     };
     // o[mt][i] is row r4[i] of the sixteen (rows 4 g + i), channel tile_chan(mt, m16), which sits at
-    // word 16 mt + m16 of an accumulator row
-    auto flush = [&](int row, const int (&r4)[4], float lp, const f32x4_t (&o)[C::MT], bool valid) {
+    // word 16 mt + m16 of an accumulator row; of every g the first `quads` rows count
+    auto flush = [&](int row, const int (&r4)[4], float lp, const f32x4_t (&o)[C::MT], bool valid, int quads) {
         lp = sum_over_g(lp);                       // the row's 32 (64) keys in one add, from one lane
         if (valid && g == 0) atomicAdd(&lsum[row], __float2int_rn(lp));
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
+            if (QUADS && i >= quads) break;
             int* orow = Os + (uint32_t)r4[i] * C::OSTRIDE + m16;
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt) atomicAdd(&orow[16 * mt], __float2int_rn(o[mt][i]));
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
                 } else {
                     attend(x, va, lp, o, GMAX == 1);
                     if (GMAX == 1) {          // (no registers to keep the sums over the groups)
-                        flush(row, r4, lp, o, true);
+                        flush(row, r4, lp, o, true, 4);
                         lp = 0.f;
                     }
                 }
@@ -259,7 +262,7 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
                 mx = max_over_g(mx);
                 if (g == 0) atomicMax(&mkey[row], float_key(mx));
             }
-            else if (GMAX > 1) flush(row, r4, lp, o, true);
+            else if (GMAX > 1) flush(row, r4, lp, o, true, 4);
         }
 
         // routed blocks
@@ -300,17 +303,21 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
                 // read (always inside the tile) and add zeros: their
                 // reference is infinite (and what a NaN would add is 0: the conversion's result for it).
                 for (int c0 = beg; c0 < end; c0 += 16) {
-                    const bool valid = m16 < end - c0;
-                    const int row = rows8[c0 + m16] & (C::TILE - 1);
+                    const bool valid = at16 < end - c0;
+                    const int row = rows8[c0 + at16] & (C::TILE - 1);
                     Frag qb[C::KS];
                     gather_q(row, qb);
                     float mr = 0.f;
                     int r4[4];
                     if (pass == 1) {
                         mr = valid ? __int_as_float(mkey[row]) : INFINITY;
-                        const uint32_t w = *reinterpret_cast<const uint32_t*>(rows8 + c0 + 4 * g);
+                        if constexpr (QUADS) {
+                            listed_rows(rows8[c0 + 4 * (m16 & 3) + g] & (C::TILE - 1), r4);
+                        } else {
+                            const uint32_t w = *reinterpret_cast<const uint32_t*>(rows8 + c0 + 4 * g);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) r4[i] = (int)(w >> (8 * i)) & (C::TILE - 1);
+                            for (int i = 0; i < 4; ++i) r4[i] = (int)(w >> (8 * i)) & (C::TILE - 1);
+                        }
                     }
                     auto scores = [&](int u, f32x4_t (&sc)[2]) {
 #pragma unroll
@@ -346,7 +353,7 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
                             for (int e = 0; e < 8; ++e) x[e] = fmaf(sc[e >> 2][e & 3], c2, -mr);
                             attend(x, va[u], lp, o, u == 0);
                         }
-                        flush(row, r4, lp, o, valid);
+                        flush(row, r4, lp, o, valid, (end - c0 + 3) >> 2);
                     }
                 }
             };

@@ -259,6 +259,21 @@ __device__ __forceinline__ void build_block_lists(const int32_t* __restrict__ id
     __syncthreads();
 }
 
+// Sixteen listed rows as the columns (or rows) of a product: column m takes the row at place listed_at(m) of the
+// sixteen.  The product's result rows 4 g + i, i fixed, are then the places 4 i + g: instruction i of the adds covers
+// four neighbouring places, and a list's last sixteen needs no more of these instructions than it has rows / 4.  For kernels
+// that meet lists of about sixteen rows (d = 64): 5.8 -> 4.4 of them per channel tile and list.  Lists of a whole tile's rows only pay for
+// it (d = 128, dense, 3 heads of 2176: dQ 155 -> 163 us; d = 64, B = 256, dense, 3 heads of 3072: forward 135 -> 138).
+__device__ __forceinline__ int listed_at(int m) { return 4 * (m & 3) + (m >> 2); }
+// the rows at places 4 i + g, i = 0 .. 3, from what the lane (g, m16) read at place 4 (m16 & 3) + g
+__device__ __forceinline__ void listed_rows(int at, int (&r4)[4])
+{
+    r4[0] = __builtin_amdgcn_mov_dpp(at, 0x00, 0xf, 0xf, true);         // quad_perm: lane i of every four
+    r4[1] = __builtin_amdgcn_mov_dpp(at, 0x55, 0xf, 0xf, true);
+    r4[2] = __builtin_amdgcn_mov_dpp(at, 0xaa, 0xf, 0xf, true);
+    r4[3] = __builtin_amdgcn_mov_dpp(at, 0xff, 0xf, 0xf, true);
+}
+
 // f(integral_constant 0), f(integral_constant 1), ...
 template <typename F, int... I>
 __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f)
