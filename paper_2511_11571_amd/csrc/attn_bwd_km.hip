@@ -25,7 +25,12 @@
 // gathered from one place make much of a difference there (17.9 -> 17.6 and 16.4 ms).
 // Against separate walks for dQ and for dK and dV: N = 524288: 28.0 -> 18.6 ms, with the rows laid out as
 // parked() says 17.9; N = 10080, B = 96, k = 10, 18 slices: 210 us; N = 16384, d = 128, B = 64, k = 16, 16 slices: 778 us,
-// with that and operands read ahead 705.
+// with that and operands read ahead 705.  Keys requested together, and kept for dQ where there are registers: whole backward
+// 22.96 -> 22.20 ms, 235 -> 230 us, 927 -> 894 us.
+//
+// Tried and left: a third wave per SIMD at d = 64 (LDS rows without padding fit three workgroups, 168 registers do not hold
+// the gathered rows: spills, 40 ms instead of 18); a slot's exponentials between the next one's products, with scheduling
+// barriers (22.3 -> 23.8 ms); list entries requested before the keys (slower at d = 128).
 #include <type_traits>
 
 #include "mfma.h"
@@ -105,18 +110,23 @@ void bwd_km_kernel(
     const char* Gg = reinterpret_cast<const char*>(dO + sbase * D);
 
     // The K rows of the part, their 8-byte pieces (four channels) in the order in which dQ's transpose reads
-    // want them: a lane of the result then holds CH / 4 consecutive channels
+    // want them: a lane of the result then holds CH / 4 consecutive channels.  All are requested before the first one is
+    // waited for: one after the other they took most of the 14000 clocks (of 122000) before a workgroup's walk.
     {
         const char* Kg = reinterpret_cast<const char*>(K + (kvbase + own0) * D);
-        for (int i = tid; i < 32 * NG * C::CPR; i += C::NT) {
-            const int row = i / C::CPR, piece = i % C::CPR;
-            const uint4 v = *reinterpret_cast<const uint4*>(Kg + (size_t)i * 16);
+        constexpr int KI = 32 * NG * C::CPR / C::NT;
+        uint4 krow[KI];
+#pragma unroll
+        for (int i = 0; i < KI; ++i) krow[i] = *reinterpret_cast<const uint4*>(Kg + (size_t)(i * C::NT + tid) * 16);
+#pragma unroll
+        for (int i = 0; i < KI; ++i) {
+            const int row = (i * C::NT + tid) / C::CPR, piece = (i * C::NT + tid) % C::CPR;
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const int ch = 2 * piece + e, half = ch / (C::CH / 4), in = ch % (C::CH / 4);
                 const int pos = half * (C::CH / 4) + 4 * (in % C::MQ) + in / C::MQ;
                 *reinterpret_cast<uint2*>(sK + parked<D>(row, pos >> 1) + 8 * (pos & 1)) =
-                    e ? make_uint2(v.z, v.w) : make_uint2(v.x, v.y);
+                    e ? make_uint2(krow[i].z, krow[i].w) : make_uint2(krow[i].x, krow[i].y);
             }
         }
     }
@@ -210,6 +220,11 @@ void bwd_km_kernel(
     const int dslot = wave / C::HV, dhalf = wave % C::HV;     // this wave's share of dQ
     const int64_t slots = (int64_t)(k + 1) * nsub;           // partials per query
 
+    // dQ's operand of K: 32 keys as contraction, channel tile it mod MQ of the wave's share.  The same in every step:
+    // with four key groups at d = 64 there are registers for all of them (16 of 93 LDS instructions of a step)
+    constexpr bool KEEP = D == 64 && NG == 4;
+    Frag kept[KEEP ? NG * C::MQ : 1];
+    auto key_operand = [&](int it) { return tr(sK + 32 * (it / C::MQ) * C::SB, dhalf * (C::CH / 4) + 4 * (it % C::MQ)); };
     auto ahead = [&]() { if constexpr (D == 128) __builtin_amdgcn_sched_barrier(0); };
     // 32 parked positions (walk positions p0 .. p0 + 31) against this wave's keys
     auto work = [&](const unsigned char* stQ, int sl, int p0, auto inside) {
@@ -332,7 +347,7 @@ void bwd_km_kernel(
         constexpr int KA = D == 64 ? 1 : 4;
         Frag ka[KA + 1], xb[NG][2];
         auto keys = [&](int it) {
-            ka[it % (KA + 1)] = tr(sK + 32 * (it / C::MQ) * C::SB, dhalf * (C::CH / 4) + 4 * (it % C::MQ));
+            if constexpr (!KEEP) ka[it % (KA + 1)] = key_operand(it);
         };
 #pragma unroll
         for (int it = 0; it < KA; ++it) keys(it);
@@ -356,7 +371,7 @@ void bwd_km_kernel(
             ahead();
 #pragma unroll
             for (int qt = 0; qt < 2; ++qt)
-                o[qt][it % C::MQ] = mfma16(ka[it % (KA + 1)], xb[it / C::MQ][qt], o[qt][it % C::MQ]);
+                o[qt][it % C::MQ] = mfma16(KEEP ? kept[it] : ka[it % (KA + 1)], xb[it / C::MQ][qt], o[qt][it % C::MQ]);
             ahead();
         }
         // the partials: this lane holds CH / 4 consecutive channels of two rows
@@ -377,6 +392,10 @@ void bwd_km_kernel(
         }
     };
     __syncthreads();                                          // K is in LDS
+    if constexpr (KEEP) {
+#pragma unroll
+        for (int it = 0; it < NG * C::MQ; ++it) kept[it] = key_operand(it);
+    }
     // the bulk of the walk: this step, the rows fetched in it and the ids looked up in it all lie inside the
     // block's list; then the general steps (own rows, causal mask, end of the walk)
     int a0 = 0;
