@@ -291,6 +291,17 @@ int moba_decode_forward(const moba_shape* shape, int32_t q_len, const void* Q, c
                         float* lse, int32_t* topk_idx, void* stream);
 
 /*
+ * The same with a workspace: where few queries have much to read, several workgroups then share a query and the
+ * last of them merges their parts (the result depends on the shape alone, but may differ in rounding from the
+ * call without a workspace).  moba_decode_workspace gives its size, 0 where nothing is gained by one.
+ *   ws   at least that many bytes, 8-byte aligned, of any content; used by one call at a time; may be NULL
+ */
+int moba_decode_workspace(const moba_shape* shape, int32_t q_len, size_t* ws_bytes);
+int moba_decode_forward_ws(const moba_shape* shape, int32_t q_len, const void* Q, const void* K_eff,
+                           const void* V, const float* centroids, int32_t centroid_blocks, void* O,
+                           float* lse, int32_t* topk_idx, void* ws, size_t ws_bytes, void* stream);
+
+/*
  * moba_backward split into its kernels, for callers that time or overlap them:
  * `parts` is a bit set of MOBA_BWD_PREPROCESS (D = rowsum(dO o O) into the workspace),
  * MOBA_BWD_DQ and MOBA_BWD_DKDV (both read D from the workspace, so PREPROCESS must have

@@ -94,7 +94,7 @@ def lib():
         for name in ("moba_routes_per_slice", "moba_workspace_bytes", "moba_centroids", "moba_topk",
                      "moba_topk_static", "moba_topk_varlen", "moba_varlen_layout", "moba_varlen_pad",
                      "moba_varlen_unpad", "moba_varlen_block_first", "moba_build_lists", "moba_forward", "moba_backward", "moba_backward_parts",
-                     "moba_decode_forward",
+                     "moba_decode_forward", "moba_decode_forward_ws", "moba_decode_workspace",
                      "moba_profile_begin", "moba_profile_end", "moba_key_conv_backward",
                      "moba_key_conv_backward_workspace", "moba_microbench_copy", "moba_microbench_mfma"):
             getattr(L, name).restype = ctypes.c_int
@@ -332,6 +332,16 @@ def backward(shape: Shape, Q, K_eff, V, O, lse, dO, idx, lists, ws=None, out=Non
     return dQ, dK, dV
 
 
+def _decode_workspace_bytes(shape: Shape, q_len):
+    known = shape.__dict__.get("_decode_ws")             # a function of the (immutable) shape and q_len
+    if known is None or known[0] != q_len:
+        n = ctypes.c_size_t(0)
+        _check(lib().moba_decode_workspace(ctypes.byref(shape.c()), q_len, ctypes.byref(n)), "moba_decode_workspace")
+        known = (q_len, n.value)
+        object.__setattr__(shape, "_decode_ws", known)
+    return known[1]
+
+
 def decode_forward(shape: Shape, q_len, Q, K_eff, V, cent, want_idx=True):
     """Decode-shaped forward for the last q_len positions of shape.seqlen keys (any length).
     -> (O [b,h,q_len,d], lse [b,h,q_len] fp32, topk_idx [b,h,q_len,k] int32 or None)."""
@@ -346,9 +356,11 @@ def decode_forward(shape: Shape, q_len, Q, K_eff, V, cent, want_idx=True):
     lse = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
     idx = (torch.empty((shape.batch, shape.heads, q_len, shape.topk), dtype=torch.int32, device=Q.device)
            if want_idx else None)
-    _check(_fn("moba_decode_forward", "pippppipppp")(shape._ref(), q_len, _p(Q), _p(K_eff),
-                                     _p(V), _p(cent), blocks, _p(O), _p(lse), _p(idx),
-                                     _stream()), "moba_decode_forward")
+    need = _decode_workspace_bytes(shape, q_len)
+    ws = torch.empty(need, dtype=torch.uint8, device=Q.device) if need else None
+    _check(_fn("moba_decode_forward_ws", "pippppippppzp")(shape._ref(), q_len, _p(Q), _p(K_eff),
+                                     _p(V), _p(cent), blocks, _p(O), _p(lse), _p(idx), _p(ws), need,
+                                     _stream()), "moba_decode_forward_ws")
     return O, lse, idx
 
 

@@ -5,9 +5,9 @@
 // algorithm of Appendix C.1 treats the tail block the same way; here its centroid is never
 // needed, because the own block is not a routing candidate).
 //
-// One workgroup of 16 waves per (query, batch*head), no workspace: gate scores against the centroids
+// One workgroup of 16 waves per (query, batch*head) (or a few, see decode_splits()): gate scores against the centroids
 // of the complete past blocks, exact top-k, attention over the kept blocks and the own block, all in
-// fp32 arithmetic; nothing is written to global memory but O, lse and (optionally) the kept blocks.
+// fp32 arithmetic; nothing is written to global memory but O, lse, (optionally) the kept blocks and the parts of shared queries.
 //
 // The work per query is a few hundred KB of reads from a chip that is mostly idle, so the kernel is
 // bound by how fast ONE compute unit takes them in and by the chain of dependent steps:
@@ -16,17 +16,24 @@
 //    parts of the dot product up by DPP;
 //  - the keys of all kept blocks and the own block count as ONE sequence that the waves walk together:
 //    with a block per wave, 9 kept blocks left 7 of 16 waves idle;
-//  - loads go out in batches of 16 per lane (a batch is one memory latency);
+//  - loads go out in batches of 16 per lane (a batch is one memory latency), the last one smaller;
 //  - every group of lanes that holds a key keeps a softmax of its own (m, l, O), merged once at the
 //    end: no cross-lane maximum or sum inside the walk;
-//  - the selection bins the scores linearly between the smallest and the largest (1024 bins, one LDS
-//    atomic per score, well spread), and ranks only the scores of the bin that holds the k-th largest;
+//  - the selection of up to 16 blocks takes a lower bound of the k-th largest score from the maxima of 64 groups and
+//    ranks the few scores that reach it, sixteen lanes per score (three barriers, 2.9 -> 1.6 us at k = 8 of 1024).  Longer rows, and
+//    calls where too many scores reach the bound, bin the scores linearly between the smallest and the largest (1024 bins, one LDS
+//    atomic per score, well spread), and rank only the scores of the bin that holds the k-th largest;
 //    the radix select over the bits of the scores remains for bins of more than 128 scores (ties, or one
 //    score far from the rest) and for non-finite scores;
 //  - queries that share a key/value head run on the same XCD at the same time (schedule()).
-// 1 query of 131109 keys x 32 slices (d = 64, B = 128, k = 8): 24.8 -> 12.8 us; 16 queries of 32805
-// keys x 16 heads on 4 key/value heads (d = 128, B = 64, k = 32): 59 -> 29 us (there
-// 340 MB go from the L2s to the compute units and 126 MB from behind them: 4.5 TB/s of the latter).
+// Of 12.3 us inside one workgroup (1 query of 131109 keys, d = 64, B = 128, k = 8) the gate took 4.2, the selection 2.9, the keys 4.5
+// and the merge 0.7; both memory phases (262 and 272 KB) run at the 25 bytes per clock one compute unit takes in here.
+// 1 query of 131109 keys x 32 slices: 24.8 -> 12.8 -> 10.4 us (now host time: a call takes the host 10 us); 16 queries of 32805
+// keys x 16 heads on 4 key/value heads (d = 128, B = 64, k = 32): 59 -> 28 -> 26.5 us (there
+// 340 MB go from the L2s to the compute units and 126 MB from behind them: 5 TB/s of the latter).
+#include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <type_traits>
 
 #include "common.h"
@@ -61,6 +68,16 @@ __device__ __forceinline__ float row_sum(float x)
         const auto q = __builtin_amdgcn_permlane16_swap(b, b, false, false);
         x = __uint_as_float(q[0]) + __uint_as_float(q[1]);
     }
+    return x;
+}
+
+// sum of the counts of 16 neighbouring lanes, in all of them
+__device__ __forceinline__ int count_16(int x)
+{
+    x += dpp<0xb1>(x);
+    x += dpp<0x4e>(x);
+    x += dpp<0x141>(x);
+    x += dpp<0x140>(x);
     return x;
 }
 
@@ -106,38 +123,56 @@ constexpr int kDecodeBins = kDecodeThreads;    // bins of the selection: one per
 // same time for any number: a score 10000 times the rest puts those into one bin (1 query, 1024 blocks, k = 8, whole call:
 // 52.0 us ranked, 17.8 by the radix select).
 constexpr int kDecodeRank = 128;
+// Rows up to this length are selected from the scores that reach a bound taken from the maxima of kDecodeGroups groups: of n
+// scores about n (1 - (1 - k / groups)^(groups / n)), 11 of 1024 at k = 8 and 90 of 4096 at k = 48.  Longer rows gain nothing or
+// lose (whole call, bins -> bound: k = 8 of 140 blocks 24.0 -> 22.0 us, 16 of 35 17.1 -> 17.6, 24 of 3750 17.0 -> 16.8, 30 of 140 12.8
+// -> 12.6, 40 of 1875 13.8 -> 14.9, 48 of 3750 18.4 -> 20.2).
+constexpr int kDecodeShort = 16;
+constexpr int kDecodeGroups = 4 * kDecodeWaves;
+static_assert(kDecodeGroups == kWave, "a group's maximum per lane");
+constexpr int kDecodeBoundBit = 18;            // the bound's lowest bit (5 bits of a score's fraction: a few scores more)
 // words that hold the ranked scores, then the waves' (m, l, O)
 template <int D>
 constexpr int kDecodeScratch = 2 * kDecodeRank > kDecodeWaves * (D + 2) ? 2 * kDecodeRank : kDecodeWaves * (D + 2);
+
+constexpr int kDecodeSplits = 8;               // most workgroups that share a query
+// Several workgroups per query: what they share
+struct DecodeSplit {
+    uint64_t* arrived;                          // [queries]
+    float* part;                                // [queries][splits][m, l, O]
+    uint64_t tag;
+};
 
 template <typename T, int D>
 __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const float* __restrict__ cent, T* __restrict__ O, float* __restrict__ lse,
     int32_t* __restrict__ idx_out, int N, int B, int k, int q_len, int cblocks, float scale, int G,
-    int bhk, int npast_max)
+    int bhk, int npast_max, int splits, DecodeSplit split)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int NT = kDecodeThreads, NW = kDecodeWaves;
     constexpr int LPR = D * (int)sizeof(T) / 16;            // lanes of a K / V row, 16 bytes each
     constexpr int EPL = 16 / (int)sizeof(T);                // elements of a lane
     constexpr int RPI = kWave / LPR;                        // rows per load instruction of a wave
-    constexpr int NB = 8;                                   // load instructions of K (and of V) in flight
     float* sc = reinterpret_cast<float*>(smem_raw);         // [npast_max rounded up to 4] gate scores
     uint32_t* hist = reinterpret_cast<uint32_t*>(sc + (npast_max + 3) / 4 * 4);   // [kDecodeBins]
-    uint2* cand = reinterpret_cast<uint2*>(hist + kDecodeBins);                   // [kDecodeRank] (key, block) of the k-th's bin
+    uint2* cand = reinterpret_cast<uint2*>(hist + kDecodeBins);                   // [kDecodeRank] scores to rank: (key, block) or, as one 64-bit number, (key, ~block)
     float* mrg = reinterpret_cast<float*>(cand);            // [NW][D + 2] the waves' (m, l, O), after the selection
     uint32_t* keep = reinterpret_cast<uint32_t*>(mrg + kDecodeScratch<D>);        // kept-block bits of the ranked bin
     float* wmx = reinterpret_cast<float*>(keep + (npast_max + 31) / 32);          // [NW] and
     float* wmn = wmx + NW;                                  // [NW]: the waves' largest and smallest score
     int* wcnt = reinterpret_cast<int*>(wmn + NW);           // [NW]
-    int* ctl = wcnt + NW;                                   // [4]
-    int* sel = ctl + 4;                                     // [k + 1] kept blocks, ascending, then the own block
+    int* ctl = wcnt + NW;                                   // [5]
+    uint32_t* gmx = reinterpret_cast<uint32_t*>(ctl + 5);   // [kDecodeGroups] order-preserving keys of the groups' largest scores
+    int* sel = ctl + 5 + kDecodeGroups;                     // [k + 1] kept blocks, ascending, then the own block
 
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     int skv, pos;
-    if (!schedule(blockIdx.x, bhk, G * q_len, skv, pos)) return;
+    if (!schedule(blockIdx.x, bhk, G * q_len * splits, skv, pos)) return;
+    const int share = splits > 1 ? pos % splits : 0;        // this workgroup's share of the query's keys
+    if (splits > 1) pos /= splits;
     const int s = skv * G + pos / q_len, r = pos % q_len;   // G query heads share a key/value head
     const int t = N - q_len + r;                            // position of the query
     const int past = t / B;                                 // complete blocks before its own block
@@ -153,7 +188,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
     }
     hist[tid] = 0u;
     for (int i = tid; i < (past + 31) / 32; i += NT) keep[i] = 0u;
-    if (tid < 4) ctl[tid] = 0;
+    if (tid < 5) ctl[tid] = 0;
 
     const int want = min(k, past);
     if (past > k && k > 0) {
@@ -165,7 +200,13 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
 #pragma unroll
             for (int c = 0; c < CL; ++c) {
                 const T* qc = Q + qrow * D + 64 * c + 4 * cl;
-                q4[c] = make_float4(to_f32<T>(qc[0]), to_f32<T>(qc[1]), to_f32<T>(qc[2]), to_f32<T>(qc[3]));
+                if constexpr (sizeof(T) == 2) {
+                    const uint2 x = *reinterpret_cast<const uint2*>(qc);
+                    q4[c] = make_float4(__uint_as_float(x.x << 16), __uint_as_float(x.x & 0xffff0000u),
+                                        __uint_as_float(x.y << 16), __uint_as_float(x.y & 0xffff0000u));
+                } else {
+                    q4[c] = *reinterpret_cast<const float4*>(qc);
+                }
             }
             const char* cs = reinterpret_cast<const char*>(cent + (int64_t)skv * cblocks * D);
             float mx = -INFINITY, mn = INFINITY;
@@ -203,6 +244,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
             auto fmx = [](float a, float b) { return __builtin_elementwise_maximum(a, b); };
             auto fmn = [](float a, float b) { return __builtin_elementwise_minimum(a, b); };
             mx = fmx(mx, dpp<0xb1>(mx)); mx = fmx(mx, dpp<0x4e>(mx)); mx = fmx(mx, dpp<0x141>(mx));
+            if (cl == 0) gmx[4 * wave + cr] = decode_key(fmx(mx, dpp<0x128>(mx)));   // (row_ror 8: the other half of the 16)
             mn = fmn(mn, dpp<0xb1>(mn)); mn = fmn(mn, dpp<0x4e>(mn)); mn = fmn(mn, dpp<0x141>(mn));
             mx = across_rows<8>(mx, fmx);
             mn = across_rows<8>(mn, fmn);
@@ -211,6 +253,62 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
         __syncthreads();
         // ---- the k largest scores, ties to the lower block (Section 2).  A thread owns up to four
         // consecutive blocks.
+        // Short rows: the k-th largest of the groups' maxima (a score of its own from every group) is a lower bound of
+        // the k-th largest score, and few scores reach it: those are ranked against each other.  At least k
+        // of them prove the result whatever the bound.  The bound itself is searched bit by bit, by every wave for itself.
+        const int j0 = 4 * tid;
+        bool chosen = false;
+        if (k <= kDecodeShort) {
+            const uint32_t mine = gmx[lane];
+            const float4 x = *reinterpret_cast<const float4*>(sc + min(j0, (past - 1) & ~3));
+            uint32_t bound = 0;
+#pragma unroll
+            for (int bit = 31; bit >= kDecodeBoundBit; --bit)
+                if (__popcll(__ballot(mine >= (bound | 1u << bit))) >= k) bound |= 1u << bit;
+            const uint32_t key[4] = {decode_key(x.x), decode_key(x.y), decode_key(x.z), decode_key(x.w)};
+            bool hit[4];
+            int hits = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                hit[i] = j0 + i < past && key[i] >= bound;
+                hits += (int)hit[i];
+            }
+            if (hits > 0) {
+                int at = atomicAdd(&ctl[4], hits);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (hit[i]) {
+                        if (at < kDecodeRank) cand[at] = make_uint2(~(uint32_t)(j0 + i), key[i]);
+                        ++at;
+                    }
+            }
+            __syncthreads();
+            const int c = ctl[4];
+            chosen = c >= k && c <= kDecodeRank;
+            if (chosen) {
+                // sixteen lanes per candidate: its place among them by (score, lower block first) as one number ...
+                const uint64_t* all = reinterpret_cast<const uint64_t*>(cand);
+                int* row = reinterpret_cast<int*>(hist);             // [k] kept blocks, best first
+                for (int i = tid >> 4; i < c; i += NT / 16) {
+                    const uint64_t me = all[i];
+                    int r = 0;
+                    for (int o = tid & 15; o < c; o += 16) r += (int)(all[o] > me);
+                    r = count_16(r);
+                    if ((tid & 15) == 0 && r < k) row[r] = (int)~(uint32_t)me;
+                }
+                __syncthreads();
+                // ... and, the kept ones, in ascending order of the blocks
+                const int i = tid >> 4;
+                if (i < k) {
+                    const int me = row[i];
+                    int r = 0;
+                    for (int o = tid & 15; o < k; o += 16) r += (int)(row[o] < me);
+                    r = count_16(r);
+                    if ((tid & 15) == 0) sel[r] = me;
+                }
+            }
+        }
+        if (!chosen) {
         // sum of the counts that the waves before this one left in wcnt
         auto waves_before = [&]() {
             return __builtin_amdgcn_readlane(wave_prefix(lane < wave ? wcnt[lane] : 0), kWave - 1);
@@ -225,7 +323,6 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
         // larger than every score of a lower one
         const float inv = (float)(kDecodeBins - 1) / (M - m);
         bool direct = M - m < INFINITY && inv < INFINITY;
-        const int j0 = 4 * tid;
         float v[4];
         int bin[4];
 #pragma unroll
@@ -338,19 +435,22 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             if (take[i] && place < k) sel[place++] = j0 + i;
+        }
     } else {
         for (int j = tid; j < want; j += NT) sel[j] = j;    // no more past blocks than k: keep them all
     }
     if (tid == 0) sel[want] = past;
     __syncthreads();
-    if (idx_out)
+    if (idx_out && share == 0)
         for (int c = tid; c < k; c += NT) idx_out[qrow * k + c] = c < want ? sel[c] : -1;
 
     // ---- attention over want * B + (t mod B) + 1 keys: position p is key p mod B of kept block p / B,
     // the own block last.  The waves walk the positions together, RPI positions per wave and load
     // instruction: the queries of a key/value head that run side by side on one XCD then pass the
     // same stretch of keys at about the same time and find each other's blocks in its L2.
-    const int total = want * B + (t - past * B) + 1;
+    const int all = want * B + (t - past * B) + 1;
+    const int each = splits > 1 ? (all + splits * RPI - 1) / (splits * RPI) * RPI : all;
+    const int first = share * each, total = min(all, first + each);     // (a share may be empty)
     float m = -INFINITY, l = 0.f, acc[EPL];                 // log2 units
 #pragma unroll
     for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
@@ -374,8 +474,9 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
     // that advance by additions.  Otherwise every lane divides.
     const bool whole = B % RPI == 0 && (int64_t)N * ROWB < ((int64_t)1 << 32);
     const int step_blk = NW * RPI / B, step_row = NW * RPI % B;
-    int blk = wave * RPI / B, in_blk = wave * RPI % B;      // whole: the next instruction's block and row
-    auto batch = [&](int p0, auto all_live) {
+    int blk = (first + wave * RPI) / B, in_blk = (first + wave * RPI) % B;      // whole: the next instruction's block and row
+    auto batch = [&](int p0, auto size, auto all_live) {
+        constexpr int NB = decltype(size)::value;           // load instructions of K (and of V) in flight
         constexpr bool ALL = decltype(all_live)::value;     // every position of the batch exists
         uint4 kr[NB], vr[NB];
         // (past the end: some row that is attended anyway, weight 0)
@@ -436,9 +537,17 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
             for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, f[e], acc[e]);
         }
     };
-    for (int p0 = wave * RPI; p0 < total; p0 += NB * NW * RPI) {
-        if (p0 + (NB - 1) * NW * RPI + RPI <= total) batch(p0, std::true_type());
-        else batch(p0, std::false_type());
+    // Batches of eight instructions; the last few go into a batch of four where that holds them (rows past the end are
+    // read and weighted like others).  Batches of ten for the ninth and tenth, of two, and a second batch on its way while one is
+    // worked on were no better over the range of sizes.
+    {
+        constexpr int STEP = NW * RPI;
+        using std::integral_constant;
+        int p0 = first + wave * RPI;
+        for (; p0 + 7 * STEP + RPI <= total; p0 += 8 * STEP) batch(p0, integral_constant<int, 8>(), std::true_type());
+        const int left = (total - p0 + STEP - 1) / STEP;             // instructions
+        if (left > 4) batch(p0, integral_constant<int, 8>(), std::false_type());
+        else if (left > 0) batch(p0, integral_constant<int, 4>(), std::false_type());
     }
     // ---- merge: the lane groups of a wave, then the waves through LDS
     auto weight = [](float a, float b) { return a == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(a - b); };
@@ -458,8 +567,8 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
         for (int e = 0; e < EPL; ++e) mw[2 + piece * EPL + e] = acc[e];
     }
     __syncthreads();
+    float top = -INFINITY, L = 0.f, o = 0.f;
     if (tid < D) {
-        float top = -INFINITY, L = 0.f, o = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) top = fmaxf(top, mrg[w * (D + 2)]);
 #pragma unroll
@@ -468,37 +577,129 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
             L = fmaf(wt, mrg[w * (D + 2) + 1], L);
             o = fmaf(wt, mrg[w * (D + 2) + 2 + tid], o);
         }
+    }
+    // ---- shares: the workgroup that is done last merges them, in their order
+    if (splits > 1) {
+        // Everything shared goes through memory operations of agent scope, which other compute units see in whatever cache
+        // they sit; the counter moves when the stores are through.  (A fence of agent scope would write back and drop
+        // the whole L2: 20 -> 99 us with 64 queries shared by four workgroups each.)
+        float* mine = split.part + (qrow * splits + share) * (D + 2);
+        auto put = [](float* p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        if (tid < D) put(mine + 2 + tid, o);
+        if (tid == 0) { put(mine, top); put(mine + 1, L); }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0);
+        asm volatile("" ::: "memory");
+        __syncthreads();
+        if (tid == 0) {
+            // A counter belongs to this launch if it carries its tag; anything else, whatever the memory held, is a
+            // count of zero.  The last one leaves zero: a launch that is replayed carries the same tag again.
+            uint64_t* at = split.arrived + qrow;
+            uint64_t old = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), next;
+            int before;
+            do {
+                before = (old >> 8) == split.tag ? (int)(old & 255u) : 0;
+                next = before + 1 == splits ? 0u : split.tag << 8 | (uint64_t)(before + 1);
+            } while (!__hip_atomic_compare_exchange_strong(at, &old, next, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT));
+            ctl[0] = before + 1 == splits;
+        }
+        __syncthreads();
+        if (!ctl[0]) return;
+        if (tid < D) {
+            float* theirs = split.part + qrow * splits * (D + 2);
+            auto get = [](float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+            float mx[kDecodeSplits], lx[kDecodeSplits], ox[kDecodeSplits];
+#pragma unroll
+            for (int x = 0; x < kDecodeSplits; ++x) {       // (all on their way at once)
+                float* p = theirs + min(x, splits - 1) * (D + 2);
+                mx[x] = get(p);
+                lx[x] = get(p + 1);
+                ox[x] = get(p + 2 + tid);
+            }
+            top = mx[0];
+#pragma unroll
+            for (int x = 1; x < kDecodeSplits; ++x) top = fmaxf(top, mx[x]);
+            L = o = 0.f;
+#pragma unroll
+            for (int x = 0; x < kDecodeSplits; ++x) {
+                const float wt = x < splits ? weight(mx[x], top) : 0.f;
+                L = fmaf(wt, lx[x], L);
+                o = fmaf(wt, ox[x], o);
+            }
+        }
+    }
+    if (tid < D) {
         O[qrow * D + tid] = from_f32<T>(o / L);
         if (tid == 0) lse[qrow] = (top + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
     }
 }
 
+// Workgroups per query.  A compute unit takes in a query's keys and values at about 25 bytes per clock whatever else is
+// idle, so where there are few queries with much to read several units share one.  Each of them scores and selects for
+// itself, which costs the others bandwidth: at most half the chip, and shares of 128 KB (up to 32 workgroups) or 256 KB.
+// Whole call, us, unshared -> 2 / 4 / 8 workgroups per query: 4 queries of 1 MB 17.8 -> - / 15.9 / 14.4; 4 of 0.5 MB 15.7 ->
+// 13.4 / 12.4 / 13.5; 16 of 1 MB 32.4 -> - / 26.8 / 28.3; 32 of 1.3 MB 40.4 -> - / 33.8 / 38.7; 64 of 0.9 MB 20.7 -> 17.9 / 18.8;
+// 16 of 0.5 MB 14.3 -> 13.7 / 14.2; 64 of 0.5 MB 15.9 -> 15.8 / 17.3; 128 of 1 MB 30.3 -> 31.5; 32 of 0.27 MB 10.4 -> 12.8 (4).
+static int decode_splits(const Dims& s, int q_len)
+{
+    const int64_t queries = (int64_t)s.bh * q_len;
+    const int64_t keys = (int64_t)std::min(s.k, (s.N - 1) / s.B) * s.B + s.B / 2;
+    const int64_t kb = 2 * keys * s.D * (s.dtype == MOBA_BF16 ? 2 : 4) >> 10;
+    if (kb < 512) return 1;
+    int n = 1;
+    while (2 * n <= kDecodeSplits && 2 * n * queries <= 128 && kb >= 2 * n * (2 * n * queries <= 32 ? 128 : 256)) n *= 2;
+    return n;
+}
+// [counters: one per query][partials: m, l, O of every share]
+static size_t decode_counters_bytes(const Dims& s, int q_len) { return ((size_t)s.bh * q_len * sizeof(uint64_t) + 255) & ~(size_t)255; }
+size_t decode_ws_bytes(const Dims& s, int q_len)
+{
+    const int n = decode_splits(s, q_len);
+    return n == 1 ? 0 : decode_counters_bytes(s, q_len) + (size_t)s.bh * q_len * n * (s.D + 2) * sizeof(float);
+}
+// a number of its own for every launch
+static uint64_t launch_tag()
+{
+    static std::atomic<uint64_t> launches{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count()};
+    uint64_t x = launches.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4a7c15ull;      // (odd: one to one)
+    x ^= x >> 32;
+    return (x >> 8) | 1u;
+}
+
 template <typename T, int D>
 static hipError_t decode_t(const Dims& s, int q_len, const void* Q, const void* K, const void* V,
-                           const float* cent, int cblocks, void* O, float* lse, int32_t* idx,
+                           const float* cent, int cblocks, void* O, float* lse, int32_t* idx, void* ws,
                            hipStream_t st)
 {
+    const int splits = ws ? decode_splits(s, q_len) : 1;
+    DecodeSplit split = {nullptr, nullptr, 0};
+    if (splits > 1) {
+        split.arrived = static_cast<uint64_t*>(ws);
+        split.part = reinterpret_cast<float*>(static_cast<char*>(ws) + decode_counters_bytes(s, q_len));
+        split.tag = launch_tag();
+    }
     const int npast_max = (s.N - 1) / s.B;
     const size_t lds = sizeof(float) * (size_t)((npast_max + 3) / 4 * 4 + kDecodeBins + kDecodeScratch<D> +
-                                                (npast_max + 31) / 32 + 3 * kDecodeWaves + 4 + s.k + 1);
+                                                (npast_max + 31) / 32 + 3 * kDecodeWaves + 5 + kDecodeGroups + s.k + 1);
     if (lds > 64 * 1024) {
         hipError_t e = ensure_dynamic_lds((const void*)decode_kernel<T, D>, (size_t)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((decode_kernel<T, D>), dim3((unsigned)schedule_grid(s.bhk, s.G * q_len)), dim3(kDecodeThreads), lds, st,
+    hipLaunchKernelGGL((decode_kernel<T, D>), dim3((unsigned)schedule_grid(s.bhk, s.G * q_len * splits)), dim3(kDecodeThreads), lds, st,
                        (const T*)Q, (const T*)K, (const T*)V, cent, (T*)O, lse, idx, s.N, s.B, s.k, q_len,
-                       cblocks, s.scale, s.G, s.bhk, npast_max);
+                       cblocks, s.scale, s.G, s.bhk, npast_max, splits, split);
     return hipGetLastError();
 }
 
 hipError_t launch_decode(const Dims& s, int q_len, const void* Q, const void* K, const void* V,
-                         const float* cent, int cblocks, void* O, float* lse, int32_t* idx, hipStream_t st)
+                         const float* cent, int cblocks, void* O, float* lse, int32_t* idx, void* ws, hipStream_t st)
 {
     if (s.dtype == MOBA_BF16)
-        return s.D == 64 ? decode_t<bf16_t, 64>(s, q_len, Q, K, V, cent, cblocks, O, lse, idx, st)
-                         : decode_t<bf16_t, 128>(s, q_len, Q, K, V, cent, cblocks, O, lse, idx, st);
-    return s.D == 64 ? decode_t<float, 64>(s, q_len, Q, K, V, cent, cblocks, O, lse, idx, st)
-                     : decode_t<float, 128>(s, q_len, Q, K, V, cent, cblocks, O, lse, idx, st);
+        return s.D == 64 ? decode_t<bf16_t, 64>(s, q_len, Q, K, V, cent, cblocks, O, lse, idx, ws, st)
+                         : decode_t<bf16_t, 128>(s, q_len, Q, K, V, cent, cblocks, O, lse, idx, ws, st);
+    return s.D == 64 ? decode_t<float, 64>(s, q_len, Q, K, V, cent, cblocks, O, lse, idx, ws, st)
+                     : decode_t<float, 128>(s, q_len, Q, K, V, cent, cblocks, O, lse, idx, ws, st);
 }
 
 }  // namespace moba

@@ -444,9 +444,19 @@ int moba_forward(const moba_shape* shape, const void* Q, const void* K_eff, cons
         launch_forward_reference(d, Q, K_eff, V, topk_idx, O, lse, (hipStream_t)stream));
 }
 
-int moba_decode_forward(const moba_shape* shape, int32_t q_len, const void* Q, const void* K_eff,
-                        const void* V, const float* centroids, int32_t centroid_blocks, void* O,
-                        float* lse, int32_t* topk_idx, void* stream)
+int moba_decode_workspace(const moba_shape* shape, int32_t q_len, size_t* ws_bytes)
+{
+    Dims d;
+    const int st = make_dims(shape, d, true);
+    if (st != MOBA_OK) return st;
+    if (q_len <= 0 || q_len > d.N || !ws_bytes) return MOBA_EINVAL;
+    *ws_bytes = decode_ws_bytes(d, q_len);
+    return MOBA_OK;
+}
+
+int moba_decode_forward_ws(const moba_shape* shape, int32_t q_len, const void* Q, const void* K_eff,
+                           const void* V, const float* centroids, int32_t centroid_blocks, void* O,
+                           float* lse, int32_t* topk_idx, void* ws, size_t ws_bytes, void* stream)
 {
     Dims d;
     const int st = make_dims(shape, d, true);              // any seqlen: the last block may be ragged
@@ -456,8 +466,17 @@ int moba_decode_forward(const moba_shape* shape, int32_t q_len, const void* Q, c
     const int past_max = (d.N - 1) / d.B;                  // complete blocks before the last query's own
     if (d.k > 0 && past_max > 0 && (!centroids || centroid_blocks < past_max)) return MOBA_EINVAL;
     if (past_max > kMaxBlocks) return MOBA_EUNSUPPORTED;
-    return hip_status(launch_decode(d, q_len, Q, K_eff, V, centroids, centroid_blocks, O, lse, topk_idx,
+    if (ws && ws_bytes < decode_ws_bytes(d, q_len)) return MOBA_EWORKSPACE;
+    return hip_status(launch_decode(d, q_len, Q, K_eff, V, centroids, centroid_blocks, O, lse, topk_idx, ws,
                                     (hipStream_t)stream));
+}
+
+int moba_decode_forward(const moba_shape* shape, int32_t q_len, const void* Q, const void* K_eff,
+                        const void* V, const float* centroids, int32_t centroid_blocks, void* O,
+                        float* lse, int32_t* topk_idx, void* stream)
+{
+    return moba_decode_forward_ws(shape, q_len, Q, K_eff, V, centroids, centroid_blocks, O, lse, topk_idx, nullptr, 0,
+                                  stream);
 }
 
 int moba_backward_parts(const moba_shape* shape, const void* Q, const void* K_eff, const void* V,
