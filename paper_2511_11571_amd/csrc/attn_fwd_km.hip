@@ -122,24 +122,31 @@ void fwd_km_kernel(
     // The part's keys go to LDS in MFMA operand order -- the 16 bytes lane (m, h) feeds as row m,
     // channels 16 ks + 8 h .. + 8 of 32-key group gi sit at (gi * KS + ks) * 1024 + 16 * lane --, its
     // values as rows, 64-byte quarters (d = 64: halves) of row r permuted by r & 3 (r >> 1 & 1): the
-    // transpose reads below take four rows' 64 bytes at a time and so meet every bank once.  All are requested before the
-    // first one is waited for (forward of N = 524288, d = 64, 32 slices 14.61 -> 14.46 ms, of 10080, B = 96, 18 slices 157.6 -> 155.6 us).
+    // transpose reads below take four rows' 64 bytes at a time and so meet every bank once.  All values are requested before the
+    // first one is waited for, then all keys: one 16-byte piece of each after the other left a workgroup waiting for them in turn, and
+    // both together made a launch whose values come from HBM (the centroids have read the keys before) slower.  Whole step of 18 slices
+    // of 10080 (B = 96, k = 10), inputs cold: in turn 487, together 480, keys first 479, values first 473 us; forward and routing of
+    // 16 slices of 8192: 150.2, 153.9, 152.7, 149.7 us.
     {
         const char* Kg = reinterpret_cast<const char*>(K + (kvbase + own0) * D);
         const char* Vg = reinterpret_cast<const char*>(V + (kvbase + own0) * D);
         constexpr int IT = NG * 32 * C::CPR / C::NT;
-        u32x4_t kr[IT], vr[IT];
+        u32x4_t piece[IT];
 #pragma unroll
-        for (int i = 0; i < IT; ++i) {
-            kr[i] = *reinterpret_cast<const u32x4_t*>(Kg + (size_t)(i * C::NT + tid) * 16);
-            vr[i] = *reinterpret_cast<const u32x4_t*>(Vg + (size_t)(i * C::NT + tid) * 16);
-        }
+        for (int i = 0; i < IT; ++i) piece[i] = *reinterpret_cast<const u32x4_t*>(Vg + (size_t)(i * C::NT + tid) * 16);
 #pragma unroll
         for (int i = 0; i < IT; ++i) {
             const int row = (i * C::NT + tid) / C::CPR, col = (i * C::NT + tid) % C::CPR;   // key of the part, 16-byte piece
-            *reinterpret_cast<u32x4_t*>(sK + ((row >> 5) * C::KS + (col >> 1)) * 1024 + ((col & 1) * 32 + (row & 31)) * 16) = kr[i];
             const int sx = D == 64 ? (row >> 1) & 1 : row & 3;
-            *reinterpret_cast<u32x4_t*>(sV + row * 2 * D + (col ^ (sx << 2)) * 16) = vr[i];
+            *reinterpret_cast<u32x4_t*>(sV + row * 2 * D + (col ^ (sx << 2)) * 16) = piece[i];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < IT; ++i) piece[i] = *reinterpret_cast<const u32x4_t*>(Kg + (size_t)(i * C::NT + tid) * 16);
+#pragma unroll
+        for (int i = 0; i < IT; ++i) {
+            const int row = (i * C::NT + tid) / C::CPR, col = (i * C::NT + tid) % C::CPR;
+            *reinterpret_cast<u32x4_t*>(sK + ((row >> 5) * C::KS + (col >> 1)) * 1024 + ((col & 1) * 32 + (row & 31)) * 16) = piece[i];
         }
     }
     __syncthreads();
