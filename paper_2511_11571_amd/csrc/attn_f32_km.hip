@@ -11,15 +11,17 @@
 // The plain kernels of attn_reference.hip, which served these shapes, read every key row again for
 // every query (64 FMAs per 256 bytes) and ran at 5 TFLOP/s; here a key row meets 16 queries per read.
 // What bounds them now is the latency between the dependent steps of few waves: at the shape below the matrix
-// pipe is busy 49 (forward) and 43 % (backward) of the clocks, the LDS pipe 15 and 17 %, VALU issue 21 and 16 %,
-// and waves wait 60 and 42 % of their cycles.
-// fp32, 2 x 4 heads, N = 4096, d = 64, B = 64, k = 7: forward 580 -> 80 us, dQ + dK + dV 1960 -> 199 us.
+// pipe is busy 49 % of the clocks of the forward, the LDS pipe 15 %, VALU issue 21 %, and waves wait 60 % of their
+// cycles; the products of the backward alone would take 68 of its 120 us.
+// fp32, 2 x 4 heads, N = 4096, d = 64, B = 64, k = 7: forward 580 -> 80 us, dQ + dK + dV 1960 -> 144 us.
 //
 // Operand layouts (lane = 16 g + m): a contraction over channels takes channels 16 t + 4 g + i in the
 // i-th of four instructions, so that one 16-byte read per lane feeds four; a contraction over keys (or
 // queries) takes rows 4 g + i, which is where the result layout of the product before has them, and
 // its other operand comes from a row-major tile with output channel 4 m + mt, one 16-byte read for the
 // four instructions mt = 0 .. 3.  Tiles in LDS have rows of D + 4 words: both reads are conflict-free.
+#include <algorithm>
+
 #include "mfma.h"
 
 namespace moba {
@@ -402,6 +404,7 @@ __global__ __launch_bounds__(256) void fwd_f32_merge_kernel(
 //   S = Q K^T, dP = dO V^T - D        queries x keys, so that P and dS are operands over the queries
 //   dV^T += dO^T P, dK^T += Q^T dS    channels x keys, kept in registers for the whole walk
 //   dQ^T  = K^T dS^T                  dS turned over through LDS; written as a partial
+// For parts of up to three 16-key tiles (d = 128: two), where bwd_f32_wide_kernel's waves would lack keys.
 // want_dq / want_dkv: which results the caller asked for.  The dK and dV of a workgroup's waves are
 // added up through LDS; with several shares of a walk or several query heads per key/value head they go
 // to sums[dK | dV][query slice][share][N][D] and kv_sum_f32_kernel adds those up in order.
@@ -638,6 +641,296 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
     });
 }
 
+// Backward for parts of four 16-key tiles: a wave of four owns one tile and keeps what it needs of K and V in registers, as
+// matrix operands, for the whole walk: K and V of its keys for S and dP, K of all keys for its share of dQ's channels.  LDS
+// only holds the gathered rows, which all waves read, and dS, on its way from the waves of the keys to the waves of the
+// channels; both twice, so that a step of RQ queries has one barrier:
+//   S, dP -> dS to LDS; dV^T, dK^T; the next step's rows to LDS | barrier | dQ^T = K^T dS^T over all keys, a partial
+// The kernel above, whose waves take 16 queries against all keys each, kept 128 sums a wave, had room for eight waves on a compute
+// unit, and added its waves' sums up one after the other at the end, as much work as the two steps that a wave had between: at the
+// shape above 167 us (1024 workgroups of eight waves) against 120 (1536 of four), whole step 301 -> 251; 2 x 8 heads of 8192,
+// d = 128, B = 64, k = 8 2309 -> 1921 (there it could take 32 keys, so that dQ had twice the partials).
+template <int D>
+struct WideCfg {
+    static constexpr int QT = D == 64 ? 2 : 1, RQ = 16 * QT;      // 16-query tiles, queries per step
+    static constexpr int NW = 4, LD = D + 4, TL = 64 + 4, WPS = D == 64 ? 3 : 2;
+    static constexpr int words = 4 * RQ * LD + 2 * RQ * TL + 2 * 3 * RQ;
+    static constexpr size_t lds = sizeof(float) * words;
+};
+
+template <typename T>
+__device__ __forceinline__ f32x4_t four(const T* p)
+{
+    if constexpr (sizeof(T) == 4) {
+        return *reinterpret_cast<const f32x4_t*>(p);
+    } else {
+        const uint2 x = *reinterpret_cast<const uint2*>(p);
+        return f32x4_t{__uint_as_float(x.x << 16), __uint_as_float(x.x & 0xffff0000u), __uint_as_float(x.y << 16),
+                       __uint_as_float(x.y & 0xffff0000u)};
+    }
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(WideCfg<D>::NW * kWave, WideCfg<D>::WPS) void bwd_f32_wide_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
+    const float2* __restrict__ ld, const int32_t* __restrict__ idx, const int32_t* __restrict__ off,
+    const int32_t* __restrict__ ql, float* __restrict__ PdQ, T* __restrict__ dK, T* __restrict__ dV, float* __restrict__ sums, int N, int B, int n,
+    int k, int nsub, int pk, int nsplit, float scale, int64_t R, int bh, int G, int want_dq, int want_dkv)
+{
+    using C = WideCfg<D>;
+    using Ga = Gather<T, D>;
+    constexpr int NW = C::NW, LD = C::LD, TL = C::TL, QT = C::QT, RQ = C::RQ, MT = D / 16, H = D / 64;
+    constexpr int RPP = NW * kWave / Ga::CPR, NI = RQ / RPP;      // rows that the workgroup gathers at once, how often
+    static_assert(NI * RPP == RQ, "");
+    extern __shared__ __align__(16) float sm[];
+    const int tid = threadIdx.x, lane = tid % kWave, m16 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    float* const sT = sm + 4 * RQ * LD;                           // dS of a step, [query][key]
+    float* const sl = sT + 2 * RQ * TL;                           // [RQ] lse log2 e, [RQ] -D, [RQ] row of the partial
+    int s, u;
+    if (!schedule(blockIdx.x, bh, n * nsub * nsplit, s, u)) return;
+    const int split = u % nsplit, jc = u / nsplit, j = jc / nsub, c = jc - j * nsub;
+    const int own_first = c * pk, nk = min(pk, B - own_first);
+    const int64_t sbase = (int64_t)s * N, kvbase = (int64_t)(s / G) * N;
+    const int32_t* os = off + (int64_t)s * (n + 1);
+    const int lo = os[j];
+    Walk w;
+    w.nlist = os[j + 1] - lo;
+    w.src = w.nlist > 0 ? ql + (int64_t)s * R + lo : os;
+    w.llast = max(w.nlist - 1, 0);
+    w.own0 = j * B + own_first;
+    w.own_e = k << 24;
+    w.total = w.nlist + (B - own_first);
+
+    const float c2 = scale * kLog2e;
+    const int slots = (k + 1) * nsub;
+    const int grow = tid / Ga::CPR, gcol = (tid % Ga::CPR) * Ga::EPL;
+    const T* Qs = Q + sbase * D + gcol;
+    const T* Gs = dO + sbase * D + gcol;
+    const int32_t* kept = k > 0 ? idx + sbase * k : os;     // (as in the forward, like `there` below)
+    // t: entries of the rows that this thread gathers a piece of; tl (the first RQ threads): of row tid
+    auto ids = [&](int a0, int (&t)[NI], int& tl) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) t[i] = w.at(a0 + RPP * i + grow);
+        if (tid < RQ) tl = w.at(a0 + tid);
+    };
+    u32x4_t qr[NI], gr[NI];
+    float2 xl = make_float2(INFINITY, 0.f);
+    int tA[NI], tN[NI], tlA = 0, tlN = 0, there = 0;
+    auto fetch = [&](int a0) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            qr[i] = *reinterpret_cast<const u32x4_t*>(Qs + (int64_t)list_query(tA[i]) * D);
+            gr[i] = *reinterpret_cast<const u32x4_t*>(Gs + (int64_t)list_query(tA[i]) * D);
+        }
+        if (tid < RQ) {
+            xl = ld[sbase + list_query(tlA)];
+            there = kept[(int64_t)list_query(tlA) * k + min(list_slot(tlA), max(k - 1, 0))];
+        }
+    };
+    // the rows of the step at a0, which have been requested, to buffer b; the requests for the step after it
+    const int stride = RQ * nsplit;
+    auto park = [&](int a0, int b) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            float* row = sm + (2 * b * RQ + grow + RPP * i) * LD + gcol;
+            put<T>(row, qr[i]);
+            put<T>(row + RQ * LD, gr[i]);
+        }
+        if (tid < RQ) {
+            const bool live = a0 + tid < w.total;
+            float* x = sl + 3 * b * RQ + tid;
+            x[0] = live ? xl.x : INFINITY;                  // (no such row: P = 0)
+            x[RQ] = live ? xl.y : 0.f;
+            // clamped as in the forward; the partials number less than 2^31 (f32_km_path)
+            const int e = place_of(tlA, there, kept + (int64_t)list_query(tlA) * k, j, k);
+            const int prow = (int)((sbase + min(list_query(tlA), N - 1)) * slots) + min(e, k) * nsub + c;
+            reinterpret_cast<int*>(x)[2 * RQ] = live && e >= 0 ? prow : -1;
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i) tA[i] = tN[i];
+        tlA = tlN;
+        ids(a0 + 2 * stride, tN, tlN);
+        fetch(a0 + stride);
+    };
+    int a0 = RQ * split;
+    ids(a0, tA, tlA);
+    ids(a0 + stride, tN, tlN);
+
+    // operands: keys 16 wave + m16 of the part, channels 16 t + 4 g ..; keys 16 kt + 4 g + i, channel 16 (H wave + h) + m16
+    f32x4_t kop[MT], vop[MT], kq[4][H];
+    {
+        const int key = 16 * wave + m16;
+        const int64_t row = (kvbase + w.own0 + min(key, nk - 1)) * D + 4 * g;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            kop[t] = four<T>(K + row + 16 * t);
+            vop[t] = four<T>(V + row + 16 * t);
+        }
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+                    kq[kt][h][i] = to_f32<T>(K[(kvbase + w.own0 + min(16 * kt + 4 * g + i, nk - 1)) * D + 16 * (H * wave + h) + m16]);
+    }
+    fetch(a0);
+    __shared__ int odd[NW];                                 // of the rows of a wave
+    {
+        uint32_t top = 0u;
+        const bool live = 16 * wave + m16 < nk;
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (!live) kop[t][i] = vop[t][i] = 0.f;
+                top = max(top, max(__float_as_uint(kop[t][i]) & 0x7fffffffu, __float_as_uint(vop[t][i]) & 0x7fffffffu));
+            }
+        odd[wave] = __ballot(top >= 0x7f800000u) != 0;
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int h = 0; h < H; ++h) kq[kt][h][i] = 16 * kt + 4 * g + i < nk ? kq[kt][h][i] : 0.f;
+    }
+    f32x4_t dKT[MT], dVT[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) dKT[mt] = dVT[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    park(a0, 0);
+    __syncthreads();
+    for (int b = 0; a0 < w.total; a0 += stride, b ^= 1) {
+        const float* stQ = sm + 2 * b * RQ * LD;
+        const float* stG = stQ + RQ * LD;
+        float* stT = sT + b * RQ * TL;
+        const float* xb = sl + 3 * b * RQ;
+        f32x4_t x[QT], dp[QT];
+        int prow[QT];
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+            x[q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            dp[q] = *reinterpret_cast<const f32x4_t*>(xb + RQ + 16 * q + 4 * g);
+            prow[q] = reinterpret_cast<const int*>(xb)[2 * RQ + 16 * q + m16];
+        }
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            f32x4_t qv[QT], gv[QT];
+#pragma unroll
+            for (int q = 0; q < QT; ++q) {
+                qv[q] = *reinterpret_cast<const f32x4_t*>(stQ + (16 * q + m16) * LD + 16 * t + 4 * g);
+                gv[q] = *reinterpret_cast<const f32x4_t*>(stG + (16 * q + m16) * LD + 16 * t + 4 * g);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int q = 0; q < QT; ++q) {
+                    x[q] = mfma4(qv[q][i], kop[t][i], x[q]);
+                    dp[q] = mfma4(gv[q][i], vop[t][i], dp[q]);
+                }
+        }
+        // this lane: key 16 wave + m16 of the part, queries a0 + 16 q + 4 g + i, which see the keys below `seen`
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+            const f32x4_t l4 = *reinterpret_cast<const f32x4_t*>(xb + 16 * q + 4 * g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int a = a0 + 16 * q + 4 * g + i, seen = a < w.nlist ? nk : min(a - w.nlist + 1, nk);
+                const float p = 16 * wave + m16 < seen ? fast_exp2(fmaf(x[q][i], c2, -l4[i])) : 0.f;
+                x[q][i] = p;
+                dp[q][i] *= p;
+                if (want_dq) stT[(16 * q + 4 * g + i) * TL + 16 * wave + m16] = dp[q][i];
+            }
+        }
+        if (want_dkv) {
+#pragma unroll
+            for (int q = 0; q < QT; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int h = 0; h < H; ++h) {
+                        const f32x4_t qv = *reinterpret_cast<const f32x4_t*>(stQ + (16 * q + 4 * g + i) * LD + 64 * h + 4 * m16);
+                        const f32x4_t gv = *reinterpret_cast<const f32x4_t*>(stG + (16 * q + 4 * g + i) * LD + 64 * h + 4 * m16);
+#pragma unroll
+                        for (int mt = 0; mt < 4; ++mt) {
+                            dVT[4 * h + mt] = mfma4(gv[mt], x[q][i], dVT[4 * h + mt]);
+                            dKT[4 * h + mt] = mfma4(qv[mt], dp[q][i], dKT[4 * h + mt]);
+                        }
+                    }
+        }
+        park(a0 + stride, b ^ 1);
+        __syncthreads();
+        if (want_dq) {
+            f32x4_t o[QT][H];
+#pragma unroll
+            for (int q = 0; q < QT; ++q)
+#pragma unroll
+                for (int h = 0; h < H; ++h) o[q][h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt) {
+                f32x4_t ds[QT];
+#pragma unroll
+                for (int q = 0; q < QT; ++q) ds[q] = *reinterpret_cast<const f32x4_t*>(stT + (16 * q + m16) * TL + 16 * kt + 4 * g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int q = 0; q < QT; ++q)
+#pragma unroll
+                        for (int h = 0; h < H; ++h) o[q][h] = mfma4(kq[kt][h][i], ds[q][i], o[q][h]);
+            }
+#pragma unroll
+            for (int q = 0; q < QT; ++q)
+                if (prow[q] >= 0) {
+#pragma unroll
+                    for (int h = 0; h < H; ++h)
+                        *reinterpret_cast<f32x4_t*>(PdQ + (int64_t)prow[q] * D + 16 * (H * wave + h) + 4 * g) = o[q][h];
+                }
+        }
+    }
+    if (want_dkv && 16 * wave + m16 < nk) {
+        // result rows 4 g + i of tile 4 h + mt: channel 64 h + 16 g + 4 i + mt of key 16 wave + m16
+        const int64_t at = w.own0 + 16 * wave + m16;
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int ch = 64 * h + 16 * g + 4 * i;
+                const f32x4_t a = f32x4_t{dKT[4 * h][i], dKT[4 * h + 1][i], dKT[4 * h + 2][i], dKT[4 * h + 3][i]} * scale;
+                const f32x4_t v = {dVT[4 * h][i], dVT[4 * h + 1][i], dVT[4 * h + 2][i], dVT[4 * h + 3][i]};
+                if (sums) {
+                    float* dst = sums + (((int64_t)s * nsplit + split) * N + at) * D + ch;
+                    *reinterpret_cast<f32x4_t*>(dst) = a;
+                    *reinterpret_cast<f32x4_t*>(dst + (int64_t)bh * nsplit * N * D) = v;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        dK[(kvbase + at) * D + ch + e] = from_f32<T>(a[e]);
+                        dV[(kvbase + at) * D + ch + e] = from_f32<T>(v[e]);
+                    }
+                }
+            }
+    }
+    int any = 0;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) any |= odd[v];
+    if (!any || !want_dq) return;
+    __threadfence();                                        // (a row's partial is all waves' work)
+    __syncthreads();
+    if (wave >= QT) return;
+    OwnRows own(off, N, B, n, nsub, pk, nsplit, bh, G, QT);
+    own.again([&](int t, int seen) {
+        float ds = 0.f;
+        if (own.lane < seen) {
+            const int64_t key = (own.kv0 + own.lane) * D;
+            const float2 x = ld[own.q0 + t];
+            const float z = scale * kLog2e * row_dot<T, D>(Q + (own.q0 + t) * D, K + key);
+            ds = fast_exp2(z - x.x) * (row_dot<T, D>(dO + (own.q0 + t) * D, V + key) + x.y);
+        }
+        weigh_rows<T, D>(ds, seen, K + own.kv0 * D, sm + own.wave * kWave,
+                         PdQ + (((own.q0 + t) * (k + 1) + k) * nsub + own.c) * D, own.lane);
+    });
+}
+
 // dK, dV of a key/value slice = its sums over shares of the walk and query heads, in order
 template <typename T>
 __global__ __launch_bounds__(256) void kv_sum_f32_kernel(const float* __restrict__ sums, T* __restrict__ dK,
@@ -706,16 +999,18 @@ Cut cut_of(const Dims& s, int cap)
     return c;
 }
 Cut fwd_cut(const Dims& s) { return cut_of(s, 64); }
-Cut bwd_cut(const Dims& s) { return cut_of(s, s.D == 64 ? 64 : 32); }    // (d = 128: registers for the dK and dV of 32 keys)
+// backward: four tiles go to bwd_f32_wide_kernel; the other kernel has registers for the dK and dV of 48 keys (d = 128: 32)
+bool bwd_wide(const Dims& s) { return cut_of(s, 64).nt == 4; }
+Cut bwd_cut(const Dims& s) { return cut_of(s, s.D == 64 || bwd_wide(s) ? 64 : 32); }
 
 size_t partials(const Dims& s, const Cut& c) { return (size_t)s.bh * s.N * (size_t)(s.k + 1) * c.nsub; }
 
-// Shares a walk is cut into: about four workgroups per compute unit, at least one step of all waves each
-// (on average: the lists of a slice's first blocks are several times longer)
-int shares(const Dims& s, const Cut& c, int waves)
+// Shares a walk is cut into: about `aim` workgroups in all, at least one step of `rows` queries each
+// (on average: the lists of a slice's first blocks are several times longer, and a launch ends with them)
+int shares(const Dims& s, const Cut& c, int rows, int aim)
 {
-    const int64_t wgs = (int64_t)s.bh * s.n * c.nsub, steps = ((int64_t)(s.k + 1) * s.B + 16 * waves - 1) / (16 * waves);
-    const int64_t want = (1024 + wgs - 1) / wgs;
+    const int64_t wgs = (int64_t)s.bh * s.n * c.nsub, steps = ((int64_t)(s.k + 1) * s.B + rows - 1) / rows;
+    const int64_t want = std::max<int64_t>(1, (aim + wgs - 1) / wgs);
     return (int)(want < steps ? want : steps);
 }
 
@@ -729,7 +1024,7 @@ bool sums_needed(const Dims& s, int nsplit) { return s.G * nsplit > 1; }
 bool f32_km_path(const Dims& s)
 {
     return !mfma_path(s) && !(s.flags & MOBA_FLAG_REFERENCE_KERNELS) && s.B >= 8 && s.k <= kKeyMajorMaxTopk &&
-           partials(s, bwd_cut(s)) * s.D * sizeof(float) <= ((size_t)16 << 30);
+           partials(s, cut_of(s, s.D == 64 ? 64 : 32)) * s.D * sizeof(float) <= ((size_t)16 << 30);
 }
 
 size_t forward_f32_km_ws_bytes(const Dims& s)
@@ -748,7 +1043,15 @@ static size_t bwd_sums_offset(const Dims& s)
 {
     return bwd_partials_offset(s) + a256(partials(s, bwd_cut(s)) * s.D * sizeof(float));
 }
-static int bwd_shares(const Dims& s) { return s.D == 64 ? shares(s, bwd_cut(s), F32Cfg<64>::NWB) : shares(s, bwd_cut(s), F32Cfg<128>::NWB); }
+// Whole step, d = 64, B = 64, k = 7, one share against two: 1024 walks 545 -> 470 us, 2048 walks 946 -> 890; 512 walks with two, three
+// and four 273, 251 and 261.  d = 128, B = 128, k = 4, 256 walks with four, five and six 328, 330 and 335.
+static int bwd_shares(const Dims& s)
+{
+    const Cut c = bwd_cut(s);
+    if (!bwd_wide(s)) return shares(s, c, 16 * (s.D == 64 ? F32Cfg<64>::NWB : F32Cfg<128>::NWB), 1024);
+    const int64_t walks = (int64_t)s.bh * s.n * c.nsub;
+    return shares(s, c, s.D == 64 ? WideCfg<64>::RQ : WideCfg<128>::RQ, walks < 3072 ? (int)std::max<int64_t>(1280, 2 * walks) : 0);
+}
 size_t backward_f32_km_ws_bytes(const Dims& s)
 {
     const int ns = bwd_shares(s);
@@ -761,7 +1064,7 @@ static hipError_t fwd_launch_nt(const Dims& s, const Cut& c, const void* Q, cons
                                 void* O, float* lse, hipStream_t st)
 {
     using C = F32Cfg<D>;
-    const int ns = shares(s, c, C::NWF);
+    const int ns = shares(s, c, 16 * C::NWF, 1024);
     hipError_t e = ensure_dynamic_lds((const void*)fwd_f32_km_kernel<T, D, NT>, C::fwd_lds(NT));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((fwd_f32_km_kernel<T, D, NT>), dim3((unsigned)schedule_grid(s.bh, s.n * c.nsub * ns)),
@@ -774,20 +1077,28 @@ static hipError_t fwd_launch_nt(const Dims& s, const Cut& c, const void* Q, cons
     return hipGetLastError();
 }
 
-template <typename T, int D, int NT>
+template <typename T, int D, int NT>                       // NT: 4 for bwd_f32_wide_kernel
 static hipError_t bwd_launch_nt(const Dims& s, const Cut& c, const void* Q, const void* K, const void* V, const void* dO,
                                 const float2* ld, const int32_t* idx, const int32_t* off, const int32_t* ql, float* PdQ,
                                 float* sums, void* dQ, void* dK, void* dV, uint32_t parts, hipStream_t st)
 {
-    using C = F32Cfg<D>;
     const int ns = bwd_shares(s);
     const int want_dq = (parts & MOBA_BWD_DQ) != 0, want_dkv = (parts & MOBA_BWD_DKDV) != 0;
-    hipError_t e = ensure_dynamic_lds((const void*)bwd_f32_km_kernel<T, D, NT>, C::bwd_lds(NT));
+    auto go = [&](auto* kernel, int threads, size_t lds) {
+        const hipError_t e = ensure_dynamic_lds((const void*)kernel, lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)schedule_grid(s.bh, s.n * c.nsub * ns)), dim3(threads), lds, st,
+                           (const T*)Q, (const T*)K, (const T*)V, (const T*)dO, ld, idx, off, ql, PdQ, (T*)dK, (T*)dV, sums,
+                           s.N, s.B, s.n, s.k, c.nsub, c.pk, ns, s.scale, s.R, s.bh, s.G, want_dq, want_dkv);
+        return hipSuccess;
+    };
+    hipError_t e;
+    if constexpr (NT == 4) {
+        e = go(bwd_f32_wide_kernel<T, D>, WideCfg<D>::NW * kWave, WideCfg<D>::lds);
+    } else {
+        e = go(bwd_f32_km_kernel<T, D, NT>, F32Cfg<D>::NWB * kWave, F32Cfg<D>::bwd_lds(NT));
+    }
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((bwd_f32_km_kernel<T, D, NT>), dim3((unsigned)schedule_grid(s.bh, s.n * c.nsub * ns)),
-                       dim3(C::NWB * kWave), C::bwd_lds(NT), st, (const T*)Q, (const T*)K, (const T*)V, (const T*)dO, ld,
-                       idx, off, ql, PdQ, (T*)dK, (T*)dV, sums, s.N, s.B, s.n, s.k, c.nsub, c.pk, ns, s.scale, s.R, s.bh, s.G,
-                       want_dq, want_dkv);
     if (want_dkv && sums) {
         const int64_t quads = (int64_t)s.N * D / 4, total = 2 * quads * s.bhk;
         hipLaunchKernelGGL(kv_sum_f32_kernel<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, sums, (T*)dK,
@@ -850,6 +1161,7 @@ hipError_t launch_backward_f32_km(const Dims& s, const void* Q, const void* K, c
     switch (c.nt) {                             \
         case 1: MOBA_F32(T, 128, 1);            \
         case 2: MOBA_F32(T, 128, 2);            \
+        case 4: MOBA_F32(T, 128, 4);            \
     }                                           \
     return hipErrorInvalidValue
     if (s.dtype == MOBA_F32) {
