@@ -13,7 +13,7 @@
 // What bounds them now is the latency between the dependent steps of few waves: at the shape below the matrix
 // pipe is busy 49 % of the clocks of the forward, the LDS pipe 15 %, VALU issue 21 %, and waves wait 60 % of their
 // cycles; the products of the backward alone would take 68 of its 120 us.
-// fp32, 2 x 4 heads, N = 4096, d = 64, B = 64, k = 7: forward 580 -> 80 us, dQ + dK + dV 1960 -> 144 us.
+// fp32, 2 x 4 heads, N = 4096, d = 64, B = 64, k = 7: forward 580 -> 80 us, dQ + dK + dV 1960 -> 144 us (forward since: 72).
 //
 // Operand layouts (lane = 16 g + m): a contraction over channels takes channels 16 t + 4 g + i in the
 // i-th of four instructions, so that one 16-byte read per lane feeds four; a contraction over keys (or
@@ -73,17 +73,25 @@ __device__ __forceinline__ void put(float* dst, const u32x4_t& x)
     }
 }
 
-// rows first .. first + rows of X -> tile[row][D + 4]; rows nk and beyond read as zero.  True: this thread
+// the first ROWS rows of X -> tile[row][D + 4]; rows nk and beyond read as zero.  True: this thread
 // brought an infinity or a NaN
-template <typename T, int D, int NTHREADS>
-__device__ __forceinline__ bool stage_rows(const T* __restrict__ X, float* tile, int rows, int nk, int tid)
+template <typename T, int D, int ROWS, int NTHREADS>
+__device__ __forceinline__ bool stage_rows(const T* __restrict__ X, float* tile, int nk, int tid)
 {
     constexpr int CPR = Gather<T, D>::CPR, EPL = Gather<T, D>::EPL;
     uint32_t top = 0u;                                      // largest magnitude, as bits: infinities and NaN come last
-    for (int i = tid; i < rows * CPR; i += NTHREADS) {
-        const int r = i / CPR, c = i % CPR;
-        u32x4_t x = {0u, 0u, 0u, 0u};
-        if (r < nk) x = *reinterpret_cast<const u32x4_t*>(X + (size_t)r * D + c * EPL);
+    constexpr int IT = (ROWS * CPR + NTHREADS - 1) / NTHREADS;
+    u32x4_t all[IT];                                        // (requested together: forward at d = 128 818 -> 758 us)
+#pragma unroll
+    for (int u = 0; u < IT; ++u) {
+        const int i = tid + u * NTHREADS;
+        all[u] = *reinterpret_cast<const u32x4_t*>(X + (size_t)min(i / CPR, nk - 1) * D + i % CPR * EPL);
+    }
+#pragma unroll
+    for (int u = 0; u < IT; ++u) {
+        const int i = tid + u * NTHREADS, r = i / CPR, c = i % CPR;
+        if (ROWS * CPR % NTHREADS != 0 && r >= ROWS) break;
+        const u32x4_t x = r < nk ? all[u] : u32x4_t{0u, 0u, 0u, 0u};
         put<T>(tile + r * (D + 4) + c * EPL, x);
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
@@ -220,9 +228,9 @@ __global__ __launch_bounds__(F32Cfg<D>::NWF * kWave) void fwd_f32_km_kernel(
     w.own0 = j * B + own_first;
     w.own_e = k << 24;
     w.total = w.nlist + (B - own_first);
-    stage_rows<T, D, NW * kWave>(K + (kvbase + w.own0) * D, sK, 16 * NT, nk, tid);
+    stage_rows<T, D, 16 * NT, NW * kWave>(K + (kvbase + w.own0) * D, sK, nk, tid);
     __shared__ int odd[NW];                                 // of the V rows that each wave brought
-    const bool mine = stage_rows<T, D, NW * kWave>(V + (kvbase + w.own0) * D, sV, 16 * NT, nk, tid);
+    const bool mine = stage_rows<T, D, 16 * NT, NW * kWave>(V + (kvbase + w.own0) * D, sV, nk, tid);
     odd[wave] = __ballot(mine) != 0;
     __syncthreads();
 
@@ -261,19 +269,26 @@ __global__ __launch_bounds__(F32Cfg<D>::NWF * kWave) void fwd_f32_km_kernel(
         ids(a0 + 2 * stride, tN, tlN);
         fetch(tA, tlA, qr, thereA);
         __builtin_amdgcn_wave_barrier();
-        // S^T: keys x queries
-        f32x4_t x[NT];
+        // S^T: keys x queries.  Operands come from LDS one step ahead, here and below: 1 % at d = 64, 4 % at 128
+        f32x4_t x[NT], qa[2], ka[2][NT];
 #pragma unroll
         for (int kt = 0; kt < NT; ++kt) x[kt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < C::MT; ++t) {
-            const f32x4_t q = *reinterpret_cast<const f32x4_t*>(stQ + m16 * LD + 16 * t + 4 * g);
+        for (int t = -1; t < C::MT; ++t) {
+            if (t + 1 < C::MT) {
+                qa[(t + 1) & 1] = *reinterpret_cast<const f32x4_t*>(stQ + m16 * LD + 16 * (t + 1) + 4 * g);
 #pragma unroll
-            for (int kt = 0; kt < NT; ++kt) {
-                const f32x4_t a = *reinterpret_cast<const f32x4_t*>(sK + (16 * kt + m16) * LD + 16 * t + 4 * g);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) x[kt] = mfma4(a[i], q[i], x[kt]);
+                for (int kt = 0; kt < NT; ++kt)
+                    ka[(t + 1) & 1][kt] = *reinterpret_cast<const f32x4_t*>(sK + (16 * kt + m16) * LD + 16 * (t + 1) + 4 * g);
             }
+            __builtin_amdgcn_sched_barrier(0);
+            if (t >= 0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int kt = 0; kt < NT; ++kt) x[kt] = mfma4(ka[t & 1][kt][i], qa[t & 1][i], x[kt]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
         // own row r sees keys 0 .. r of the part; keys beyond the part's do not exist
         const int av = a0 + m16, r = av < w.nlist ? nk - 1 : min(av - w.nlist, nk - 1);
@@ -302,16 +317,23 @@ __global__ __launch_bounds__(F32Cfg<D>::NWF * kWave) void fwd_f32_km_kernel(
         f32x4_t o[C::MT];
 #pragma unroll
         for (int mt = 0; mt < C::MT; ++mt) o[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        f32x4_t va[2][C::H];
+        auto value = [&](int r) {
 #pragma unroll
-        for (int kt = 0; kt < NT; ++kt)
+            for (int h = 0; h < C::H; ++h)
+                va[r & 1][h] = *reinterpret_cast<const f32x4_t*>(sV + (16 * (r / 4) + 4 * g + r % 4) * LD + 64 * h + 4 * m16);
+        };
+        value(0);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+        for (int r = 0; r < 4 * NT; ++r) {
+            if (r + 1 < 4 * NT) value(r + 1);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int h = 0; h < C::H; ++h) {
-                    const f32x4_t a = *reinterpret_cast<const f32x4_t*>(sV + (16 * kt + 4 * g + i) * LD + 64 * h + 4 * m16);
+            for (int h = 0; h < C::H; ++h)
 #pragma unroll
-                    for (int mt = 0; mt < 4; ++mt) o[4 * h + mt] = mfma4(a[mt], x[kt][i], o[4 * h + mt]);
-                }
+                for (int mt = 0; mt < 4; ++mt) o[4 * h + mt] = mfma4(va[r & 1][h][mt], x[r / 4][r % 4], o[4 * h + mt]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         // the partial: this lane holds channels 64 h + 16 g .. + 15 of its row
         // (clamped: lists that do not match the rows of kept blocks give a wrong result, never an address
         // outside the partials)
@@ -441,8 +463,8 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
     w.own_e = k << 24;
     w.total = w.nlist + (B - own_first);
     __shared__ int odd[NW];                                 // of the rows that each wave brought
-    bool mine = stage_rows<T, D, NW * kWave>(K + (kvbase + w.own0) * D, sK, 16 * NT, nk, tid);
-    mine = stage_rows<T, D, NW * kWave>(V + (kvbase + w.own0) * D, sV, 16 * NT, nk, tid) || mine;
+    bool mine = stage_rows<T, D, 16 * NT, NW * kWave>(K + (kvbase + w.own0) * D, sK, nk, tid);
+    mine = stage_rows<T, D, 16 * NT, NW * kWave>(V + (kvbase + w.own0) * D, sV, nk, tid) || mine;
     odd[wave] = __ballot(mine) != 0;
     __syncthreads();
 
@@ -1014,6 +1036,15 @@ int shares(const Dims& s, const Cut& c, int rows, int aim)
     return (int)(want < steps ? want : steps);
 }
 
+// The workgroups to aim at, 512 to 768 of which run at once; with `two`, two shares also for somewhat more walks than that.
+// Forward and routing, d = 64, B = 64, k = 7: 1024 walks with one and two shares 217 and 185 us, 2048 walks 369 and 344 (d = 128: 741 and
+// 784); 512 walks with two and three 113 and 106.
+int wide_aim(const Dims& s, const Cut& c, bool two)
+{
+    const int64_t walks = (int64_t)s.bh * s.n * c.nsub;
+    return two && walks < 3072 ? (int)std::max<int64_t>(1280, 2 * walks) : 1280;
+}
+
 bool sums_needed(const Dims& s, int nsplit) { return s.G * nsplit > 1; }
 
 }  // namespace
@@ -1049,8 +1080,7 @@ static int bwd_shares(const Dims& s)
 {
     const Cut c = bwd_cut(s);
     if (!bwd_wide(s)) return shares(s, c, 16 * (s.D == 64 ? F32Cfg<64>::NWB : F32Cfg<128>::NWB), 1024);
-    const int64_t walks = (int64_t)s.bh * s.n * c.nsub;
-    return shares(s, c, s.D == 64 ? WideCfg<64>::RQ : WideCfg<128>::RQ, walks < 3072 ? (int)std::max<int64_t>(1280, 2 * walks) : 0);
+    return shares(s, c, s.D == 64 ? WideCfg<64>::RQ : WideCfg<128>::RQ, wide_aim(s, c, true));
 }
 size_t backward_f32_km_ws_bytes(const Dims& s)
 {
@@ -1064,7 +1094,7 @@ static hipError_t fwd_launch_nt(const Dims& s, const Cut& c, const void* Q, cons
                                 void* O, float* lse, hipStream_t st)
 {
     using C = F32Cfg<D>;
-    const int ns = shares(s, c, 16 * C::NWF, 1024);
+    const int ns = shares(s, c, 16 * C::NWF, wide_aim(s, c, D == 64));
     hipError_t e = ensure_dynamic_lds((const void*)fwd_f32_km_kernel<T, D, NT>, C::fwd_lds(NT));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((fwd_f32_km_kernel<T, D, NT>), dim3((unsigned)schedule_grid(s.bh, s.n * c.nsub * ns)),
