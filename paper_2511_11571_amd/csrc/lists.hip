@@ -2,7 +2,7 @@
 // "Reformatting Indices to Varlen Key-Block-Major").  The paper scatters with global
 // atomics, which leaves the order inside a list to chance; here the lists come out
 // ascending and bit-reproducible:
-//   1. count: a workgroup takes a chunk of 256 consecutive queries and ORs one bit per
+//   1. count: a workgroup takes a chunk of 256 consecutive queries (several, where routing is sparse) and ORs one bit per
 //      (query, kept block) into an LDS bit matrix [block][256 bits]; the population
 //      count of a row is the number of queries of this chunk that kept that block.
 //   2. scan: per key block an exclusive scan over chunks (start of each chunk's segment
@@ -22,10 +22,12 @@
 // workgroup is the number of set bits below r in b's row of the bit matrix, and is stored there at once.
 // (Collecting e per run in LDS first and writing row by row took longer at every shape measured; without
 // places the walk over the rows of the matrix is the faster one up to 4096 blocks.)
-// us, both passes and scans, before -> after: 32 slices, N = 524288, 4096 blocks, k = 8: 4180 -> 2890;
-// 16 slices, N = 131072, 1024 blocks, k = 8: 261 -> 151, 2048 blocks, k = 32: 693 -> 637; 8 slices, N = 131072,
+// us, both passes and scans, before -> after: 32 slices, N = 524288, 4096 blocks, k = 8: 4180 -> 2890
+// (with several chunks to a workgroup since: 1935); 16 slices, N = 131072, 1024 blocks, k = 8: 261 -> 151, 2048 blocks, k = 32: 693 -> 637; 8 slices, N = 131072,
 // 4096 blocks, k = 32: 552 -> 356; 16 slices, N = 16384, 256 blocks, k = 16: 55 -> 38.  Bound by the scattered
 // 4-byte stores and, in the count, by the walk over a matrix that is mostly empty.
+#include <algorithm>
+
 #include "mfma.h"
 
 namespace moba {
@@ -145,99 +147,133 @@ __device__ __forceinline__ void starts_from_counts(const int32_t* __restrict__ c
 }
 
 // kRange: key blocks per LDS bit matrix (blockIdx.y counts the ranges of a slice's blocks).
-// SELF (fill, one range): no scans went before, see above
+// A workgroup takes `group` chunks one after the other; the counts are those of all of them, and `groups` of a slice are scanned.
+// SELF (fill, one range, one chunk): no scans went before, see above
 template <bool FILL, bool SLOTS, int kRange, bool SELF = false>
 __global__ __launch_bounds__(256) void lists_chunk_kernel(
     const int32_t* __restrict__ idx, int32_t* __restrict__ cnt2, int32_t* __restrict__ off,
-    int32_t* __restrict__ ql, int N, int B, int n, int k, int nchunk, int64_t R, int bh)
+    int32_t* __restrict__ ql, int N, int B, int n, int k, int groups, int group, int64_t R, int bh)
 {
     __shared__ __align__(16) uint32_t mask[kRange * kWords];
-    __shared__ int32_t start[FILL ? kRange : 1];         // where this workgroup's queries start in each list
+    __shared__ int32_t start[FILL ? kRange : 1];         // where the next chunk's queries start in each list
     // consecutive query chunks of a slice go to the same XCD: the 128-byte lines of a block's
     // list are completed by neighbouring chunks and should meet in one L2 before they are written back
     int c, s;
-    if (!schedule(blockIdx.x, bh, nchunk, s, c)) return;
+    if (!schedule(blockIdx.x, bh, groups, s, c)) return;
     const int lo = blockIdx.y * kRange;
     const int hi = min(n, lo + kRange);
-    const int t0 = c * kListQ;
-    const int rows = min(N - t0, kListQ);
-    const int nblk = min(hi, (t0 + rows - 1) / B) - lo;   // kept blocks are < own block of the last query
+    const int first = c * group * kListQ, end = min(N, first + group * kListQ);
+    // kept blocks are < own block of the query: of a chunk's last, of the last of all
+    auto blocks = [&](int queries_end) { return min(hi, (queries_end - 1) / B) - lo; };
+    const int most = blocks(end);
     const int tid = threadIdx.x;
-    int32_t* crow = cnt2 + ((int64_t)s * (nchunk + 1) + c) * n + lo;
+    int32_t* crow = cnt2 + ((int64_t)s * (groups + 1) + c) * n + lo;
     if constexpr (SELF)
-        starts_from_counts<kRange>(cnt2 + (int64_t)s * (nchunk + 1) * n, off + (int64_t)s * (n + 1), n, nchunk, c,
+        starts_from_counts<kRange>(cnt2 + (int64_t)s * (groups + 1) * n, off + (int64_t)s * (n + 1), n, groups, c,
                                    reinterpret_cast<int32_t*>(mask), start, tid);
-    if (nblk <= 0) {
+    if (most <= 0) {
         if (!FILL)
             for (int j = tid; j < hi - lo; j += 256) crow[j] = 0;
         return;
     }
-    for (int i = tid; i < nblk * kWords; i += 256) mask[i] = 0u;
+    for (int i = tid; i < most * kWords; i += 256) mask[i] = 0u;
     if (FILL && !SELF) {
         const int32_t* orow = off + (int64_t)s * (n + 1) + lo;
-        for (int j = tid; j < nblk; j += 256) {
+        for (int j = tid; j < most; j += 256) {
             start[j] = orow[j] + crow[j];
         }
     }
-    __syncthreads();
-    const int32_t* rows0 = idx + ((int64_t)s * N + t0) * k;
-    // only past blocks count: lists never exceed R
-    for_each_entry(rows0, rows, k, tid, [&](int r, int b) {
-        b -= lo;
-        // (block b + lo lies before the own block of query t0 + r: its last key does)
-        if (b >= 0 && b < nblk && (b + lo + 1) * B <= t0 + r) atomicOr(&mask[b * kWords + (r >> 5)], 1u << (r & 31));
-    });
-    __syncthreads();
-    if (!FILL) {
-        for (int j = tid; j < hi - lo; j += 256) {
-            int c0 = 0;
-            if (j < nblk) {
+    auto bits_of = [&](int j) {
+        int c0 = 0;
 #pragma unroll
-                for (int wd = 0; wd < kWords; ++wd) c0 += __popc(mask[j * kWords + wd]);
-            }
-            crow[j] = c0;
-        }
-    } else if constexpr (SLOTS) {
-        int32_t* qs = ql + (int64_t)s * R;
-        for_each_entry_slot(rows0, rows, k, tid, [&](int r, int b, int e) {
+        for (int wd = 0; wd < kWords; ++wd) c0 += __popc(mask[j * kWords + wd]);
+        return c0;
+    };
+    auto clear = [&](int j) {
+#pragma unroll
+        for (int wd = 0; wd < kWords; ++wd) mask[j * kWords + wd] = 0u;
+    };
+    int count[FILL ? 1 : kRange / 256] = {};             // of blocks tid + 256 u
+    for (int t0 = first; t0 < end; t0 += kListQ) {
+        const int rows = min(end - t0, kListQ), nblk = blocks(t0 + rows);
+        if (nblk <= 0) continue;
+        const bool more = t0 + kListQ < end;
+        __syncthreads();
+        const int32_t* rows0 = idx + ((int64_t)s * N + t0) * k;
+        // only past blocks count: lists never exceed R
+        for_each_entry(rows0, rows, k, tid, [&](int r, int b) {
             b -= lo;
-            if (b >= 0 && b < nblk && (b + lo + 1) * B <= t0 + r) {
-                const uint32_t* mrow = mask + b * kWords;
-                const int last = r >> 5;
-                int rank = 0;
-#pragma unroll
-                for (int wd = 0; wd < kWords; ++wd) {
-                    const uint32_t below = wd < last ? ~0u : wd == last ? (1u << (r & 31)) - 1u : 0u;
-                    rank += __popc(mrow[wd] & below);
-                }
-                const int64_t pos = (int64_t)start[b] + rank;
-                // a routing that breaks the contract (repeats, too many kept blocks) must not
-                // write outside the slice's lists
-                if (pos < R) qs[pos] = (t0 + r) | e << kQueryBits;
-            }
+            // (block b + lo lies before the own block of query t0 + r: its last key does)
+            if (b >= 0 && b < nblk && (b + lo + 1) * B <= t0 + r) atomicOr(&mask[b * kWords + (r >> 5)], 1u << (r & 31));
         });
-    } else {
-        // Eight lanes per block, one 32-query word each: a lane writes the queries of its word
-        // after those of the lanes before it.  The 256 queries of this workgroup are neighbours
-        // in every list, so a store instruction touches one short run of addresses per block.
-        int32_t* qs = ql + (int64_t)s * R;
-        const int lane8 = tid & 7;
-        for (int b = tid >> 3; b < nblk; b += 256 / 8) {
-            uint32_t word = mask[b * kWords + lane8];
-            const int cnt = __popc(word);
-            int incl = cnt;
+        __syncthreads();
+        if constexpr (!FILL) {
 #pragma unroll
-            for (int o = 1; o < 8; o <<= 1) {
-                const int up = __shfl_up(incl, o, 8);
-                if (lane8 >= o) incl += up;
+            for (int u = 0; u < kRange / 256; ++u) {
+                const int j = tid + 256 * u;
+                if (j >= nblk) break;
+                count[u] += bits_of(j);
+                if (more) clear(j);
             }
-            int64_t pos = (int64_t)start[b] + (incl - cnt);
-            while (word) {
-                if (pos < R) qs[pos] = t0 + 32 * lane8 + (__ffs(word) - 1);      // (as above)
-                ++pos;
-                word &= word - 1u;
+        } else if constexpr (SLOTS) {
+            int32_t* qs = ql + (int64_t)s * R;
+            for_each_entry_slot(rows0, rows, k, tid, [&](int r, int b, int e) {
+                b -= lo;
+                if (b >= 0 && b < nblk && (b + lo + 1) * B <= t0 + r) {
+                    const uint32_t* mrow = mask + b * kWords;
+                    const int last = r >> 5;
+                    int rank = 0;
+#pragma unroll
+                    for (int wd = 0; wd < kWords; ++wd) {
+                        const uint32_t below = wd < last ? ~0u : wd == last ? (1u << (r & 31)) - 1u : 0u;
+                        rank += __popc(mrow[wd] & below);
+                    }
+                    const int64_t pos = (int64_t)start[b] + rank;
+                    // a routing that breaks the contract (repeats, too many kept blocks) must not
+                    // write outside the slice's lists
+                    if (pos < R) qs[pos] = (t0 + r) | e << kQueryBits;
+                }
+            });
+            if (more) {
+                __syncthreads();
+                for (int j = tid; j < nblk; j += 256) {
+                    start[j] += bits_of(j);
+                    clear(j);
+                }
+            }
+        } else {
+            // Eight lanes per block, one 32-query word each: a lane writes the queries of its word
+            // after those of the lanes before it.  The 256 queries of a chunk are neighbours
+            // in every list, so a store instruction touches one short run of addresses per block.
+            int32_t* qs = ql + (int64_t)s * R;
+            const int lane8 = tid & 7;
+            for (int b = tid >> 3; b < nblk; b += 256 / 8) {
+                uint32_t word = mask[b * kWords + lane8];
+                const int cnt = __popc(word);
+                int incl = cnt;
+#pragma unroll
+                for (int o = 1; o < 8; o <<= 1) {
+                    const int up = __shfl_up(incl, o, 8);
+                    if (lane8 >= o) incl += up;
+                }
+                const int at = start[b];
+                int64_t pos = (int64_t)at + (incl - cnt);
+                while (word) {
+                    if (pos < R) qs[pos] = t0 + 32 * lane8 + (__ffs(word) - 1);      // (as above)
+                    ++pos;
+                    word &= word - 1u;
+                }
+                if (more) {                              // (the eight lanes of a block are one wave's: all have read)
+                    mask[b * kWords + lane8] = 0u;
+                    if (lane8 == 7) start[b] = at + incl;
+                }
             }
         }
+    }
+    if constexpr (!FILL) {
+#pragma unroll
+        for (int u = 0; u < kRange / 256; ++u)
+            if (tid + 256 * u < hi - lo) crow[tid + 256 * u] = count[u];
     }
 }
 
@@ -432,28 +468,43 @@ static bool fill_adds_up(const Dims& s)
     return s.R > 0 && counts <= kSelfCounts && counts * s.nchunk * s.bh <= kSelfAdditions;
 }
 
+// Chunks that a workgroup takes one after the other: what they cost in memory is then one count per block, written, scanned (two
+// reads and a write) and read back, for all of them.  As many as leave 4096 workgroups and bring a block about two queries: beyond
+// that the lists cost more than the counts, and workgroups far apart share fewer of the lists' lines in an L2 at a time.
+// us of the whole builder, one chunk -> this many: 32 slices, N = 524288, 4096 blocks, k = 8 (4 chunks) 2890 -> 1935;
+// 16 slices, N = 524288, 4096 blocks, k = 2 (16) 1176 -> 421; 16 slices, N = 261888, 2728 blocks, k = 10 (2) 807 -> 689, with 4 765,
+// 8 869; 64 slices, N = 65536, 2048 blocks, k = 4 (4) 290 -> 204; 16 slices, N = 131072, 2048 blocks, k = 32 (1) 637, with 4 714.
+constexpr int kGroupWgs = 4096, kGroupRows = 2, kGroupMost = 16;
+static int chunks_together(const Dims& s, int nranges)
+{
+    const int64_t wgs = (int64_t)s.bh * s.nchunk * nranges;
+    const int64_t group = std::min<int64_t>(wgs / kGroupWgs, (int64_t)kGroupRows * s.n / std::max(1, kListQ * s.k));
+    return (int)std::min<int64_t>(std::max<int64_t>(group, 1), kGroupMost);
+}
+
 template <int RANGE>
 static hipError_t build_lists_launch(const Dims& s, const int32_t* idx, int32_t* off, int32_t* ql,
                                      int32_t* cnt2, hipStream_t st)
 {
     const int nranges = (s.n + RANGE - 1) / RANGE;
-    dim3 grid(schedule_grid(s.bh, s.nchunk), nranges), block(256);
+    const int group = chunks_together(s, nranges), groups = (s.nchunk + group - 1) / group;
+    dim3 grid(schedule_grid(s.bh, groups), nranges), block(256);
     hipLaunchKernelGGL((lists_chunk_kernel<false, false, RANGE>), grid, block, 0, st, idx, cnt2, off, ql, s.N, s.B,
-                       s.n, s.k, s.nchunk, s.R, s.bh);
+                       s.n, s.k, groups, group, s.R, s.bh);
     static_assert(kKeyMajorMaxTopk <= 127, "the place of a block in the high byte of an entry");
     const bool places = lists_with_places(s);
 #define MOBA_FILL(PLACES, SELF)                                                                                          \
     hipLaunchKernelGGL((lists_chunk_kernel<true, PLACES, RANGE, SELF>), grid, block, 0, st, idx, cnt2, off, ql, s.N, s.B, \
-                       s.n, s.k, s.nchunk, s.R, s.bh)
+                       s.n, s.k, groups, group, s.R, s.bh)
     // (without places this range serves slices of more than kRangeMax blocks, which have too many counts)
     if constexpr (RANGE == kRangeLong) {
-        if (places && s.n <= RANGE && fill_adds_up(s)) {
+        if (places && s.n <= RANGE && group == 1 && fill_adds_up(s)) {
             MOBA_FILL(true, true);
             return hipGetLastError();
         }
     }
     hipLaunchKernelGGL(lists_scan_kernel, dim3((s.n + 31) / 32, s.bh), block, 0, st, cnt2, off, s.n,
-                       s.nchunk);
+                       groups);
     hipLaunchKernelGGL(lists_offsets_kernel, dim3(s.bh), block, 0, st, off, s.n);
     if (s.R > 0) {
         if (places) MOBA_FILL(true, false);
