@@ -865,31 +865,46 @@ __global__ __launch_bounds__(WideCfg<D>::NW * kWave, WideCfg<D>::WPS) void bwd_f
             }
         }
         if (want_dkv) {
+            // (the sums of sixteen queries first, then the walk's: one chain over all of a walk's queries is 5 % further from 64 bits than
+            // the waves of bwd_f32_km_kernel, which share them out; so it is no further)
+            auto add = [&](const float* rows, const f32x4_t (&y)[QT], f32x4_t (&acc)[MT]) {
 #pragma unroll
-            for (int q = 0; q < QT; ++q)
+                for (int h = 0; h < H; ++h) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                    for (int q = 0; q < QT; ++q) {
+                        f32x4_t z[4];
 #pragma unroll
-                    for (int h = 0; h < H; ++h) {
-                        const f32x4_t qv = *reinterpret_cast<const f32x4_t*>(stQ + (16 * q + 4 * g + i) * LD + 64 * h + 4 * m16);
-                        const f32x4_t gv = *reinterpret_cast<const f32x4_t*>(stG + (16 * q + 4 * g + i) * LD + 64 * h + 4 * m16);
+                        for (int mt = 0; mt < 4; ++mt) z[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int mt = 0; mt < 4; ++mt) {
-                            dVT[4 * h + mt] = mfma4(gv[mt], x[q][i], dVT[4 * h + mt]);
-                            dKT[4 * h + mt] = mfma4(qv[mt], dp[q][i], dKT[4 * h + mt]);
+                        for (int i = 0; i < 4; ++i) {
+                            const f32x4_t v = *reinterpret_cast<const f32x4_t*>(rows + (16 * q + 4 * g + i) * LD + 64 * h + 4 * m16);
+#pragma unroll
+                            for (int mt = 0; mt < 4; ++mt) z[mt] = mfma4(v[mt], y[q][i], z[mt]);
                         }
+#pragma unroll
+                        for (int mt = 0; mt < 4; ++mt) acc[4 * h + mt] += z[mt];
                     }
+                }
+            };
+            add(stG, x, dVT);
+            add(stQ, dp, dKT);
         }
         park(a0 + stride, b ^ 1);
         __syncthreads();
         if (want_dq) {
-            f32x4_t o[QT][H];
+            f32x4_t o[QT][H], half[QT][H];                  // (d = 128: of 32 keys each)
 #pragma unroll
             for (int q = 0; q < QT; ++q)
 #pragma unroll
                 for (int h = 0; h < H; ++h) o[q][h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kt = 0; kt < 4; ++kt) {
+                if (D == 128 && kt == 2) {
+#pragma unroll
+                    for (int q = 0; q < QT; ++q)
+#pragma unroll
+                        for (int h = 0; h < H; ++h) { half[q][h] = o[q][h]; o[q][h] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+                }
                 f32x4_t ds[QT];
 #pragma unroll
                 for (int q = 0; q < QT; ++q) ds[q] = *reinterpret_cast<const f32x4_t*>(stT + (16 * q + m16) * TL + 16 * kt + 4 * g);
@@ -899,6 +914,12 @@ __global__ __launch_bounds__(WideCfg<D>::NW * kWave, WideCfg<D>::WPS) void bwd_f
                     for (int q = 0; q < QT; ++q)
 #pragma unroll
                         for (int h = 0; h < H; ++h) o[q][h] = mfma4(kq[kt][h][i], ds[q][i], o[q][h]);
+            }
+            if constexpr (D == 128) {
+#pragma unroll
+                for (int q = 0; q < QT; ++q)
+#pragma unroll
+                    for (int h = 0; h < H; ++h) o[q][h] += half[q][h];
             }
 #pragma unroll
             for (int q = 0; q < QT; ++q)

@@ -126,27 +126,31 @@ void fwd_km_kernel(
     // first one is waited for, then all keys: one 16-byte piece of each after the other left a workgroup waiting for them in turn, and
     // both together made a launch whose values come from HBM (the centroids have read the keys before) slower.  Whole step of 18 slices
     // of 10080 (B = 96, k = 10), inputs cold: in turn 487, together 480, keys first 479, values first 473 us; forward and routing of
-    // 16 slices of 8192: 150.2, 153.9, 152.7, 149.7 us.
+    // 16 slices of 8192: 150.2, 153.9, 152.7, 149.7 us.  One piece of each (d = 64, B = 32) comes at once: 12 slices of 38848, k = 8,
+    // kernel 255 us, values first 271.
     {
         const char* Kg = reinterpret_cast<const char*>(K + (kvbase + own0) * D);
         const char* Vg = reinterpret_cast<const char*>(V + (kvbase + own0) * D);
         constexpr int IT = NG * 32 * C::CPR / C::NT;
-        u32x4_t piece[IT];
+        u32x4_t vr[IT], kr[IT];
 #pragma unroll
-        for (int i = 0; i < IT; ++i) piece[i] = *reinterpret_cast<const u32x4_t*>(Vg + (size_t)(i * C::NT + tid) * 16);
+        for (int i = 0; i < IT; ++i) vr[i] = *reinterpret_cast<const u32x4_t*>(Vg + (size_t)(i * C::NT + tid) * 16);
+        if constexpr (IT == 1) kr[0] = *reinterpret_cast<const u32x4_t*>(Kg + (size_t)tid * 16);
 #pragma unroll
         for (int i = 0; i < IT; ++i) {
             const int row = (i * C::NT + tid) / C::CPR, col = (i * C::NT + tid) % C::CPR;   // key of the part, 16-byte piece
             const int sx = D == 64 ? (row >> 1) & 1 : row & 3;
-            *reinterpret_cast<u32x4_t*>(sV + row * 2 * D + (col ^ (sx << 2)) * 16) = piece[i];
+            *reinterpret_cast<u32x4_t*>(sV + row * 2 * D + (col ^ (sx << 2)) * 16) = vr[i];
         }
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (IT > 1) {
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < IT; ++i) piece[i] = *reinterpret_cast<const u32x4_t*>(Kg + (size_t)(i * C::NT + tid) * 16);
+            for (int i = 0; i < IT; ++i) kr[i] = *reinterpret_cast<const u32x4_t*>(Kg + (size_t)(i * C::NT + tid) * 16);
+        }
 #pragma unroll
         for (int i = 0; i < IT; ++i) {
             const int row = (i * C::NT + tid) / C::CPR, col = (i * C::NT + tid) % C::CPR;
-            *reinterpret_cast<u32x4_t*>(sK + ((row >> 5) * C::KS + (col >> 1)) * 1024 + ((col & 1) * 32 + (row & 31)) * 16) = piece[i];
+            *reinterpret_cast<u32x4_t*>(sK + ((row >> 5) * C::KS + (col >> 1)) * 1024 + ((col & 1) * 32 + (row & 31)) * 16) = kr[i];
         }
     }
     __syncthreads();
