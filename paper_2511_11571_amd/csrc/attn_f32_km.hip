@@ -12,8 +12,8 @@
 // every query (64 FMAs per 256 bytes) and ran at 5 TFLOP/s; here a key row meets 16 queries per read.
 // What bounds them now is the latency between the dependent steps of few waves: at the shape below the matrix
 // pipe is busy 49 % of the clocks of the forward, the LDS pipe 15 %, VALU issue 21 %, and waves wait 60 % of their
-// cycles; the products of the backward alone would take 68 of its 120 us.
-// fp32, 2 x 4 heads, N = 4096, d = 64, B = 64, k = 7: forward 580 -> 80 us, dQ + dK + dV 1960 -> 144 us (forward since: 72).
+// cycles; the products of the backward alone would take 68 of its 131 us.
+// fp32, 2 x 4 heads, N = 4096, d = 64, B = 64, k = 7: forward 580 -> 80 us, dQ + dK + dV 1960 -> 155 us (forward since: 75).
 //
 // Operand layouts (lane = 16 g + m): a contraction over channels takes channels 16 t + 4 g + i in the
 // i-th of four instructions, so that one 16-byte read per lane feeds four; a contraction over keys (or
@@ -670,8 +670,8 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
 //   S, dP -> dS to LDS; dV^T, dK^T; the next step's rows to LDS | barrier | dQ^T = K^T dS^T over all keys, a partial
 // The kernel above, whose waves take 16 queries against all keys each, kept 128 sums a wave, had room for eight waves on a compute
 // unit, and added its waves' sums up one after the other at the end, as much work as the two steps that a wave had between: at the
-// shape above 167 us (1024 workgroups of eight waves) against 120 (1536 of four), whole step 301 -> 251; 2 x 8 heads of 8192,
-// d = 128, B = 64, k = 8 2309 -> 1921 (there it could take 32 keys, so that dQ had twice the partials).
+// shape above 167 us (1024 workgroups of eight waves) against 131 (1536 of four), whole step 301 -> 256; 2 x 8 heads of 8192,
+// d = 128, B = 64, k = 8 2309 -> 1875 (there it could take 32 keys, so that dQ had twice the partials).
 template <int D>
 struct WideCfg {
     static constexpr int QT = D == 64 ? 2 : 1, RQ = 16 * QT;      // 16-query tiles, queries per step
@@ -866,7 +866,8 @@ __global__ __launch_bounds__(WideCfg<D>::NW * kWave, WideCfg<D>::WPS) void bwd_f
         }
         if (want_dkv) {
             // (the sums of sixteen queries first, then the walk's: one chain over all of a walk's queries is 5 % further from 64 bits than
-            // the waves of bwd_f32_km_kernel, which share them out; so it is no further)
+            // the waves of bwd_f32_km_kernel, which share them out; so it is no further: dK of 4096 queries, k = 7 4.71e-7, now 4.47e-7, there
+            // 4.50e-7; for 32 queries at a time 4.51e-7 and, of 2048, B = 128, k = 3, 4.19e-7 against 4.15e-7, but 12 us less)
             auto add = [&](const float* rows, const f32x4_t (&y)[QT], f32x4_t (&acc)[MT]) {
 #pragma unroll
                 for (int h = 0; h < H; ++h) {
@@ -1095,7 +1096,7 @@ static size_t bwd_sums_offset(const Dims& s)
 {
     return bwd_partials_offset(s) + a256(partials(s, bwd_cut(s)) * s.D * sizeof(float));
 }
-// Whole step, d = 64, B = 64, k = 7, one share against two: 1024 walks 545 -> 470 us, 2048 walks 946 -> 890; 512 walks with two, three
+// Whole step (with one chain of sums per walk), d = 64, B = 64, k = 7, one share against two: 1024 walks 545 -> 470 us, 2048 walks 946 -> 890; 512 walks with two, three
 // and four 273, 251 and 261.  d = 128, B = 128, k = 4, 256 walks with four, five and six 328, 330 and 335.
 static int bwd_shares(const Dims& s)
 {
