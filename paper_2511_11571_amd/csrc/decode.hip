@@ -622,8 +622,9 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
             for (int x = 1; x < kDecodeSplits; ++x) top = fmaxf(top, mx[x]);
             L = o = 0.f;
 #pragma unroll
-            for (int x = 0; x < kDecodeSplits; ++x) {
-                const float wt = x < splits ? weight(mx[x], top) : 0.f;
+            for (int x = 0; x < kDecodeSplits; ++x) {       // (left out, not weighted by zero: a part may be infinite)
+                if (x >= splits) break;
+                const float wt = weight(mx[x], top);
                 L = fmaf(wt, lx[x], L);
                 o = fmaf(wt, ox[x], o);
             }

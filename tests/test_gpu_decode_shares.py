@@ -103,6 +103,29 @@ def test_shared_queries(case):
     assert torch.equal(O, first[0]) and torch.equal(lse, first[1])
 
 
+def _infinite_values(heads, N, d, B, k, keys):
+    """Queries that attend all N keys, keys[c] with an infinite value in channel c: infinite exactly there, as every
+    key's weight is positive, and the other channels as without."""
+    assert (N - 1) // B <= k and len(keys) < d
+    sh, Q, K, V, cent = _case(1, heads, 0, N, d, B, k, 1, binding.BF16)
+    want, lse, _ = moba.decode_forward(sh, 1, Q, K, V, cent)
+    for c, key in enumerate(keys):
+        V[0, :, key, c] = float("inf")
+    got = moba.decode_forward(sh, 1, Q, K, V, cent)
+    assert torch.equal(got[1], lse)
+    assert bool((got[0][..., :len(keys)] == float("inf")).all()), got[0][..., :len(keys)]
+    assert torch.equal(got[0][..., len(keys):], want[..., len(keys):])
+
+
+@pytest.mark.parametrize("heads,N,d,B,k,workgroups", [(1, 4001, 64, 128, 31, 4), (1, 1999, 128, 64, 31, 4), (40, 4001, 64, 128, 31, 2),
+                                                      (1, 4100, 64, 128, 32, 8)])
+def test_infinite_values_of_every_share(heads, N, d, B, k, workgroups):
+    """... in two keys from the middle of each workgroup's share (whole load instructions of 512 / d keys)."""
+    each = -(-N // (workgroups * 512 // d)) * (512 // d)
+    assert workgroups == _workgroups(_shape(1, heads, 0, N, d, B, k, 1, binding.BF16), 1)
+    _infinite_values(heads, N, d, B, k, [each * w + each // 2 + i for w in range(workgroups) for i in (0, 5)])
+
+
 def test_shared_queries_in_a_graph():
     sh, Q, K, V, cent = _case(*SHARED[1])
     eager = moba.decode_forward(sh, 1, Q, K, V, cent, want_idx=False)
@@ -131,6 +154,12 @@ def test_workspace_sizes():
     one = ctypes.c_void_p(256)                                                # (never dereferenced: refused on the host)
     assert binding.lib().moba_decode_forward_ws(ctypes.byref(sh.c()), 1, one, one, one, one, 70, one, one, None, one,
                                                 ctypes.c_size_t(n - 1), None) == -3
+
+
+def _workgroups(sh, q_len):
+    """Workgroups per query, from the size of the workspace: a counter per query, rounded up, and d + 2 floats a workgroup."""
+    need, queries = binding._decode_workspace_bytes(sh, q_len), sh.batch * sh.heads * q_len
+    return max(1, (need - (8 * queries + 255) // 256 * 256) // (queries * (sh.head_dim + 2) * 4))
 
 
 def _shape(batch, heads, kv, N, d, B, k, q_len, dtype):
