@@ -479,7 +479,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
         constexpr int NB = decltype(size)::value;           // load instructions of K (and of V) in flight
         constexpr bool ALL = decltype(all_live)::value;     // every position of the batch exists
         uint4 kr[NB], vr[NB];
-        // (past the end: some row that is attended anyway, weight 0)
+        // (past the end: some row that is attended anyway, logit -inf and values 0)
         if (whole) {
 #pragma unroll
             for (int u = 0; u < NB; ++u) {
@@ -516,7 +516,10 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
                 for (int e = 0; e < EPL; ++e) a = fmaf(f[e], __uint_as_float(qb[e]), a);
             }
             z[u] = row_sum<LPR>(a) * c2;
-            if (!ALL && p0 + u * (NW * RPI) + kslot >= total) z[u] = -INFINITY;
+            if (!ALL && p0 + u * (NW * RPI) + kslot >= total) {
+                z[u] = -INFINITY;
+                vr[u] = make_uint4(0u, 0u, 0u, 0u);         // (weight 0 times an infinity would add NaN)
+            }
             top = fmaxf(top, z[u]);
         }
         // (a lane group without a key so far that exists and has a finite logit keeps m = -inf, l = 0: exponents
@@ -529,6 +532,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
         for (int e = 0; e < EPL; ++e) acc[e] *= alpha;
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
+            if (!ALL && p0 + u * (NW * RPI) >= total) break;        // (uniform: no lane has a position left)
             const float p = __builtin_amdgcn_exp2f(z[u] - ref);
             float f[EPL];
             widen(vr[u], f);
@@ -538,7 +542,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
         }
     };
     // Batches of eight instructions; the last few go into a batch of four where that holds them (rows past the end are
-    // read and weighted like others).  Batches of ten for the ninth and tenth, of two, and a second batch on its way while one is
+    // read like others).  Batches of ten for the ninth and tenth, of two, and a second batch on its way while one is
     // worked on were no better over the range of sizes.
     {
         constexpr int STEP = NW * RPI;

@@ -126,6 +126,16 @@ def test_infinite_values_of_every_share(heads, N, d, B, k, workgroups):
     _infinite_values(heads, N, d, B, k, [each * w + each // 2 + i for w in range(workgroups) for i in (0, 5)])
 
 
+@pytest.mark.parametrize("heads,N,d,B,k,workgroups", [(1, 4001, 64, 128, 31, 4), (1, 4100, 64, 128, 32, 8), (40, 2013, 128, 33, 60, 2), (1, 1999, 128, 64, 31, 4),
+                                                      (3, 700, 64, 64, 10, 1), (2, 1000, 128, 33, 30, 1)])
+def test_infinite_values_around_the_ends_of_shares(heads, N, d, B, k, workgroups):
+    """... in the last and first keys of shares, of the own block and of the sequence: rows that a neighbour's last loads read too."""
+    each = -(-N // (workgroups * 512 // d)) * (512 // d)
+    assert workgroups == _workgroups(_shape(1, heads, 0, N, d, B, k, 1, binding.BF16), 1)
+    edges = [each * w + i for w in range(1, workgroups) for i in (-1, 0, 5)] + [(N - 1) // B * B, N - 2, N - 1]
+    _infinite_values(heads, N, d, B, k, sorted(set(edges)))
+
+
 def test_shared_queries_in_a_graph():
     sh, Q, K, V, cent = _case(*SHARED[1])
     eager = moba.decode_forward(sh, 1, Q, K, V, cent, want_idx=False)
