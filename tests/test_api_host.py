@@ -48,6 +48,20 @@ def test_decode_forward_rejects_bad_arguments(lib):
     assert f(ctypes.byref(big), 1, one, one, one, one, 5000, one, one, None, None) == -2
 
 
+def test_decode_workspace_counts_the_keys_there_are(lib):
+    """Queries are shared by workgroups, which takes a workspace, from 512 KB of keys and values each: a block that is
+    longer than the sequence brings no more than the sequence's."""
+    def need(**kw):
+        n = ctypes.c_size_t(99)
+        assert lib.moba_decode_workspace(ctypes.byref(_shape(heads=1, **kw).c()), 1, ctypes.byref(n)) == 0
+        return n.value
+    assert need(seqlen=50, block=4096, topk=1) == 0
+    assert need(seqlen=500, block=1 << 20, topk=8, head_dim=128) == 0
+    assert need(seqlen=2047, block=4096, topk=1) == 0             # 512 KB less a row
+    assert need(seqlen=2048, block=4096, topk=1) > 0
+    assert need(seqlen=4096 + 7, block=4096, topk=1) > 0
+
+
 def test_grouped_query_shapes_are_accepted(lib):
     R = ctypes.c_int64(0)
     for kv in (0, 1, 2, 4):
