@@ -143,13 +143,17 @@ struct DecodeSplit {
     uint64_t tag;
 };
 
-template <typename T, int D>
+// SHARED: several workgroups per query.  SHORT: rows of up to kDecodeShort kept blocks.  Instantiations of their own: in one, calls of
+// longer rows that nobody shares paid for registers and code of both (graph of calls, us, one kernel -> four: 60 queries, d = 64, B = 32,
+// k = 29 of 48 blocks 11.40 -> 11.24, 60 of B = 64 14.78 -> 14.64, as before either was there: 11.27, 14.64).
+template <typename T, int D, bool SHARED, bool SHORT>
 __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const float* __restrict__ cent, T* __restrict__ O, float* __restrict__ lse,
     int32_t* __restrict__ idx_out, int N, int B, int k, int q_len, int cblocks, float scale, int G,
-    int bhk, int npast_max, int splits, DecodeSplit split)
+    int bhk, int npast_max, int shares, DecodeSplit split)
 {
+    const int splits = SHARED ? shares : 1;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int NT = kDecodeThreads, NW = kDecodeWaves;
     constexpr int LPR = D * (int)sizeof(T) / 16;            // lanes of a K / V row, 16 bytes each
@@ -171,8 +175,8 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     int skv, pos;
     if (!schedule(blockIdx.x, bhk, G * q_len * splits, skv, pos)) return;
-    const int share = splits > 1 ? pos % splits : 0;        // this workgroup's share of the query's keys
-    if (splits > 1) pos /= splits;
+    const int share = SHARED ? pos % splits : 0;        // this workgroup's share of the query's keys
+    if (SHARED) pos /= splits;
     const int s = skv * G + pos / q_len, r = pos % q_len;   // G query heads share a key/value head
     const int t = N - q_len + r;                            // position of the query
     const int past = t / B;                                 // complete blocks before its own block
@@ -244,7 +248,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
             auto fmx = [](float a, float b) { return __builtin_elementwise_maximum(a, b); };
             auto fmn = [](float a, float b) { return __builtin_elementwise_minimum(a, b); };
             mx = fmx(mx, dpp<0xb1>(mx)); mx = fmx(mx, dpp<0x4e>(mx)); mx = fmx(mx, dpp<0x141>(mx));
-            if (cl == 0) gmx[4 * wave + cr] = decode_key(fmx(mx, dpp<0x128>(mx)));   // (row_ror 8: the other half of the 16)
+            if (SHORT && cl == 0) gmx[4 * wave + cr] = decode_key(fmx(mx, dpp<0x128>(mx)));   // (row_ror 8: the other half of the 16)
             mn = fmn(mn, dpp<0xb1>(mn)); mn = fmn(mn, dpp<0x4e>(mn)); mn = fmn(mn, dpp<0x141>(mn));
             mx = across_rows<8>(mx, fmx);
             mn = across_rows<8>(mn, fmn);
@@ -258,7 +262,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
         // of them prove the result whatever the bound.  The bound itself is searched bit by bit, by every wave for itself.
         const int j0 = 4 * tid;
         bool chosen = false;
-        if (k <= kDecodeShort) {
+        if constexpr (SHORT) {
             const uint32_t mine = gmx[lane];
             const float4 x = *reinterpret_cast<const float4*>(sc + min(j0, (past - 1) & ~3));
             uint32_t bound = 0;
@@ -449,7 +453,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
     // instruction: the queries of a key/value head that run side by side on one XCD then pass the
     // same stretch of keys at about the same time and find each other's blocks in its L2.
     const int all = want * B + (t - past * B) + 1;
-    const int each = splits > 1 ? (all + splits * RPI - 1) / (splits * RPI) * RPI : all;
+    const int each = SHARED ? (all + splits * RPI - 1) / (splits * RPI) * RPI : all;
     const int first = share * each, total = min(all, first + each);     // (a share may be empty)
     float m = -INFINITY, l = 0.f, acc[EPL];                 // log2 units
 #pragma unroll
@@ -583,7 +587,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
         }
     }
     // ---- shares: the workgroup that is done last merges them, in their order
-    if (splits > 1) {
+    if constexpr (SHARED) {
         // Everything shared goes through memory operations of agent scope, which other compute units see in whatever cache
         // they sit; the counter moves when the stores are through.  (A fence of agent scope would write back and drop
         // the whole L2: 20 -> 99 us with 64 queries shared by four workgroups each.)
@@ -688,14 +692,18 @@ static hipError_t decode_t(const Dims& s, int q_len, const void* Q, const void* 
     const int npast_max = (s.N - 1) / s.B;
     const size_t lds = sizeof(float) * (size_t)((npast_max + 3) / 4 * 4 + kDecodeBins + kDecodeScratch<D> +
                                                 (npast_max + 31) / 32 + 3 * kDecodeWaves + 5 + kDecodeGroups + s.k + 1);
-    if (lds > 64 * 1024) {
-        hipError_t e = ensure_dynamic_lds((const void*)decode_kernel<T, D>, (size_t)lds);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((decode_kernel<T, D>), dim3((unsigned)schedule_grid(s.bhk, s.G * q_len * splits)), dim3(kDecodeThreads), lds, st,
-                       (const T*)Q, (const T*)K, (const T*)V, cent, (T*)O, lse, idx, s.N, s.B, s.k, q_len,
-                       cblocks, s.scale, s.G, s.bhk, npast_max, splits, split);
-    return hipGetLastError();
+    auto go = [&](auto* kernel) {
+        if (lds > 64 * 1024) {
+            const hipError_t e = ensure_dynamic_lds((const void*)kernel, lds);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)schedule_grid(s.bhk, s.G * q_len * splits)), dim3(kDecodeThreads), lds, st,
+                           (const T*)Q, (const T*)K, (const T*)V, cent, (T*)O, lse, idx, s.N, s.B, s.k, q_len,
+                           cblocks, s.scale, s.G, s.bhk, npast_max, splits, split);
+        return hipGetLastError();
+    };
+    if (s.k <= kDecodeShort) return splits > 1 ? go(decode_kernel<T, D, true, true>) : go(decode_kernel<T, D, false, true>);
+    return splits > 1 ? go(decode_kernel<T, D, true, false>) : go(decode_kernel<T, D, false, false>);
 }
 
 hipError_t launch_decode(const Dims& s, int q_len, const void* Q, const void* K, const void* V,
