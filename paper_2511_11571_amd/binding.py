@@ -333,33 +333,37 @@ def backward(shape: Shape, Q, K_eff, V, O, lse, dO, idx, lists, ws=None, out=Non
 
 
 def _decode_workspace_bytes(shape: Shape, q_len):
-    known = shape.__dict__.get("_decode_ws")             # a function of the (immutable) shape and q_len
-    if known is None or known[0] != q_len:
-        n = ctypes.c_size_t(0)
-        _check(lib().moba_decode_workspace(ctypes.byref(shape.c()), q_len, ctypes.byref(n)), "moba_decode_workspace")
-        known = (q_len, n.value)
-        object.__setattr__(shape, "_decode_ws", known)
-    return known[1]
+    """Bytes that moba_decode_workspace names.  A sequence that grows by a token per call has a new shape every time, so
+    the library is only asked where queries can have enough to read for several workgroups each and are few enough (the
+    bounds of its rule: 512 KB of keys and values, 128 workgroups)."""
+    B = shape.block
+    rows = min(shape.topk * B + B // 2, shape.seqlen)
+    if rows * shape.head_dim < (1 << 17 if shape.dtype == BF16 else 1 << 16) or shape.batch * shape.heads * q_len > 64:
+        return 0
+    n = ctypes.c_size_t(0)
+    _check(_fn("moba_decode_workspace", "pip")(shape._ref(), q_len, ctypes.addressof(n)), "moba_decode_workspace")
+    return n.value
 
 
 def decode_forward(shape: Shape, q_len, Q, K_eff, V, cent, want_idx=True):
     """Decode-shaped forward for the last q_len positions of shape.seqlen keys (any length).
     -> (O [b,h,q_len,d], lse [b,h,q_len] fp32, topk_idx [b,h,q_len,k] int32 or None)."""
+    dt = shape.torch_dtype
     for t in (Q, K_eff, V):
-        assert t.is_contiguous() and t.dtype == shape.torch_dtype
+        assert t.is_contiguous() and t.dtype == dt
     assert Q.shape[2] == q_len and K_eff.shape[2] == shape.seqlen
     blocks = 0
     if cent is not None:
         assert cent.is_contiguous() and cent.dtype == torch.float32
         blocks = cent.shape[2]
     O = torch.empty_like(Q)
-    lse = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
+    lse = Q.new_empty(Q.shape[:3], dtype=torch.float32)
     idx = (torch.empty((shape.batch, shape.heads, q_len, shape.topk), dtype=torch.int32, device=Q.device)
            if want_idx else None)
     need = _decode_workspace_bytes(shape, q_len)
-    ws = torch.empty(need, dtype=torch.uint8, device=Q.device) if need else None
-    _check(_fn("moba_decode_forward_ws", "pippppippppzp")(shape._ref(), q_len, _p(Q), _p(K_eff),
-                                     _p(V), _p(cent), blocks, _p(O), _p(lse), _p(idx), _p(ws), need,
+    ws = Q.new_empty(need, dtype=torch.uint8) if need else None
+    _check(_fn("moba_decode_forward_ws", "pippppippppzp")(shape._ref(), q_len, Q.data_ptr(), K_eff.data_ptr(),
+                                     V.data_ptr(), _p(cent), blocks, O.data_ptr(), lse.data_ptr(), _p(idx), _p(ws), need,
                                      _stream()), "moba_decode_forward_ws")
     return O, lse, idx
 

@@ -2,6 +2,7 @@
 and rejects bad arguments before anything is launched (so this runs without a GPU)."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
@@ -60,6 +61,46 @@ def test_decode_workspace_counts_the_keys_there_are(lib):
     assert need(seqlen=2047, block=4096, topk=1) == 0             # 512 KB less a row
     assert need(seqlen=2048, block=4096, topk=1) > 0
     assert need(seqlen=4096 + 7, block=4096, topk=1) > 0
+
+
+def _decode_shapes():
+    rng = random.Random(5)
+    for _ in range(4000):
+        d, dtype = rng.choice([64, 128]), rng.choice([binding.F32, binding.BF16])
+        block, topk = rng.choice([1, 16, 33, 64, 128, 1000, 4096]), rng.choice([0, 1, 3, 8, 16, 17, 40, 64, 300])
+        seqlen = rng.choice([1, 50, 2047, 2048, 4096, 8193, 30000]) + rng.choice([0, 0, 1, 31])
+        yield binding.Shape(rng.choice([1, 2, 5]), rng.choice([1, 4, 13, 32]), seqlen, d, block, topk, 0, dtype), rng.choice([1, 2, 3, 16])
+    for es, d in ((2, 64), (2, 128), (4, 64), (4, 128)):          # at 512 KB, of a sequence and of kept blocks, and at 64 queries
+        rows = (1 << 18) // (d * es)
+        for seqlen, block, topk in ((rows, 4096, 1), (rows - 1, 4096, 1), (99999, 2, rows // 2), (99999, 2, rows // 2 - 1)):
+            for heads, q_len in ((1, 1), (64, 1), (65, 1), (8, 8), (3, 22)):
+                yield binding.Shape(1, heads, min(seqlen, 4096 * block), d, block, topk, 0, binding.BF16 if es == 2 else binding.F32), q_len
+
+
+def test_decode_asks_for_a_workspace_where_there_can_be_one(lib, monkeypatch):
+    """The binding's answer is the library's, for every shape, kept by no shape, and the library is not called where the
+    answer is 0 by the rule's bounds: a decode step with a new shape is bound by the host."""
+    asked = []
+    binding._decode_workspace_bytes(_shape(heads=1, seqlen=9000, topk=255), 1)          # (looks the entry point up)
+    real = binding._fn
+    monkeypatch.setattr(binding, "_fn", lambda name, sig: asked.append(name) or real(name, sig))
+    monkeypatch.setattr(binding, "lib", lambda: asked.append("lib") or lib)
+    zero = shared = 0
+    for sh, q_len in _decode_shapes():
+        n = ctypes.c_size_t(99)
+        if lib.moba_decode_workspace(ctypes.byref(sh.c()), q_len, ctypes.byref(n)) != 0:
+            continue
+        del asked[:]
+        assert binding._decode_workspace_bytes(sh, q_len) == n.value, (sh, q_len)
+        assert len(asked) <= 1
+        shared += n.value > 0
+        zero += not asked
+    assert zero > 1000 and shared > 100
+    # a step of a small model, a step against a long cache, many queries
+    for sh, q_len in ((_shape(seqlen=700), 1), (_shape(heads=16, seqlen=131109, block=128, topk=8), 1),
+                      (_shape(heads=16, batch=8, seqlen=30000, head_dim=128, block=64, topk=32), 1)):
+        del asked[:]
+        assert binding._decode_workspace_bytes(sh, q_len) == 0 and not asked
 
 
 def test_grouped_query_shapes_are_accepted(lib):
