@@ -337,7 +337,7 @@ def _decode_workspace_bytes(shape: Shape, q_len):
     the library is only asked where queries can have enough to read for several workgroups each and are few enough (the
     bounds of its rule: 512 KB of keys and values, 128 workgroups)."""
     B = shape.block
-    rows = min(shape.topk * B + B // 2, shape.seqlen)
+    rows = min(shape.topk * B + B, shape.seqlen)
     if rows * shape.head_dim < (1 << 17 if shape.dtype == BF16 else 1 << 16) or shape.batch * shape.heads * q_len > 64:
         return 0
     n = ctypes.c_size_t(0)

@@ -665,11 +665,11 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
 // Whole call, us, unshared -> 2 / 4 / 8 workgroups per query: 4 queries of 1 MB 17.8 -> - / 15.9 / 14.4; 4 of 0.5 MB 15.7 ->
 // 13.4 / 12.4 / 13.5; 16 of 1 MB 32.4 -> - / 26.8 / 28.3; 32 of 1.3 MB 40.4 -> - / 33.8 / 38.7; 64 of 0.9 MB 20.7 -> 17.9 / 18.8;
 // 16 of 0.5 MB 14.3 -> 13.7 / 14.2; 64 of 0.5 MB 15.9 -> 15.8 / 17.3; 128 of 1 MB 30.3 -> 31.5; 32 of 0.27 MB 10.4 -> 12.8 (4).
-// (Half of the own block counts, of as many keys as there are: 8 queries of 50 keys of a block of 4096 8.1 us shared, 5.4 not.)
+// (The own block counts with the keys it has: 8 queries of 50 keys, in a block of 4096, take 8.1 us shared and 5.4 not.)
 static int decode_splits(const Dims& s, int q_len)
 {
     const int64_t queries = (int64_t)s.bh * q_len;
-    const int64_t keys = std::min<int64_t>((int64_t)std::min(s.k, (s.N - 1) / s.B) * s.B + s.B / 2, s.N);
+    const int64_t keys = (int64_t)std::min(s.k, (s.N - 1) / s.B) * s.B + (s.N - 1) % s.B + 1;     // of the last position
     const int64_t kb = 2 * keys * s.D * (s.dtype == MOBA_BF16 ? 2 : 4) >> 10;
     if (kb < 512) return 1;
     int n = 1;

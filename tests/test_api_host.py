@@ -50,8 +50,8 @@ def test_decode_forward_rejects_bad_arguments(lib):
 
 
 def test_decode_workspace_counts_the_keys_there_are(lib):
-    """Queries are shared by workgroups, which takes a workspace, from 512 KB of keys and values each: a block that is
-    longer than the sequence brings no more than the sequence's."""
+    """Queries are shared by workgroups, which takes a workspace, from 512 KB of keys and values each: an own block that
+    is hardly begun, or longer than the sequence, brings no more keys than it has."""
     def need(**kw):
         n = ctypes.c_size_t(99)
         assert lib.moba_decode_workspace(ctypes.byref(_shape(heads=1, **kw).c()), 1, ctypes.byref(n)) == 0
@@ -61,6 +61,8 @@ def test_decode_workspace_counts_the_keys_there_are(lib):
     assert need(seqlen=2047, block=4096, topk=1) == 0             # 512 KB less a row
     assert need(seqlen=2048, block=4096, topk=1) > 0
     assert need(seqlen=4096 + 7, block=4096, topk=1) > 0
+    assert need(seqlen=(1 << 14) + 9, block=1 << 14, topk=0) == 0                # nine keys of the own block
+    assert need(seqlen=(1 << 14) + 9000, block=1 << 14, topk=0) > 0
 
 
 def _decode_shapes():
@@ -72,9 +74,9 @@ def _decode_shapes():
         yield binding.Shape(rng.choice([1, 2, 5]), rng.choice([1, 4, 13, 32]), seqlen, d, block, topk, 0, dtype), rng.choice([1, 2, 3, 16])
     for es, d in ((2, 64), (2, 128), (4, 64), (4, 128)):          # at 512 KB, of a sequence and of kept blocks, and at 64 queries
         rows = (1 << 18) // (d * es)
-        for seqlen, block, topk in ((rows, 4096, 1), (rows - 1, 4096, 1), (99999, 2, rows // 2), (99999, 2, rows // 2 - 1)):
+        for seqlen, block, topk in ((rows, 4096, 1), (rows - 1, 4096, 1), (8191, 2, rows // 2), (8191, 2, rows // 2 - 1), (8192, 2, rows // 2 - 1)):
             for heads, q_len in ((1, 1), (64, 1), (65, 1), (8, 8), (3, 22)):
-                yield binding.Shape(1, heads, min(seqlen, 4096 * block), d, block, topk, 0, binding.BF16 if es == 2 else binding.F32), q_len
+                yield binding.Shape(1, heads, seqlen, d, block, topk, 0, binding.BF16 if es == 2 else binding.F32), q_len
 
 
 def test_decode_asks_for_a_workspace_where_there_can_be_one(lib, monkeypatch):
