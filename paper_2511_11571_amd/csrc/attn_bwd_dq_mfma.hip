@@ -45,7 +45,8 @@ struct DqCfg {
 constexpr float kDqBits = 30.f;
 constexpr int kNanRow = 1 << 20;          // in place of a row's scale exponent: the row's dQ is NaN
 
-template <int D>
+// QUADS: the adds of four places that no row has are skipped (listed_at())
+template <int D, bool QUADS>
 __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Ka, const bf16_t* __restrict__ Va,
     const bf16_t* __restrict__ Kt, const uint32_t* __restrict__ kmax,
@@ -71,7 +72,6 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
 
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    constexpr bool QUADS = D == 64;                        // skip the adds of four places that no row has (listed_at())
     const int m16 = lane & 15, g = lane >> 4, at16 = QUADS ? listed_at(m16) : m16;
     int s, pos;
     if (!schedule(blockIdx.x, bh, ntiles, s, pos)) return;
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(DqCfg<D>::NT) void dq_mfma_kernel(
     }
 }
 
-template <int D>
+template <int D, bool QUADS>
 static hipError_t dq_launch(const Dims& s, const void* Q, const void* Ka, const void* Va, const void* Kt,
                             const uint32_t* kmax, const uint32_t* vmax, const void* dO,
                             const float* lse, const float* Dv, const int32_t* idx, void* dQ,
@@ -312,10 +312,10 @@ static hipError_t dq_launch(const Dims& s, const void* Q, const void* Ka, const 
 {
     using C = DqCfg<D>;
     const int ntiles = (s.N + C::TILE - 1) / C::TILE;
-    hipError_t e = ensure_dynamic_lds((const void*)dq_mfma_kernel<D>, (size_t)(C::LDS));
+    hipError_t e = ensure_dynamic_lds((const void*)dq_mfma_kernel<D, QUADS>, (size_t)(C::LDS));
     if (e != hipSuccess) return e;
     ProfileScope timing(MOBA_PROFILE_DQ, st);
-    hipLaunchKernelGGL((dq_mfma_kernel<D>), dim3((unsigned)schedule_grid(s.bh, ntiles)), dim3(C::NT), C::LDS, st,
+    hipLaunchKernelGGL((dq_mfma_kernel<D, QUADS>), dim3((unsigned)schedule_grid(s.bh, ntiles)), dim3(C::NT), C::LDS, st,
                        (const bf16_t*)Q, (const bf16_t*)Ka, (const bf16_t*)Va, (const bf16_t*)Kt, kmax,
                        vmax, (const bf16_t*)dO, lse, Dv, idx, (bf16_t*)dQ, s.N, s.B, s.k, s.scale,
                        ntiles, s.bh, s.G);
@@ -345,8 +345,9 @@ hipError_t launch_dq_mfma(const Dims& s, const void* Q, const void* K, const voi
         hipError_t e = launch_prepare(kv_view(s), K, V, p, st);
         if (e != hipSuccess) return e;
     }
-    return s.D == 64 ? dq_launch<64>(s, Q, p.Ka, p.Va, p.Kt, p.kmax, p.vmax, dO, lse, Dv, idx, dQ, st)
-                     : dq_launch<128>(s, Q, p.Ka, p.Va, p.Kt, p.kmax, p.vmax, dO, lse, Dv, idx, dQ, st);
+    auto go = [&](auto* launch) { return launch(s, Q, p.Ka, p.Va, p.Kt, p.kmax, p.vmax, dO, lse, Dv, idx, dQ, st); };
+    if (s.D == 128) return go(dq_launch<128, false>);
+    return short_lists(s, DqCfg<64>::TILE, kShortListsDq) ? go(dq_launch<64, true>) : go(dq_launch<64, false>);
 }
 
 }  // namespace moba

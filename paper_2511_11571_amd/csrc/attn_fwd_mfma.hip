@@ -98,8 +98,8 @@ __device__ __forceinline__ float max_over_g(float x)
 }
 
 // GMAX: 32-key groups of a block that one unit takes together (2 needs B >= 64 and the registers
-// of d = 64)
-template <int D, int GMAX>
+// of d = 64).  QUADS: the adds of four places that no row has are skipped (listed_at())
+template <int D, int GMAX, bool QUADS>
 __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Ka, const bf16_t* __restrict__ Vt,
     const uint32_t* __restrict__ vmax, const int32_t* __restrict__ idx, bf16_t* __restrict__ O,
@@ -121,7 +121,6 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
 
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    constexpr bool QUADS = D == 64 && GMAX == 1;           // skip the adds of four places that no row has (listed_at())
     const int m16 = lane & 15, g = lane >> 4, at16 = QUADS ? listed_at(m16) : m16;
     int s, pos;
     if (!schedule(blockIdx.x, bh, ntiles, s, pos)) return;
@@ -440,17 +439,17 @@ __global__ __launch_bounds__(FwdCfg<D>::NT) void forward_mfma_kernel(
     }
 }
 
-template <int D, int GMAX>
+template <int D, int GMAX, bool QUADS>
 static hipError_t fwd_launch(const Dims& s, const void* Q, const void* K, const void* Vt,
                              const uint32_t* vmax, const int32_t* idx, void* O, float* lse,
                              hipStream_t st)
 {
     using C = FwdCfg<D>;
     const int ntiles = (s.N + C::TILE - 1) / C::TILE;
-    hipError_t e = ensure_dynamic_lds((const void*)forward_mfma_kernel<D, GMAX>, (size_t)(C::LDS));
+    hipError_t e = ensure_dynamic_lds((const void*)forward_mfma_kernel<D, GMAX, QUADS>, (size_t)(C::LDS));
     if (e != hipSuccess) return e;
     ProfileScope timing(MOBA_PROFILE_FORWARD, st);
-    hipLaunchKernelGGL((forward_mfma_kernel<D, GMAX>), dim3((unsigned)schedule_grid(s.bh, ntiles)), dim3(C::NT), C::LDS,
+    hipLaunchKernelGGL((forward_mfma_kernel<D, GMAX, QUADS>), dim3((unsigned)schedule_grid(s.bh, ntiles)), dim3(C::NT), C::LDS,
                        st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)Vt, vmax, idx,
                        (bf16_t*)O, lse, s.N, s.B, s.k, s.scale, ntiles, s.bh, s.G);
     return hipGetLastError();
@@ -478,9 +477,10 @@ hipError_t launch_forward_mfma(const Dims& s, const void* Q, const void* K, cons
     }
     hipError_t e = launch_prepare(kv_view(s), K, V, p, st);  // K and V: one slice per key/value head
     if (e != hipSuccess) return e;
-    if (s.D == 128) return fwd_launch<128, 1>(s, Q, p.Ka, p.Vt, p.vmax, idx, O, lse, st);
-    return s.B >= 64 ? fwd_launch<64, 2>(s, Q, p.Ka, p.Vt, p.vmax, idx, O, lse, st)
-                     : fwd_launch<64, 1>(s, Q, p.Ka, p.Vt, p.vmax, idx, O, lse, st);
+    auto go = [&](auto* launch) { return launch(s, Q, p.Ka, p.Vt, p.vmax, idx, O, lse, st); };
+    if (s.D == 128) return go(fwd_launch<128, 1, false>);
+    if (s.B >= 64) return go(fwd_launch<64, 2, false>);
+    return short_lists(s, FwdCfg<64>::TILE, kShortListsForward) ? go(fwd_launch<64, 1, true>) : go(fwd_launch<64, 1, false>);
 }
 
 }  // namespace moba

@@ -261,9 +261,18 @@ __device__ __forceinline__ void build_block_lists(const int32_t* __restrict__ id
 
 // Sixteen listed rows as the columns (or rows) of a product: column m takes the row at place listed_at(m) of the
 // sixteen.  The product's result rows 4 g + i, i fixed, are then the places 4 i + g: instruction i of the adds covers
-// four neighbouring places, and a list's last sixteen needs no more of these instructions than it has rows / 4.  For kernels
-// that meet lists of about sixteen rows (d = 64): 5.8 -> 4.4 of them per channel tile and list.  Lists of a whole tile's rows only pay for
-// it (d = 128, dense, 3 heads of 2176: dQ 155 -> 163 us; d = 64, B = 256, dense, 3 heads of 3072: forward 135 -> 138).
+// four neighbouring places, and a list's last sixteen needs no more of these instructions than it has rows / 4: 5.8 -> 4.4 of them
+// per channel tile and list of about sixteen rows.  Long lists only pay for it: taken where lists have up to `line` rows
+// on average, by the shape (d = 64; d = 128, dense, 3 heads of 2176: dQ 155 -> 163 us).
+// us without -> with it, at so many rows a list: forward (B = 32) 16 201.5 -> 197.3; 31 966.7 -> 947.0; 38 97.9 -> 97.6;
+// 66 225.8 -> 228.6; 87 159.7 -> 160.3; 254 206.5 -> 212.5.  dQ 20 760.5 -> 754.7; 31 910.0 -> 882.4; 60 (hot blocks) 783.4 -> 771.5;
+// 87 151.2 -> 148.9 (B = 64: 152.8 -> 152.3); 148 160.5 -> 158.0 (B = 128: 248.8 -> 251.5, B = 256: 103.5 -> 105.3); 254 155.9 -> 159.9.
+constexpr int kShortListsForward = 48, kShortListsDq = 128;
+inline bool short_lists(const Dims& s, int tile, int line)
+{
+    const int64_t tiles = (s.N + tile - 1) / tile;
+    return 2 * s.R <= line * tiles * s.n;                   // half of all (tile, block) pairs are past blocks
+}
 __device__ __forceinline__ int listed_at(int m) { return 4 * (m & 3) + (m >> 2); }
 // the rows at places 4 i + g, i = 0 .. 3, from what the lane (g, m16) read at place 4 (m16 & 3) + g
 __device__ __forceinline__ void listed_rows(int at, int (&r4)[4])

@@ -29,6 +29,8 @@ def skewed_routing(batch, heads, N, B, k, seed):
 # (batch, heads, kv_heads, N, d, B, k)
 @pytest.mark.parametrize("batch,heads,kv,N,d,B,k", [
     (1, 2, 0, 1024, 64, 32, 5), (1, 2, 0, 1056, 64, 32, 8), (1, 1, 0, 4096, 64, 32, 72), (2, 2, 1, 1088, 64, 64, 4),
+    # lists of 30, 45 and 248 rows on average (the kernels for short ones end at 48, forward, and 128, dQ; above: 72, 88, 206, B = 64: 87)
+    (1, 2, 0, 1024, 64, 32, 2), (1, 2, 0, 1024, 64, 32, 3), (1, 1, 0, 1024, 64, 32, 31),
     (1, 2, 0, 960, 64, 96, 3), (1, 2, 0, 1024, 128, 32, 7), (1, 4, 2, 1312, 128, 32, 12), (1, 1, 0, 8320, 128, 64, 130)])
 def test_query_tiles_against_the_plain_kernels(batch, heads, kv, N, d, B, k):
     import paper_2511_11571_amd as moba
