@@ -101,10 +101,14 @@ typedef struct moba_shape {
  *   bf16, key-block-major kernels: 2 d + 8 bytes each forward (and the size of V once), 2 d backward; parts of 128
  *       keys (d = 64) or 64 (d = 128; backward: 128 where B is a multiple of that, else 64).
  *   fp32 tensors, and bf16 with B not a multiple of 32 (B >= 8, topk <= 64): 4 d + 8 bytes each forward, 4 d
- *       backward; parts of at most 64 keys (backward at d = 128: 32).  fp32, 16 heads, N = 32768, d = 64:
- *       1.2 GB each with B = 64 and topk = 8, 9.0 and 8.7 GB with B = 32 and topk = 64.  Where the backward's
- *       partials would take more than 16 GiB both directions run on the plain kernels instead, which need
- *       next to no workspace and are several times slower: cut such calls by heads or batch. */
+ *       backward; parts of at most 64 keys (backward at d = 128: 32 where a block's parts of 64 come to 48 keys or
+ *       less).  Where a key block's queries are shared out among workgroups, or heads share keys and values, the
+ *       backward adds fp32 dK and dV of every share: 8 d bytes per query and share, at most 16 shares, two wherever
+ *       batch * heads * N < 196608 with B = 64.  fp32, 16 heads, N = 32768, d = 64: 1.2 GB each with B = 64 and
+ *       topk = 8, 9.0 and 8.7 GB with B = 32 and topk = 64; N = 8192, B = 64, topk = 7: 277 and 404 MB (134 MB of
+ *       it sums).  Where the backward's partials (at d = 128 in parts of 32) would take more than 16 GiB both
+ *       directions run on the plain kernels instead, which need next to no workspace and are several times slower:
+ *       cut such calls by heads or batch. */
 int moba_routes_per_slice(const moba_shape* shape, int64_t* R);
 int moba_workspace_bytes(const moba_shape* shape, size_t* topk_ws, size_t* fwd_ws, size_t* bwd_ws);
 

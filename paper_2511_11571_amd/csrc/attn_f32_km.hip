@@ -21,6 +21,7 @@
 // its other operand comes from a row-major tile with output channel 4 m + mt, one 16-byte read for the
 // four instructions mt = 0 .. 3.  Tiles in LDS have rows of D + 4 words: both reads are conflict-free.
 #include <algorithm>
+#include <cmath>
 
 #include "mfma.h"
 
@@ -1049,22 +1050,36 @@ Cut bwd_cut(const Dims& s) { return cut_of(s, s.D == 64 || bwd_wide(s) ? 64 : 32
 
 size_t partials(const Dims& s, const Cut& c) { return (size_t)s.bh * s.N * (size_t)(s.k + 1) * c.nsub; }
 
-// Shares a walk is cut into: about `aim` workgroups in all, at least one step of `rows` queries each
-// (on average: the lists of a slice's first blocks are several times longer, and a launch ends with them)
-int shares(const Dims& s, const Cut& c, int rows, int aim)
+// Steps of `rows` queries in a walk of average length
+int64_t steps(const Dims& s, int rows) { return ((int64_t)(s.k + 1) * s.B + rows - 1) / rows; }
+
+// Shares a walk is cut into, bwd_f32_km_kernel: about four workgroups per compute unit, at least one step of all waves each
+int few_shares(const Dims& s, const Cut& c, int rows)
 {
-    const int64_t wgs = (int64_t)s.bh * s.n * c.nsub, steps = ((int64_t)(s.k + 1) * s.B + rows - 1) / rows;
-    const int64_t want = std::max<int64_t>(1, (aim + wgs - 1) / wgs);
-    return (int)(want < steps ? want : steps);
+    const int64_t wgs = (int64_t)s.bh * s.n * c.nsub, want = (1024 + wgs - 1) / wgs;
+    return (int)std::min(want, steps(s, rows));
 }
 
-// The workgroups to aim at, 512 to 768 of which run at once; with `two`, two shares also for somewhat more walks than that.
-// Forward and routing, d = 64, B = 64, k = 7: 1024 walks with one and two shares 217 and 185 us, 2048 walks 369 and 344 (d = 128: 741 and
-// 784); 512 walks with two and three 113 and 106.
-int wide_aim(const Dims& s, const Cut& c, bool two)
+// The others: the number with the least estimated time, in rows of a walk.  A launch takes what its `places` (three workgroups on a
+// compute unit) have to do, `fixed` rows more per workgroup for its keys and values, its fill and the sums of dK and dV, or what is left
+// when its longest walk begins and that walk, whose rows count `tail` of the average (they have a place to themselves in the end).  The longest
+// walks are those of a slice's first blocks, B min(1, k / t) rows of the query blocks t = 1, 2, ...: they begin first, or, where the number of slices
+// is a multiple of 8, with their XCD's last slice (schedule()).  The fourth powers round the corner between the two.
+// Measured with one to 32 shares at 8 to 6144 walks, B = 16 to 4096, k = 0 to 20, which tail, fixed and places are fitted to: the number taken is
+// about 1 % slower than the best on average (backward, d = 128: 3 %, for the two shares that bwd_shares() keeps); 1280 workgroups at least, and
+// two shares up to 3072 walks, were 2 to 5 %.  Figures beside the calls.
+int shares(const Dims& s, const Cut& c, int64_t most, double tail, double fixed, double places = 768.)
 {
-    const int64_t walks = (int64_t)s.bh * s.n * c.nsub;
-    return two && walks < 3072 ? (int)std::max<int64_t>(1280, 2 * walks) : 1280;
+    const double walks = (double)s.bh * s.n * c.nsub, kept = std::min(s.k, s.n - 1);
+    const double rows = (double)(s.k + 1) * s.B, longest = s.B * (1. + kept + kept * std::log(s.n / (kept + 1.)));
+    const double before = s.bh % kXcds == 0 ? 1. - (double)kXcds / s.bh : 0.;      // of a launch, when the last slices begin
+    auto time = [&](int ns) {
+        const double all = walks / places * (rows + fixed * ns), last = before * all + tail * (longest / ns + fixed);
+        return all * all * all * all + last * last * last * last;
+    };
+    int ns = 1;
+    for (double t = time(1), more; ns < most && (more = time(ns + 1)) < t; ++ns) t = more;
+    return ns;
 }
 
 bool sums_needed(const Dims& s, int nsplit) { return s.G * nsplit > 1; }
@@ -1096,13 +1111,17 @@ static size_t bwd_sums_offset(const Dims& s)
 {
     return bwd_partials_offset(s) + a256(partials(s, bwd_cut(s)) * s.D * sizeof(float));
 }
-// Whole step (with one chain of sums per walk), d = 64, B = 64, k = 7, one share against two: 1024 walks 545 -> 470 us, 2048 walks 946 -> 890; 512 walks with two, three
-// and four 273, 251 and 261.  d = 128, B = 128, k = 4, 256 walks with four, five and six 328, 330 and 335.
 static int bwd_shares(const Dims& s)
 {
     const Cut c = bwd_cut(s);
-    if (!bwd_wide(s)) return shares(s, c, 16 * (s.D == 64 ? F32Cfg<64>::NWB : F32Cfg<128>::NWB), 1024);
-    return shares(s, c, s.D == 64 ? WideCfg<64>::RQ : WideCfg<128>::RQ, wide_aim(s, c, true));
+    if (!bwd_wide(s)) return few_shares(s, c, 16 * (s.D == 64 ? F32Cfg<64>::NWB : F32Cfg<128>::NWB));
+    // us, shares of 1280 workgroups (two up to 3072 walks) -> these, B = 64: d = 64, 2 slices of 32768, k = 8 377 -> 329; 24 of 8192, k = 7 875 -> 818;
+    // 6 of 8192 247 -> 224; d = 128, 12 of 2048, k = 2 127 -> 120.  Sixteen at most: 8 walks of 512 rows, d = 128, take 31 us, in 32 shares 38, and
+    // the chain of sums over shares would cost more precision than shorter walks gain.  Two up to 3072 walks also where one is faster, for the
+    // same reason: 20 slices of 4096, k = 2, dK 4.22e-7 from 64 bits in two shares, 4.25e-7 in one, which takes 20 % less.
+    const int64_t most = std::min<int64_t>(16, steps(s, s.D == 64 ? WideCfg<64>::RQ : WideCfg<128>::RQ));
+    const int ns = s.D == 64 ? shares(s, c, most, 0.8, 80.) : shares(s, c, most, 0.6, 80.);
+    return (int64_t)s.bh * s.n * c.nsub < 3072 ? std::max(ns, (int)std::min<int64_t>(2, most)) : ns;
 }
 size_t backward_f32_km_ws_bytes(const Dims& s)
 {
@@ -1116,7 +1135,12 @@ static hipError_t fwd_launch_nt(const Dims& s, const Cut& c, const void* Q, cons
                                 void* O, float* lse, hipStream_t st)
 {
     using C = F32Cfg<D>;
-    const int ns = shares(s, c, 16 * C::NWF, wide_aim(s, c, D == 64));
+    // Shorter parts take less to begin with, and at d = 128 leave room for more workgroups.  us, shares of 1280 workgroups (d = 64: two up to
+    // 3072 walks) -> these, B = 64: d = 64, 20 slices of 8192, k = 2 155 -> 141; 36 of 4096, k = 4 196 -> 181; 24 of 8192, k = 7 408 -> 382; d = 128,
+    // 8 of 8192, k = 7 298 -> 277; 28 of 2048, k = 2 127 -> 114.
+    const double part = std::sqrt(NT / 4.);
+    const int ns = D == 64 ? shares(s, c, steps(s, 16 * C::NWF), 0.6, 56. * part)
+                           : shares(s, c, steps(s, 16 * C::NWF), 0.3, 80. * part, 768. / part);
     hipError_t e = ensure_dynamic_lds((const void*)fwd_f32_km_kernel<T, D, NT>, C::fwd_lds(NT));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((fwd_f32_km_kernel<T, D, NT>), dim3((unsigned)schedule_grid(s.bh, s.n * c.nsub * ns)),

@@ -114,6 +114,25 @@ def test_grouped_query_shapes_are_accepted(lib):
     assert moba.workspace_bytes(_shape(heads=4, kv_heads=1))[1] < moba.workspace_bytes(_shape(heads=4))[1]
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_f32_backward_keeps_room_for_a_bounded_number_of_sums(lib, d):
+    """fp32: a partial of dQ per (query, block) and part, (lse, -D) per query, D; with several shares of a walk, of which there are
+    16 at most, fp32 dK and dV of every share."""
+    several = 0
+    for block, topk, n, heads in [(64, 0, 1, 1), (64, 0, 5, 3), (64, 7, 8, 1), (64, 8, 512, 2), (64, 2, 64, 40), (128, 3, 4096, 64),
+                                  (4096, 0, 1, 1), (64, 1, 2, 4000), (256, 9, 30, 8)]:
+        sh = _shape(heads=heads, seqlen=n * block, head_dim=d, block=block, topk=topk, dtype=binding.F32)
+        rows, parts = heads * n * block, -(-block // 64)
+        partials = 4 * d * rows * (topk + 1) * parts
+        sums, rest = 8 * d * rows, 12 * rows + 1024
+        if partials * (2 if d == 128 else 1) > 1 << 34:
+            continue
+        room = moba.workspace_bytes(sh)[2] - partials - rest
+        assert -1024 <= room <= 16 * sums, (d, block, topk, n, heads)
+        several += room >= 2 * sums - 1024
+    assert several >= 4
+
+
 def test_routes_and_workspace(lib):
     sh = _shape()
     n = 32

@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 #        dtype   d   B   blocks  k  heads kv
 CASES = [("f32", 64, 49, 20, 4, 2, 0), ("f32", 128, 64, 24, 3, 2, 1), ("bf16", 128, 50, 12, 4, 2, 0), ("f32", 64, 114, 9, 3, 4, 2),
-         ("f32", 128, 114, 9, 0, 1, 0), ("f32", 64, 64, 1, 0, 1, 0), ("bf16", 64, 62, 300, 2, 12, 0), ("f32", 64, 64, 16, 2, 200, 0)]
+         ("f32", 128, 114, 9, 0, 1, 0), ("f32", 64, 64, 1, 0, 1, 0), ("bf16", 64, 62, 300, 2, 12, 0), ("f32", 64, 64, 16, 2, 200, 0),
+         # many shares of few short walks, several slices to an XCD
+         ("f32", 64, 64, 8, 7, 1, 0), ("f32", 128, 64, 9, 8, 2, 0), ("f32", 64, 64, 24, 5, 24, 0)]
 
 
 @pytest.mark.parametrize("odd", [False, True])
