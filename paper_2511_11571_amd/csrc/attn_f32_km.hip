@@ -673,6 +673,8 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
 // unit, and added its waves' sums up one after the other at the end, as much work as the two steps that a wave had between: at the
 // shape above 167 us (1024 workgroups of eight waves) against 131 (1536 of four), whole step 301 -> 256; 2 x 8 heads of 8192,
 // d = 128, B = 64, k = 8 2309 -> 1875 (there it could take 32 keys, so that dQ had twice the partials).
+// Three waves per SIMD leave 168 registers at d = 64, fp32, and the walk just fits them (one value is stored before it and read after it):
+// with six values spilled in every step the shape's backward, all of it, took 154 us instead of 147, 16 slices of 8192 552 instead of 519.
 template <int D>
 struct WideCfg {
     static constexpr int QT = D == 64 ? 2 : 1, RQ = 16 * QT;      // 16-query tiles, queries per step
@@ -728,8 +730,8 @@ __global__ __launch_bounds__(WideCfg<D>::NW * kWave, WideCfg<D>::WPS) void bwd_f
     const float c2 = scale * kLog2e;
     const int slots = (k + 1) * nsub;
     const int grow = tid / Ga::CPR, gcol = (tid % Ga::CPR) * Ga::EPL;
-    const T* Qs = Q + sbase * D + gcol;
-    const T* Gs = dO + sbase * D + gcol;
+    Q += sbase * D;
+    dO += sbase * D;
     const int32_t* kept = k > 0 ? idx + sbase * k : os;     // (as in the forward, like `there` below)
     // t: entries of the rows that this thread gathers a piece of; tl (the first RQ threads): of row tid
     auto ids = [&](int a0, int (&t)[NI], int& tl) {
@@ -743,8 +745,9 @@ __global__ __launch_bounds__(WideCfg<D>::NW * kWave, WideCfg<D>::WPS) void bwd_f
     auto fetch = [&](int a0) {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            qr[i] = *reinterpret_cast<const u32x4_t*>(Qs + (int64_t)list_query(tA[i]) * D);
-            gr[i] = *reinterpret_cast<const u32x4_t*>(Gs + (int64_t)list_query(tA[i]) * D);
+            const int64_t o = (int64_t)list_query(tA[i]) * D + gcol;   // (pointers of a lane's own would be two registers more each)
+            qr[i] = *reinterpret_cast<const u32x4_t*>(Q + o);
+            gr[i] = *reinterpret_cast<const u32x4_t*>(dO + o);
         }
         if (tid < RQ) {
             xl = ld[sbase + list_query(tlA)];
@@ -829,12 +832,10 @@ __global__ __launch_bounds__(WideCfg<D>::NW * kWave, WideCfg<D>::WPS) void bwd_f
         float* stT = sT + b * RQ * TL;
         const float* xb = sl + 3 * b * RQ;
         f32x4_t x[QT], dp[QT];
-        int prow[QT];
 #pragma unroll
         for (int q = 0; q < QT; ++q) {
             x[q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             dp[q] = *reinterpret_cast<const f32x4_t*>(xb + RQ + 16 * q + 4 * g);
-            prow[q] = reinterpret_cast<const int*>(xb)[2 * RQ + 16 * q + m16];
         }
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
@@ -868,7 +869,7 @@ __global__ __launch_bounds__(WideCfg<D>::NW * kWave, WideCfg<D>::WPS) void bwd_f
         if (want_dkv) {
             // (the sums of sixteen queries first, then the walk's: one chain over all of a walk's queries is 5 % further from 64 bits than
             // the waves of bwd_f32_km_kernel, which share them out; so it is no further: dK of 4096 queries, k = 7 4.71e-7, now 4.47e-7, there
-            // 4.50e-7; for 32 queries at a time 4.51e-7 and, of 2048, B = 128, k = 3, 4.19e-7 against 4.15e-7, but 12 us less)
+            // 4.50e-7; for 32 queries at a time 4.51e-7 and, of 2048, B = 128, k = 3, 4.19e-7 against 4.15e-7, and 1 to 2 % less time)
             auto add = [&](const float* rows, const f32x4_t (&y)[QT], f32x4_t (&acc)[MT]) {
 #pragma unroll
                 for (int h = 0; h < H; ++h) {
@@ -892,6 +893,9 @@ __global__ __launch_bounds__(WideCfg<D>::NW * kWave, WideCfg<D>::WPS) void bwd_f
             add(stQ, dp, dKT);
         }
         park(a0 + stride, b ^ 1);
+        int prow[QT];                                       // (before the barrier: the step after it parks the next but one's rows there)
+#pragma unroll
+        for (int q = 0; q < QT; ++q) prow[q] = reinterpret_cast<const int*>(xb)[2 * RQ + 16 * q + m16];
         __syncthreads();
         if (want_dq) {
             f32x4_t o[QT][H], half[QT][H];                  // (d = 128: of 32 keys each)
@@ -968,8 +972,8 @@ __global__ __launch_bounds__(WideCfg<D>::NW * kWave, WideCfg<D>::WPS) void bwd_f
         if (own.lane < seen) {
             const int64_t key = (own.kv0 + own.lane) * D;
             const float2 x = ld[own.q0 + t];
-            const float z = scale * kLog2e * row_dot<T, D>(Q + (own.q0 + t) * D, K + key);
-            ds = fast_exp2(z - x.x) * (row_dot<T, D>(dO + (own.q0 + t) * D, V + key) + x.y);
+            const float z = scale * kLog2e * row_dot<T, D>(Q + (int64_t)t * D, K + key);
+            ds = fast_exp2(z - x.x) * (row_dot<T, D>(dO + (int64_t)t * D, V + key) + x.y);
         }
         weigh_rows<T, D>(ds, seen, K + own.kv0 * D, sm + own.wave * kWave,
                          PdQ + (((own.q0 + t) * (k + 1) + k) * nsub + own.c) * D, own.lane);
