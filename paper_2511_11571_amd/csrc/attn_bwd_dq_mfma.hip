@@ -15,9 +15,9 @@
 // lists per key block in LDS, K and V read in MFMA operand order, XCD-aware schedule.  The Q
 // and dO tiles sit in LDS unpadded, with the 16-byte chunks of row r permuted by r & 7 so
 // that a gather of arbitrary rows still spreads over the banks.  As there, the LDS pipe bounds it
-// (busy all the time by the counters, 36 % of that bank conflicts; vector issue 58 %, matrix pipe 25 %):
+// (busy 96 % of the clocks by the counters, 38 % of that bank conflicts; vector issue 57 %, matrix pipe 26 %):
 // 957 -> 945 us (16 heads of 32768, B = 32, k = 64) with adds of sixteen consecutive words of a row each, 945 -> 920 without
-// those of a list's last sixteen places that no row has.
+// those of a list's last sixteen places that no row has (short_lists()).
 #include "mfma.h"
 
 namespace moba {

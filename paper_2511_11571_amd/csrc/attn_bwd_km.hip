@@ -19,9 +19,9 @@
 //              both operands through the transpose read.
 //
 // One walk for all three gradients: dQ on its own repeats the gather of Q and dO and the products S and dP
-// (5 products instead of 7).  No pipe is full: at N = 524288, d = 64, B = 128, k = 8, 32 slices VALU issue is
-// busy 34 % of the clocks, the matrix pipe 31 %, the LDS pipe about half; the latencies of two waves per SIMD
-// (d = 64), one (d = 128) are what is left.  Neither whole-line nor streaming stores of the partials nor rows
+// (5 products instead of 7).  No pipe is full: at N = 65536, d = 64, B = 128, k = 8, 32 slices the LDS pipe is
+// busy 64 % of the clocks, VALU issue 41 %, the matrix pipe 38 % (N = 16384, d = 128, B = 64, k = 16: 43, 26 and 25 %); the latencies of two
+// waves per SIMD (d = 64), one (d = 128) are what is left.  Neither whole-line nor streaming stores of the partials nor rows
 // gathered from one place make much of a difference there (17.9 -> 17.6 and 16.4 ms).
 // Against separate walks for dQ and for dK and dV: N = 524288: 28.0 -> 18.6 ms, with the rows laid out as
 // parked() says 17.9; N = 10080, B = 96, k = 10, 18 slices: 210 us; N = 16384, d = 128, B = 64, k = 16, 16 slices: 778 us,

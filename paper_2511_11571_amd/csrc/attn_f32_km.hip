@@ -10,10 +10,10 @@
 //
 // The plain kernels of attn_reference.hip, which served these shapes, read every key row again for
 // every query (64 FMAs per 256 bytes) and ran at 5 TFLOP/s; here a key row meets 16 queries per read.
-// What bounds them now is the latency between the dependent steps of few waves: at the shape below the matrix
-// pipe is busy 49 % of the clocks of the forward, the LDS pipe 15 %, VALU issue 21 %, and waves wait 60 % of their
-// cycles; the products of the backward alone would take 68 of its 131 us.
-// fp32, 2 x 4 heads, N = 4096, d = 64, B = 64, k = 7: forward 580 -> 80 us, dQ + dK + dV 1960 -> 155 us (forward since: 75).
+// What bounds them now is the latency between the dependent steps of few waves, and the longest walks: at the shape below the matrix
+// pipe is busy 57 % (forward) and 66 % (backward) of the clocks, the LDS pipe 19 %, VALU issue 26 and 24 %, and waves wait 64 % of their
+// cycles; the products of the backward alone would take 68 of its 123 us.
+// fp32, 2 x 4 heads, N = 4096, d = 64, B = 64, k = 7: forward 580 -> 74 us, backward 1960 -> 147 us.
 //
 // Operand layouts (lane = 16 g + m): a contraction over channels takes channels 16 t + 4 g + i in the
 // i-th of four instructions, so that one 16-byte read per lane feeds four; a contraction over keys (or
@@ -671,7 +671,7 @@ __global__ __launch_bounds__(F32Cfg<D>::NWB * kWave) void bwd_f32_km_kernel(
 //   S, dP -> dS to LDS; dV^T, dK^T; the next step's rows to LDS | barrier | dQ^T = K^T dS^T over all keys, a partial
 // The kernel above, whose waves take 16 queries against all keys each, kept 128 sums a wave, had room for eight waves on a compute
 // unit, and added its waves' sums up one after the other at the end, as much work as the two steps that a wave had between: at the
-// shape above 167 us (1024 workgroups of eight waves) against 131 (1536 of four), whole step 301 -> 256; 2 x 8 heads of 8192,
+// shape above 167 us (1024 workgroups of eight waves) against 123 (1536 of four), whole step 300 -> 244; 2 x 8 heads of 8192,
 // d = 128, B = 64, k = 8 2309 -> 1875 (there it could take 32 keys, so that dQ had twice the partials).
 // Three waves per SIMD leave 168 registers at d = 64, fp32, and the walk just fits them (one value is stored before it and read after it):
 // with six values spilled in every step the shape's backward, all of it, took 154 us instead of 147, 16 slices of 8192 552 instead of 519.

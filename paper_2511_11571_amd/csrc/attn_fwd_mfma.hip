@@ -38,11 +38,11 @@
 // the rate of the row-major pattern on this chip), (b) the workgroups of one XCD work on the same
 // slice and walk its blocks in ascending order, so these reads hit that XCD's L2, and (c) 16
 // waves per workgroup keep loads, LDS traffic and MFMA work of different units overlapped.
-// What bounds it then is the LDS pipe: busy all the time by the counters at 16 heads of 32768, B = 32, k = 64 (16 adds
+// What bounds it then is the LDS pipe: busy 92 % of the clocks by the counters at 16 heads of 32768, B = 32, k = 64 (up to 16 adds
 // per sub-tile, gathered rows, lists), a third of that in bank conflicts, with the issue of vector instructions at
-// 74 % and the matrix pipe at 23 %.  The product's orientation by itself took conflicts from 219 to 187 M clocks and
-// gained 0.2 %; a list's last adds left out where no row has them (d = 64, B = 32) gain 1 to 2 % (8 heads of 32768, k = 30, copies
-// included: 378 -> 370 us).  Measured, kernel alone, all of the above but that: that shape 1095 -> 1042 us; 32 slices of 16384, B = 64,
+// 73 % and the matrix pipe at 23 %.  The product's orientation by itself took conflicts from 219 to 187 M clocks and
+// gained 0.2 %; a list's last adds left out where no row has them (short_lists()) gain 2 % there and 1 to 2 % at others (8 heads of
+// 32768, k = 30, copies included: 378 -> 370 us).  Measured, kernel alone, all of the above but that: that shape 1095 -> 1042 us; 32 slices of 16384, B = 64,
 // k = 32, hot blocks 762 -> 708 us.
 #include <type_traits>
 

@@ -26,10 +26,10 @@
 //    the radix select over the bits of the scores remains for bins of more than 128 scores (ties, or one
 //    score far from the rest) and for non-finite scores;
 //  - queries that share a key/value head run on the same XCD at the same time (schedule()).
-// Of 12.3 us inside one workgroup (1 query of 131109 keys, d = 64, B = 128, k = 8) the gate took 4.2, the selection 2.9, the keys 4.5
-// and the merge 0.7; both memory phases (262 and 272 KB) run at the 25 bytes per clock one compute unit takes in here.
-// 1 query of 131109 keys x 32 slices: 24.8 -> 12.8 -> 10.4 us (now host time: a call takes the host 10 us); 16 queries of 32805
-// keys x 16 heads on 4 key/value heads (d = 128, B = 64, k = 32): 59 -> 28 -> 26.5 us (there
+// Of 12.3 us inside one workgroup (1 query of 131109 keys, d = 64, B = 128, k = 8; binned selection) the gate took 4.2, the selection
+// 2.9, the keys 4.5 and the merge 0.7; both memory phases (262 and 272 KB) run at the 25 bytes per clock one compute unit takes in here.
+// 1 query of 131109 keys x 32 slices: 24.8 -> 13.1 -> 11.5 us (the kernel alone 11.1; a call takes the host 9 to 10); 16 queries of 32805
+// keys x 16 heads on 4 key/value heads (d = 128, B = 64, k = 32): 59 -> 27.7 -> 26.3 us (there
 // 340 MB go from the L2s to the compute units and 126 MB from behind them: 5 TB/s of the latter).
 #include <algorithm>
 #include <atomic>
@@ -454,7 +454,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
     // same stretch of keys at about the same time and find each other's blocks in its L2.
     const int all = want * B + (t - past * B) + 1;
     const int each = SHARED ? (all + splits * RPI - 1) / (splits * RPI) * RPI : all;
-    const int first = share * each, total = min(all, first + each);     // (a share may be empty)
+    const int first = share * each, total = min(all, first + each);     // (no share is empty where queries are shared, see decode_splits(); one would weigh nothing)
     float m = -INFINITY, l = 0.f, acc[EPL];                 // log2 units
 #pragma unroll
     for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
@@ -683,11 +683,12 @@ size_t decode_ws_bytes(const Dims& s, int q_len)
     const int n = decode_splits(s, q_len);
     return n == 1 ? 0 : decode_counters_bytes(s, q_len) + (size_t)s.bh * q_len * n * (s.D + 2) * sizeof(float);
 }
-// a number of its own for every launch
+// A number that launches hardly ever share (55 bits of a count, mixed).  Two that do are told apart all the same where the first is over,
+// as it leaves zeros behind.
 static uint64_t launch_tag()
 {
     static std::atomic<uint64_t> launches{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count()};
-    uint64_t x = launches.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4a7c15ull;      // (odd: one to one)
+    uint64_t x = launches.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4a7c15ull;
     x ^= x >> 32;
     return (x >> 8) | 1u;
 }
