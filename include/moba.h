@@ -298,7 +298,7 @@ int moba_decode_forward(const moba_shape* shape, int32_t q_len, const void* Q, c
  * The same with a workspace: where few queries have much to read, several workgroups then share a query and the
  * last of them merges their parts (the result depends on the shape alone, but may differ in rounding from the
  * call without a workspace).  moba_decode_workspace gives its size, 0 where nothing is gained by one.
- *   ws   at least that many bytes, 8-byte aligned, of any content; used by one call at a time; may be NULL
+ *   ws   at least that many bytes, 8-byte aligned (else MOBA_EINVAL), of any content; used by one call at a time; may be NULL
  */
 int moba_decode_workspace(const moba_shape* shape, int32_t q_len, size_t* ws_bytes);
 int moba_decode_forward_ws(const moba_shape* shape, int32_t q_len, const void* Q, const void* K_eff,

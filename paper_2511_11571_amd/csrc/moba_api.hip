@@ -467,6 +467,7 @@ int moba_decode_forward_ws(const moba_shape* shape, int32_t q_len, const void* Q
     if (d.k > 0 && past_max > 0 && (!centroids || centroid_blocks < past_max)) return MOBA_EINVAL;
     if (past_max > kMaxBlocks) return MOBA_EUNSUPPORTED;
     if (ws && ws_bytes < decode_ws_bytes(d, q_len)) return MOBA_EWORKSPACE;
+    if (reinterpret_cast<uintptr_t>(ws) % sizeof(uint64_t)) return MOBA_EINVAL;     // (64-bit atomics: misaligned ones fault)
     return hip_status(launch_decode(d, q_len, Q, K_eff, V, centroids, centroid_blocks, O, lse, topk_idx, ws,
                                     (hipStream_t)stream));
 }

@@ -65,6 +65,14 @@ def test_decode_workspace_counts_the_keys_there_are(lib):
     assert need(seqlen=(1 << 14) + 9000, block=1 << 14, topk=0) > 0
 
 
+def test_decode_refuses_a_misaligned_workspace(lib):
+    """The counters in it are counted up by 64-bit atomics.  (Host-side: nothing is launched.)"""
+    one, sh = ctypes.c_void_p(256), _shape(heads=1, seqlen=4096 + 7, block=4096, topk=1).c()
+    call = lambda ws, n: lib.moba_decode_forward_ws(ctypes.byref(sh), 1, one, one, one, one, 1, one, one, None, ctypes.c_void_p(ws), ctypes.c_size_t(n), None)  # noqa: E731
+    assert call(256 + 4, 1 << 20) == -1 and call(256 + 1, 1 << 20) == -1
+    assert call(256 + 4, 16) == -3                            # too small, as before
+
+
 def _decode_shapes():
     rng = random.Random(5)
     for _ in range(4000):
